@@ -140,21 +140,37 @@ def _i32(x):
     return torch.as_tensor(np.ascontiguousarray(x), dtype=torch.int32, device=DEV)
 
 
+def _context(c, gen, ctx):
+    """The rows of every layer's and sequence's cached context, in the order in which they are drawn: (layer, sequence, K, V)."""
+    et = torch.float32 if c["kv"] == "fp32" else torch.bfloat16
+    for l in range(c["layers"]):
+        for b in range(c["B"]):
+            shape = (1, int(ctx[b]), c["Hkv"], c["D"])
+            K = _randn(gen, shape, et)
+            yield l, b, K, _randn(gen, shape, et)
+
+
+def _step_rows(c, gen):
+    """Queries and new K and V rows of every layer, drawn after the context."""
+    et = torch.float32 if c["kv"] == "fp32" else torch.bfloat16
+    lead, Hq, Hkv, D = (c["layers"], c["B"], c["kmax"]), c["Hq"], c["Hkv"], c["D"]
+    # grouped-query recipe: scores of unit variance come from smaller queries
+    q_mult = 1.0 if Hq == Hkv else 1.0 / math.sqrt(D)
+    Q = _randn(gen, lead + (Hq, D), torch.float32).mul_(q_mult).to(et)
+    K = _randn(gen, lead + (Hkv, D), et)
+    return Q, K, _randn(gen, lead + (Hkv, D), et)
+
+
 def _prepare_caches(c, s, gen, ctx):
     """One slab for all layers' K and one for their V, the cached context of every sequence in place."""
     d = s.desc
-    et = torch.float32 if c["kv"] == "fp32" else torch.bfloat16
     size = bass.bass_kv_cache_bytes(d)
     s.Kslab = torch.zeros((c["layers"], size), dtype=torch.uint8, device=DEV)
     s.Vslab = torch.zeros((c["layers"], size), dtype=torch.uint8, device=DEV)
     per_seq, zero = size // c["B"], torch.zeros(1, dtype=torch.int32, device=DEV)
-    for l in range(c["layers"]):
-        for b in range(c["B"]):
-            L = int(ctx[b])
-            K = _randn(gen, (1, L, c["Hkv"], c["D"]), et)
-            V = _randn(gen, (1, L, c["Hkv"], c["D"]), et)
-            at = slice(b * per_seq, (b + 1) * per_seq)
-            bass.bass_kv_append(d.replace(B=1, kmax=L), s.Kslab[l, at], s.Vslab[l, at], K, V, zero, s.ctx[b:b + 1])
+    for l, b, K, V in _context(c, gen, ctx):
+        at = slice(b * per_seq, (b + 1) * per_seq)
+        bass.bass_kv_append(d.replace(B=1, kmax=K.shape[1]), s.Kslab[l, at], s.Vslab[l, at], K, V, zero, s.ctx[b:b + 1])
     s.K, s.V = list(s.Kslab), list(s.Vslab)
 
 
@@ -225,11 +241,7 @@ def prepare(case, seed):
             s.Vn = [_randn(gen, (B, kmax, Hkv, D), et) for _ in range(c["layers"])]
         return s
     _prepare_caches(c, s, gen, ctx)
-    # grouped-query recipe: scores of unit variance come from smaller queries
-    q_mult = 1.0 if Hq == Hkv else 1.0 / math.sqrt(D)
-    s.Q = list(_randn(gen, (c["layers"], B, kmax, Hq, D), torch.float32).mul_(q_mult).to(et))
-    s.Kn = list(_randn(gen, (c["layers"], B, kmax, Hkv, D), et))
-    s.Vn = list(_randn(gen, (c["layers"], B, kmax, Hkv, D), et))
+    s.Q, s.Kn, s.Vn = (list(t) for t in _step_rows(c, gen))
     s.Oall = torch.zeros((c["layers"], B, kmax, Hq, D), dtype=torch.float32, device=DEV)
     s.O = list(s.Oall)
     s.ws = bass.alloc_workspace(s.desc, DEV)
@@ -327,3 +339,58 @@ def tolerance(case):
     if case["kv"] == "fp32":
         return {"rel": 1.2e-6, "max": 5.5e-6}
     return {"rel": 7e-3, "max": 8.5e-2}
+
+
+# ---- what a pass returns, in 64 bits ----------------------------------------------------------------
+
+def _represented(x, c):
+    """Rows as an attention over this cache sees them: the values themselves, or code * scale of INT8 rows, in 64 bits."""
+    if c["kv"] != "int8kv":
+        return x.double()
+    x = x.float()  # every step below is one operation in 32 bits
+    amax = x.abs().amax(-1, keepdim=True)
+    codes = torch.round(x * torch.where(amax > 0, 127.0 / amax, torch.zeros_like(amax)))
+    return codes.double() * (amax / 127.0).double()
+
+
+def _warped(z, temperature, top_p):
+    """Probability rows: temperature, the shortest prefix of the sorted tokens that reaches top_p, renormalised."""
+    p = torch.softmax(z.double() / temperature, -1)
+    if top_p >= 1.0:
+        return p
+    sorted_p, order = torch.sort(p, dim=-1, descending=True, stable=True)
+    before = sorted_p.cumsum(-1) - sorted_p
+    p = torch.zeros_like(p).scatter_(-1, order, torch.where(before < top_p, sorted_p, torch.zeros_like(sorted_p)))
+    return p / p.sum(-1, keepdim=True)
+
+
+def exact(case, seed):
+    c = case
+    if c["kind"] in ("fill", "move"):
+        return None  # whole numbers and copies
+    gen = torch.Generator(device=DEV)
+    gen.manual_seed(seed)
+    ctx, nq = _lengths(c)
+    if c["kind"] == "rows":
+        p, q = (torch.stack([_warped(z, c["temperature"], c["top_p"]) for z in t]) if t.numel() else t.double()
+                for t in _prepare_logits(c, gen, c["kmax"] - 1))
+        return {"p": p, "q": q, "n_accept": None, "next_token": None, "status": None}
+    Hq, Hkv, D = c["Hq"], c["Hkv"], c["D"]
+    g, scale = Hq // Hkv, 1.0 / math.sqrt(D)
+    at_context = gen.get_state()
+    for _ in _context(c, gen, ctx):
+        pass
+    Q, Kn, Vn = _step_rows(c, gen)
+    gen.set_state(at_context)
+    O = torch.zeros((c["layers"], c["B"], c["kmax"], Hq, D), dtype=torch.float64, device=DEV)
+    for l, b, K, V in _context(c, gen, ctx):
+        L, n = int(ctx[b]), int(nq[b])
+        K = _represented(torch.cat([K[0], Kn[l, b, :n]]), c).permute(1, 2, 0).contiguous()  # [Hkv, D, L + n]
+        V = _represented(torch.cat([V[0], Vn[l, b, :n]]), c).permute(1, 0, 2).contiguous()
+        q = _represented(Q[l, b, :n], c).view(n, Hkv, g, D).permute(1, 0, 2, 3).reshape(Hkv, n * g, D)
+        s = torch.matmul(q, K).mul_(scale).view(Hkv, n, g, L + n)
+        hidden = torch.arange(L + n, device=DEV) > L + torch.arange(n, device=DEV).unsqueeze(1)
+        s.masked_fill_(hidden.view(1, n, 1, L + n), float("-inf"))
+        o = torch.matmul(torch.softmax(s, -1).view(Hkv, n * g, L + n), V)
+        O[l, b, :n] = o.view(Hkv, n, g, D).permute(1, 0, 2, 3).reshape(n, Hq, D)
+    return {"O": O, "K": None, "V": None, "n_accept": None, "next_token": None, "status": None}
