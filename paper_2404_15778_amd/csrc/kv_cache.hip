@@ -79,58 +79,257 @@ __global__ __launch_bounds__(256) void kv_rows_bf16(KvParams p) {
   }
 }
 
-// Appends of many rows (a prompt, a moved sequence): one workgroup per (sequence, kv head, 32-token
-// cache block).  K rows go out as the 16-byte chunks they already are; the V tile is turned in LDS so
-// that the cache receives whole 16-byte chunks (eight tokens of one head element) instead of 2-byte
-// scatters.  A block that the rows cover only partly keeps its other tokens (read-modify-write; no
-// other workgroup touches the block).
-template <int D>
-__global__ __launch_bounds__(256) void kv_blocks_bf16(KvParams p, int blocks_per_seq) {
-  __shared__ __align__(16) uint16_t vt[kBlockTokens][D + 8];
-  const int tid = threadIdx.x;
-  const int j = blockIdx.x % blocks_per_seq;
-  const int unit = blockIdx.x / blocks_per_seq;
-  const int kvh = unit % p.Hkv, b = unit / p.Hkv;
-  int n = p.cnt[b];
+// ---------------------------------------------------------------------------------------
+// Many rows at once (a prompt, a moved sequence): one workgroup per (sequence, kv head, 32-token cache block),
+// in either direction and for bf16 and INT8 caches.  Bound by memory; what matters is that both sides are whole
+// 16-byte chunks of consecutive addresses.  A cache block mixes its 32 tokens (and V turns them: eight tokens of
+// one head element per chunk), so the block is turned in LDS instead of by 1- or 2-byte accesses to memory.
+// A block that the rows cover only partly keeps its other tokens (read-modify-write; no other workgroup
+// touches the block).
+// Measured, 8 prompts of up to 2048 tokens, 32 heads of 128, one layer: INT8 append 162 -> 52 us (4.7 TB/s), bf16
+// append and gather together 209 -> 131 us (4.9 TB/s); before: one thread per 16 bytes of a row, V by single bytes
+// (INT8) or halfwords (bf16 gather).
+// ---------------------------------------------------------------------------------------
+constexpr int kXcds = 8;  // workgroups are dealt to the XCDs in turn
+
+// The block a workgroup handles, and the tokens t0 .. t1 - 1 of it that take part (row slot = token - off).
+struct BlockJob {
+  int b, kvh, blk;
+  long off, t0, t1;
+  bool whole;
+};
+
+// All kv heads of a block of tokens go to the same XCD, one after the other: a token's rows of all heads lie
+// side by side in the row tensors, and so do its scales there (4 bytes per head), which then leave that XCD's
+// L2 as whole cache lines.  False (for the whole workgroup): nothing to do.
+__device__ inline bool block_job(const KvParams& p, int blocks_per_seq, BlockJob& o) {
+  const int xcd = (int)(blockIdx.x % kXcds), local = (int)(blockIdx.x / kXcds);
+  const int group = local / p.Hkv * kXcds + xcd;  // over [B][blocks_per_seq]
+  if (group >= p.B * blocks_per_seq) return false;
+  o.kvh = local % p.Hkv;
+  o.b = group / blocks_per_seq;
+  const int j = group - o.b * blocks_per_seq;
+  int n = p.cnt[o.b];
   bool bad = false;
   if (n < 0) { n = 0; bad = true; }
   if (n > p.kmax) { n = p.kmax; bad = true; }
-  const long off = p.off[b];
-  const long lo = max(off, 0l), hi = min(off + n, (long)p.Lcap);  // tokens that exist in the cache
-  if (n > 0 && (off < 0 || off + n > p.Lcap)) bad = true;
-  if (bad && j == 0 && kvh == 0 && tid == 0 && p.status) atomicOr(p.status, BASS_STATUS_LEN_CLAMPED);
-  if (hi <= lo) return;
-  const int blk = (int)(lo / kBlockTokens) + j;
-  const long t0 = max(lo, (long)blk * kBlockTokens), t1 = min(hi, (long)(blk + 1) * kBlockTokens);
-  if (t1 <= t0) return;  // uniform for the workgroup
-  const size_t base = (((size_t)b * p.Hkv + kvh) * p.nblk + blk) * ((size_t)kBlockTokens * D);
+  o.off = p.off[o.b];
+  const long lo = max(o.off, 0l), hi = min(o.off + n, (long)p.Lcap);  // tokens that exist in the cache
+  if (n > 0 && (o.off < 0 || o.off + n > p.Lcap)) bad = true;
+  if (bad && j == 0 && o.kvh == 0 && threadIdx.x == 0 && p.status) atomicOr(p.status, BASS_STATUS_LEN_CLAMPED);
+  if (hi <= lo) return false;
+  o.blk = (int)(lo / kBlockTokens) + j;
+  const long first = (long)o.blk * kBlockTokens;
+  o.t0 = max(lo, first);
+  o.t1 = min(hi, first + kBlockTokens);
+  o.whole = o.t1 - o.t0 == kBlockTokens;
+  return o.t1 > o.t0;
+}
+
+// First element of token slot w's row in a row tensor [B][kmax][Hkv][D]
+__device__ inline size_t row_element(const KvParams& p, const BlockJob& o, int w, int D) {
+  return (((size_t)o.b * p.kmax + (size_t)((long)o.blk * kBlockTokens + w - o.off)) * p.Hkv + o.kvh) * D;
+}
+__device__ inline bool takes_part(const BlockJob& o, int w) {
+  const long tok = (long)o.blk * kBlockTokens + w;
+  return tok >= o.t0 && tok < o.t1;
+}
+
+// Token slot j (0 .. 7) of a V chunk of lane group grp
+__device__ inline int v_token(int grp, int j) { return j < 4 ? 4 * grp + j : 16 + 4 * grp + (j - 4); }
+
+template <int D>
+__global__ __launch_bounds__(256) void kv_blocks_bf16_append(KvParams p, int blocks_per_seq) {
+  __shared__ __align__(16) uint16_t vt[kBlockTokens][D + 8];
+  const int tid = threadIdx.x;
+  BlockJob o;
+  if (!block_job(p, blocks_per_seq, o)) return;
+  const size_t base = (((size_t)o.b * p.Hkv + o.kvh) * p.nblk + o.blk) * ((size_t)kBlockTokens * D);
   uint16_t* kc = (uint16_t*)p.Kc + base;
   uint16_t* vc = (uint16_t*)p.Vc + base;
   constexpr int CPR = D / 8;  // 16-byte chunks per row
   for (int c = tid; c < kBlockTokens * CPR; c += 256) {
     const int w = c / CPR, ck = c % CPR;
-    const long tok = (long)blk * kBlockTokens + w;
-    if (tok >= t0 && tok < t1) {
-      const size_t src = ((((size_t)b * p.kmax + (size_t)(tok - off)) * p.Hkv + kvh) * D) + ck * 8;
+    if (takes_part(o, w)) {
+      const size_t src = row_element(p, o, w, D) + ck * 8;
       *(uint4*)(kc + k_elem_offset(D, w, ck * 8)) = *(const uint4*)((const uint16_t*)p.Kr + src);
       *(uint4*)&vt[w][ck * 8] = *(const uint4*)((const uint16_t*)p.Vr + src);
     }
   }
   __syncthreads();
-  const bool whole = t0 == (long)blk * kBlockTokens && t1 == (long)(blk + 1) * kBlockTokens;
   for (int c = tid; c < (D / 16) * 64; c += 256) {
     const int mt = c / 64, l = c % 64, grp = l >> 4, dr = l & 15;
     uint4* dst = (uint4*)(vc + (size_t)c * 8);
     uint4 cur = make_uint4(0, 0, 0, 0);
-    if (!whole) cur = *dst;
+    if (!o.whole) cur = *dst;
     uint16_t* e = (uint16_t*)&cur;
 #pragma unroll
     for (int jj = 0; jj < 8; ++jj) {
-      const int w = jj < 4 ? 4 * grp + jj : 16 + 4 * grp + (jj - 4);
-      const long tok = (long)blk * kBlockTokens + w;
-      if (whole || (tok >= t0 && tok < t1)) e[jj] = vt[w][16 * mt + dr];
+      const int w = v_token(grp, jj);
+      if (o.whole || takes_part(o, w)) e[jj] = vt[w][16 * mt + dr];
     }
     *dst = cur;
+  }
+}
+
+// Rows read back from a bf16 cache.  Both tensors pass through LDS, so that a row leaves as D / 8 consecutive
+// chunks; rows are 8 elements longer there than in memory, which keeps the 2-byte writes of a V chunk (lanes:
+// 16 head elements of 4 token groups) off each other's banks.
+template <int D>
+__global__ __launch_bounds__(256) void kv_blocks_bf16_gather(KvParams p, int blocks_per_seq) {
+  __shared__ __align__(16) uint16_t kt[kBlockTokens][D + 8], vt[kBlockTokens][D + 8];
+  const int tid = threadIdx.x;
+  BlockJob o;
+  if (!block_job(p, blocks_per_seq, o)) return;
+  const size_t base = (((size_t)o.b * p.Hkv + o.kvh) * p.nblk + o.blk) * ((size_t)kBlockTokens * D);
+  const uint4* kc = (const uint4*)((const uint16_t*)p.Kc + base);
+  const uint4* vc = (const uint4*)((const uint16_t*)p.Vc + base);
+  constexpr int CPR = D / 8, kTurns = kBlockTokens * CPR / 256;  // 16-byte chunks per row; chunks per thread and tensor
+  uint4 k[kTurns], v[kTurns];
+#pragma unroll
+  for (int i = 0; i < kTurns; ++i) {
+    k[i] = kc[tid + 256 * i];
+    v[i] = vc[tid + 256 * i];
+  }
+#pragma unroll
+  for (int i = 0; i < kTurns; ++i) {
+    const int c = tid + 256 * i, l = c % 64, grp = l >> 4, r = l & 15;
+    const int tile = c / 64 / (D / 32), t = c / 64 % (D / 32);  // K: token 16 tile + r, head elements 32 t + 8 grp ..
+    *(uint4*)&kt[16 * tile + r][32 * t + 8 * grp] = k[i];
+    const uint32_t e[4] = {v[i].x, v[i].y, v[i].z, v[i].w};     // V: head element 16 (c / 64) + r of eight tokens
+#pragma unroll
+    for (int j = 0; j < 8; ++j) vt[v_token(grp, j)][16 * (c / 64) + r] = (uint16_t)(e[j >> 1] >> (16 * (j & 1)));
+  }
+  __syncthreads();
+#pragma unroll
+  for (int i = 0; i < kTurns; ++i) {
+    const int c = tid + 256 * i, w = c / CPR, ck = c % CPR;
+    if (takes_part(o, w)) {
+      const size_t dst = row_element(p, o, w, D) + ck * 8;
+      *(uint4*)((uint16_t*)p.Kr + dst) = *(const uint4*)&kt[w][ck * 8];
+      *(uint4*)((uint16_t*)p.Vr + dst) = *(const uint4*)&vt[w][ck * 8];
+    }
+  }
+}
+
+// Rows quantized into an INT8 cache: codes and scales as in kv_rows_i8_append below (the same operations on the
+// same row).  The codes are laid down row by row in LDS (rows 16 bytes longer than in memory: chunks of
+// different tokens start at different banks); the block's chunks are put together from there -- K: 16 codes of
+// one row, V: one byte of 16 rows each -- and stored in consecutive order.
+template <int D>
+__global__ __launch_bounds__(256) void kv_blocks_i8_append(KvParams p, int blocks_per_seq) {
+  __shared__ __align__(16) uint8_t kt[kBlockTokens][D + 16], vt[kBlockTokens][D + 16];
+  __shared__ float kscale[kBlockTokens], vscale[kBlockTokens];
+  const int tid = threadIdx.x;
+  BlockJob o;
+  if (!block_job(p, blocks_per_seq, o)) return;
+  constexpr int CPR = D / 8, kTurns = kBlockTokens * CPR / 256;  // chunks of 8 elements per row; per thread and tensor
+  uint4 k[kTurns], v[kTurns];
+#pragma unroll
+  for (int i = 0; i < kTurns; ++i) {
+    const int c = tid + 256 * i, w = c / CPR, ck = c % CPR;
+    k[i] = v[i] = make_uint4(0, 0, 0, 0);
+    if (takes_part(o, w)) {
+      const size_t src = row_element(p, o, w, D) + ck * 8;
+      k[i] = *(const uint4*)((const uint16_t*)p.Kr + src);
+      v[i] = *(const uint4*)((const uint16_t*)p.Vr + src);
+    }
+  }
+#pragma unroll
+  for (int i = 0; i < kTurns; ++i) {
+    const int c = tid + 256 * i, w = c / CPR, ck = c % CPR;
+    float ka = amax8(k[i]), va = amax8(v[i]);
+#pragma unroll
+    for (int s = CPR >> 1; s >= 1; s >>= 1) {  // the threads of a row are consecutive lanes
+      ka = fmaxf(ka, __shfl_xor(ka, s));
+      va = fmaxf(va, __shfl_xor(va, s));
+    }
+    const float kinv = ka > 0.f ? 127.0f / ka : 0.f;
+    const float vinv = va > 0.f ? 127.0f / va : 0.f;
+    *(uint2*)&kt[w][ck * 8] = quantize8(k[i], kinv);
+    *(uint2*)&vt[w][ck * 8] = quantize8(v[i], vinv);
+    if (ck == 0) {
+      kscale[w] = ka / 127.0f;
+      vscale[w] = va / 127.0f;
+    }
+  }
+  __syncthreads();
+  const size_t base = (((size_t)o.b * p.Hkv + o.kvh) * p.nblk + o.blk) * i8_block_bytes(D);
+  uint8_t* kc = (uint8_t*)p.Kc + base;
+  uint8_t* vc = (uint8_t*)p.Vc + base;
+  for (int c = tid; c < 2 * D; c += 256) {  // the block's 16-byte chunks of codes
+    const int l = c % 64, grp = l >> 4, r = l & 15;
+    const int tile = c / 64 / (D / 64), ks = c / 64 % (D / 64);  // K: token 16 tile + r, head elements 64 ks + 16 grp ..
+    if (takes_part(o, 16 * tile + r)) *(uint4*)(kc + 16 * c) = *(const uint4*)&kt[16 * tile + r][64 * ks + 16 * grp];
+    const int d = 32 * (c / 64) + r;  // V: head elements d and d + 16 of eight tokens
+    uint4* dst = (uint4*)(vc + 16 * c);
+    uint32_t word[4] = {0u, 0u, 0u, 0u};
+    if (!o.whole) {
+      const uint4 cur = *dst;
+      word[0] = cur.x; word[1] = cur.y; word[2] = cur.z; word[3] = cur.w;
+    }
+#pragma unroll
+    for (int e = 0; e < 16; ++e) {
+      const int w = v_token(grp, e & 7);
+      if (o.whole || takes_part(o, w)) {
+        const uint32_t code = vt[w][d + 16 * (e >> 3)];
+        word[e >> 2] = (word[e >> 2] & ~(0xFFu << (8 * (e & 3)))) | (code << (8 * (e & 3)));
+      }
+    }
+    *dst = make_uint4(word[0], word[1], word[2], word[3]);
+  }
+  if (tid < kBlockTokens && takes_part(o, tid)) {
+    ((float*)(kc + (size_t)kBlockTokens * D))[tid] = kscale[tid];
+    ((float*)(vc + (size_t)kBlockTokens * D))[tid] = vscale[tid];
+  }
+}
+
+// Codes and scales read back from an INT8 cache: the inverse of the turn above.
+template <int D>
+__global__ __launch_bounds__(256) void kv_blocks_i8_gather(KvParams p, int blocks_per_seq) {
+  __shared__ __align__(16) uint8_t kt[kBlockTokens][D + 16], vt[kBlockTokens][D + 16];
+  const int tid = threadIdx.x;
+  BlockJob o;
+  if (!block_job(p, blocks_per_seq, o)) return;
+  const size_t base = (((size_t)o.b * p.Hkv + o.kvh) * p.nblk + o.blk) * i8_block_bytes(D);
+  const uint8_t* kc = (const uint8_t*)p.Kc + base;
+  const uint8_t* vc = (const uint8_t*)p.Vc + base;
+  for (int c = tid; c < 2 * D; c += 256) {
+    const uint4 k = *(const uint4*)(kc + 16 * c), v = *(const uint4*)(vc + 16 * c);
+    const int l = c % 64, grp = l >> 4, r = l & 15;
+    const int tile = c / 64 / (D / 64), ks = c / 64 % (D / 64);
+    *(uint4*)&kt[16 * tile + r][64 * ks + 16 * grp] = k;
+    const uint32_t word[4] = {v.x, v.y, v.z, v.w};
+    const int d = 32 * (c / 64) + r;
+#pragma unroll
+    for (int e = 0; e < 16; ++e) vt[v_token(grp, e & 7)][d + 16 * (e >> 3)] = (uint8_t)(word[e >> 2] >> (8 * (e & 3)));
+  }
+  __syncthreads();
+  constexpr int CPR = D / 8;
+  for (int c = tid; c < kBlockTokens * CPR; c += 256) {
+    const int w = c / CPR, ck = c % CPR;
+    if (takes_part(o, w)) {
+      const size_t dst = row_element(p, o, w, D) + ck * 8;
+      *(uint2*)((uint8_t*)p.Kr + dst) = *(const uint2*)&kt[w][ck * 8];
+      *(uint2*)((uint8_t*)p.Vr + dst) = *(const uint2*)&vt[w][ck * 8];
+    }
+  }
+  if (tid < kBlockTokens && takes_part(o, tid)) {
+    const size_t row = row_element(p, o, tid, 1);  // [B][kmax][Hkv]
+    p.Ks[row] = ((const float*)(kc + (size_t)kBlockTokens * D))[tid];
+    p.Vs[row] = ((const float*)(vc + (size_t)kBlockTokens * D))[tid];
+  }
+}
+
+template <int D>
+static void launch_blocks(bool gather, bool int8, dim3 grid, hipStream_t s, const KvParams& p, int blocks_per_seq) {
+  const dim3 block(256);
+  if (int8) {
+    if (gather) hipLaunchKernelGGL(kv_blocks_i8_gather<D>, grid, block, 0, s, p, blocks_per_seq);
+    else hipLaunchKernelGGL(kv_blocks_i8_append<D>, grid, block, 0, s, p, blocks_per_seq);
+  } else {
+    if (gather) hipLaunchKernelGGL(kv_blocks_bf16_gather<D>, grid, block, 0, s, p, blocks_per_seq);
+    else hipLaunchKernelGGL(kv_blocks_bf16_append<D>, grid, block, 0, s, p, blocks_per_seq);
   }
 }
 
@@ -241,18 +440,19 @@ static int launch_rows(const bass_attn_desc* d, void* Kc, void* Vc, void* Kr, vo
   KvParams p{d->B, d->kmax, d->Hkv, d->D, d->Lcap, num_blocks(d->Lcap), Kc, Vc, Kr, Vr, off, cnt, status, Ks, Vs};
   dim3 grid((unsigned)((items + 255) / 256));
   hipStream_t s = (hipStream_t)stream;
-  if (d->dtype == BASS_DTYPE_INT8KV) {
+  // From one block of rows on, by blocks; fewer rows (a step's drafts) by single rows, whose launch is one short
+  // dependent chain.
+  const int64_t per_seq = (d->kmax + kBlockTokens - 1) / kBlockTokens + 1;  // blocks the rows of a sequence can touch
+  const int64_t wgs = ((int64_t)d->B * per_seq + kXcds - 1) / kXcds * kXcds * d->Hkv;
+  if (d->dtype != BASS_DTYPE_FP32 && d->kmax >= kBlockTokens && wgs <= 0x7fffffff) {
+    const bool int8 = d->dtype == BASS_DTYPE_INT8KV;
+    if (d->D == 128) launch_blocks<128>(kGather, int8, dim3((unsigned)wgs), s, p, (int)per_seq);
+    else launch_blocks<64>(kGather, int8, dim3((unsigned)wgs), s, p, (int)per_seq);
+  } else if (d->dtype == BASS_DTYPE_INT8KV) {
     if (kGather) hipLaunchKernelGGL(kv_rows_i8_gather, grid, dim3(256), 0, s, p);
     else hipLaunchKernelGGL(kv_rows_i8_append, grid, dim3(256), 0, s, p);
   } else if (d->dtype == BASS_DTYPE_BF16) {
-    const int64_t per_seq = (d->kmax + kBlockTokens - 1) / kBlockTokens + 1;  // blocks the rows of a sequence can touch
-    const int64_t wgs = (int64_t)d->B * d->Hkv * per_seq;
-    if (!kGather && d->kmax >= kBlockTokens && wgs <= 0x7fffffff) {
-      if (d->D == 128) hipLaunchKernelGGL(kv_blocks_bf16<128>, dim3((unsigned)wgs), dim3(256), 0, s, p, (int)per_seq);
-      else hipLaunchKernelGGL(kv_blocks_bf16<64>, dim3((unsigned)wgs), dim3(256), 0, s, p, (int)per_seq);
-    } else {
-      hipLaunchKernelGGL(kv_rows_bf16<kGather>, grid, dim3(256), 0, s, p);
-    }
+    hipLaunchKernelGGL(kv_rows_bf16<kGather>, grid, dim3(256), 0, s, p);
   } else
     hipLaunchKernelGGL(kv_rows_fp32<kGather>, grid, dim3(256), 0, s, p);
   return launch_status();
