@@ -51,6 +51,8 @@ struct PlanShape {
   int32_t pad_before;  // how many of them sit in front of the unit's last real block
   int32_t span;        // BASS-PAD variant: every active sequence is processed over at least this many cache
                        // positions (0: over its own length); the positions beyond its length are masked
+  int32_t min_entries = 0;  // shares are not made shorter than this many entries (0: no bound) ...
+  int32_t per_unit = 0;     // ... but this many per unit there may always be
 };
 
 // Real blocks of a sequence (per kv head) after clamping; 0 for an inactive sequence.
@@ -94,7 +96,10 @@ BASS_HD inline Split make_split(int total, int n) { return Split{total / n, tota
 // are correspondingly more of them (at most nshares: the share length grows until they fit); the last one
 // takes what is left, the launch's remaining wavefronts stay idle.
 BASS_HD inline Split plan_split(const PlanShape& s, int total) {
-  if (s.target >= s.nshares || total <= 0) return make_split(total, s.nshares);
+  // A short list is divided over fewer shares of about min_entries each: every share of a unit costs a partial
+  // result, its acknowledged store, and a share of the merge that waits for the last of them.
+  const int wanted = s.min_entries > 0 ? imax(1, imin(s.nshares, imax(total / s.min_entries, s.per_unit * s.B * s.Hkv))) : s.nshares;
+  if (s.target >= s.nshares || total <= 0) return make_split(total, wanted);
   int per = imax(1, total / s.target);
   while ((total + per - 1) / per > s.nshares) ++per;
   return Split{per, 0, total};

@@ -128,6 +128,15 @@ constexpr int kAppendPad = 3;     // virtual blocks per unit when the append is 
 constexpr int kPlainPad = 2;      // ... and when it is not (the unit's last blocks are the masked, slower ones)
 constexpr int kAppendBefore = 1;  // how many of those sit in front of the unit's last real block (one-tile matrix-core
 constexpr int kPlainBefore = 0;   // kernel; measured: +0.5 % with the fused append, slightly slower without)
+// Matrix-core kernels: where a unit would get more than kPerUnit shares of fewer than kMinEntries blocks, the list is divided over
+// fewer shares.  Every share of a unit leaves a partial result that the wavefront merging the unit has to fetch: one
+// sequence and 32 heads of 128, bf16, took 19.8 us with 24 shares per unit, 15.0 us with 8 and takes 13.2 us
+// with 5.  Measured with at least 1 / 4 / 5 / 6 / 9 / 12 blocks per share: 675 / 517 / 463 / 491 / 514 / 551 us for
+// the step of 32 such layers.  Units with fewer shares keep them, and more of them over INT8 caches, where
+// a block costs its wavefront about 1 us (4 sequences of 217 tokens, 32 heads, 6 shares per unit: 534 us; of 4 blocks at
+// least, 576).
+constexpr int kMinEntries = 5;
+constexpr int kPerUnit = 5, kPerUnitInt8 = 8;
 constexpr int kMaxStagedElems = 2048;  // kmax * D up to which the step's rows are appended inside the attention launch
 
 int attention_waves_setting();  // bass_set_attention_waves (0 = defaults); verify_attention.hip
@@ -136,7 +145,7 @@ struct LaunchShape {
   bool mfma;        // bf16 or INT8 caches: the matrix-core kernels
   bool tiles;       // bf16 caches, more than one 16-row query tile per kv head: the workgroup-level kernel
   bool fused_append;  // the step's rows are appended inside the attention launch
-  int rows_max, nwaves, nshares, target, pad, pad_before, fused_reduce;
+  int rows_max, nwaves, nshares, target, pad, pad_before, min_entries, per_unit, fused_reduce;
 };
 
 // many_rows: more than one 16-row query tile per kv head (grouped-query attention); a separate
@@ -167,6 +176,8 @@ inline LaunchShape launch_shape(const bass_attn_desc* d, bool append) {
   s.nshares = !s.tiles ? s.nwaves : setting > 0 ? (s.nwaves / 2 > 16 ? s.nwaves / 2 : 16) : 256;
   s.target = !s.tiles ? aim : s.nshares;
   s.pad = s.fused_append ? kAppendPad : kPlainPad;
+  s.min_entries = setting > 0 || s.tiles || !s.mfma ? 0 : kMinEntries;
+  s.per_unit = d->dtype == BASS_DTYPE_INT8KV ? kPerUnitInt8 : kPerUnit;
   s.pad_before = 0;
   if (s.mfma && s.rows_max <= 16) s.pad_before = s.fused_append ? kAppendBefore : kPlainBefore;
   // one query tile per kv head: the last-arriving wavefront reduces; more: a second, chip-wide launch

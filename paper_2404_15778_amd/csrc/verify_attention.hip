@@ -214,23 +214,36 @@ __device__ inline float group16_sum(float v) {
   return v;
 }
 
-// Split-context reduction of a unit, four query rows per sweep: 16 lanes per row, each lane owning
-// KC float4 chunks of its row.  Two phases, so that the requests of two sweeps can be in flight
-// together:
-//   issue : requests, for the first 8 partials, the row's (max, sum) pairs (every lane of a row
+// Split-context reduction of a unit, 64 / LPR query rows per sweep: LPR lanes per row, each lane owning
+// KC float4 chunks of its row.  A round takes eight partials, in two phases, so that the requests of two
+// rounds (of two sweeps, or of one sweep with more than eight partials) can be in flight together:
+//   issue : requests, for the round's partials, the row's (max, sum) pairs (every lane of a row
 //           asks for all of them, so no cross-lane traffic is needed later) and the lane's
-//           output chunks -- one round trip to memory in the common case;
-//   finish: weights 2^(m_s - M) / L and the weighted sum, all lane-local; units with more than 8
-//           partials (work spread very thin) continue one partial at a time; writes O and lse.
+//           output chunks -- one round trip to memory;
+//   fold  : weights 2^(m_s - M) and the weighted sum, all lane-local; a later round rescales what is there
+//           by the change of the running maximum.
+// combine_finish then divides and writes O and lse.
+// Few units leave many partials each (one sequence of 32 heads over 768 wavefronts: 24 per unit).  They used to be
+// fetched two per round trip after the first eight, behind a pass of their own over the maxima: ten round
+// trips to memory in a row instead of two for 24 partials.
 // Device-scope requests cost a trip to memory each: partials that do not exist are skipped by
 // wave-uniform branches, and idle row slots get an offset beyond the buffer descriptor's size,
 // which the hardware answers with zeros without touching memory.
+constexpr int kRound = 8;  // partials per round
+
 template <int KC>
 struct CombineRegs {
   bool rok;
   int r;
-  float2 ml[8];
-  f32x4 a[8][KC];
+  float2 ml[kRound];
+  f32x4 a[kRound][KC];
+};
+
+// What a sweep has merged so far: running maximum, sum of weights, weighted output chunks
+template <int KC>
+struct MergeState {
+  float M, L;
+  f32x4 acc[KC];
 };
 
 struct CombineJob {
@@ -250,24 +263,24 @@ __device__ inline float2 load_dev2(__amdgpu_buffer_rsrc_t rs, unsigned byte_off)
 }
 
 // A sweep merges 64 / LPR rows: LPR lanes share a row, lane dl of them holds the 16-byte chunks dl + LPR k
-// (k < KC) of it.
+// (k < KC) of it.  Requests partials j0 .. j0 + 7 of the job (those that exist).
 template <int KC, int DC, int LPR = 16>
-__device__ inline void combine_issue(const AttnParams& p, const CombineJob& job, int r0, int lane, CombineRegs<KC>& c) {
+__device__ inline void combine_issue(const AttnParams& p, const CombineJob& job, int r0, int j0, int lane, CombineRegs<KC>& c) {
   const Unit& u = job.u;
   const int D = DC > 0 ? DC : p.D;
   const int rr = lane / LPR, dl = lane % LPR;
   const int rows = uniform(u.nq * p.g);
-  const int S8 = min(uniform(job.w_hi - job.w_lo + 1), 8);
-  const size_t slot0 = (size_t)uniform(job.w_lo + u.b * p.Hkv + u.kvh);
+  const int n = min(uniform(job.w_hi - job.w_lo + 1 - j0), kRound);
+  const size_t slot0 = (size_t)uniform(job.w_lo + j0 + u.b * p.Hkv + u.kvh);
   const unsigned slot_bytes = (unsigned)p.rows_max * D * 4, ml_bytes = (unsigned)p.rows_max * 8;
-  const __amdgpu_buffer_rsrc_t rs = dev_buffer(p.part_acc + slot0 * p.rows_max * D, (unsigned)S8 * slot_bytes);
-  const __amdgpu_buffer_rsrc_t rs_ml = dev_buffer(p.part_ml + slot0 * p.rows_max * 2, (unsigned)S8 * ml_bytes);
+  const __amdgpu_buffer_rsrc_t rs = dev_buffer(p.part_acc + slot0 * p.rows_max * D, (unsigned)n * slot_bytes);
+  const __amdgpu_buffer_rsrc_t rs_ml = dev_buffer(p.part_ml + slot0 * p.rows_max * 2, (unsigned)n * ml_bytes);
   c.rok = r0 + rr < rows;
   c.r = r0 + rr;
   const unsigned ml_off = c.rok ? (unsigned)c.r * 8 : kNoSuchOffset;
 #pragma unroll
-  for (int j = 0; j < 8; ++j) {
-    if (j >= S8) break;  // wave-uniform: no such partial (combine_finish never looks at it)
+  for (int j = 0; j < kRound; ++j) {
+    if (j >= n) break;  // wave-uniform: no such partial (combine_fold never looks at it)
     c.ml[j] = load_dev2(rs_ml, (unsigned)j * ml_bytes + ml_off);
 #pragma unroll
     for (int k = 0; k < KC; ++k) {
@@ -278,91 +291,78 @@ __device__ inline void combine_issue(const AttnParams& p, const CombineJob& job,
   }
 }
 
-constexpr int kMore = 2;  // partials beyond the eighth are fetched this many at a time (registers: the streaming kernel is full)
+// Adds partials j0 .. j0 + 7 (issued into c) to what the sweep has merged; j0 = 0 starts it.
+template <int KC>
+__device__ inline void combine_fold(const CombineJob& job, int j0, const CombineRegs<KC>& c, MergeState<KC>& t) {
+  const int n = uniform(job.w_hi - job.w_lo + 1 - j0);
+  // M = max_s m_s, L = sum_s l_s 2^(m_s - M).  A valid row has at least one partial with a
+  // visible token (token 0, which the first partial holds), so M is finite from the first round on; a partial
+  // that saw none has m = -inf, weight 0.  (Idle row slots were answered with zeros.)
+  float M = j0 == 0 ? -INFINITY : t.M;
+#pragma unroll
+  for (int j = 0; j < kRound; ++j)
+    if (j < n) M = fmaxf(M, c.ml[j].x);  // wave-uniform guards: partials beyond n were never requested
+  const float Mf = (M == -INFINITY) ? 0.f : M;
+  if (j0 == 0) {
+    t.L = 0.f;
+#pragma unroll
+    for (int k = 0; k < KC; ++k) t.acc[k] = f32x4{0.f, 0.f, 0.f, 0.f};
+  } else {
+    const float alpha = __builtin_amdgcn_exp2f(t.M - Mf);
+    t.L *= alpha;
+#pragma unroll
+    for (int k = 0; k < KC; ++k) t.acc[k] *= alpha;
+  }
+  t.M = M;
+#pragma unroll
+  for (int j = 0; j < kRound; ++j) {
+    if (j < n) {
+      const float wgt = __builtin_amdgcn_exp2f(c.ml[j].x - Mf);
+      t.L = fmaf(c.ml[j].y, wgt, t.L);
+#pragma unroll
+      for (int k = 0; k < KC; ++k) t.acc[k] += c.a[j][k] * wgt;
+    }
+  }
+}
 
 template <int KC, int DC, int LPR = 16>
-__device__ inline void combine_finish(const AttnParams& p, const CombineJob& job, int lane, const CombineRegs<KC>& c) {
+__device__ inline void combine_finish(const AttnParams& p, const CombineJob& job, int lane, const CombineRegs<KC>& c,
+                                      const MergeState<KC>& t) {
   const Unit& u = job.u;
   const int D = DC > 0 ? DC : p.D;
-  const int dl = lane % LPR;
-  const int S = uniform(job.w_hi - job.w_lo + 1);
-  const size_t slot0 = (size_t)uniform(job.w_lo + u.b * p.Hkv + u.kvh);
-  const unsigned slot_bytes = (unsigned)p.rows_max * D * 4, ml_bytes = (unsigned)p.rows_max * 8;
-  const f32x4 zero4 = {0.f, 0.f, 0.f, 0.f};
-  const int r = c.r;
-  // M = max_s m_s, L = sum_s l_s 2^(m_s - M).  A valid row has at least one partial with a
-  // visible token (token 0), so M ends finite; a partial that saw none has m = -inf, weight 0.
-  // (Idle row slots were answered with zeros.)
-  float M = -INFINITY;
-#pragma unroll
-  for (int j = 0; j < 8; ++j)
-    if (j < S) M = fmaxf(M, c.ml[j].x);  // wave-uniform guards: partials beyond S were never requested
-  const unsigned row8 = c.rok ? (unsigned)r * 8 : kNoSuchOffset;
-  if (S > 8) {  // further partials, eight per round trip (a load per iteration would be a round trip each)
-    const __amdgpu_buffer_rsrc_t rs_ml = dev_buffer(p.part_ml + slot0 * p.rows_max * 2, (unsigned)S * ml_bytes);
-#pragma unroll 1
-    for (int j0 = 8; j0 < S; j0 += 8) {
-      float2 t[8];
-#pragma unroll
-      for (int i = 0; i < 8; ++i) t[i] = load_dev2(rs_ml, j0 + i < S ? (unsigned)(j0 + i) * ml_bytes + row8 : kNoSuchOffset);
-#pragma unroll
-      for (int i = 0; i < 8; ++i) M = fmaxf(M, j0 + i < S ? t[i].x : -INFINITY);
-    }
-  }
-  const float Mf = (M == -INFINITY) ? 0.f : M;  // idle row slots only
-  float L = 0.f;
-  f32x4 acc[KC];
-#pragma unroll
-  for (int k = 0; k < KC; ++k) acc[k] = zero4;
-#pragma unroll
-  for (int j = 0; j < 8; ++j) {
-    if (j < S) {
-      const float wgt = __builtin_amdgcn_exp2f(c.ml[j].x - Mf);
-      L = fmaf(c.ml[j].y, wgt, L);
-#pragma unroll
-      for (int k = 0; k < KC; ++k) acc[k] += c.a[j][k] * wgt;
-    }
-  }
-  if (S > 8) {  // further partials, kMore per round trip: all loads of a round are issued before the first use
-    const __amdgpu_buffer_rsrc_t rs = dev_buffer(p.part_acc + slot0 * p.rows_max * D, (unsigned)S * slot_bytes);
-    const __amdgpu_buffer_rsrc_t rs_ml = dev_buffer(p.part_ml + slot0 * p.rows_max * 2, (unsigned)S * ml_bytes);
-    unsigned row_off[KC];
-#pragma unroll
-    for (int k = 0; k < KC; ++k) {
-      const int d = 4 * (dl + LPR * k);
-      row_off[k] = (c.rok && d < D) ? (unsigned)(r * D + d) * 4 : kNoSuchOffset;
-    }
-#pragma unroll 1
-    for (int j0 = 8; j0 < S; j0 += kMore) {
-      float2 ml[kMore];
-      f32x4 a[kMore][KC];
-#pragma unroll
-      for (int i = 0; i < kMore; ++i) {
-        const bool have = j0 + i < S;  // wave-uniform; a missing partial is requested out of range (zeros, no memory access)
-        ml[i] = load_dev2(rs_ml, have ? (unsigned)(j0 + i) * ml_bytes + row8 : kNoSuchOffset);
-#pragma unroll
-        for (int k = 0; k < KC; ++k) a[i][k] = load_dev4(rs, have ? (unsigned)(j0 + i) * slot_bytes + row_off[k] : kNoSuchOffset);
-      }
-#pragma unroll
-      for (int i = 0; i < kMore; ++i) {
-        const float w = j0 + i < S ? __builtin_amdgcn_exp2f(ml[i].x - Mf) : 0.f;
-        L = fmaf(ml[i].y, w, L);
-#pragma unroll
-        for (int k = 0; k < KC; ++k) acc[k] += a[i][k] * w;
-      }
-    }
-  }
+  const int dl = lane % LPR, r = c.r;
   if (c.rok) {
-    const float invL = __builtin_amdgcn_rcpf(L);  // 1 ulp: far inside both tolerances, and a fraction of the instructions of a division
+    const float invL = __builtin_amdgcn_rcpf(t.L);  // 1 ulp: far inside both tolerances, and a fraction of the instructions of a division
     const int i = row_token(p, r), hg = r - i * p.g;
     const size_t orow = ((size_t)u.b * p.kmax + i) * p.Hq + u.kvh * p.g + hg;
 #pragma unroll
     for (int k = 0; k < KC; ++k) {
       const int d = 4 * (dl + LPR * k);
-      if (d < D) *(f32x4*)(p.O + orow * D + d) = acc[k] * invL;
+      if (d < D) *(f32x4*)(p.O + orow * D + d) = t.acc[k] * invL;
     }
-    if (p.lse && dl == 0) p.lse[orow] = (M + __builtin_amdgcn_logf(L)) * 0.6931471805599453f;
+    if (p.lse && dl == 0) p.lse[orow] = (t.M + __builtin_amdgcn_logf(t.L)) * 0.6931471805599453f;
   }
+}
+
+// One sweep with any number of partials; kTwo: two rounds in flight at a time.
+template <int KC, int DC, int LPR, bool kTwo>
+__device__ inline void combine_sweep(const AttnParams& p, const CombineJob& job, int r0, int lane) {
+  const int S = uniform(job.w_hi - job.w_lo + 1);
+  MergeState<KC> t;
+  CombineRegs<KC> cx, cy;
+#pragma unroll 1
+  for (int j0 = 0; j0 < S; j0 += kTwo ? 2 * kRound : kRound) {
+    combine_issue<KC, DC, LPR>(p, job, r0, j0, lane, cx);
+    if constexpr (kTwo) {
+      const bool more = j0 + kRound < S;  // wave-uniform
+      if (more) combine_issue<KC, DC, LPR>(p, job, r0, j0 + kRound, lane, cy);
+      combine_fold<KC>(job, j0, cx, t);
+      if (more) combine_fold<KC>(job, j0 + kRound, cy, t);
+    } else {
+      combine_fold<KC>(job, j0, cx, t);
+    }
+  }
+  combine_finish<KC, DC, LPR>(p, job, lane, cx, t);
 }
 
 // Reduction of the one or two units this wavefront completed.  The sweeps of both jobs are laid end to
@@ -379,22 +379,31 @@ __device__ inline void combine_jobs(const AttnParams& p, const CombineJob& ja, b
   const bool two = do_a && do_b;
   const int n0 = (j0.u.nq * p.g + RPS - 1) / RPS;
   const int n1 = two ? (jb.u.nq * p.g + RPS - 1) / RPS : 0;
+  const bool many = uniform(j0.w_hi - j0.w_lo) >= kRound || (two && uniform(jb.w_hi - jb.w_lo) >= kRound);
+  if (!kOverlap || many) {
 #pragma unroll 1
-  for (int t = 0; t < n0 + n1; t += (kOverlap ? 2 : 1)) {
-    const bool has_y = kOverlap && t + 1 < n0 + n1;
+    for (int t = 0; t < n0 + n1; ++t) {
+      const CombineJob jx = (t < n0) ? j0 : jb;
+      combine_sweep<KC, DC, LPR, kOverlap>(p, jx, (t < n0) ? RPS * t : RPS * (t - n0), lane);
+    }
+    return;
+  }
+#pragma unroll 1
+  for (int t = 0; t < n0 + n1; t += 2) {
+    const bool has_y = t + 1 < n0 + n1;
     const CombineJob jx = (t < n0) ? j0 : jb;
     const int rx = (t < n0) ? RPS * t : RPS * (t - n0);
     const CombineJob jy = (t + 1 < n0) ? j0 : jb;
     const int ry = (t + 1 < n0) ? RPS * (t + 1) : RPS * (t + 1 - n0);
-    CombineRegs<KC> cx;
-    combine_issue<KC, DC, LPR>(p, jx, rx, lane, cx);
-    if constexpr (kOverlap) {
-      CombineRegs<KC> cy;
-      if (has_y) combine_issue<KC, DC, LPR>(p, jy, ry, lane, cy);
-      combine_finish<KC, DC, LPR>(p, jx, lane, cx);
-      if (has_y) combine_finish<KC, DC, LPR>(p, jy, lane, cy);
-    } else {
-      combine_finish<KC, DC, LPR>(p, jx, lane, cx);
+    CombineRegs<KC> cx, cy;
+    MergeState<KC> tx, ty;
+    combine_issue<KC, DC, LPR>(p, jx, rx, 0, lane, cx);
+    if (has_y) combine_issue<KC, DC, LPR>(p, jy, ry, 0, lane, cy);
+    combine_fold<KC>(jx, 0, cx, tx);
+    combine_finish<KC, DC, LPR>(p, jx, lane, cx, tx);
+    if (has_y) {
+      combine_fold<KC>(jy, 0, cy, ty);
+      combine_finish<KC, DC, LPR>(p, jy, lane, cy, ty);
     }
   }
 }
@@ -1010,7 +1019,8 @@ __global__ __launch_bounds__(256) void verify_attn_bf16(AttnParams p) {
   // sit in the ring's wait counts.)
   constexpr bool kPair = (NT == 1);
   const int lane = threadIdx.x & 63;
-  const int w = uniform(blockIdx.x * p.wpw + (threadIdx.x >> 6));
+  // consecutive shares go to consecutive workgroups: a list shorter than the launch still uses every compute unit
+  const int w = uniform((threadIdx.x >> 6) * gridDim.x + blockIdx.x);
   const int col = lane & 15, grp = lane >> 4;
 
   // This wavefront's share: the first two segments come with the record, in one round trip; the plan's
@@ -1393,9 +1403,7 @@ __global__ __launch_bounds__(256) void reduce_partials(AttnParams p) {
   if (nq == 0 || 4 * sweep >= nq * p.g) return;
   const int owners = uniform(p.unit_owners[unit]);
   CombineJob job{Unit{b, kvh, uniform(p.seq_L[b]), nq}, owners & 0xFFFF, (owners >> 16) & 0xFFFF};
-  CombineRegs<KC> regs;
-  combine_issue<KC, DC>(p, job, 4 * sweep, lane, regs);
-  combine_finish<KC, DC>(p, job, lane, regs);
+  combine_sweep<KC, DC, 16, false>(p, job, 4 * sweep, lane);
 }
 
 // ---------------------------------------------------------------------------------------
@@ -1407,7 +1415,7 @@ constexpr int kRowChunk = 8;
 
 __global__ __launch_bounds__(256) void verify_attn_fp32(AttnParams p) {
   const int lane = threadIdx.x & 63;
-  const int w = uniform(blockIdx.x * p.wpw + (threadIdx.x >> 6));
+  const int w = uniform((threadIdx.x >> 6) * gridDim.x + blockIdx.x);  // as in verify_attn_bf16
   const int D = p.D;
   const int nd = (D + 63) / 64;  // head elements per lane (<= 4)
 
