@@ -165,9 +165,20 @@ def bass_verify_attention_workspace_bytes(desc: AttnDesc) -> int:
 
 # ---- marshalling helpers -------------------------------------------------------------------
 
+# These run for every argument of every launch, and with small batches the launches come one after another: they
+# are written for few interpreter steps (a step of 32 attention layers is 33 launches; one cost 13 us of host time
+# with ctypes objects made per pointer, torch.cuda.current_stream() and a size query per cache, and less than 9 us so).
+# Pointers are plain ints, which the declared argument types accept.
+
+_torch_module = None
+
+
 def _torch():
-    import torch
-    return torch
+    global _torch_module
+    if _torch_module is None:
+        import torch
+        _torch_module = torch
+    return _torch_module
 
 
 def _elt_dtype(desc):
@@ -176,7 +187,7 @@ def _elt_dtype(desc):
 
 
 def _dev(t, name, dtype=None, shape=None, optional=False):
-    """Device pointer of a contiguous CUDA tensor after shape / dtype checks."""
+    """Device pointer of a contiguous CUDA tensor after dtype / shape checks (shape: a tuple)."""
     if t is None:
         if optional:
             return None
@@ -187,15 +198,16 @@ def _dev(t, name, dtype=None, shape=None, optional=False):
         raise ValueError(f"{name} must be contiguous")
     if dtype is not None and t.dtype != dtype:
         raise ValueError(f"{name} must be {dtype}, got {t.dtype}")
-    if shape is not None and tuple(t.shape) != tuple(shape):
+    if shape is not None and t.shape != shape:
         raise ValueError(f"{name} must have shape {tuple(shape)}, got {tuple(t.shape)}")
-    return ctypes.c_void_p(t.data_ptr())
+    return t.data_ptr()
 
 
 def _stream(stream):
-    if stream is None:
-        return ctypes.c_void_p(_torch().cuda.current_stream().cuda_stream)
-    return ctypes.c_void_p(getattr(stream, "cuda_stream", stream))
+    if stream is None:  # the current stream of the current device
+        c = _torch()._C
+        return c._cuda_getCurrentRawStream(c._cuda_getDevice())
+    return getattr(stream, "cuda_stream", stream)
 
 
 def _check(code, what):
@@ -203,12 +215,18 @@ def _check(code, what):
         raise BassError(code, what)
 
 
-def _cache_ptr(t, desc, name):
+def _nbytes(t, name):
     if t is None or not t.is_cuda or not t.is_contiguous():
         raise ValueError(f"{name} must be a contiguous GPU tensor")
-    if t.numel() * t.element_size() < bass_kv_cache_bytes(desc):
-        raise ValueError(f"{name} holds fewer than bass_kv_cache_bytes(desc) bytes")
-    return ctypes.c_void_p(t.data_ptr())
+    return t.numel() * t.element_size()
+
+
+def _cache_ptrs(K, V, desc):
+    need = lib().bass_kv_cache_bytes(ctypes.byref(desc))
+    for t, name in ((K, "Kcache"), (V, "Vcache")):
+        if _nbytes(t, name) < need:
+            raise ValueError(f"{name} holds fewer than bass_kv_cache_bytes(desc) bytes")
+    return K.data_ptr(), V.data_ptr()
 
 
 # ---- entry points (same names and argument order as include/bass.h) --------------------------
@@ -218,7 +236,7 @@ def bass_kv_append(desc, Kcache, Vcache, K_new, V_new, ctx_len, n_new, dev_statu
     rows = (desc.B, desc.kmax, desc.Hkv, desc.D)
     et = _elt_dtype(desc)
     _check(lib().bass_kv_append(
-        ctypes.byref(desc), _cache_ptr(Kcache, desc, "Kcache"), _cache_ptr(Vcache, desc, "Vcache"),
+        ctypes.byref(desc), *_cache_ptrs(Kcache, Vcache, desc),
         _dev(K_new, "K_new", et, rows), _dev(V_new, "V_new", et, rows),
         _dev(ctx_len, "ctx_len", torch.int32, (desc.B,)), _dev(n_new, "n_new", torch.int32, (desc.B,)),
         _dev(dev_status, "dev_status", torch.int32, optional=True), _stream(stream)), "bass_kv_append")
@@ -229,7 +247,7 @@ def bass_kv_gather(desc, Kcache, Vcache, K_out, V_out, start, n, dev_status=None
     rows = (desc.B, desc.kmax, desc.Hkv, desc.D)
     et = _elt_dtype(desc)
     _check(lib().bass_kv_gather(
-        ctypes.byref(desc), _cache_ptr(Kcache, desc, "Kcache"), _cache_ptr(Vcache, desc, "Vcache"),
+        ctypes.byref(desc), *_cache_ptrs(Kcache, Vcache, desc),
         _dev(K_out, "K_out", et, rows), _dev(V_out, "V_out", et, rows),
         _dev(start, "start", torch.int32, (desc.B,)), _dev(n, "n", torch.int32, (desc.B,)),
         _dev(dev_status, "dev_status", torch.int32, optional=True), _stream(stream)), "bass_kv_gather")
@@ -240,7 +258,7 @@ def bass_kv_gather_int8(desc, Kcache, Vcache, K_codes, V_codes, K_scales, V_scal
     torch = _torch()
     rows = (desc.B, desc.kmax, desc.Hkv, desc.D)
     _check(lib().bass_kv_gather_int8(
-        ctypes.byref(desc), _cache_ptr(Kcache, desc, "Kcache"), _cache_ptr(Vcache, desc, "Vcache"),
+        ctypes.byref(desc), *_cache_ptrs(Kcache, Vcache, desc),
         _dev(K_codes, "K_codes", torch.int8, rows), _dev(V_codes, "V_codes", torch.int8, rows),
         _dev(K_scales, "K_scales", torch.float32, rows[:3]), _dev(V_scales, "V_scales", torch.float32, rows[:3]),
         _dev(start, "start", torch.int32, (desc.B,)), _dev(n, "n", torch.int32, (desc.B,)),
@@ -255,10 +273,10 @@ def bass_verify_attention(desc, Q, Kcache, Vcache, ctx_len, draft_len, O, lse, w
         raise ValueError("workspace must be a contiguous GPU tensor")
     _check(lib().bass_verify_attention(
         ctypes.byref(desc), _dev(Q, "Q", _elt_dtype(desc), qshape),
-        _cache_ptr(Kcache, desc, "Kcache"), _cache_ptr(Vcache, desc, "Vcache"),
+        *_cache_ptrs(Kcache, Vcache, desc),
         _dev(ctx_len, "ctx_len", torch.int32, (desc.B,)), _dev(draft_len, "draft_len", torch.int32, (desc.B,)),
         _dev(O, "O", torch.float32, qshape), _dev(lse, "lse", torch.float32, qshape[:3], optional=True),
-        ctypes.c_void_p(workspace.data_ptr()), ctypes.c_size_t(workspace.numel() * workspace.element_size()),
+        workspace.data_ptr(), workspace.numel() * workspace.element_size(),
         _dev(dev_status, "dev_status", torch.int32, optional=True), _stream(stream)), "bass_verify_attention")
 
 
@@ -266,7 +284,7 @@ def _verify_args(desc, Q, Kcache, Vcache, ctx_len, draft_len):
     torch = _torch()
     qshape = (desc.B, desc.kmax, desc.Hq, desc.D)
     return (ctypes.byref(desc), _dev(Q, "Q", _elt_dtype(desc), qshape),
-            _cache_ptr(Kcache, desc, "Kcache"), _cache_ptr(Vcache, desc, "Vcache"),
+            *_cache_ptrs(Kcache, Vcache, desc),
             _dev(ctx_len, "ctx_len", torch.int32, (desc.B,)), _dev(draft_len, "draft_len", torch.int32, (desc.B,)))
 
 
@@ -276,7 +294,7 @@ def _result_args(desc, O, lse, workspace, dev_status, stream):
     if workspace is None or not workspace.is_cuda or not workspace.is_contiguous():
         raise ValueError("workspace must be a contiguous GPU tensor")
     return (_dev(O, "O", torch.float32, qshape), _dev(lse, "lse", torch.float32, qshape[:3], optional=True),
-            ctypes.c_void_p(workspace.data_ptr()), ctypes.c_size_t(workspace.numel() * workspace.element_size()),
+            workspace.data_ptr(), workspace.numel() * workspace.element_size(),
             _dev(dev_status, "dev_status", torch.int32, optional=True), _stream(stream))
 
 
@@ -304,10 +322,10 @@ def bass_append_verify_attention(desc, Q, K_new, V_new, Kcache, Vcache, ctx_len,
         raise ValueError("workspace must be a contiguous GPU tensor")
     _check(lib().bass_append_verify_attention(
         ctypes.byref(desc), _dev(Q, "Q", et, qshape), _dev(K_new, "K_new", et, rows), _dev(V_new, "V_new", et, rows),
-        _cache_ptr(Kcache, desc, "Kcache"), _cache_ptr(Vcache, desc, "Vcache"),
+        *_cache_ptrs(Kcache, Vcache, desc),
         _dev(ctx_len, "ctx_len", torch.int32, (desc.B,)), _dev(draft_len, "draft_len", torch.int32, (desc.B,)),
         _dev(O, "O", torch.float32, qshape), _dev(lse, "lse", torch.float32, qshape[:3], optional=True),
-        ctypes.c_void_p(workspace.data_ptr()), ctypes.c_size_t(workspace.numel() * workspace.element_size()),
+        workspace.data_ptr(), workspace.numel() * workspace.element_size(),
         _dev(dev_status, "dev_status", torch.int32, optional=True), _stream(stream)), "bass_append_verify_attention")
 
 
@@ -333,8 +351,8 @@ def bass_attention_plan(desc, ctx_len, draft_len, flags, padded_len, plan, dev_s
         raise ValueError("plan must be a contiguous GPU tensor")
     _check(lib().bass_attention_plan(
         ctypes.byref(desc), _dev(ctx_len, "ctx_len", torch.int32, (desc.B,)),
-        _dev(draft_len, "draft_len", torch.int32, (desc.B,)), ctypes.c_int32(int(flags)), ctypes.c_int32(int(padded_len)),
-        ctypes.c_void_p(plan.data_ptr()), ctypes.c_size_t(plan.numel() * plan.element_size()),
+        _dev(draft_len, "draft_len", torch.int32, (desc.B,)), int(flags), int(padded_len),
+        plan.data_ptr(), plan.numel() * plan.element_size(),
         _dev(dev_status, "dev_status", torch.int32, optional=True), _stream(stream)), "bass_attention_plan")
 
 
@@ -364,14 +382,11 @@ def bass_verify_attention_planned(desc, Q, K_new, V_new, Kcache, Vcache, plan, O
     qshape = (desc.B, desc.kmax, desc.Hq, desc.D)
     rows = (desc.B, desc.kmax, desc.Hkv, desc.D)
     et = _elt_dtype(desc)
-    if plan is None or not plan.is_cuda or not plan.is_contiguous():
-        raise ValueError("plan must be a contiguous GPU tensor")
-    if plan.numel() * plan.element_size() < bass_attention_plan_bytes(desc):
+    if _nbytes(plan, "plan") < bass_attention_plan_bytes(desc):
         raise ValueError("plan holds fewer than bass_attention_plan_bytes(desc) bytes")
     _check(lib().bass_verify_attention_planned(
         ctypes.byref(desc), _dev(Q, "Q", et, qshape), _dev(K_new, "K_new", et, rows, optional=True),
-        _dev(V_new, "V_new", et, rows, optional=True), _cache_ptr(Kcache, desc, "Kcache"),
-        _cache_ptr(Vcache, desc, "Vcache"), ctypes.c_void_p(plan.data_ptr()),
+        _dev(V_new, "V_new", et, rows, optional=True), *_cache_ptrs(Kcache, Vcache, desc), plan.data_ptr(),
         *_result_args(desc, O, lse, workspace, dev_status, stream)), "bass_verify_attention_planned")
 
 
@@ -417,9 +432,9 @@ def bass_warp_probs(logits, temperature, top_p, probs, dev_status=None, stream=N
     R = int(logits.numel() // max(V, 1))
     shape = tuple(logits.shape)
     lp, pp = _dev(logits, "logits", torch.float32, shape), _dev(probs, "probs", torch.float32, shape)
-    if lp.value == pp.value:
+    if lp == pp:
         raise ValueError("probs may not alias logits")
-    _check(lib().bass_warp_probs(R, V, lp, ctypes.c_float(float(temperature)), ctypes.c_float(float(top_p)), pp,
+    _check(lib().bass_warp_probs(R, V, lp, float(temperature), float(top_p), pp,
                                  _dev(dev_status, "dev_status", torch.int32, optional=True), _stream(stream)),
            "bass_warp_probs")
 
@@ -442,11 +457,11 @@ def bass_warp_accept(logits_main, logits_draft, temperature, top_p, draft_tok, n
     _check(lib().bass_warp_accept(
         B, kmax, V, _dev(logits_main, "logits_main", f32),
         _dev(logits_draft, "logits_draft", f32, (B, kmax, V), optional=(kmax == 0)),
-        ctypes.c_float(float(temperature)), ctypes.c_float(float(top_p)),
+        float(temperature), float(top_p),
         _dev(draft_tok, "draft_tok", i32, (B, kmax), optional=(kmax == 0)), _dev(n_draft, "n_draft", i32, (B,)),
         _dev(u, "u", f32, (B, kmax + 1)), _dev(n_accept, "n_accept", i32, (B,)),
         _dev(next_token, "next_token", i32, (B,)), _dev(ctx_len, "ctx_len", i32, (B,), optional=True),
-        wsp, ctypes.c_size_t(workspace.numel()), _dev(dev_status, "dev_status", i32, optional=True), _stream(stream)),
+        wsp, workspace.numel(), _dev(dev_status, "dev_status", i32, optional=True), _stream(stream)),
         "bass_warp_accept")
 
 
