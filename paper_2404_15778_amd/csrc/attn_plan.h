@@ -90,16 +90,19 @@ struct Split {
 // Even division over exactly n shares: they differ by at most one entry.
 BASS_HD inline Split make_split(int total, int n) { return Split{total / n, total % n, total}; }
 
+// A short list is divided over fewer shares of about min_entries each: every share of a unit costs a partial
+// result, its acknowledged store, and a share of the merge that waits for the last of them.
+BASS_HD inline int shares_wanted(const PlanShape& s, int total) {
+  return s.min_entries > 0 ? imax(1, imin(s.nshares, imax(total / s.min_entries, s.per_unit * s.B * s.Hkv))) : s.nshares;
+}
+
 // The division a plan uses.  A launch lasts as long as its longest share, and with an even division over
 // `target` shares most of them are one entry longer than total / target.  If the launch has room for more
 // shares than it aims at (nshares > target), all shares get floor(total / target) entries instead and there
 // are correspondingly more of them (at most nshares: the share length grows until they fit); the last one
 // takes what is left, the launch's remaining wavefronts stay idle.
 BASS_HD inline Split plan_split(const PlanShape& s, int total) {
-  // A short list is divided over fewer shares of about min_entries each: every share of a unit costs a partial
-  // result, its acknowledged store, and a share of the merge that waits for the last of them.
-  const int wanted = s.min_entries > 0 ? imax(1, imin(s.nshares, imax(total / s.min_entries, s.per_unit * s.B * s.Hkv))) : s.nshares;
-  if (s.target >= s.nshares || total <= 0) return make_split(total, wanted);
+  if (s.target >= s.nshares || total <= 0) return make_split(total, shares_wanted(s, total));
   int per = imax(1, total / s.target);
   while ((total + per - 1) / per > s.nshares) ++per;
   return Split{per, 0, total};
@@ -130,8 +133,9 @@ struct ShareRecord {
   int32_t overflow;   // index of segment 2 in the overflow list (segments 2 .. nseg-1 are consecutive there); it is
                       // share + unit index of that segment, which keeps the runs of different shares apart
   int32_t signature;  // plan_signature() of the plan: what a launch checks before it trusts the record
-  int32_t flags;      // kRecAnyInactive (the same in every record)
+  int32_t flags;      // kRecAnyInactive, kRecFewShares (the same in every record)
 };
+constexpr int32_t kRecFewShares = 2;    // the list was divided over fewer shares than the launch has (the same in every record)
 constexpr int32_t kRecAnyInactive = 1;  // some sequence has no query token: its output rows still have to be cleared
 
 // What a launch and its plan must agree on, folded into one word that every record carries (a launch then

@@ -713,7 +713,7 @@ template <int D, int NT, bool kMasked, bool kI8 = false>
 __device__ inline void block_step(KvRegs<D>& r, const bf16x8 (&qf)[NT][D / 32], RowState<D, NT>& st, int tok0,
                                   int n_valid, const int (&lim)[NT], float scale_log2, int lane,
                                   bool fused = false, const NewRows& nr = NewRows{}, uint4* kdst = nullptr,
-                                  uint4* vdst = nullptr, const I8Operands<D, NT>* i8 = nullptr) {
+                                  uint4* vdst = nullptr, const I8Operands<D, NT>* i8 = nullptr, bool fine = false) {
   constexpr int KS = D / 32, MT = D / 16;
   const int grp = lane >> 4;
   // INT8 caches: a score is the integer product (q codes . k codes) * q-scale * k-scale, a value is
@@ -843,9 +843,22 @@ __device__ inline void block_step(KvRegs<D>& r, const bf16x8 (&qf)[NT][D / 32], 
     for (int j = 0; j < 8; ++j) {
       const float pj = __builtin_amdgcn_exp2f(s[j] - m_use);
       psum += pj;
-      pf[j] = (__bf16)(kI8 ? pj * vsl[j] : pj);
+      s[j] = kI8 ? pj * vsl[j] : pj;
+      pf[j] = (__bf16)s[j];
     }
     st.l[nt] += psum;
+    // Short lists over fewer shares (wave-uniform): what the rounding of the probabilities to bf16 left over is
+    // multiplied as well.  A share's first block holds its largest probability, 1, which is exact; with a fifth
+    // as many shares per unit that is lost for most of them (one sequence of 32 heads: error against 64 bits
+    // 1.3e-3 with 24 shares per unit, 1.6e-3 with 5, 2.3e-6 this way; the step of 32 layers 463 -> 489 us).
+    if (fine) {
+      bf16x8 pr;
+#pragma unroll
+      for (int j = 0; j < 8; ++j) pr[j] = (__bf16)(s[j] - (float)pf[j]);
+#pragma unroll
+      for (int mt = 0; mt < MT; ++mt)
+        st.acc[nt][mt] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(__builtin_bit_cast(bf16x8, r.v[mt]), pr, st.acc[nt][mt], 0, 0, 0);
+    }
 #pragma unroll
     for (int mt = 0; mt < MT; ++mt)
       st.acc[nt][mt] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(__builtin_bit_cast(bf16x8, r.v[mt]), pf, st.acc[nt][mt], 0, 0, 0);
@@ -856,14 +869,14 @@ template <int D, int NT, bool kI8 = false>
 __device__ inline void block_dispatch(KvRegs<D>& r, const bf16x8 (&qf)[NT][D / 32], RowState<D, NT>& st, int blk,
                                       int L, int n_valid, const int (&lim)[NT], float scale_log2, int lane,
                                       bool fused, const NewRows& nr, uint4* kdst, uint4* vdst,
-                                      const I8Operands<D, NT>* i8 = nullptr) {
+                                      const I8Operands<D, NT>* i8 = nullptr, bool fine = false) {
   const int tok0 = blk * kBlockTokens;
   // plain step: every token of the block is visible to every query (tokens <= L) and, with a fused
   // append, none of them is new (tokens < L)
   if (tok0 + kBlockTokens - 1 < L + (fused ? 0 : 1))
-    block_step<D, NT, false, kI8>(r, qf, st, tok0, n_valid, lim, scale_log2, lane, false, NewRows{}, nullptr, nullptr, i8);
+    block_step<D, NT, false, kI8>(r, qf, st, tok0, n_valid, lim, scale_log2, lane, false, NewRows{}, nullptr, nullptr, i8, fine);
   else
-    block_step<D, NT, true, kI8>(r, qf, st, tok0, n_valid, lim, scale_log2, lane, fused, nr, kdst, vdst, i8);
+    block_step<D, NT, true, kI8>(r, qf, st, tok0, n_valid, lim, scale_log2, lane, fused, nr, kdst, vdst, i8, fine);
 }
 
 // fp32 path: the wavefront whose share holds the new rows copies them into the (token-major) cache
@@ -1031,6 +1044,7 @@ __global__ __launch_bounds__(256) void verify_attn_bf16(AttnParams p) {
   Segment sb = load_segment(&rec->seg[1]);
   int nseg_plan = uniform(rec->nseg), overflow = uniform(rec->overflow);
   const int rec_flags = uniform(rec->flags);
+  const bool fine = (rec_flags & kRecFewShares) != 0;
   __builtin_amdgcn_sched_barrier(0);  // the loads above are issued here, whatever is scheduled below
   bool ok;
   int nseg;
@@ -1164,9 +1178,9 @@ __global__ __launch_bounds__(256) void verify_attn_bf16(AttnParams p) {
         const I8Operands<D, NT> i8{r.k, qc.q, qc.q_scale_log2, &sc};
         const bf16x8 no_q[NT][D / 32] = {};
         block_dispatch<D, NT, true>(t, no_q, st, cur_blk + s, cur_L, cur_valid, qc.lim, p.scale_log2, lane, false,
-                                    cur_new, nullptr, nullptr, &i8);  // the codes are patched already: no fused work inside
+                                    cur_new, nullptr, nullptr, &i8, fine);  // the codes are patched already: no fused work inside
       } else {
-        block_dispatch<D, NT>(r, qc.q, st, cur_blk + s, cur_L, cur_valid, qc.lim, p.scale_log2, lane, fused, cur_new, kdst, vdst);
+        block_dispatch<D, NT>(r, qc.q, st, cur_blk + s, cur_L, cur_valid, qc.lim, p.scale_log2, lane, fused, cur_new, kdst, vdst, nullptr, fine);
       }
     };
     // Unused query rows of a unit are cleared by the wavefront that holds the unit's last block (it is handed
