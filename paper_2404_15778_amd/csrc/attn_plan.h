@@ -53,6 +53,7 @@ struct PlanShape {
                        // positions (0: over its own length); the positions beyond its length are masked
   int32_t min_entries = 0;  // shares are not made shorter than this many entries (0: no bound) ...
   int32_t per_unit = 0;     // ... but this many per unit there may always be
+  int32_t used = 0;         // the list is divided over at most this many of the shares (0: all of them)
 };
 
 // Real blocks of a sequence (per kv head) after clamping; 0 for an inactive sequence.
@@ -93,7 +94,8 @@ BASS_HD inline Split make_split(int total, int n) { return Split{total / n, tota
 // A short list is divided over fewer shares of about min_entries each: every share of a unit costs a partial
 // result, its acknowledged store, and a share of the merge that waits for the last of them.
 BASS_HD inline int shares_wanted(const PlanShape& s, int total) {
-  return s.min_entries > 0 ? imax(1, imin(s.nshares, imax(total / s.min_entries, s.per_unit * s.B * s.Hkv))) : s.nshares;
+  const int most = s.used > 0 ? imin(s.used, s.nshares) : s.nshares;
+  return s.min_entries > 0 ? imax(1, imin(most, imax(total / s.min_entries, s.per_unit * s.B * s.Hkv))) : most;
 }
 
 // The division a plan uses.  A launch lasts as long as its longest share, and with an even division over

@@ -137,20 +137,27 @@ constexpr int kPlainBefore = 0;   // kernel; measured: +0.5 % with the fused app
 // least, 576).
 constexpr int kMinEntries = 5;
 constexpr int kPerUnit = 5, kPerUnitInt8 = 8;
-constexpr int kMaxStagedElems = 2048;  // kmax * D up to which the step's rows are appended inside the attention launch
+// Workgroups of the workgroup-level kernels.  bf16: one per compute unit (512: more partials, no faster).  INT8: two,
+// because a step's conversions and softmax leave issue slots to fill: 16 sequences of 1024 - 4096 tokens, 64/8 heads, 64
+// rows, 128 / 256 / 384 / 512 / 640 / 1024 workgroups: 1467 / 869 / 788 / 756 / 889 / 903 us for 16 layers; 32 heads and
+// 32 rows: 1665 / 972 / 835 / 745 / 919 / 949.
+constexpr int kTileShares = 256, kTileSharesInt8 = 512;
+constexpr int kMaxStagedElems = 2048;  // kmax * D up to which the one-tile kernels stage the step's rows in LDS
 
 int attention_waves_setting();  // bass_set_attention_waves (0 = defaults); verify_attention.hip
 
 struct LaunchShape {
   bool mfma;        // bf16 or INT8 caches: the matrix-core kernels
-  bool tiles;       // bf16 caches, more than one 16-row query tile per kv head: the workgroup-level kernel
-  bool fused_append;  // the step's rows are appended inside the attention launch
-  int rows_max, nwaves, nshares, target, pad, pad_before, min_entries, per_unit, fused_reduce;
+  bool tiles;       // more than one 16-row query tile per kv head: the workgroup-level kernels
+  bool fused_append;  // the step's rows are appended inside the attention launch, and its plan says so
+  bool tiles_append;  // longer drafts, workgroup-level kernels: they patch a block at a time and stage nothing, so
+                      // planned launches append there too; the plan is the one of a launch that does not append
+  int rows_max, nwaves, nshares, used_shares, target, pad, pad_before, min_entries, per_unit, fused_reduce;
 };
 
-// many_rows: more than one 16-row query tile per kv head (grouped-query attention); a separate
-// launch merges the partials there, and a wider spread measured best: 896, and with INT8 caches, where the
-// kernel is bound by its conversion instructions, every SIMD (1024).  One query tile: 768 for INT8 caches
+// many_rows: more than one 16-row query tile per kv head (grouped-query attention), the workgroup-level kernels:
+// the count sizes the plan (INT8) and grades an explicit setting; how many workgroups there are by default stands
+// at kTileShares.  One query tile: 768 for INT8 caches
 // too -- as 256 workgroups of three they measured level with 1024 on the long-context shape and 2 - 3 %
 // shorter on the benchmark shape (a fourth wavefront on a compute unit costs the others issue slots).
 inline int attention_waves(int setting, bool many_rows, bool int8) {
@@ -165,19 +172,23 @@ inline LaunchShape launch_shape(const bass_attn_desc* d, bool append) {
   const int setting = attention_waves_setting();
   s.rows_max = d->kmax * (d->Hq / d->Hkv);
   s.mfma = d->dtype != BASS_DTYPE_FP32;
-  s.tiles = d->dtype == BASS_DTYPE_BF16 && s.rows_max > 16;
+  const bool int8 = d->dtype == BASS_DTYPE_INT8KV;
+  s.tiles = s.mfma && s.rows_max > 16;
   s.fused_append = append && (d->dtype == BASS_DTYPE_FP32 || (int64_t)d->kmax * d->D <= kMaxStagedElems);
+  s.tiles_append = append && s.tiles && !s.fused_append;
   // (a launch wider than the shares it aims at, with all shares equally long -- plan_split -- was measured
   // 1 - 2 % slower than the even division on the benchmark shapes: more wavefronts, more partials to merge)
-  const int aim = attention_waves(setting, s.mfma && s.rows_max > 16, d->dtype == BASS_DTYPE_INT8KV);
+  const int aim = attention_waves(setting, s.mfma && s.rows_max > 16, int8);
   s.nwaves = aim;
   // the workgroup-level kernel takes one stretch per workgroup (default 256, measured best: fewer
   // partials to merge; a wavefront setting W gives W / 2)
-  s.nshares = !s.tiles ? s.nwaves : setting > 0 ? (s.nwaves / 2 > 16 ? s.nwaves / 2 : 16) : 256;
+  const int stretches = setting > 0 ? (s.nwaves / 2 > 16 ? s.nwaves / 2 : 16) : (int8 ? kTileSharesInt8 : kTileShares);
+  s.nshares = s.tiles && !int8 ? stretches : s.nwaves;  // INT8: plans keep room for a share per wavefront
+  s.used_shares = s.tiles ? imin(stretches, s.nshares) : s.nshares;
   s.target = !s.tiles ? aim : s.nshares;
   s.pad = s.fused_append ? kAppendPad : kPlainPad;
   s.min_entries = setting > 0 || s.tiles || !s.mfma ? 0 : kMinEntries;
-  s.per_unit = d->dtype == BASS_DTYPE_INT8KV ? kPerUnitInt8 : kPerUnit;
+  s.per_unit = int8 ? kPerUnitInt8 : kPerUnit;
   s.pad_before = 0;
   if (s.mfma && s.rows_max <= 16) s.pad_before = s.fused_append ? kAppendBefore : kPlainBefore;
   // one query tile per kv head: the last-arriving wavefront reduces; more: a second, chip-wide launch

@@ -935,11 +935,12 @@ struct QFragI8 {
 };
 
 template <int D, int NT>
-__device__ inline void load_queries_i8(const AttnParams& p, const Unit& u, bool enable, int col, int grp, QFragI8<D, NT>& f) {
+__device__ inline void load_queries_i8(const AttnParams& p, const Unit& u, bool enable, int col, int grp, QFragI8<D, NT>& f,
+                                       int row0 = 0) {
   const int rows = u.nq * p.g;
 #pragma unroll
   for (int nt = 0; nt < NT; ++nt) {
-    const int rrow = nt * 16 + col;
+    const int rrow = row0 + nt * 16 + col;
     const bool ok = enable && rrow < rows;
     const int i = ok ? row_token(p, rrow) : 0, hg = ok ? rrow - i * p.g : 0;
     f.lim[nt] = u.L + i;
@@ -1020,7 +1021,9 @@ __device__ inline void finalize_single(const AttnParams& p, const Unit& u, const
   }
 }
 
-template <int D, int NT, bool kI8 = false>
+// kFew: so few units that a plan may have divided the list over fewer shares (the records say whether it did); the
+// others are spared the branch in every block step (1 % of a step of eight sequences).
+template <int D, int NT, bool kI8, bool kFew>
 __global__ __launch_bounds__(256) void verify_attn_bf16(AttnParams p) {
   // uint4 per block: 32 tokens of D bf16, or of D INT8 codes followed by 32 fp32 scales
   constexpr ptrdiff_t kBlkVec = kI8 ? 2 * D + 8 : (ptrdiff_t)kBlockTokens * D * 2 / 16;
@@ -1044,7 +1047,7 @@ __global__ __launch_bounds__(256) void verify_attn_bf16(AttnParams p) {
   Segment sb = load_segment(&rec->seg[1]);
   int nseg_plan = uniform(rec->nseg), overflow = uniform(rec->overflow);
   const int rec_flags = uniform(rec->flags);
-  const bool fine = (rec_flags & kRecFewShares) != 0;
+  const bool fine = kFew && (rec_flags & kRecFewShares) != 0;
   __builtin_amdgcn_sched_barrier(0);  // the loads above are issued here, whatever is scheduled below
   bool ok;
   int nseg;
@@ -1197,39 +1200,22 @@ __global__ __launch_bounds__(256) void verify_attn_bf16(AttnParams p) {
       next_sa = arrived_segment(nextA);
       next_sb = arrived_segment(nextB);
     };
-    if constexpr (NT <= 2) {
-      // three-deep register ring: two blocks (32 KiB per wavefront) in flight while one is computed
-      Regs r1, r2;  // r0 is on its way already
-      fetch(r1, 1);
-      if (stage1) {
-        commit(u1, 0, sr, new1);  // these loads were issued before the fetches
-        stage_rest();
-      }
-      clear_unused();
-      next_arrived();
-      for (int s = 0; s < n; s += 3) {
-        fetch(r2, s + 2);
-        step(r0, s);
-        fetch(r0, s + 3);
-        if (s + 1 < n) step(r1, s + 1);
-        fetch(r1, s + 4);
-        if (s + 2 < n) step(r2, s + 2);
-      }
-    } else {
-      // many query rows need the registers for accumulators: two-deep ring
-      Regs r1;
-      if (stage1) {
-        commit(u1, 0, sr, new1);
-        stage_rest();
-      }
-      clear_unused();
-      next_arrived();
-      for (int s = 0; s < n; s += 2) {
-        fetch(r1, s + 1);
-        step(r0, s);
-        fetch(r0, s + 2);
-        if (s + 1 < n) step(r1, s + 1);
-      }
+    // three-deep register ring: two blocks (32 KiB per wavefront) in flight while one is computed
+    Regs r1, r2;  // r0 is on its way already
+    fetch(r1, 1);
+    if (stage1) {
+      commit(u1, 0, sr, new1);  // these loads were issued before the fetches
+      stage_rest();
+    }
+    clear_unused();
+    next_arrived();
+    for (int s = 0; s < n; s += 3) {
+      fetch(r2, s + 2);
+      step(r0, s);
+      fetch(r0, s + 3);
+      if (s + 1 < n) step(r1, s + 1);
+      fetch(r1, s + 4);
+      if (s + 2 < n) step(r2, s + 2);
     }
     // A unit that lies wholly inside this share (common with many short sequences) is finished from the
     // registers; the others leave a partial, and the wavefront that delivers a unit's last partial merges.
@@ -1344,21 +1330,21 @@ __global__ __launch_bounds__(256, 2) void verify_attn_tiles_bf16(AttnParams p) {
       const int tok0 = (blk0 + s) * kBlockTokens;
       if (kFused && s < n && u.nq > 0 && tok0 < u.L + u.nq && tok0 + kBlockTokens > u.L) {
         __syncthreads();  // the block is complete in LDS
-        const int i_hi = min(u.nq, tok0 + kBlockTokens - u.L);
-        for (int i = max(0, tok0 - u.L) + wv; i < i_hi; i += 4) {  // new rows of this block, one per wavefront and turn
-          const int tw = u.L + i - tok0;                              // its token slot in the block
-          if (lane < D / 8) {                                         // one 16-byte chunk of the row per lane
-            const size_t src = (((size_t)u.b * p.kmax + i) * p.Hkv + u.kvh) * D + 8 * lane;
-            const uint4 kv = *(const uint4*)((const uint16_t*)p.Knew + src);
-            const uint4 vv = *(const uint4*)((const uint16_t*)p.Vnew + src);
-            const size_t ko = k_elem_offset(D, tw, 8 * lane) / 8;  // in 16-byte chunks
-            ring_k[slot][ko] = kv;
-            ((uint4*)const_cast<void*>(p.Kc))[vec0 + (ptrdiff_t)s * kBlkVec + (ptrdiff_t)ko] = kv;
-            const uint32_t vw[4] = {vv.x, vv.y, vv.z, vv.w};
+        const int i_lo = max(0, tok0 - u.L), i_hi = min(u.nq, tok0 + kBlockTokens - u.L);
+        // the new rows of this block by 16-byte chunks, 256 at a time: 16 rows of 128 head elements per round trip
+        for (int c = threadIdx.x; c < (i_hi - i_lo) * (D / 8); c += 256) {
+          const int i = i_lo + c / (D / 8), ck = c % (D / 8);
+          const int tw = u.L + i - tok0;  // its token slot in the block
+          const size_t src = (((size_t)u.b * p.kmax + i) * p.Hkv + u.kvh) * D + 8 * ck;
+          const uint4 kv = *(const uint4*)((const uint16_t*)p.Knew + src);
+          const uint4 vv = *(const uint4*)((const uint16_t*)p.Vnew + src);
+          const size_t ko = k_elem_offset(D, tw, 8 * ck) / 8;  // in 16-byte chunks
+          ring_k[slot][ko] = kv;
+          ((uint4*)const_cast<void*>(p.Kc))[vec0 + (ptrdiff_t)s * kBlkVec + (ptrdiff_t)ko] = kv;
+          const uint32_t vw[4] = {vv.x, vv.y, vv.z, vv.w};
 #pragma unroll
-            for (int e = 0; e < 8; ++e)
-              ((uint16_t*)&ring_v[slot][0])[v_elem_offset(D, tw, 8 * lane + e)] = (uint16_t)(vw[e >> 1] >> (16 * (e & 1)));
-          }
+          for (int e = 0; e < 8; ++e)
+            ((uint16_t*)&ring_v[slot][0])[v_elem_offset(D, tw, 8 * ck + e)] = (uint16_t)(vw[e >> 1] >> (16 * (e & 1)));
         }
         __syncthreads();  // the patches are visible
         for (int c = threadIdx.x; c < (D / 16) * 64; c += 256) {  // V chunks that hold a new token: back into the cache
@@ -1390,6 +1376,187 @@ __global__ __launch_bounds__(256, 2) void verify_attn_tiles_bf16(AttnParams p) {
     for (int s = 0; s < n; s += kTileAhead) {  // workgroup-uniform trip count
 #pragma unroll
       for (int j = 0; j < kTileAhead; ++j) step(g[j], s + j);
+    }
+    if (active) store_partial<D, 1>(p, u, wg, st, col, grp, row0);
+  }
+}
+
+// ---------------------------------------------------------------------------------------
+// The same for INT8 caches.  A block's codes and scales are fetched once by the workgroup; the wavefront that fetched a
+// V chunk widens it to bf16 on its way into LDS, so that every code is widened once per block instead of once per
+// query tile, and no wavefront holds more than one tile.  (Up to four tiles in one wavefront spilled registers and left
+// one wavefront per SIMD: what bounds these shapes is instruction issue, not memory.  Attention of 16 sequences of 1024 -
+// 4096 tokens, 64/8 heads of 128, 64 rows per kv head, with its merge: 72 -> 48 us per layer, 94 MB.)
+// ---------------------------------------------------------------------------------------
+constexpr int kTileAheadI8 = 4;  // blocks a workgroup has in flight from memory
+
+template <int D, bool kFused>
+__global__ __launch_bounds__(256, 2) void verify_attn_tiles_i8(AttnParams p) {
+  constexpr int kCodeVec = 2 * D;             // uint4 of codes per block and tensor
+  constexpr int kBlkVec = kCodeVec + 8;       // ... and its 32 scales
+  constexpr int kChunks = D / 32;             // 64-lane chunks of codes per tensor
+  constexpr int kLoads = 2 * kChunks / 4;     // chunks a wavefront moves per block: numbers wv, wv + 4, ... of K's, then V's
+  __shared__ uint4 ring_k[2][kCodeVec];       // codes
+  __shared__ uint4 ring_v[2][2 * kCodeVec];   // the codes as bf16, fragments as in a bf16 cache
+  __shared__ __align__(16) float ring_s[2][2 * kBlockTokens];  // K scales, V scales
+  const int lane = threadIdx.x & 63, wv = uniform(threadIdx.x >> 6);
+  const int col = lane & 15, grp = lane >> 4;
+  const int wg = blockIdx.x;
+  const int row0 = 16 * wv;
+
+  const ShareRecord* rec = p.records + wg;
+  const int nseg = uniform(rec->nseg), overflow = uniform(rec->overflow);
+  if (!record_matches(p, rec)) {
+    report_mismatch(p, wg == 0 && threadIdx.x == 0);
+    return;
+  }
+
+  const uint4* kc = (const uint4*)p.Kc;
+  const uint4* vc = (const uint4*)p.Vc;
+  struct Stage {
+    u32x4 c[kLoads];
+    float scale;
+  };
+
+  for (int si = 0; si < nseg; ++si) {
+    const Segment seg = si == 0 ? load_segment(&rec->seg[0]) : later_segment(p, rec, overflow, si);
+    const Unit u = unit_of(seg);
+    const int n = seg.n;
+    const bool active = row0 < u.nq * p.g;  // this wavefront owns a query tile of the unit
+    QFragI8<D, 1> q;
+    load_queries_i8<D, 1>(p, u, active, col, grp, q, row0);
+    RowState<D, 1> st;
+    clear_state<D, 1>(st);
+    const int blk0 = seg.first;
+    const ptrdiff_t vec0 = (((ptrdiff_t)u.b * p.Hkv + u.kvh) * p.nblk_cap + blk0) * kBlkVec;
+
+    // all fetches unconditional (exact wait counts); one past the end re-reads the stretch's first block
+    auto fetch = [&](Stage& g, int s) {
+      const ptrdiff_t off = vec0 + (s < n ? (ptrdiff_t)s * kBlkVec : 0);
+#pragma unroll
+      for (int i = 0; i < kLoads; ++i) {
+        const int c = wv + 4 * i;
+        const uint4* src = (c < kChunks ? kc + off + c * 64 : vc + off + (c - kChunks) * 64) + lane;
+        g.c[i] = __builtin_nontemporal_load((const u32x4*)src);
+      }
+      g.scale = ((const float*)((lane < kBlockTokens ? kc : vc) + off + kCodeVec))[lane % kBlockTokens];
+    };
+    auto step = [&](Stage& g, int s) {
+      const int slot = s & 1;
+#pragma unroll
+      for (int i = 0; i < kLoads; ++i) {
+        const int c = wv + 4 * i;
+        if (c < kChunks) {
+          ring_k[slot][c * 64 + lane] = __builtin_bit_cast(uint4, g.c[i]);
+        } else {
+          const int m = c - kChunks;
+          ring_v[slot][(2 * m) * 64 + lane] = codes_to_bf16(g.c[i][0], g.c[i][1]);
+          ring_v[slot][(2 * m + 1) * 64 + lane] = codes_to_bf16(g.c[i][2], g.c[i][3]);
+        }
+      }
+      if (wv == 0) ring_s[slot][lane] = g.scale;
+      fetch(g, s + kTileAheadI8);
+      // Fused append: as in the bf16 kernel; the rows are quantized as the append kernel does (a row's D / 8 lanes agree
+      // on its largest magnitude), codes and scales go into LDS and, K and the scales, into the cache; V chunks
+      // follow from LDS.
+      const int tok0 = (blk0 + s) * kBlockTokens;
+      if (kFused && s < n && u.nq > 0 && tok0 < u.L + u.nq && tok0 + kBlockTokens > u.L) {
+        uint8_t* kblk = (uint8_t*)((uint4*)const_cast<void*>(p.Kc) + vec0 + (ptrdiff_t)s * kBlkVec);
+        uint8_t* vblk = (uint8_t*)((uint4*)const_cast<void*>(p.Vc) + vec0 + (ptrdiff_t)s * kBlkVec);
+        __syncthreads();  // the block is complete in LDS
+        const int i_lo = max(0, tok0 - u.L), n_ck = (min(u.nq, tok0 + kBlockTokens - u.L) - i_lo) * (D / 8);
+        for (int c0 = 0; c0 < n_ck; c0 += 256) {  // the new rows of this block, 8 elements per lane
+          const int c = min(c0 + (int)threadIdx.x, n_ck - 1);  // whole rows: a row's lanes stay together past the end too
+          const int ck = threadIdx.x % (D / 8), i = i_lo + c / (D / 8);
+          const int tw = u.L + i - tok0;  // its token slot in the block
+          const size_t src = (((size_t)u.b * p.kmax + i) * p.Hkv + u.kvh) * D + 8 * ck;
+          const uint4 kv = *(const uint4*)((const uint16_t*)p.Knew + src);
+          const uint4 vv = *(const uint4*)((const uint16_t*)p.Vnew + src);
+          float ka = amax8(kv), va = amax8(vv);
+#pragma unroll
+          for (int o = D / 16; o >= 1; o >>= 1) {
+            ka = fmaxf(ka, __shfl_xor(ka, o));
+            va = fmaxf(va, __shfl_xor(va, o));
+          }
+          const float kinv = ka > 0.f ? 127.0f / ka : 0.f;
+          const float vinv = va > 0.f ? 127.0f / va : 0.f;
+          if (c0 + (int)threadIdx.x < n_ck) {
+            const uint2 kq = quantize8(kv, kinv), vq = quantize8(vv, vinv);
+            const size_t ko = i8_k_offset(D, tw, 8 * ck);
+            *(uint2*)((uint8_t*)&ring_k[slot][0] + ko) = kq;
+            *(uint2*)(kblk + ko) = kq;
+            const uint4 vb = codes_to_bf16(vq.x, vq.y);
+            const uint32_t vw[4] = {vb.x, vb.y, vb.z, vb.w};
+#pragma unroll
+            for (int e = 0; e < 8; ++e)
+              ((uint16_t*)&ring_v[slot][0])[v_elem_offset(D, tw, 8 * ck + e)] = (uint16_t)(vw[e >> 1] >> (16 * (e & 1)));
+            if (ck == 0) {
+              const float ks = ka / 127.0f, vs = va / 127.0f;
+              ring_s[slot][tw] = ks;
+              ring_s[slot][kBlockTokens + tw] = vs;
+              ((float*)(kblk + kBlockTokens * D))[tw] = ks;
+              ((float*)(vblk + kBlockTokens * D))[tw] = vs;
+            }
+          }
+        }
+        __syncthreads();  // the patches are visible
+        for (int c = threadIdx.x; c < kCodeVec; c += 256) {  // V chunks that hold a new token: back into the cache
+          const int cg = (c & 63) >> 4;
+          bool any = false;
+#pragma unroll
+          for (int jj = 0; jj < 8; ++jj) {
+            const int t = tok0 + (jj < 4 ? 4 * cg + jj : 16 + 4 * cg + (jj - 4));
+            any |= t >= u.L && t < u.L + u.nq;
+          }
+          if (any) {
+            uint32_t w[4] = {0u, 0u, 0u, 0u};
+#pragma unroll
+            for (int f = 0; f < 2; ++f) {
+              const uint4 frag = ring_v[slot][(2 * (c >> 6) + f) * 64 + (c & 63)];
+              const uint32_t fw[4] = {frag.x, frag.y, frag.z, frag.w};
+#pragma unroll
+              for (int e = 0; e < 8; ++e) {  // codes are whole numbers of at most 7 bits: exact in bf16
+                const int code = (int)bf16_bits_to_float((fw[e >> 1] >> (16 * (e & 1))) & 0xFFFFu);
+                w[2 * f + (e >> 2)] |= ((uint32_t)code & 0xFFu) << (8 * (e & 3));
+              }
+            }
+            *(uint4*)(vblk + 16 * c) = make_uint4(w[0], w[1], w[2], w[3]);
+          }
+        }
+      } else {
+        __syncthreads();
+      }
+      if (active && s < n) {
+        KvRegs<D> r;
+        u32x4 k[kChunks];
+        TokenScales sc;
+#pragma unroll
+        for (int i = 0; i < kChunks; ++i) k[i] = __builtin_bit_cast(u32x4, ring_k[slot][i * 64 + lane]);
+#pragma unroll
+        for (int i = 0; i < D / 16; ++i) r.v[i] = ring_v[slot][i * 64 + lane];
+#pragma unroll
+        for (int h = 0; h < 2; ++h) {
+          const f32x4 ks = *(const f32x4*)&ring_s[slot][16 * h + 4 * grp];
+          const f32x4 vs = *(const f32x4*)&ring_s[slot][kBlockTokens + 16 * h + 4 * grp];
+#pragma unroll
+          for (int j = 0; j < 4; ++j) {
+            sc.k[4 * h + j] = ks[j];
+            sc.v[4 * h + j] = vs[j];
+          }
+        }
+        const I8Operands<D, 1> i8{k, q.q, q.q_scale_log2, &sc};
+        const bf16x8 no_q[1][D / 32] = {};
+        block_dispatch<D, 1, true>(r, no_q, st, blk0 + s, u.L, u.L + u.nq, q.lim, p.scale_log2, lane, false, NewRows{}, nullptr,
+                                   nullptr, &i8);
+      }
+    };
+    __syncthreads();  // the previous unit's last step has left the ring
+    Stage g[kTileAheadI8];
+#pragma unroll
+    for (int j = 0; j < kTileAheadI8; ++j) fetch(g[j], j);
+    for (int s = 0; s < n; s += kTileAheadI8) {  // workgroup-uniform trip count
+#pragma unroll
+      for (int j = 0; j < kTileAheadI8; ++j) step(g[j], s + j);
     }
     if (active) store_partial<D, 1>(p, u, wg, st, col, grp, row0);
   }
@@ -1604,7 +1771,7 @@ static int launch_attention(const bass_attn_desc* d, const LaunchShape& ls, cons
   const PlanLayout pl = plan_layout(d->B, d->Hkv, ls.nshares);
   const char* pb = (const char*)plan;
   p.plan = (const PlanHeader*)pb;
-  p.signature = plan_signature(d->B, d->kmax, d->Hkv, d->Lcap, ls.nshares, K_new ? kPlanAppend : 0);
+  p.signature = plan_signature(d->B, d->kmax, d->Hkv, d->Lcap, ls.nshares, K_new && ls.fused_append ? kPlanAppend : 0);
   p.records = (const ShareRecord*)(pb + pl.records);
   p.overflow = (const Segment*)(pb + pl.overflow);
   p.seq_L = (const int32_t*)(pb + pl.seq_L);
@@ -1621,36 +1788,36 @@ static int launch_attention(const bass_attn_desc* d, const LaunchShape& ls, cons
   if (d->dtype == BASS_DTYPE_FP32) {
     hipLaunchKernelGGL(verify_attn_fp32, grid, block, 0, s, p);
   } else if (ls.tiles) {
-    const dim3 tgrid((unsigned)p.nshares), tblock(256);
-    if (d->D == 128) {
-      if (K_new) hipLaunchKernelGGL((verify_attn_tiles_bf16<128, true>), tgrid, tblock, 0, s, p);
-      else hipLaunchKernelGGL((verify_attn_tiles_bf16<128, false>), tgrid, tblock, 0, s, p);
-    } else {
-      if (K_new) hipLaunchKernelGGL((verify_attn_tiles_bf16<64, true>), tgrid, tblock, 0, s, p);
-      else hipLaunchKernelGGL((verify_attn_tiles_bf16<64, false>), tgrid, tblock, 0, s, p);
-    }
-  } else {
-    const int nt = (rows_max + 15) / 16;
+    const dim3 tgrid((unsigned)ls.used_shares), tblock(256);
+#define BASS_LAUNCH_TILES(KERNEL)                                                         \
+  do {                                                                                    \
+    if (d->D == 128) {                                                                    \
+      if (K_new) hipLaunchKernelGGL((KERNEL<128, true>), tgrid, tblock, 0, s, p);         \
+      else hipLaunchKernelGGL((KERNEL<128, false>), tgrid, tblock, 0, s, p);              \
+    } else {                                                                              \
+      if (K_new) hipLaunchKernelGGL((KERNEL<64, true>), tgrid, tblock, 0, s, p);          \
+      else hipLaunchKernelGGL((KERNEL<64, false>), tgrid, tblock, 0, s, p);               \
+    }                                                                                     \
+  } while (0)
+    if (d->dtype == BASS_DTYPE_INT8KV) BASS_LAUNCH_TILES(verify_attn_tiles_i8);
+    else BASS_LAUNCH_TILES(verify_attn_tiles_bf16);
+#undef BASS_LAUNCH_TILES
+  } else {  // one query tile
     // LDS slice per wavefront of a fused append: K and V rows of two units (bf16, or INT8 codes + scales)
     const size_t unit_lds = d->dtype == BASS_DTYPE_INT8KV ? (size_t)2 * d->kmax * d->D + 8 * d->kmax
                                                           : (size_t)2 * d->kmax * d->D * 2;
     const size_t lds = K_new ? (size_t)p.wpw * 2 * unit_lds : 0;
-#define BASS_LAUNCH(DD, NN) hipLaunchKernelGGL((verify_attn_bf16<DD, NN>), grid, block, lds, s, p)
-#define BASS_LAUNCH_I8(DD, NN) hipLaunchKernelGGL((verify_attn_bf16<DD, NN, true>), grid, block, lds, s, p)
+    const bool few = ls.min_entries > 0 && (int64_t)ls.per_unit * d->B * d->Hkv < ls.nshares;
+#define BASS_LAUNCH(DD, I8)                                                                          \
+  do {                                                                                               \
+    if (few) hipLaunchKernelGGL((verify_attn_bf16<DD, 1, I8, true>), grid, block, lds, s, p);        \
+    else hipLaunchKernelGGL((verify_attn_bf16<DD, 1, I8, false>), grid, block, lds, s, p);           \
+  } while (0)
     if (d->dtype == BASS_DTYPE_INT8KV) {
-      if (d->D == 128) {
-        if (nt == 1) BASS_LAUNCH_I8(128, 1); else if (nt == 2) BASS_LAUNCH_I8(128, 2);
-        else if (nt == 3) BASS_LAUNCH_I8(128, 3); else BASS_LAUNCH_I8(128, 4);
-      } else {
-        if (nt == 1) BASS_LAUNCH_I8(64, 1); else if (nt == 2) BASS_LAUNCH_I8(64, 2);
-        else if (nt == 3) BASS_LAUNCH_I8(64, 3); else BASS_LAUNCH_I8(64, 4);
-      }
-    } else if (d->D == 128) {  // bf16, one query tile (more tiles: the workgroup-level kernel above)
-      BASS_LAUNCH(128, 1);
+      if (d->D == 128) BASS_LAUNCH(128, true); else BASS_LAUNCH(64, true);
     } else {
-      BASS_LAUNCH(64, 1);
+      if (d->D == 128) BASS_LAUNCH(128, false); else BASS_LAUNCH(64, false);
     }
-#undef BASS_LAUNCH_I8
 #undef BASS_LAUNCH
   }
   if (launch_status() != BASS_OK) return BASS_ERR_HIP;
@@ -1753,7 +1920,7 @@ extern "C" int bass_verify_attention_planned(const bass_attn_desc* d, const void
   if (rc != BASS_OK) return rc;
   const bass::Workspace wl = bass::workspace_layout(d, bass::kMaxWaves);
   if (workspace_bytes < wl.bytes) return BASS_ERR_WORKSPACE_TOO_SMALL;
-  if (K_new && !ls.fused_append) {
+  if (K_new && !ls.fused_append && !ls.tiles_append) {
     // more new rows than a wavefront stages in LDS: append with a launch of its own, at the (clamped)
     // lengths the plan holds
     const bass::PlanLayout pl = bass::plan_layout(d->B, d->Hkv, ls.nshares);
