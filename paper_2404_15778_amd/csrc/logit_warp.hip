@@ -18,7 +18,7 @@ struct WarpParams {
 };
 
 template <int W, int NG>
-__global__ __launch_bounds__(kWarpThreads) void warp_probs_kernel(WarpParams a) {
+__global__ __launch_bounds__(kWarpThreads, NG == 0 ? 8 : 4) void warp_probs_kernel(WarpParams a) {
   warp_row<W, NG, false>(a.logits + (size_t)blockIdx.x * a.V, a.probs + (size_t)blockIdx.x * a.V, a.V, a.c, a.top_p,
                          a.status, nullptr);
 }

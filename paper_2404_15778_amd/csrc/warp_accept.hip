@@ -42,7 +42,7 @@ struct SummaryParams {
 };
 
 template <int W, int NG>
-__global__ __launch_bounds__(kWarpThreads) void warp_summaries_kernel(SummaryParams a) {
+__global__ __launch_bounds__(kWarpThreads, NG == 0 ? 8 : 4) void warp_summaries_kernel(SummaryParams a) {
   const int r = blockIdx.x;
   if (r == 0)
     for (int b = threadIdx.x; b < a.B; b += kWarpThreads) a.counter[b] = 0u;
