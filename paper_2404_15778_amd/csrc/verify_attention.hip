@@ -1252,35 +1252,43 @@ __global__ __launch_bounds__(256) void verify_attn_bf16(AttnParams p) {
 }
 
 // ---------------------------------------------------------------------------------------
-// Workgroup-level kernel for kv heads with more than 16 query rows (grouped-query attention), bf16.
+// Workgroup-level kernel for kv heads with more than 16 query rows (grouped-query attention, long drafts), bf16.
 // The accumulators of two to four 16-row tiles in ONE wavefront leave registers for a single block in
 // flight, and re-reading blocks by several wavefronts crosses the fabric twice.  Here a workgroup of
-// four wavefronts takes a stretch of the block list together: every K/V block is fetched from memory
-// once (each wavefront a quarter of it, three blocks ahead), put into a two-slot ring in LDS, and
-// read from there by the wavefronts that own a query tile (wavefront t: rows 16 t .. 16 t + 15), each
-// running the one-tile block step.  A wavefront needs < 256 registers, so two workgroups share a
-// compute unit.  One barrier per block: a slot is rewritten only after the barrier that follows the
-// last step that read it.  Every barrier sits in workgroup-uniform control flow (the stretch, the
-// units and the block counts depend on the workgroup index and the lengths only).
+// 2 TW wavefronts takes a stretch of the block list together: every K/V block is fetched from memory
+// once (each wavefront a part of it), put into a ring in LDS, and read from there by the wavefronts that own
+// a query tile (rows 16 t .. 16 t + 15), each running the one-tile block step.  A step is a serial chain (scores,
+// maximum, exponentials, products) of about a microsecond that one wavefront per SIMD cannot hide, so the
+// ring holds two blocks per phase and each tile has two wavefronts, one for the even and one for the odd
+// blocks, whose states are merged through LDS at the end of the unit.  One barrier per phase: a slot is rewritten
+// only after the barrier that follows the last step that read it.  Every barrier sits in workgroup-uniform
+// control flow (the stretch, the units and the block counts depend on the workgroup index and the lengths only).
+// TW: tiles a workgroup has room for, 2 or 4 -- with two, four wavefronts are enough and all of them have a tile.
+// Steps of 16 layers (attention, merge): 16 sequences of 1024 - 4096 tokens, 64/8 heads of 128, 48 rows per kv head
+// 817 -> 759 us; 8 sequences of 512 - 2048 tokens, 32 heads, 32 rows 922 -> 907 us (one block per phase, four
+// wavefronts before).  Three and four phases ahead spill: 775 and 803, 1005 and 1568 us.
 // ---------------------------------------------------------------------------------------
-constexpr int kTileAhead = 3;  // blocks a workgroup has in flight from memory (measured best: 3)
+constexpr int kTileAhead = 2;  // phases of two blocks a workgroup has in flight from memory
 
-template <int D, bool kFused>
-__global__ __launch_bounds__(256, 2) void verify_attn_tiles_bf16(AttnParams p) {
+template <int D, bool kFused, int TW>
+__global__ __launch_bounds__(128 * TW, 2) void verify_attn_tiles_bf16(AttnParams p) {
+  constexpr int kThreads = 128 * TW;
   constexpr int kBlkVec = kBlockTokens * D * 2 / 16;  // uint4 per block and tensor
-  constexpr int kQuarter = kBlkVec / 4;                // uint4 a wavefront moves per block and tensor
-  constexpr int kLoads = kQuarter / 64;                // 16-byte loads per lane, block and tensor
-  __shared__ uint4 ring_k[2][kBlkVec];
-  __shared__ uint4 ring_v[2][kBlkVec];
-  const int lane = threadIdx.x & 63, wv = threadIdx.x >> 6;
+  constexpr int kPhase = 2 * kBlkVec;                  // ... and per phase (a unit's blocks lie one after the other)
+  constexpr int kLoads = kPhase / kThreads;            // 16-byte loads per lane, phase and tensor
+  __shared__ uint4 ring_k[2][kPhase];
+  __shared__ uint4 ring_v[2][kPhase];
+  __shared__ float other_m[TW][64], other_l[TW][64];  // states of the odd blocks' wavefronts (accumulators: in ring_k)
+  const int tid = threadIdx.x, lane = tid & 63, wv = tid >> 6;
+  const int tile = wv % TW, half = wv / TW;
   const int col = lane & 15, grp = lane >> 4;
   const int wg = blockIdx.x;  // the stretch of this workgroup
-  const int row0 = 16 * wv;
+  const int row0 = 16 * tile;
 
   const ShareRecord* rec = p.records + wg;
   const int nseg = uniform(rec->nseg), overflow = uniform(rec->overflow);
   if (!record_matches(p, rec)) {
-    report_mismatch(p, wg == 0 && threadIdx.x == 0);
+    report_mismatch(p, wg == 0 && tid == 0);
     return;
   }
   // (the unused query rows are cleared by the merge launch, which visits every row of every unit anyway)
@@ -1295,89 +1303,112 @@ __global__ __launch_bounds__(256, 2) void verify_attn_tiles_bf16(AttnParams p) {
     const Segment seg = si == 0 ? load_segment(&rec->seg[0]) : later_segment(p, rec, overflow, si);
     const Unit u = unit_of(seg);
     const int n = seg.n;  // real blocks seg.first .. seg.first + n - 1 of the unit
-    const bool active = row0 < u.nq * p.g;  // this wavefront owns a query tile of the unit
+    const bool active = uniform(row0 < u.nq * p.g);  // this wavefront owns a query tile of the unit
     QFrag<D, 1> q;
     load_queries<D, 1>(p, u, active, col, grp, q, row0);
     RowState<D, 1> st;
     clear_state<D, 1>(st);
     const int blk0 = seg.first;
     const ptrdiff_t vec0 = (((ptrdiff_t)u.b * p.Hkv + u.kvh) * p.nblk_cap + blk0) * kBlkVec;
-    const int mine = wv * kQuarter + lane;  // first uint4 this lane moves
 
-    // all fetches unconditional (exact wait counts); one past the end re-reads the stretch's first block
-    auto fetch = [&](Stage& g, int s) {
-      const ptrdiff_t off = vec0 + (s < n ? (ptrdiff_t)s * kBlkVec : 0) + mine;
-#pragma unroll
-      for (int i = 0; i < kLoads; ++i) g.k[i] = __builtin_bit_cast(uint4, __builtin_nontemporal_load((const u32x4*)(kc + off + i * 64)));
-#pragma unroll
-      for (int i = 0; i < kLoads; ++i) g.v[i] = __builtin_bit_cast(uint4, __builtin_nontemporal_load((const u32x4*)(vc + off + i * 64)));
-    };
-    // block s: own quarter into LDS, next fetch, barrier -- for every s, also past the end (the loads and
-    // the barrier stay outside all branches: a load under a branch costs a full wait at the join) --
-    // then, for real blocks, the one-tile step from LDS
-    auto step = [&](Stage& g, int s) {
-      const int slot = s & 1;
+    // all fetches unconditional (exact wait counts); a block past the end re-reads the stretch's first block
+    auto fetch = [&](Stage& g, int ph) {
 #pragma unroll
       for (int i = 0; i < kLoads; ++i) {
-        ring_k[slot][mine + i * 64] = g.k[i];
-        ring_v[slot][mine + i * 64] = g.v[i];
+        const int c = i * kThreads + tid, h = i * kThreads / kBlkVec + (tid >= kBlkVec ? 1 : 0);
+        const ptrdiff_t off = vec0 + (2 * ph + h < n ? (ptrdiff_t)ph * kPhase + c : (ptrdiff_t)(c - h * kBlkVec));
+        g.k[i] = __builtin_bit_cast(uint4, __builtin_nontemporal_load((const u32x4*)(kc + off)));
+        g.v[i] = __builtin_bit_cast(uint4, __builtin_nontemporal_load((const u32x4*)(vc + off)));
       }
-      fetch(g, s + kTileAhead);
-      // Fused append: a block that holds new tokens is patched in LDS once it is complete there (K: the
+    };
+    // phase ph (blocks 2 ph and 2 ph + 1): own part into LDS, next fetch, barrier -- for every phase, also past the
+    // end (the loads and the barrier stay outside all branches: a load under a branch costs a full wait at the
+    // join) -- then, for real blocks, the one-tile step from LDS
+    auto phase = [&](Stage& g, int ph) {
+      const int slot = ph & 1;
+#pragma unroll
+      for (int i = 0; i < kLoads; ++i) {
+        ring_k[slot][i * kThreads + tid] = g.k[i];
+        ring_v[slot][i * kThreads + tid] = g.v[i];
+      }
+      fetch(g, ph + kTileAhead);
+      // Fused append: blocks that hold new tokens are patched in LDS once they are complete there (K: the
       // 16-byte chunks of the new rows; V: their elements, 2 bytes each), and the patched chunks go into the
       // cache from LDS as whole 16-byte chunks.  The test is workgroup-uniform; the loads of the new rows
-      // sit under this branch and cost a full wait, in these one or two blocks per unit only.
-      const int tok0 = (blk0 + s) * kBlockTokens;
-      if (kFused && s < n && u.nq > 0 && tok0 < u.L + u.nq && tok0 + kBlockTokens > u.L) {
-        __syncthreads();  // the block is complete in LDS
-        const int i_lo = max(0, tok0 - u.L), i_hi = min(u.nq, tok0 + kBlockTokens - u.L);
-        // the new rows of this block by 16-byte chunks, 256 at a time: 16 rows of 128 head elements per round trip
-        for (int c = threadIdx.x; c < (i_hi - i_lo) * (D / 8); c += 256) {
+      // sit under this branch and cost a full wait, in these one or two phases per unit only.
+      const int tok0 = (blk0 + 2 * ph) * kBlockTokens;                     // the phase's tokens that are ours:
+      const int tok1 = (blk0 + min(2 * ph + 2, n)) * kBlockTokens;         // tok0 .. tok1 - 1
+      if (kFused && u.nq > 0 && tok0 < min(u.L + u.nq, tok1) && tok1 > u.L) {
+        __syncthreads();  // the blocks are complete in LDS
+        const int i_lo = max(0, tok0 - u.L), i_hi = min(u.nq, tok1 - u.L);
+        uint4* kdst = (uint4*)const_cast<void*>(p.Kc) + vec0 + (ptrdiff_t)ph * kPhase;
+        uint4* vdst = (uint4*)const_cast<void*>(p.Vc) + vec0 + (ptrdiff_t)ph * kPhase;
+        for (int c = tid; c < (i_hi - i_lo) * (D / 8); c += kThreads) {  // the new rows by 16-byte chunks
           const int i = i_lo + c / (D / 8), ck = c % (D / 8);
-          const int tw = u.L + i - tok0;  // its token slot in the block
+          const int t = u.L + i - tok0, h = t / kBlockTokens, tw = t % kBlockTokens;  // its token slot in the phase's blocks
           const size_t src = (((size_t)u.b * p.kmax + i) * p.Hkv + u.kvh) * D + 8 * ck;
           const uint4 kv = *(const uint4*)((const uint16_t*)p.Knew + src);
           const uint4 vv = *(const uint4*)((const uint16_t*)p.Vnew + src);
-          const size_t ko = k_elem_offset(D, tw, 8 * ck) / 8;  // in 16-byte chunks
+          const size_t ko = h * kBlkVec + k_elem_offset(D, tw, 8 * ck) / 8;  // in 16-byte chunks
           ring_k[slot][ko] = kv;
-          ((uint4*)const_cast<void*>(p.Kc))[vec0 + (ptrdiff_t)s * kBlkVec + (ptrdiff_t)ko] = kv;
+          kdst[ko] = kv;
           const uint32_t vw[4] = {vv.x, vv.y, vv.z, vv.w};
 #pragma unroll
           for (int e = 0; e < 8; ++e)
-            ((uint16_t*)&ring_v[slot][0])[v_elem_offset(D, tw, 8 * ck + e)] = (uint16_t)(vw[e >> 1] >> (16 * (e & 1)));
+            ((uint16_t*)&ring_v[slot][h * kBlkVec])[v_elem_offset(D, tw, 8 * ck + e)] = (uint16_t)(vw[e >> 1] >> (16 * (e & 1)));
         }
         __syncthreads();  // the patches are visible
-        for (int c = threadIdx.x; c < (D / 16) * 64; c += 256) {  // V chunks that hold a new token: back into the cache
-          const int cg = (c & 63) >> 4;
+        for (int c = tid; c < kPhase; c += kThreads) {  // V chunks that hold a new token: back into the cache
+          const int cg = (c & 63) >> 4, first = tok0 + c / kBlkVec * kBlockTokens;
           bool any = false;
 #pragma unroll
           for (int jj = 0; jj < 8; ++jj) {
-            const int t = tok0 + (jj < 4 ? 4 * cg + jj : 16 + 4 * cg + (jj - 4));
-            any |= t >= u.L && t < u.L + u.nq;
+            const int t = first + (jj < 4 ? 4 * cg + jj : 16 + 4 * cg + (jj - 4));
+            any |= t >= u.L && t < min(u.L + u.nq, tok1);
           }
-          if (any) ((uint4*)const_cast<void*>(p.Vc))[vec0 + (ptrdiff_t)s * kBlkVec + c] = ring_v[slot][c];
+          if (any) vdst[c] = ring_v[slot][c];
         }
       } else {
         __syncthreads();
       }
-      if (active && s < n) {
+      if (active && 2 * ph + half < n) {
         KvRegs<D> r;
+        const uint4* lk = &ring_k[slot][half * kBlkVec + lane];
+        const uint4* lv = &ring_v[slot][half * kBlkVec + lane];
 #pragma unroll
-        for (int i = 0; i < 2 * (D / 32); ++i) r.k[i] = ring_k[slot][i * 64 + lane];
+        for (int i = 0; i < 2 * (D / 32); ++i) r.k[i] = lk[i * 64];
 #pragma unroll
-        for (int i = 0; i < D / 16; ++i) r.v[i] = ring_v[slot][i * 64 + lane];
-        block_dispatch<D, 1>(r, q.q, st, blk0 + s, u.L, u.L + u.nq, q.lim, p.scale_log2, lane, false, NewRows{}, nullptr, nullptr);
+        for (int i = 0; i < D / 16; ++i) r.v[i] = lv[i * 64];
+        block_dispatch<D, 1>(r, q.q, st, blk0 + 2 * ph + half, u.L, u.L + u.nq, q.lim, p.scale_log2, lane, false, NewRows{}, nullptr, nullptr);
       }
     };
-    __syncthreads();  // the previous unit's last step has left the ring
+    __syncthreads();  // the previous unit's merge has left the ring
     Stage g[kTileAhead];
 #pragma unroll
     for (int j = 0; j < kTileAhead; ++j) fetch(g[j], j);
-    for (int s = 0; s < n; s += kTileAhead) {  // workgroup-uniform trip count
+    for (int ph = 0; 2 * ph < n; ph += kTileAhead) {  // workgroup-uniform trip count
 #pragma unroll
-      for (int j = 0; j < kTileAhead; ++j) step(g[j], s + j);
+      for (int j = 0; j < kTileAhead; ++j) phase(g[j], ph + j);
     }
-    if (active) store_partial<D, 1>(p, u, wg, st, col, grp, row0);
+    // the odd blocks' state joins the even blocks' (a state that saw no visible token has m = -inf and no weight)
+    __syncthreads();  // the last steps have left the ring
+    f32x4* other_acc = (f32x4*)&ring_k[0][0] + tile * (D / 16) * 64 + lane;
+    if (half == 1 && active) {
+#pragma unroll
+      for (int mt = 0; mt < D / 16; ++mt) other_acc[mt * 64] = st.acc[0][mt];
+      other_m[tile][lane] = st.m[0];
+      other_l[tile][lane] = st.l[0];
+    }
+    __syncthreads();
+    if (half == 0 && active) {
+      const float m1 = other_m[tile][lane], M = fmaxf(st.m[0], m1), Mf = M == -INFINITY ? 0.f : M;
+      const float w0 = __builtin_amdgcn_exp2f(st.m[0] - Mf), w1 = __builtin_amdgcn_exp2f(m1 - Mf);
+      st.m[0] = M;
+      st.l[0] = st.l[0] * w0 + other_l[tile][lane] * w1;
+#pragma unroll
+      for (int mt = 0; mt < D / 16; ++mt) st.acc[0][mt] = st.acc[0][mt] * w0 + other_acc[mt * 64] * w1;
+      store_partial<D, 1>(p, u, wg, st, col, grp, row0);
+    }
   }
 }
 
@@ -1788,19 +1819,21 @@ static int launch_attention(const bass_attn_desc* d, const LaunchShape& ls, cons
   if (d->dtype == BASS_DTYPE_FP32) {
     hipLaunchKernelGGL(verify_attn_fp32, grid, block, 0, s, p);
   } else if (ls.tiles) {
-    const dim3 tgrid((unsigned)ls.used_shares), tblock(256);
-#define BASS_LAUNCH_TILES(KERNEL)                                                         \
-  do {                                                                                    \
-    if (d->D == 128) {                                                                    \
-      if (K_new) hipLaunchKernelGGL((KERNEL<128, true>), tgrid, tblock, 0, s, p);         \
-      else hipLaunchKernelGGL((KERNEL<128, false>), tgrid, tblock, 0, s, p);              \
-    } else {                                                                              \
-      if (K_new) hipLaunchKernelGGL((KERNEL<64, true>), tgrid, tblock, 0, s, p);          \
-      else hipLaunchKernelGGL((KERNEL<64, false>), tgrid, tblock, 0, s, p);               \
-    }                                                                                     \
+    const dim3 tgrid((unsigned)ls.used_shares);
+    const bool two = rows_max <= 32;  // bf16: two tiles, four wavefronts
+#define BASS_LAUNCH_TILES(THREADS, KERNEL, ...)                                                                    \
+  do {                                                                                                             \
+    if (d->D == 128) {                                                                                             \
+      if (K_new) hipLaunchKernelGGL((KERNEL<128, true __VA_ARGS__>), tgrid, dim3(THREADS), 0, s, p);               \
+      else hipLaunchKernelGGL((KERNEL<128, false __VA_ARGS__>), tgrid, dim3(THREADS), 0, s, p);                    \
+    } else {                                                                                                       \
+      if (K_new) hipLaunchKernelGGL((KERNEL<64, true __VA_ARGS__>), tgrid, dim3(THREADS), 0, s, p);                \
+      else hipLaunchKernelGGL((KERNEL<64, false __VA_ARGS__>), tgrid, dim3(THREADS), 0, s, p);                     \
+    }                                                                                                              \
   } while (0)
-    if (d->dtype == BASS_DTYPE_INT8KV) BASS_LAUNCH_TILES(verify_attn_tiles_i8);
-    else BASS_LAUNCH_TILES(verify_attn_tiles_bf16);
+    if (d->dtype == BASS_DTYPE_INT8KV) BASS_LAUNCH_TILES(256, verify_attn_tiles_i8);
+    else if (two) BASS_LAUNCH_TILES(256, verify_attn_tiles_bf16, , 2);
+    else BASS_LAUNCH_TILES(512, verify_attn_tiles_bf16, , 4);
 #undef BASS_LAUNCH_TILES
   } else {  // one query tile
     // LDS slice per wavefront of a fused append: K and V rows of two units (bf16, or INT8 codes + scales)
