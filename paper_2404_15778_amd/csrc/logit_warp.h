@@ -24,9 +24,9 @@
 // them are kept).
 //
 // A compute unit fetches at most some 150 GB/s, so every pass over a 200 KB row from memory or L2
-// costs it microseconds.  Rows of up to 65536 aligned logits are therefore read ONCE, into registers
-// (NG 16-byte groups per thread), and all passes run on the registers; only the result is stored.
-// Longer or unaligned rows take the streaming variant (NG = 0).  On peaked rows -- the usual case at low temperatures --
+// costs it microseconds.  Rows of up to 65536 aligned logits (53248 unaligned ones) are therefore read ONCE, into
+// registers (NG groups of W logits per thread), and all passes run on the registers; only the result is stored.
+// Longer rows take the streaming variant (NG = 0).  On peaked rows -- the usual case at low temperatures --
 // only a few of their tokens have mass at all (2^-40 of the largest's); the pass that finds the maximum keeps every
 // token that can have mass, by the maximum known so far, in a list of up to kListMax (token, logit) pairs in LDS.  All
 // later passes run on the list: the row is read once, and written once, as zeros and a few values.  Whether a row
@@ -46,10 +46,17 @@ constexpr float kMassScale = 1099511627776.0f;  // 2^40
 // log2(e) / T: the factor of (z - z_max) in the exponent
 inline float warp_exponent_scale(float temperature) { return (float)(1.4426950408889634 / (double)temperature); }
 
-// Which variant serves rows of V logits: 1 = unaligned rows, one logit per load, streaming; 8 / 13 / 16 = that
-// many 16-byte groups per thread held in registers; 0 = 16-byte loads, streaming
+// Which variant serves rows of V logits: 8 / 13 / 16 = that many 16-byte groups per thread held in registers; 0 = 16-byte
+// loads, streaming; rows that are not aligned (one logit per load): -8 / -32 / -52 = that many logits per thread held
+// in registers, -1 = streaming.  480 rows of 50001 / 8001 tokens at T = 0.2 with their acceptance: 122 -> 90 / 33 -> 27 us;
+// unaligned rows of more than 53248 would spill.
 inline int warp_variant(int V, bool rows_16_byte_aligned) {
-  if (!rows_16_byte_aligned) return 1;
+  if (!rows_16_byte_aligned) {
+    if (V <= 8 * kWarpThreads) return -8;
+    if (V <= 32 * kWarpThreads) return -32;
+    if (V <= 52 * kWarpThreads) return -52;
+    return -1;
+  }
   if (V <= 8 * 4 * kWarpThreads) return 8;
   if (V <= 13 * 4 * kWarpThreads) return 13;
   if (V <= 16 * 4 * kWarpThreads) return 16;
@@ -85,8 +92,9 @@ __device__ inline KeyRange keys_with_prefix(uint32_t prefix, int shift) {
 }
 __device__ inline uint64_t warp_mass(float e) { return has_mass(e) ? mass_of(e) : 0; }
 
-constexpr int kWarpUnroll = 4;  // groups a thread keeps in flight (with 8, one workgroup per compute unit instead of two)
-constexpr int kListUnroll = 4;  // ... in the pass that makes the list
+template <int W>
+constexpr int kStreamUnroll = W == 1 ? 8 : 4;  // groups a thread of the streaming variant takes at a time: 64 registers, so
+                                               // that two workgroups fit a compute unit
 constexpr int kListMax = 4096;  // tokens of the list: 32 KB, so that two workgroups fit a compute unit
 
 // W logits per thread and load: 4 (16-byte loads; V a multiple of 4 and 16-byte aligned rows) or 1
@@ -132,7 +140,7 @@ __device__ inline float warped_prob(const RowSummary& s, float c, float z, int i
 }
 
 // The warp of one row by one workgroup of kWarpThreads threads.
-// NG > 0: the row lives in registers, NG groups of W = 4 per thread (V <= 4096 NG); NG = 0: streaming.
+// NG > 0: the row lives in registers, NG groups of W per thread (V <= 1024 W NG); NG = 0: streaming.
 // kSummary = false: the probabilities are written to `out`.  kSummary = true: nothing of the row is written,
 // *summary receives what warped_prob needs (the streaming variant then recomputes e_i from the logits in every
 // pass instead of re-reading it from the output row).
@@ -171,12 +179,12 @@ __device__ __forceinline__ void warp_row(const float* z, float* out, int V, floa
         if (g < groups) f(g, held[k], k);
       }
     } else {
-      for (int base = tid; base < groups; base += kWarpUnroll * kWarpThreads) {
-        Group<W> gr[kWarpUnroll];
+      for (int base = tid; base < groups; base += kStreamUnroll<W> * kWarpThreads) {
+        Group<W> gr[kStreamUnroll<W>];
 #pragma unroll
-        for (int k = 0; k < kWarpUnroll; ++k) gr[k] = load_group<W>(row, min(base + k * kWarpThreads, groups - 1));
+        for (int k = 0; k < kStreamUnroll<W>; ++k) gr[k] = load_group<W>(row, min(base + k * kWarpThreads, groups - 1));
 #pragma unroll
-        for (int k = 0; k < kWarpUnroll; ++k) {
+        for (int k = 0; k < kStreamUnroll<W>; ++k) {
           const int g = base + k * kWarpThreads;
           if (g < groups) f(g, gr[k], 0);
         }
@@ -205,12 +213,12 @@ __device__ __forceinline__ void warp_row(const float* z, float* out, int V, floa
     float known = -INFINITY;
     if (tid == 0) sh_listed = 0;
 #pragma unroll 1
-    for (int base = tid; base - tid < groups; base += kListUnroll * kWarpThreads) {  // the same trips for every thread
-      Group<W> gr[kListUnroll];
+    for (int base = tid; base - tid < groups; base += kStreamUnroll<W> * kWarpThreads) {  // the same trips for every thread
+      Group<W> gr[kStreamUnroll<W>];
 #pragma unroll
-      for (int k = 0; k < kListUnroll; ++k) gr[k] = load_group<W>(z, min(base + k * kWarpThreads, groups - 1));
+      for (int k = 0; k < kStreamUnroll<W>; ++k) gr[k] = load_group<W>(z, min(base + k * kWarpThreads, groups - 1));
 #pragma unroll
-      for (int k = 0; k < kListUnroll; ++k)
+      for (int k = 0; k < kStreamUnroll<W>; ++k)
 #pragma unroll
         for (int e = 0; e < W; ++e) m = fmaxf(m, gr[k].v[e]);
       if (!collect) continue;
@@ -223,7 +231,7 @@ __device__ __forceinline__ void warp_row(const float* z, float* out, int V, floa
       }
       uint32_t mine = 0;  // bit k W + e: entry e of group k may have mass
 #pragma unroll
-      for (int k = 0; k < kListUnroll; ++k) {
+      for (int k = 0; k < kStreamUnroll<W>; ++k) {
         const bool exists = base + k * kWarpThreads < groups;
 #pragma unroll
         for (int e = 0; e < W; ++e)
@@ -241,7 +249,7 @@ __device__ __forceinline__ void warp_row(const float* z, float* out, int V, floa
         __syncthreads();
         int64_t all = 0;
         for (int k = 0; k < kWarpWaves; ++k) all += sh_first_count[k];
-        const int batch = min(groups, kListUnroll * kWarpThreads);
+        const int batch = min(groups, kStreamUnroll<W> * kWarpThreads);
         collect = all * groups <= (int64_t)kListMax * batch;
         if (!collect) continue;
       }
@@ -249,7 +257,7 @@ __device__ __forceinline__ void warp_row(const float* z, float* out, int V, floa
       if (lane == 63 && incl > 0) at = atomicAdd(&sh_listed, incl);
       at = __builtin_amdgcn_readlane(at, 63) + incl - cnt;
 #pragma unroll
-      for (int k = 0; k < kListUnroll; ++k)
+      for (int k = 0; k < kStreamUnroll<W>; ++k)
 #pragma unroll
         for (int e = 0; e < W; ++e)
           if (mine & (1u << (k * W + e))) {

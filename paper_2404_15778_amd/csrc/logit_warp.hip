@@ -36,7 +36,10 @@ extern "C" int bass_warp_probs(int32_t R, int32_t V, const float* logits, float 
   const dim3 grid((unsigned)R), block(kWarpThreads);
   hipStream_t s = (hipStream_t)stream;
   switch (warp_variant(V, wide)) {
-    case 1: hipLaunchKernelGGL((warp_probs_kernel<1, 0>), grid, block, 0, s, a); break;
+    case -1: hipLaunchKernelGGL((warp_probs_kernel<1, 0>), grid, block, 0, s, a); break;
+    case -8: hipLaunchKernelGGL((warp_probs_kernel<1, 8>), grid, block, 0, s, a); break;
+    case -32: hipLaunchKernelGGL((warp_probs_kernel<1, 32>), grid, block, 0, s, a); break;
+    case -52: hipLaunchKernelGGL((warp_probs_kernel<1, 52>), grid, block, 0, s, a); break;
     case 8: hipLaunchKernelGGL((warp_probs_kernel<4, 8>), grid, block, 0, s, a); break;
     case 13: hipLaunchKernelGGL((warp_probs_kernel<4, 13>), grid, block, 0, s, a); break;
     case 16: hipLaunchKernelGGL((warp_probs_kernel<4, 16>), grid, block, 0, s, a); break;

@@ -252,7 +252,10 @@ extern "C" int bass_warp_accept(int32_t B, int32_t kmax, int32_t V, const float*
   const bool wide = V % 4 == 0 && (((uintptr_t)logits_main | (uintptr_t)logits_draft) & 15) == 0;
   const dim3 grid((unsigned)rows_all), block(kWarpThreads);
   switch (warp_variant(V, wide)) {
-    case 1: hipLaunchKernelGGL((warp_summaries_kernel<1, 0>), grid, block, 0, s, sp); break;
+    case -1: hipLaunchKernelGGL((warp_summaries_kernel<1, 0>), grid, block, 0, s, sp); break;
+    case -8: hipLaunchKernelGGL((warp_summaries_kernel<1, 8>), grid, block, 0, s, sp); break;
+    case -32: hipLaunchKernelGGL((warp_summaries_kernel<1, 32>), grid, block, 0, s, sp); break;
+    case -52: hipLaunchKernelGGL((warp_summaries_kernel<1, 52>), grid, block, 0, s, sp); break;
     case 8: hipLaunchKernelGGL((warp_summaries_kernel<4, 8>), grid, block, 0, s, sp); break;
     case 13: hipLaunchKernelGGL((warp_summaries_kernel<4, 13>), grid, block, 0, s, sp); break;
     case 16: hipLaunchKernelGGL((warp_summaries_kernel<4, 16>), grid, block, 0, s, sp); break;

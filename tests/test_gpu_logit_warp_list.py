@@ -1,6 +1,6 @@
-"""Rows too long for registers: the list of tokens with mass, and the streaming passes where the list does not apply, give
-the bits of the register variant.  A short row spread over a long one, in order, with tokens without mass in between, has
-the short row's probabilities."""
+"""Every variant of the front end gives the same bits: aligned rows in registers, unaligned ones, and for rows too long for
+registers the list of tokens with mass and the streaming passes where the list does not apply.  A short row spread over a
+long one, in order, with tokens without mass in between, has the short row's probabilities."""
 import numpy as np
 import pytest
 
@@ -21,7 +21,7 @@ def rows(rng):
     return z
 
 
-@pytest.mark.parametrize("V", [65540, 70001, 131072, 262145])
+@pytest.mark.parametrize("V", [20003, 32769, 53247, 53251, 65540, 70001, 131072, 262145])
 @pytest.mark.parametrize("temperature,top_p", [(0.05, 0.95), (0.2, 0.95), (0.35, 0.5), (0.5, 0.9), (1.0, 0.95), (0.2, 1.0)])
 def test_long_rows_have_the_bits_of_short_ones(V, temperature, top_p):
     import torch
