@@ -29,3 +29,10 @@ def test_explicit_spread_and_fp32_are_left_alone():
         assert max(int(r[8 * i + 5]) for r in plan["records"] for i in range(min(2, int(r[16])))) == 1
     finally:
         bass.bass_set_attention_waves(0)
+
+
+@pytest.mark.parametrize("B,ctx,few", [(1, 1000, True), (2, 1000, True), (3, 640, False), (4, 20, False), (3, 200, False), (2, 20, True)])
+def test_fewer_shares_only_where_they_are_worth_it(B, ctx, few):
+    d = bass.make_desc(B, 4, 32, 32, 128, 4096, "bf16", 1.0)
+    plan = check_plan(d, [ctx] * B, [4] * B, bass.PLAN_APPEND, 0, expect_shares=768)
+    assert all(bool(int(r[19]) & 2) == few for r in plan["records"])  # the flag under which remainders are multiplied
