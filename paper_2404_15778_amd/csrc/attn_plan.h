@@ -152,11 +152,13 @@ constexpr int32_t kRecFewShares = 2;    // the list was divided over fewer share
 constexpr int32_t kRecAnyInactive = 1;  // some sequence has no query token: its output rows still have to be cleared
 
 // What a launch and its plan must agree on, folded into one word that every record carries (a launch then
-// needs no second read to know that the record was made for it).  Never 0: cleared memory does not match.
-BASS_HD inline int32_t plan_signature(int B, int kmax, int Hkv, int Lcap, int nshares, int flags) {
-  const int32_t v[6] = {B, kmax, Hkv, Lcap, nshares, flags};
+// needs no second read to know that the record was made for it): everything the division depends on besides the
+// lengths and the span, and `used`, which sizes the grid of the workgroup-level kernels.  Never 0: cleared memory
+// does not match.
+BASS_HD inline int32_t plan_signature(const PlanShape& s, int flags) {
+  const int32_t v[12] = {s.B, s.kmax, s.Hkv, s.Lcap, s.nshares, s.target, s.pad, s.pad_before, s.min_entries, s.per_unit, s.used, flags};
   uint32_t h = 2166136261u;
-  for (int i = 0; i < 6; ++i) h = (h ^ (uint32_t)v[i]) * 16777619u;
+  for (int i = 0; i < 12; ++i) h = (h ^ (uint32_t)v[i]) * 16777619u;
   return (int32_t)(h | 1u);
 }
 

@@ -158,7 +158,7 @@ __global__ __launch_bounds__(kPlanThreads) void attention_plan_kernel(PlanShape 
   const int32_t* rd_inc = in_lds ? lds_inc : inc;
 
   // phase 2
-  const int32_t signature = plan_signature(s.B, s.kmax, s.Hkv, s.Lcap, s.nshares, flags);
+  const int32_t signature = plan_signature(s, flags);
   for (int w = gtid; w < s.nshares; w += gthreads)
     write_record(s, rd_L, rd_nq, rd_inc, total, w, signature, any_inactive != 0, records, overflow);
 
@@ -190,7 +190,7 @@ static bool plan_on_host(const PlanShape& s, int flags, const int32_t* ctx_len, 
   }
   const int total = carry * s.Hkv;
   *(PlanHeader*)plan = make_header(s, flags, total, any_inactive, bad);
-  const int32_t signature = plan_signature(s.B, s.kmax, s.Hkv, s.Lcap, s.nshares, flags);
+  const int32_t signature = plan_signature(s, flags);
   for (int w = 0; w < s.nshares; ++w) write_record(s, seq_L, seq_nq, inc, total, w, signature, any_inactive, records, overflow);
   const Split sp = plan_split(s, total);
   const int pb = pad_before_in_effect(s, sp);

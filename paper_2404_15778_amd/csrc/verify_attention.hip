@@ -1803,7 +1803,7 @@ static int launch_attention(const bass_attn_desc* d, const LaunchShape& ls, cons
   const PlanLayout pl = plan_layout(d->B, d->Hkv, ls.nshares);
   const char* pb = (const char*)plan;
   p.plan = (const PlanHeader*)pb;
-  p.signature = plan_signature(d->B, d->kmax, d->Hkv, d->Lcap, ls.nshares, K_new && ls.fused_append ? kPlanAppend : 0);
+  p.signature = plan_signature(plan_shape(d, ls, 0), K_new && ls.fused_append ? kPlanAppend : 0);
   p.records = (const ShareRecord*)(pb + pl.records);
   p.overflow = (const Segment*)(pb + pl.overflow);
   p.seq_L = (const int32_t*)(pb + pl.seq_L);
