@@ -976,6 +976,20 @@ __device__ inline void clear_state(RowState<D, NT>& st) {
   }
 }
 
+// Whether some accumulator of the wavefront is NaN or infinite (wave-uniform)
+template <int D, int NT>
+__device__ inline bool any_not_finite(const RowState<D, NT>& st) {
+  f32x4 t = {0.f, 0.f, 0.f, 0.f};  // 0 * finite is 0, 0 * anything else NaN
+#pragma unroll
+  for (int nt = 0; nt < NT; ++nt)
+#pragma unroll
+    for (int mt = 0; mt < D / 16; ++mt)
+#pragma unroll
+      for (int e = 0; e < 4; ++e) t[e] = fmaf(st.acc[nt][mt][e], 0.f, t[e]);
+  const float sum = (t[0] + t[1]) + (t[2] + t[3]);
+  return __any(sum != sum);
+}
+
 // Partial of (wavefront w, unit u): slot ids w + unit are unique because both grow monotonically
 // along the flattened list.
 template <int D, int NT>
@@ -1155,7 +1169,7 @@ __global__ __launch_bounds__(256) void verify_attn_bf16(AttnParams p) {
         load_block<D>(r, kc + off, vc + off);
       }
     };
-    auto step = [&](Regs& r, int s) {
+    auto step = [&](Regs& r, int s, bool fine) {
       if constexpr (kPair) {
         if (s == nA) {  // first block of unit B: park A's state (register moves only)
           parked = st;
@@ -1212,25 +1226,49 @@ __global__ __launch_bounds__(256) void verify_attn_bf16(AttnParams p) {
     next_arrived();
     for (int s = 0; s < n; s += 3) {
       fetch(r2, s + 2);
-      step(r0, s);
+      step(r0, s, fine);
       fetch(r0, s + 3);
-      if (s + 1 < n) step(r1, s + 1);
+      if (s + 1 < n) step(r1, s + 1, fine);
       fetch(r1, s + 4);
-      if (s + 2 < n) step(r2, s + 2);
+      if (s + 2 < n) step(r2, s + 2, fine);
     }
     // A unit that lies wholly inside this share (common with many short sequences) is finished from the
     // registers; the others leave a partial, and the wavefront that delivers a unit's last partial merges.
     // (With a merge launch of its own -- more than one query tile -- every unit leaves a partial.)
     const bool soloA = p.fused_reduce && ja.w_lo == ja.w_hi;
     const bool soloB = p.fused_reduce && hasB && jb.w_lo == jb.w_hi;
-    if (hasB) {
-      if (soloA) finalize_single<D, NT>(p, uA, parked, col, grp);
-      else store_partial<D, NT>(p, uA, w, parked, col, grp);
-      if (soloB) finalize_single<D, NT>(p, uB, st, col, grp);
-      else store_partial<D, NT>(p, uB, w, st, col, grp);
-    } else {
-      if (soloA) finalize_single<D, NT>(p, uA, st, col, grp);
-      else store_partial<D, NT>(p, uA, w, st, col, grp);
+    auto deliver = [&]() {
+      if (hasB) {
+        if (soloA) finalize_single<D, NT>(p, uA, parked, col, grp);
+        else store_partial<D, NT>(p, uA, w, parked, col, grp);
+        if (soloB) finalize_single<D, NT>(p, uB, st, col, grp);
+        else store_partial<D, NT>(p, uB, w, st, col, grp);
+      } else {
+        if (soloA) finalize_single<D, NT>(p, uA, st, col, grp);
+        else store_partial<D, NT>(p, uA, w, st, col, grp);
+      }
+    };
+    deliver();
+    // An infinite element of V decides its outputs, but times the remainder of a probability, which may be zero or negative,
+    // it is NaN.  Units in which that may have happened are streamed once more without the remainder products, and what
+    // was stored is stored again; what is not finite then is so by the inputs.  (Looked at under the way of the stores: level
+    // at head size 128, 0.1 - 0.3 us of launches of 5 - 10 us at 64.  An INT8 row with an infinite element has no finite
+    // scale: NaN either way.)
+    if constexpr (kFew && !kI8) {
+      if (__builtin_expect(fine && (any_not_finite<D, NT>(st) || (hasB && any_not_finite<D, NT>(parked))), 0)) {
+        load_queries<D, NT>(p, uA, true, col, grp, qc);
+        clear_state<D, NT>(st);
+        cur_L = uA.L;
+        cur_valid = uA.L + uA.nq;
+        cur_blk = firstA;
+        cur_new = newA;
+#pragma unroll 1
+        for (int s = 0; s < n; ++s) {
+          fetch(r0, s);
+          step(r0, s, false);
+        }
+        deliver();
+      }
     }
     const bool exchA = !soloA, exchB = hasB && !soloB;
     if (p.fused_reduce && (exchA || exchB)) {
