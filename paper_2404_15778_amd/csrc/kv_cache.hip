@@ -84,8 +84,8 @@ __global__ __launch_bounds__(256) void kv_rows_bf16(KvParams p) {
 // in either direction and for bf16 and INT8 caches.  Bound by memory; what matters is that both sides are whole
 // 16-byte chunks of consecutive addresses.  A cache block mixes its 32 tokens (and V turns them: eight tokens of
 // one head element per chunk), so the block is turned in LDS instead of by 1- or 2-byte accesses to memory.
-// A block that the rows cover only partly keeps its other tokens (read-modify-write; no other workgroup
-// touches the block).
+// Of a block that the rows cover only partly nothing but their own bytes is written, element by element in V: appends
+// to other tokens of the block may run at the same time.
 // Measured, 8 prompts of up to 2048 tokens, 32 heads of 128, one layer: INT8 append 162 -> 52 us (4.7 TB/s), bf16
 // append and gather together 209 -> 131 us (4.9 TB/s); before: one thread per 16 bytes of a row, V by single bytes
 // (INT8) or halfwords (bf16 gather).
@@ -159,16 +159,20 @@ __global__ __launch_bounds__(256) void kv_blocks_bf16_append(KvParams p, int blo
   __syncthreads();
   for (int c = tid; c < (D / 16) * 64; c += 256) {
     const int mt = c / 64, l = c % 64, grp = l >> 4, dr = l & 15;
-    uint4* dst = (uint4*)(vc + (size_t)c * 8);
-    uint4 cur = make_uint4(0, 0, 0, 0);
-    if (!o.whole) cur = *dst;
-    uint16_t* e = (uint16_t*)&cur;
+    uint16_t* dst = vc + (size_t)c * 8;
+    if (o.whole) {
+      uint4 chunk;
+      uint16_t* e = (uint16_t*)&chunk;
 #pragma unroll
-    for (int jj = 0; jj < 8; ++jj) {
-      const int w = v_token(grp, jj);
-      if (o.whole || takes_part(o, w)) e[jj] = vt[w][16 * mt + dr];
+      for (int jj = 0; jj < 8; ++jj) e[jj] = vt[v_token(grp, jj)][16 * mt + dr];
+      *(uint4*)dst = chunk;
+    } else {
+#pragma unroll
+      for (int jj = 0; jj < 8; ++jj) {
+        const int w = v_token(grp, jj);
+        if (takes_part(o, w)) dst[jj] = vt[w][16 * mt + dr];
+      }
     }
-    *dst = cur;
   }
 }
 
@@ -262,21 +266,19 @@ __global__ __launch_bounds__(256) void kv_blocks_i8_append(KvParams p, int block
     const int tile = c / 64 / (D / 64), ks = c / 64 % (D / 64);  // K: token 16 tile + r, head elements 64 ks + 16 grp ..
     if (takes_part(o, 16 * tile + r)) *(uint4*)(kc + 16 * c) = *(const uint4*)&kt[16 * tile + r][64 * ks + 16 * grp];
     const int d = 32 * (c / 64) + r;  // V: head elements d and d + 16 of eight tokens
-    uint4* dst = (uint4*)(vc + 16 * c);
-    uint32_t word[4] = {0u, 0u, 0u, 0u};
-    if (!o.whole) {
-      const uint4 cur = *dst;
-      word[0] = cur.x; word[1] = cur.y; word[2] = cur.z; word[3] = cur.w;
-    }
+    uint8_t* dst = vc + 16 * c;
+    if (o.whole) {
+      uint32_t word[4] = {0u, 0u, 0u, 0u};
 #pragma unroll
-    for (int e = 0; e < 16; ++e) {
-      const int w = v_token(grp, e & 7);
-      if (o.whole || takes_part(o, w)) {
-        const uint32_t code = vt[w][d + 16 * (e >> 3)];
-        word[e >> 2] = (word[e >> 2] & ~(0xFFu << (8 * (e & 3)))) | (code << (8 * (e & 3)));
+      for (int e = 0; e < 16; ++e) word[e >> 2] |= (uint32_t)vt[v_token(grp, e & 7)][d + 16 * (e >> 3)] << (8 * (e & 3));
+      *(uint4*)dst = make_uint4(word[0], word[1], word[2], word[3]);
+    } else {
+#pragma unroll
+      for (int e = 0; e < 16; ++e) {
+        const int w = v_token(grp, e & 7);
+        if (takes_part(o, w)) dst[e] = vt[w][d + 16 * (e >> 3)];
       }
     }
-    *dst = make_uint4(word[0], word[1], word[2], word[3]);
   }
   if (tid < kBlockTokens && takes_part(o, tid)) {
     ((float*)(kc + (size_t)kBlockTokens * D))[tid] = kscale[tid];
