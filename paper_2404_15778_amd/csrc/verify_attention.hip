@@ -1372,9 +1372,10 @@ __global__ __launch_bounds__(128 * TW, 2) void verify_attn_tiles_bf16(AttnParams
       }
       fetch(g, ph + kTileAhead);
       // Fused append: blocks that hold new tokens are patched in LDS once they are complete there (K: the
-      // 16-byte chunks of the new rows; V: their elements, 2 bytes each), and the patched chunks go into the
-      // cache from LDS as whole 16-byte chunks.  The test is workgroup-uniform; the loads of the new rows
-      // sit under this branch and cost a full wait, in these one or two phases per unit only.
+      // 16-byte chunks of the new rows; V: their elements, 2 bytes each), and the same bytes go into the cache: nothing
+      // but the new rows is written, other appends may write other tokens of the block.  The test is
+      // workgroup-uniform; the loads of the new rows sit under this branch and cost a full wait, in these one or
+      // two phases per unit only.
       const int tok0 = (blk0 + 2 * ph) * kBlockTokens;                     // the phase's tokens that are ours:
       const int tok1 = (blk0 + min(2 * ph + 2, n)) * kBlockTokens;         // tok0 .. tok1 - 1
       if (kFused && u.nq > 0 && tok0 < min(u.L + u.nq, tok1) && tok1 > u.L) {
@@ -1393,20 +1394,14 @@ __global__ __launch_bounds__(128 * TW, 2) void verify_attn_tiles_bf16(AttnParams
           kdst[ko] = kv;
           const uint32_t vw[4] = {vv.x, vv.y, vv.z, vv.w};
 #pragma unroll
-          for (int e = 0; e < 8; ++e)
-            ((uint16_t*)&ring_v[slot][h * kBlkVec])[v_elem_offset(D, tw, 8 * ck + e)] = (uint16_t)(vw[e >> 1] >> (16 * (e & 1)));
+          for (int e = 0; e < 8; ++e) {
+            const uint16_t v = (uint16_t)(vw[e >> 1] >> (16 * (e & 1)));
+            const size_t vo = h * kBlkVec * 8 + v_elem_offset(D, tw, 8 * ck + e);
+            ((uint16_t*)&ring_v[slot][0])[vo] = v;
+            ((uint16_t*)vdst)[vo] = v;
+          }
         }
         __syncthreads();  // the patches are visible
-        for (int c = tid; c < kPhase; c += kThreads) {  // V chunks that hold a new token: back into the cache
-          const int cg = (c & 63) >> 4, first = tok0 + c / kBlkVec * kBlockTokens;
-          bool any = false;
-#pragma unroll
-          for (int jj = 0; jj < 8; ++jj) {
-            const int t = first + (jj < 4 ? 4 * cg + jj : 16 + 4 * cg + (jj - 4));
-            any |= t >= u.L && t < min(u.L + u.nq, tok1);
-          }
-          if (any) vdst[c] = ring_v[slot][c];
-        }
       } else {
         __syncthreads();
       }
@@ -1527,8 +1522,7 @@ __global__ __launch_bounds__(256, 2) void verify_attn_tiles_i8(AttnParams p) {
       if (wv == 0) ring_s[slot][lane] = g.scale;
       fetch(g, s + kTileAheadI8);
       // Fused append: as in the bf16 kernel; the rows are quantized as the append kernel does (a row's D / 8 lanes agree
-      // on its largest magnitude), codes and scales go into LDS and, K and the scales, into the cache; V chunks
-      // follow from LDS.
+      // on its largest magnitude), codes and scales go into LDS and into the cache.
       const int tok0 = (blk0 + s) * kBlockTokens;
       if (kFused && s < n && u.nq > 0 && tok0 < u.L + u.nq && tok0 + kBlockTokens > u.L) {
         uint8_t* kblk = (uint8_t*)((uint4*)const_cast<void*>(p.Kc) + vec0 + (ptrdiff_t)s * kBlkVec);
@@ -1558,8 +1552,10 @@ __global__ __launch_bounds__(256, 2) void verify_attn_tiles_i8(AttnParams p) {
             const uint4 vb = codes_to_bf16(vq.x, vq.y);
             const uint32_t vw[4] = {vb.x, vb.y, vb.z, vb.w};
 #pragma unroll
-            for (int e = 0; e < 8; ++e)
+            for (int e = 0; e < 8; ++e) {
               ((uint16_t*)&ring_v[slot][0])[v_elem_offset(D, tw, 8 * ck + e)] = (uint16_t)(vw[e >> 1] >> (16 * (e & 1)));
+              vblk[i8_v_offset(D, tw, 8 * ck + e)] = (uint8_t)((e < 4 ? vq.x : vq.y) >> (8 * (e & 3)));
+            }
             if (ck == 0) {
               const float ks = ka / 127.0f, vs = va / 127.0f;
               ring_s[slot][tw] = ks;
@@ -1570,29 +1566,6 @@ __global__ __launch_bounds__(256, 2) void verify_attn_tiles_i8(AttnParams p) {
           }
         }
         __syncthreads();  // the patches are visible
-        for (int c = threadIdx.x; c < kCodeVec; c += 256) {  // V chunks that hold a new token: back into the cache
-          const int cg = (c & 63) >> 4;
-          bool any = false;
-#pragma unroll
-          for (int jj = 0; jj < 8; ++jj) {
-            const int t = tok0 + (jj < 4 ? 4 * cg + jj : 16 + 4 * cg + (jj - 4));
-            any |= t >= u.L && t < u.L + u.nq;
-          }
-          if (any) {
-            uint32_t w[4] = {0u, 0u, 0u, 0u};
-#pragma unroll
-            for (int f = 0; f < 2; ++f) {
-              const uint4 frag = ring_v[slot][(2 * (c >> 6) + f) * 64 + (c & 63)];
-              const uint32_t fw[4] = {frag.x, frag.y, frag.z, frag.w};
-#pragma unroll
-              for (int e = 0; e < 8; ++e) {  // codes are whole numbers of at most 7 bits: exact in bf16
-                const int code = (int)bf16_bits_to_float((fw[e >> 1] >> (16 * (e & 1))) & 0xFFFFu);
-                w[2 * f + (e >> 2)] |= ((uint32_t)code & 0xFFu) << (8 * (e & 3));
-              }
-            }
-            *(uint4*)(vblk + 16 * c) = make_uint4(w[0], w[1], w[2], w[3]);
-          }
-        }
       } else {
         __syncthreads();
       }
