@@ -476,15 +476,19 @@ static int launch_rows(const bass_attn_desc* d, void* Kc, void* Vc, void* Kr, vo
   KvParams p{d->B, d->kmax, d->Hkv, d->D, d->Lcap, num_blocks(d->Lcap), Kc, Vc, Kr, Vr, off, cnt, status, Ks, Vs};
   dim3 grid((unsigned)((items + 255) / 256));
   hipStream_t s = (hipStream_t)stream;
-  // From one block of rows on, by blocks; fewer rows (a step's drafts) by single rows, whose launch is one short
-  // dependent chain.
+  // From one block of row slots on, by blocks; fewer (a step's drafts) by single rows, whose launch is one short
+  // dependent chain.  So are appends to INT8 caches that fill less than 192 workgroups by rows: the turn in LDS costs
+  // 0.3 - 0.8 us, and there is a fraction of a wave of workgroups to gain.  Against blocks, calls of up to 192 such
+  // workgroups: 4 - 5 us, up to 20 % shorter with few rows in many slots, 0 - 5 % longer with all slots used; of 192 - 256 and
+  // more: blocks 16 % and more shorter with all slots used.
   const int64_t per_seq = (d->kmax + kBlockTokens - 1) / kBlockTokens + 1;  // blocks the rows of a sequence can touch
   const int64_t wgs = ((int64_t)d->B * per_seq + kXcds - 1) / kXcds * kXcds * d->Hkv;
-  if (d->dtype != BASS_DTYPE_FP32 && d->kmax >= kBlockTokens && wgs <= 0x7fffffff) {
-    const bool int8 = d->dtype == BASS_DTYPE_INT8KV;
+  const bool int8 = d->dtype == BASS_DTYPE_INT8KV;
+  const bool few_rows = int8 && !kGather && items <= 192 * 256;
+  if (d->dtype != BASS_DTYPE_FP32 && d->kmax >= kBlockTokens && !few_rows && wgs <= 0x7fffffff) {
     if (d->D == 128) launch_blocks<128>(kGather, int8, dim3((unsigned)wgs), s, p, (int)per_seq);
     else launch_blocks<64>(kGather, int8, dim3((unsigned)wgs), s, p, (int)per_seq);
-  } else if (d->dtype == BASS_DTYPE_INT8KV) {
+  } else if (int8) {
     if (kGather) hipLaunchKernelGGL(kv_rows_i8_gather, grid, dim3(256), 0, s, p);
     else hipLaunchKernelGGL(kv_rows_i8_append, grid, dim3(256), 0, s, p);
   } else if (d->dtype == BASS_DTYPE_BF16) {

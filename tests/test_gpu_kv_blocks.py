@@ -10,7 +10,7 @@ SPANS = [(0, 0), (0, 32), (31, 1), (1, 31), (5, 70), (32, 64), (90, 33), (63, 2)
 
 @pytest.mark.parametrize("dtype", ["bf16", "int8kv"])
 @pytest.mark.parametrize("D", [64, 128])
-@pytest.mark.parametrize("Hkv", [1, 3, 8])
+@pytest.mark.parametrize("Hkv", [1, 3, 8, 9])
 def test_blocks_and_rows_leave_the_same_bytes(dtype, D, Hkv):
     import torch
     import paper_2404_15778_amd as bass
