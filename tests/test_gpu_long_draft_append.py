@@ -42,3 +42,61 @@ def test_planned_append_of_long_drafts(dtype, D, kmax, Hq, Hkv):
     assert status.item() == 0
     for a, b in zip(got, want):
         assert torch.equal(a, b)
+
+
+# Stretches of several blocks: 32 workgroups share 65 - 170 blocks, so a stretch has 2 - 6 of them, even and odd counts, new
+# tokens in either or both blocks of a phase and in later phases, and units that begin and end inside a stretch.
+@pytest.mark.parametrize("dtype", ["bf16", "int8kv"])
+@pytest.mark.parametrize("ctx", [[900, 333, 640, 64, 5], [31, 400, 1000, 959, 0]])
+@pytest.mark.parametrize("D,kmax,Hq,Hkv", [(128, 20, 2, 2), (128, 32, 1, 1), (128, 64, 2, 2), (128, 24, 4, 2), (64, 32, 2, 2), (64, 60, 2, 2)])
+def test_stretches_of_several_blocks(dtype, ctx, D, kmax, Hq, Hkv):
+    import numpy as np
+    import torch
+    import oracle
+    import paper_2404_15778_amd as bass
+    from oracle.kv_int8 import dequantize_rows, quantize_rows
+    dev, B = "cuda:0", len(ctx)
+    nq = [kmax, kmax - 3, 1, kmax, kmax]
+    Lcap = max(ctx) + kmax
+    gen = torch.Generator(device=dev)
+    gen.manual_seed(D + kmax + ctx[0])
+    rand = lambda n, H: torch.randn((B, n, H, D), generator=gen, device=dev).to(torch.bfloat16)  # noqa: E731
+    i32 = lambda x: torch.tensor(x, dtype=torch.int32, device=dev)  # noqa: E731
+    d = bass.make_desc(B, kmax, Hq, Hkv, D, Lcap, dtype, 1.0 / math.sqrt(D))
+    old, new, Q = [rand(max(ctx), Hkv) for _ in range(2)], [rand(kmax, Hkv) for _ in range(2)], rand(kmax, Hq)
+    caches = [torch.full((bass.bass_kv_cache_bytes(d),), 0x7F, dtype=torch.uint8, device=dev) for _ in range(2)]
+    bass.bass_kv_append(d.replace(kmax=max(ctx)), *caches, *old, i32([0] * B), i32(ctx))
+    by_append = [t.clone() for t in caches]
+    bass.bass_kv_append(d, *by_append, *new, i32(ctx), i32(nq))
+    rows = []  # keys and values as the oracle takes them
+    for o, n in zip(old, new):
+        r = np.zeros((B, Lcap, Hkv, D), np.float32)
+        for b in range(B):
+            r[b, :ctx[b]], r[b, ctx[b]:ctx[b] + nq[b]] = o[b, :ctx[b]].float().cpu().numpy(), n[b, :nq[b]].float().cpu().numpy()
+        rows.append(r)
+    q = Q.float().cpu().numpy()
+    if dtype == "int8kv":
+        q, *rows = [dequantize_rows(*quantize_rows(x)) for x in (q, *rows)]
+    want, want_lse = oracle.verify_attention(q, *rows, np.array(ctx, np.int32), np.array(nq, np.int32), d.scale)
+    O, lse = torch.full((B, kmax, Hq, D), 7.0, device=dev), torch.full((B, kmax, Hq), 7.0, device=dev)
+    status, plan, ws = torch.zeros(1, dtype=torch.int32, device=dev), bass.alloc_plan(d, dev), bass.alloc_workspace(d, dev)
+    bass.bass_set_attention_waves(64)
+    try:
+        bass.bass_attention_plan(d, i32(ctx), i32(nq), bass.PLAN_APPEND, 0, plan, status)
+        bass.bass_verify_attention_planned(d, Q, *new, *caches, plan, O, lse, ws, status)
+    finally:
+        bass.bass_set_attention_waves(0)
+    assert status.item() == 0
+    # valid tokens: the same codes and scales (stale ones may differ)
+    def tokens(c):
+        out = [torch.zeros((B, Lcap, Hkv, D), dtype=torch.int8 if dtype == "int8kv" else torch.bfloat16, device=dev) for _ in range(2)]
+        start, n = i32([0] * B), i32([c_ + n_ for c_, n_ in zip(ctx, nq)])
+        if dtype == "int8kv":
+            out += [torch.zeros((B, Lcap, Hkv), device=dev) for _ in range(2)]
+            bass.bass_kv_gather_int8(d.replace(kmax=Lcap), *c, *out, start, n)
+        else:
+            bass.bass_kv_gather(d.replace(kmax=Lcap), *c, *out, start, n)
+        return out
+    assert all(torch.equal(a, b) for a, b in zip(tokens(caches), tokens(by_append)))
+    # probabilities are rounded to bf16: 2^-9 of each, times values of up to 5; the rows' sums stay in 32 bits
+    assert np.abs(O.cpu().numpy() - want).max() <= 2e-2 and np.abs(lse.cpu().numpy() - want_lse).max() <= 1e-3
