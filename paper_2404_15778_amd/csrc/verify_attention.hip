@@ -1294,30 +1294,28 @@ __global__ __launch_bounds__(256) void verify_attn_bf16(AttnParams p) {
 // Workgroup-level kernel for kv heads with more than 16 query rows (grouped-query attention, long drafts), bf16.
 // The accumulators of two to four 16-row tiles in ONE wavefront leave registers for a single block in
 // flight, and re-reading blocks by several wavefronts crosses the fabric twice.  Here a workgroup of
-// 2 TW wavefronts takes a stretch of the block list together: every K/V block is fetched from memory
+// TW H wavefronts takes a stretch of the block list together: every K/V block is fetched from memory
 // once (each wavefront a part of it), put into a ring in LDS, and read from there by the wavefronts that own
 // a query tile (rows 16 t .. 16 t + 15), each running the one-tile block step.  A step is a serial chain (scores,
-// maximum, exponentials, products) of about a microsecond that one wavefront per SIMD cannot hide, so the
+// maximum, exponentials, products) of about a microsecond that one wavefront per SIMD cannot hide, so with H = 2 the
 // ring holds two blocks per phase and each tile has two wavefronts, one for the even and one for the odd
 // blocks, whose states are merged through LDS at the end of the unit.  One barrier per phase: a slot is rewritten
 // only after the barrier that follows the last step that read it.  Every barrier sits in workgroup-uniform
 // control flow (the stretch, the units and the block counts depend on the workgroup index and the lengths only).
-// TW: tiles a workgroup has room for, 2 or 4 -- with two, four wavefronts are enough and all of them have a tile.
-// Steps of 16 layers (attention, merge): 16 sequences of 1024 - 4096 tokens, 64/8 heads of 128, 48 rows per kv head
-// 817 -> 759 us; 8 sequences of 512 - 2048 tokens, 32 heads, 32 rows 922 -> 907 us (one block per phase, four
-// wavefronts before).  Three and four phases ahead spill: 775 and 803, 1005 and 1568 us.
+// TW: tiles a workgroup has room for (launch_tiles says which form serves which call).  H = 2, 16 layers of 16 sequences of
+// 1024 - 4096 tokens, 64/8 heads of 128, 48 rows per kv head: 817 -> 759 us (attention, merge); three and four phases
+// ahead spill: 775 and 803.
 // ---------------------------------------------------------------------------------------
-constexpr int kTileAhead = 2;  // phases of two blocks a workgroup has in flight from memory
-
-template <int D, bool kFused, int TW>
-__global__ __launch_bounds__(128 * TW, 2) void verify_attn_tiles_bf16(AttnParams p) {
-  constexpr int kThreads = 128 * TW;
+template <int D, bool kFused, int TW, int H>
+__global__ __launch_bounds__(64 * TW * H, 2) void verify_attn_tiles_bf16(AttnParams p) {
+  constexpr int kThreads = 64 * TW * H;
+  constexpr int kTileAhead = H == 2 ? 2 : 3;          // phases a workgroup has in flight from memory
   constexpr int kBlkVec = kBlockTokens * D * 2 / 16;  // uint4 per block and tensor
-  constexpr int kPhase = 2 * kBlkVec;                  // ... and per phase (a unit's blocks lie one after the other)
+  constexpr int kPhase = H * kBlkVec;                  // ... and per phase (a unit's blocks lie one after the other)
   constexpr int kLoads = kPhase / kThreads;            // 16-byte loads per lane, phase and tensor
   __shared__ uint4 ring_k[2][kPhase];
   __shared__ uint4 ring_v[2][kPhase];
-  __shared__ float other_m[TW][64], other_l[TW][64];  // states of the odd blocks' wavefronts (accumulators: in ring_k)
+  __shared__ float other_m[H == 2 ? TW : 1][64], other_l[H == 2 ? TW : 1][64];  // states of the odd blocks' wavefronts (accumulators: in ring_k)
   const int tid = threadIdx.x, lane = tid & 63, wv = tid >> 6;
   const int tile = wv % TW, half = wv / TW;
   const int col = lane & 15, grp = lane >> 4;
@@ -1354,8 +1352,8 @@ __global__ __launch_bounds__(128 * TW, 2) void verify_attn_tiles_bf16(AttnParams
     auto fetch = [&](Stage& g, int ph) {
 #pragma unroll
       for (int i = 0; i < kLoads; ++i) {
-        const int c = i * kThreads + tid, h = i * kThreads / kBlkVec + (tid >= kBlkVec ? 1 : 0);
-        const ptrdiff_t off = vec0 + (2 * ph + h < n ? (ptrdiff_t)ph * kPhase + c : (ptrdiff_t)(c - h * kBlkVec));
+        const int c = i * kThreads + tid, h = H == 1 ? 0 : i * kThreads / kBlkVec + (tid >= kBlkVec ? 1 : 0);
+        const ptrdiff_t off = vec0 + (H * ph + h < n ? (ptrdiff_t)ph * kPhase + c : (ptrdiff_t)(c - h * kBlkVec));
         g.k[i] = __builtin_bit_cast(uint4, __builtin_nontemporal_load((const u32x4*)(kc + off)));
         g.v[i] = __builtin_bit_cast(uint4, __builtin_nontemporal_load((const u32x4*)(vc + off)));
       }
@@ -1376,8 +1374,8 @@ __global__ __launch_bounds__(128 * TW, 2) void verify_attn_tiles_bf16(AttnParams
       // but the new rows is written, other appends may write other tokens of the block.  The test is
       // workgroup-uniform; the loads of the new rows sit under this branch and cost a full wait, in these one or
       // two phases per unit only.
-      const int tok0 = (blk0 + 2 * ph) * kBlockTokens;                     // the phase's tokens that are ours:
-      const int tok1 = (blk0 + min(2 * ph + 2, n)) * kBlockTokens;         // tok0 .. tok1 - 1
+      const int tok0 = (blk0 + H * ph) * kBlockTokens;                     // the phase's tokens that are ours:
+      const int tok1 = (blk0 + min(H * ph + H, n)) * kBlockTokens;         // tok0 .. tok1 - 1
       if (kFused && u.nq > 0 && tok0 < min(u.L + u.nq, tok1) && tok1 > u.L) {
         __syncthreads();  // the blocks are complete in LDS
         const int i_lo = max(0, tok0 - u.L), i_hi = min(u.nq, tok1 - u.L);
@@ -1405,7 +1403,7 @@ __global__ __launch_bounds__(128 * TW, 2) void verify_attn_tiles_bf16(AttnParams
       } else {
         __syncthreads();
       }
-      if (active && 2 * ph + half < n) {
+      if (active && H * ph + half < n) {
         KvRegs<D> r;
         const uint4* lk = &ring_k[slot][half * kBlkVec + lane];
         const uint4* lv = &ring_v[slot][half * kBlkVec + lane];
@@ -1413,36 +1411,38 @@ __global__ __launch_bounds__(128 * TW, 2) void verify_attn_tiles_bf16(AttnParams
         for (int i = 0; i < 2 * (D / 32); ++i) r.k[i] = lk[i * 64];
 #pragma unroll
         for (int i = 0; i < D / 16; ++i) r.v[i] = lv[i * 64];
-        block_dispatch<D, 1>(r, q.q, st, blk0 + 2 * ph + half, u.L, u.L + u.nq, q.lim, p.scale_log2, lane, false, NewRows{}, nullptr, nullptr);
+        block_dispatch<D, 1>(r, q.q, st, blk0 + H * ph + half, u.L, u.L + u.nq, q.lim, p.scale_log2, lane, false, NewRows{}, nullptr, nullptr);
       }
     };
     __syncthreads();  // the previous unit's merge has left the ring
     Stage g[kTileAhead];
 #pragma unroll
     for (int j = 0; j < kTileAhead; ++j) fetch(g[j], j);
-    for (int ph = 0; 2 * ph < n; ph += kTileAhead) {  // workgroup-uniform trip count
+    for (int ph = 0; H * ph < n; ph += kTileAhead) {  // workgroup-uniform trip count
 #pragma unroll
       for (int j = 0; j < kTileAhead; ++j) phase(g[j], ph + j);
     }
-    // the odd blocks' state joins the even blocks' (a state that saw no visible token has m = -inf and no weight)
-    __syncthreads();  // the last steps have left the ring
-    f32x4* other_acc = (f32x4*)&ring_k[0][0] + tile * (D / 16) * 64 + lane;
-    if (half == 1 && active) {
+    // the odd blocks' state joins the even blocks' (one that saw no visible token has m = -inf and no weight)
+    if (H == 2 && n > 1) {
+      __syncthreads();  // the last steps have left the ring
+      f32x4* other_acc = (f32x4*)&ring_k[0][0] + tile * (D / 16) * 64 + lane;
+      if (half == 1 && active) {
 #pragma unroll
-      for (int mt = 0; mt < D / 16; ++mt) other_acc[mt * 64] = st.acc[0][mt];
-      other_m[tile][lane] = st.m[0];
-      other_l[tile][lane] = st.l[0];
-    }
-    __syncthreads();
-    if (half == 0 && active) {
-      const float m1 = other_m[tile][lane], M = fmaxf(st.m[0], m1), Mf = M == -INFINITY ? 0.f : M;
-      const float w0 = __builtin_amdgcn_exp2f(st.m[0] - Mf), w1 = __builtin_amdgcn_exp2f(m1 - Mf);
-      st.m[0] = M;
-      st.l[0] = st.l[0] * w0 + other_l[tile][lane] * w1;
+        for (int mt = 0; mt < D / 16; ++mt) other_acc[mt * 64] = st.acc[0][mt];
+        other_m[tile][lane] = st.m[0];
+        other_l[tile][lane] = st.l[0];
+      }
+      __syncthreads();
+      if (half == 0 && active) {
+        const float m1 = other_m[tile][lane], M = fmaxf(st.m[0], m1), Mf = M == -INFINITY ? 0.f : M;
+        const float w0 = __builtin_amdgcn_exp2f(st.m[0] - Mf), w1 = __builtin_amdgcn_exp2f(m1 - Mf);
+        st.m[0] = M;
+        st.l[0] = st.l[0] * w0 + other_l[tile][lane] * w1;
 #pragma unroll
-      for (int mt = 0; mt < D / 16; ++mt) st.acc[0][mt] = st.acc[0][mt] * w0 + other_acc[mt * 64] * w1;
-      store_partial<D, 1>(p, u, wg, st, col, grp, row0);
+        for (int mt = 0; mt < D / 16; ++mt) st.acc[0][mt] = st.acc[0][mt] * w0 + other_acc[mt * 64] * w1;
+      }
     }
+    if (half == 0 && active) store_partial<D, 1>(p, u, wg, st, col, grp, row0);
   }
 }
 
@@ -1795,6 +1795,26 @@ static int check_attention_args(const bass_attn_desc* d, const LaunchShape& ls, 
   return BASS_OK;
 }
 
+// The workgroup-level kernels.  bf16: two wavefronts per query tile and two blocks per phase, but for at most two tiles of head
+// size 128: there one block per phase with two of four wavefronts only copying is as quick or quicker.  64/8 heads, 24 rows,
+// 1 - 16 sequences of 20 - 4000 tokens: 0 - 12 %; 32 heads, 32 rows, 8 sequences of 1200 / 4000 tokens: 42.5 -> 42.4 /
+// 136 -> 110 us, 16 of 1200: 81 -> 78; 20 rows, 16 sequences of 100 / 4000: 25.0 -> 25.9 / 182.9 -> 183.7.  At head size 64
+// two blocks per phase are 0 - 17 % quicker.
+template <bool kFused>
+static void launch_tiles(const bass_attn_desc* d, dim3 grid, hipStream_t s, const AttnParams& p) {
+  const bool big = d->D == 128, two = p.rows_max <= 32;
+  if (d->dtype == BASS_DTYPE_INT8KV) {
+    if (big) hipLaunchKernelGGL((verify_attn_tiles_i8<128, kFused>), grid, dim3(256), 0, s, p);
+    else hipLaunchKernelGGL((verify_attn_tiles_i8<64, kFused>), grid, dim3(256), 0, s, p);
+  } else if (!two) {
+    if (big) hipLaunchKernelGGL((verify_attn_tiles_bf16<128, kFused, 4, 2>), grid, dim3(512), 0, s, p);
+    else hipLaunchKernelGGL((verify_attn_tiles_bf16<64, kFused, 4, 2>), grid, dim3(512), 0, s, p);
+  } else {
+    if (big) hipLaunchKernelGGL((verify_attn_tiles_bf16<128, kFused, 4, 1>), grid, dim3(256), 0, s, p);
+    else hipLaunchKernelGGL((verify_attn_tiles_bf16<64, kFused, 2, 2>), grid, dim3(256), 0, s, p);
+  }
+}
+
 // The attention launch (and, with many query rows per kv head, the merge launch) for a plan that lies at
 // `plan`, made for the shape `ls`; K_new / V_new: the rows a fused append puts into the caches, or null.
 static int launch_attention(const bass_attn_desc* d, const LaunchShape& ls, const void* Q, const void* K_new,
@@ -1832,21 +1852,8 @@ static int launch_attention(const bass_attn_desc* d, const LaunchShape& ls, cons
     hipLaunchKernelGGL(verify_attn_fp32, grid, block, 0, s, p);
   } else if (ls.tiles) {
     const dim3 tgrid((unsigned)ls.used_shares);
-    const bool two = rows_max <= 32;  // bf16: two tiles, four wavefronts
-#define BASS_LAUNCH_TILES(THREADS, KERNEL, ...)                                                                    \
-  do {                                                                                                             \
-    if (d->D == 128) {                                                                                             \
-      if (K_new) hipLaunchKernelGGL((KERNEL<128, true __VA_ARGS__>), tgrid, dim3(THREADS), 0, s, p);               \
-      else hipLaunchKernelGGL((KERNEL<128, false __VA_ARGS__>), tgrid, dim3(THREADS), 0, s, p);                    \
-    } else {                                                                                                       \
-      if (K_new) hipLaunchKernelGGL((KERNEL<64, true __VA_ARGS__>), tgrid, dim3(THREADS), 0, s, p);                \
-      else hipLaunchKernelGGL((KERNEL<64, false __VA_ARGS__>), tgrid, dim3(THREADS), 0, s, p);                     \
-    }                                                                                                              \
-  } while (0)
-    if (d->dtype == BASS_DTYPE_INT8KV) BASS_LAUNCH_TILES(256, verify_attn_tiles_i8);
-    else if (two) BASS_LAUNCH_TILES(256, verify_attn_tiles_bf16, , 2);
-    else BASS_LAUNCH_TILES(512, verify_attn_tiles_bf16, , 4);
-#undef BASS_LAUNCH_TILES
+    if (K_new) launch_tiles<true>(d, tgrid, s, p);
+    else launch_tiles<false>(d, tgrid, s, p);
   } else {  // one query tile
     // LDS slice per wavefront of a fused append: K and V rows of two units (bf16, or INT8 codes + scales)
     const size_t unit_lds = d->dtype == BASS_DTYPE_INT8KV ? (size_t)2 * d->kmax * d->D + 8 * d->kmax
