@@ -1306,6 +1306,31 @@ __global__ __launch_bounds__(256) void verify_attn_bf16(AttnParams p) {
 // 1024 - 4096 tokens, 64/8 heads of 128, 48 rows per kv head: 817 -> 759 us (attention, merge); three and four phases
 // ahead spill: 775 and 803.
 // ---------------------------------------------------------------------------------------
+// Two wavefronts per tile: the state of the odd blocks joins that of the even ones (one that saw no visible token has
+// m = -inf and no weight).  All wavefronts call; a stretch of one block has nothing to join.  acc: LDS for TW tiles' accumulators.
+template <int D, int TW>
+__device__ inline void merge_halves(RowState<D, 1>& st, int n, int half, int tile, bool active, int lane, f32x4* acc,
+                                    float (&other_m)[TW][64], float (&other_l)[TW][64]) {
+  if (n <= 1) return;  // workgroup-uniform
+  __syncthreads();     // the last steps have left the ring
+  f32x4* other_acc = acc + tile * (D / 16) * 64 + lane;
+  if (half == 1 && active) {
+#pragma unroll
+    for (int mt = 0; mt < D / 16; ++mt) other_acc[mt * 64] = st.acc[0][mt];
+    other_m[tile][lane] = st.m[0];
+    other_l[tile][lane] = st.l[0];
+  }
+  __syncthreads();
+  if (half == 0 && active) {
+    const float m1 = other_m[tile][lane], M = fmaxf(st.m[0], m1), Mf = M == -INFINITY ? 0.f : M;
+    const float w0 = __builtin_amdgcn_exp2f(st.m[0] - Mf), w1 = __builtin_amdgcn_exp2f(m1 - Mf);
+    st.m[0] = M;
+    st.l[0] = st.l[0] * w0 + other_l[tile][lane] * w1;
+#pragma unroll
+    for (int mt = 0; mt < D / 16; ++mt) st.acc[0][mt] = st.acc[0][mt] * w0 + other_acc[mt * 64] * w1;
+  }
+}
+
 template <int D, bool kFused, int TW, int H>
 __global__ __launch_bounds__(64 * TW * H, 2) void verify_attn_tiles_bf16(AttnParams p) {
   constexpr int kThreads = 64 * TW * H;
@@ -1422,26 +1447,7 @@ __global__ __launch_bounds__(64 * TW * H, 2) void verify_attn_tiles_bf16(AttnPar
 #pragma unroll
       for (int j = 0; j < kTileAhead; ++j) phase(g[j], ph + j);
     }
-    // the odd blocks' state joins the even blocks' (one that saw no visible token has m = -inf and no weight)
-    if (H == 2 && n > 1) {
-      __syncthreads();  // the last steps have left the ring
-      f32x4* other_acc = (f32x4*)&ring_k[0][0] + tile * (D / 16) * 64 + lane;
-      if (half == 1 && active) {
-#pragma unroll
-        for (int mt = 0; mt < D / 16; ++mt) other_acc[mt * 64] = st.acc[0][mt];
-        other_m[tile][lane] = st.m[0];
-        other_l[tile][lane] = st.l[0];
-      }
-      __syncthreads();
-      if (half == 0 && active) {
-        const float m1 = other_m[tile][lane], M = fmaxf(st.m[0], m1), Mf = M == -INFINITY ? 0.f : M;
-        const float w0 = __builtin_amdgcn_exp2f(st.m[0] - Mf), w1 = __builtin_amdgcn_exp2f(m1 - Mf);
-        st.m[0] = M;
-        st.l[0] = st.l[0] * w0 + other_l[tile][lane] * w1;
-#pragma unroll
-        for (int mt = 0; mt < D / 16; ++mt) st.acc[0][mt] = st.acc[0][mt] * w0 + other_acc[mt * 64] * w1;
-      }
-    }
+    if constexpr (H == 2) merge_halves<D, TW>(st, n, half, tile, active, lane, (f32x4*)&ring_k[0][0], other_m, other_l);
     if (half == 0 && active) store_partial<D, 1>(p, u, wg, st, col, grp, row0);
   }
 }
@@ -1452,22 +1458,28 @@ __global__ __launch_bounds__(64 * TW * H, 2) void verify_attn_tiles_bf16(AttnPar
 // query tile, and no wavefront holds more than one tile.  (Up to four tiles in one wavefront spilled registers and left
 // one wavefront per SIMD: what bounds these shapes is instruction issue, not memory.  Attention of 16 sequences of 1024 -
 // 4096 tokens, 64/8 heads of 128, 64 rows per kv head, with its merge: 72 -> 48 us per layer, 94 MB.)
+// Four wavefronts: H = 1, TW = 4, one block per phase; with at most two tiles H = 2, TW = 2, two wavefronts per tile, as above,
+// which take S blocks each per phase.
 // ---------------------------------------------------------------------------------------
-constexpr int kTileAheadI8 = 4;  // blocks a workgroup has in flight from memory
-
-template <int D, bool kFused>
+template <int D, bool kFused, int TW, int H, int S>
 __global__ __launch_bounds__(256, 2) void verify_attn_tiles_i8(AttnParams p) {
+  static_assert(TW * H == 4, "four wavefronts");
+  constexpr int P = H * S;                    // blocks per phase
+  constexpr int kAhead = P <= 2 ? 4 / P : 2;  // phases a workgroup has in flight from memory
   constexpr int kCodeVec = 2 * D;             // uint4 of codes per block and tensor
   constexpr int kBlkVec = kCodeVec + 8;       // ... and its 32 scales
   constexpr int kChunks = D / 32;             // 64-lane chunks of codes per tensor
-  constexpr int kLoads = 2 * kChunks / 4;     // chunks a wavefront moves per block: numbers wv, wv + 4, ... of K's, then V's
-  __shared__ uint4 ring_k[2][kCodeVec];       // codes
-  __shared__ uint4 ring_v[2][2 * kCodeVec];   // the codes as bf16, fragments as in a bf16 cache
-  __shared__ __align__(16) float ring_s[2][2 * kBlockTokens];  // K scales, V scales
+  constexpr int kMoves = 2 * kChunks / 4;     // chunks a wavefront moves per block: numbers wv, wv + 4, ... of K's, then V's
+  constexpr int kLoads = P * kMoves;          // ... and per phase
+  __shared__ uint4 ring_k[2][P * kCodeVec];      // codes
+  __shared__ uint4 ring_v[2][P * 2 * kCodeVec];  // the codes as bf16, fragments as in a bf16 cache
+  __shared__ __align__(16) float ring_s[2][P * 2 * kBlockTokens];  // K scales, V scales of each block
+  __shared__ float other_m[H == 2 ? TW : 1][64], other_l[H == 2 ? TW : 1][64];  // as in the bf16 kernel (accumulators: in ring_v)
   const int lane = threadIdx.x & 63, wv = uniform(threadIdx.x >> 6);
   const int col = lane & 15, grp = lane >> 4;
   const int wg = blockIdx.x;
-  const int row0 = 16 * wv;
+  const int tile = wv % TW, half = wv / TW;
+  const int row0 = 16 * tile;
 
   const ShareRecord* rec = p.records + wg;
   const int nseg = uniform(rec->nseg), overflow = uniform(rec->overflow);
@@ -1495,44 +1507,44 @@ __global__ __launch_bounds__(256, 2) void verify_attn_tiles_i8(AttnParams p) {
     const int blk0 = seg.first;
     const ptrdiff_t vec0 = (((ptrdiff_t)u.b * p.Hkv + u.kvh) * p.nblk_cap + blk0) * kBlkVec;
 
-    // all fetches unconditional (exact wait counts); one past the end re-reads the stretch's first block
-    auto fetch = [&](Stage& g, int s) {
-      const ptrdiff_t off = vec0 + (s < n ? (ptrdiff_t)s * kBlkVec : 0);
+    // all fetches unconditional (exact wait counts); a block past the end re-reads the stretch's first block
+    auto block_at = [&](int s) { return vec0 + (s < n ? (ptrdiff_t)s * kBlkVec : 0); };
+    auto fetch = [&](Stage& g, int ph) {
 #pragma unroll
       for (int i = 0; i < kLoads; ++i) {
-        const int c = wv + 4 * i;
+        const ptrdiff_t off = block_at(P * ph + i / kMoves);
+        const int c = wv + 4 * (i % kMoves);
         const uint4* src = (c < kChunks ? kc + off + c * 64 : vc + off + (c - kChunks) * 64) + lane;
         g.c[i] = __builtin_nontemporal_load((const u32x4*)src);
       }
-      g.scale = ((const float*)((lane < kBlockTokens ? kc : vc) + off + kCodeVec))[lane % kBlockTokens];
+      const ptrdiff_t at = block_at(P * ph + wv % P);
+      g.scale = ((const float*)((lane < kBlockTokens ? kc : vc) + at + kCodeVec))[lane % kBlockTokens];
     };
-    auto step = [&](Stage& g, int s) {
-      const int slot = s & 1;
+    auto phase = [&](Stage& g, int ph) {
+      const int slot = ph & 1;
 #pragma unroll
       for (int i = 0; i < kLoads; ++i) {
-        const int c = wv + 4 * i;
+        const int h = i / kMoves, c = wv + 4 * (i % kMoves);
         if (c < kChunks) {
-          ring_k[slot][c * 64 + lane] = __builtin_bit_cast(uint4, g.c[i]);
+          ring_k[slot][h * kCodeVec + c * 64 + lane] = __builtin_bit_cast(uint4, g.c[i]);
         } else {
           const int m = c - kChunks;
-          ring_v[slot][(2 * m) * 64 + lane] = codes_to_bf16(g.c[i][0], g.c[i][1]);
-          ring_v[slot][(2 * m + 1) * 64 + lane] = codes_to_bf16(g.c[i][2], g.c[i][3]);
+          ring_v[slot][h * 2 * kCodeVec + (2 * m) * 64 + lane] = codes_to_bf16(g.c[i][0], g.c[i][1]);
+          ring_v[slot][h * 2 * kCodeVec + (2 * m + 1) * 64 + lane] = codes_to_bf16(g.c[i][2], g.c[i][3]);
         }
       }
-      if (wv == 0) ring_s[slot][lane] = g.scale;
-      fetch(g, s + kTileAheadI8);
+      if (wv < P) ring_s[slot][wv * 64 + lane] = g.scale;
+      fetch(g, ph + kAhead);
       // Fused append: as in the bf16 kernel; the rows are quantized as the append kernel does (a row's D / 8 lanes agree
       // on its largest magnitude), codes and scales go into LDS and into the cache.
-      const int tok0 = (blk0 + s) * kBlockTokens;
-      if (kFused && s < n && u.nq > 0 && tok0 < u.L + u.nq && tok0 + kBlockTokens > u.L) {
-        uint8_t* kblk = (uint8_t*)((uint4*)const_cast<void*>(p.Kc) + vec0 + (ptrdiff_t)s * kBlkVec);
-        uint8_t* vblk = (uint8_t*)((uint4*)const_cast<void*>(p.Vc) + vec0 + (ptrdiff_t)s * kBlkVec);
-        __syncthreads();  // the block is complete in LDS
-        const int i_lo = max(0, tok0 - u.L), n_ck = (min(u.nq, tok0 + kBlockTokens - u.L) - i_lo) * (D / 8);
-        for (int c0 = 0; c0 < n_ck; c0 += 256) {  // the new rows of this block, 8 elements per lane
+      const int tok0 = (blk0 + P * ph) * kBlockTokens, tok1 = (blk0 + min(P * ph + P, n)) * kBlockTokens;
+      if (kFused && u.nq > 0 && tok0 < min(u.L + u.nq, tok1) && tok1 > u.L) {
+        __syncthreads();  // the blocks are complete in LDS
+        const int i_lo = max(0, tok0 - u.L), n_ck = (min(u.nq, tok1 - u.L) - i_lo) * (D / 8);
+        for (int c0 = 0; c0 < n_ck; c0 += 256) {  // the new rows of these blocks, 8 elements per lane
           const int c = min(c0 + (int)threadIdx.x, n_ck - 1);  // whole rows: a row's lanes stay together past the end too
           const int ck = threadIdx.x % (D / 8), i = i_lo + c / (D / 8);
-          const int tw = u.L + i - tok0;  // its token slot in the block
+          const int t = u.L + i - tok0, h = t / kBlockTokens, tw = t % kBlockTokens;  // its token slot in the phase's blocks
           const size_t src = (((size_t)u.b * p.kmax + i) * p.Hkv + u.kvh) * D + 8 * ck;
           const uint4 kv = *(const uint4*)((const uint16_t*)p.Knew + src);
           const uint4 vv = *(const uint4*)((const uint16_t*)p.Vnew + src);
@@ -1546,20 +1558,22 @@ __global__ __launch_bounds__(256, 2) void verify_attn_tiles_i8(AttnParams p) {
           const float vinv = va > 0.f ? 127.0f / va : 0.f;
           if (c0 + (int)threadIdx.x < n_ck) {
             const uint2 kq = quantize8(kv, kinv), vq = quantize8(vv, vinv);
+            uint8_t* kblk = (uint8_t*)((uint4*)const_cast<void*>(p.Kc) + vec0 + (ptrdiff_t)(P * ph + h) * kBlkVec);
+            uint8_t* vblk = (uint8_t*)((uint4*)const_cast<void*>(p.Vc) + vec0 + (ptrdiff_t)(P * ph + h) * kBlkVec);
             const size_t ko = i8_k_offset(D, tw, 8 * ck);
-            *(uint2*)((uint8_t*)&ring_k[slot][0] + ko) = kq;
+            *(uint2*)((uint8_t*)&ring_k[slot][h * kCodeVec] + ko) = kq;
             *(uint2*)(kblk + ko) = kq;
             const uint4 vb = codes_to_bf16(vq.x, vq.y);
             const uint32_t vw[4] = {vb.x, vb.y, vb.z, vb.w};
 #pragma unroll
             for (int e = 0; e < 8; ++e) {
-              ((uint16_t*)&ring_v[slot][0])[v_elem_offset(D, tw, 8 * ck + e)] = (uint16_t)(vw[e >> 1] >> (16 * (e & 1)));
+              ((uint16_t*)&ring_v[slot][h * 2 * kCodeVec])[v_elem_offset(D, tw, 8 * ck + e)] = (uint16_t)(vw[e >> 1] >> (16 * (e & 1)));
               vblk[i8_v_offset(D, tw, 8 * ck + e)] = (uint8_t)((e < 4 ? vq.x : vq.y) >> (8 * (e & 3)));
             }
             if (ck == 0) {
               const float ks = ka / 127.0f, vs = va / 127.0f;
-              ring_s[slot][tw] = ks;
-              ring_s[slot][kBlockTokens + tw] = vs;
+              ring_s[slot][h * 64 + tw] = ks;
+              ring_s[slot][h * 64 + kBlockTokens + tw] = vs;
               ((float*)(kblk + kBlockTokens * D))[tw] = ks;
               ((float*)(vblk + kBlockTokens * D))[tw] = vs;
             }
@@ -1569,18 +1583,21 @@ __global__ __launch_bounds__(256, 2) void verify_attn_tiles_i8(AttnParams p) {
       } else {
         __syncthreads();
       }
-      if (active && s < n) {
+#pragma unroll
+      for (int j0 = 0; j0 < S; ++j0) {
+        const int bl = half + H * j0;
+        if (!active || P * ph + bl >= n) break;
         KvRegs<D> r;
         u32x4 k[kChunks];
         TokenScales sc;
 #pragma unroll
-        for (int i = 0; i < kChunks; ++i) k[i] = __builtin_bit_cast(u32x4, ring_k[slot][i * 64 + lane]);
+        for (int i = 0; i < kChunks; ++i) k[i] = __builtin_bit_cast(u32x4, ring_k[slot][bl * kCodeVec + i * 64 + lane]);
 #pragma unroll
-        for (int i = 0; i < D / 16; ++i) r.v[i] = ring_v[slot][i * 64 + lane];
+        for (int i = 0; i < D / 16; ++i) r.v[i] = ring_v[slot][bl * 2 * kCodeVec + i * 64 + lane];
 #pragma unroll
         for (int h = 0; h < 2; ++h) {
-          const f32x4 ks = *(const f32x4*)&ring_s[slot][16 * h + 4 * grp];
-          const f32x4 vs = *(const f32x4*)&ring_s[slot][kBlockTokens + 16 * h + 4 * grp];
+          const f32x4 ks = *(const f32x4*)&ring_s[slot][bl * 64 + 16 * h + 4 * grp];
+          const f32x4 vs = *(const f32x4*)&ring_s[slot][bl * 64 + kBlockTokens + 16 * h + 4 * grp];
 #pragma unroll
           for (int j = 0; j < 4; ++j) {
             sc.k[4 * h + j] = ks[j];
@@ -1589,19 +1606,20 @@ __global__ __launch_bounds__(256, 2) void verify_attn_tiles_i8(AttnParams p) {
         }
         const I8Operands<D, 1> i8{k, q.q, q.q_scale_log2, &sc};
         const bf16x8 no_q[1][D / 32] = {};
-        block_dispatch<D, 1, true>(r, no_q, st, blk0 + s, u.L, u.L + u.nq, q.lim, p.scale_log2, lane, false, NewRows{}, nullptr,
+        block_dispatch<D, 1, true>(r, no_q, st, blk0 + P * ph + bl, u.L, u.L + u.nq, q.lim, p.scale_log2, lane, false, NewRows{}, nullptr,
                                    nullptr, &i8);
       }
     };
-    __syncthreads();  // the previous unit's last step has left the ring
-    Stage g[kTileAheadI8];
+    __syncthreads();  // the previous unit's last step (merge) has left the ring
+    Stage g[kAhead];
 #pragma unroll
-    for (int j = 0; j < kTileAheadI8; ++j) fetch(g[j], j);
-    for (int s = 0; s < n; s += kTileAheadI8) {  // workgroup-uniform trip count
+    for (int j = 0; j < kAhead; ++j) fetch(g[j], j);
+    for (int ph = 0; P * ph < n; ph += kAhead) {  // workgroup-uniform trip count
 #pragma unroll
-      for (int j = 0; j < kTileAheadI8; ++j) step(g[j], s + j);
+      for (int j = 0; j < kAhead; ++j) phase(g[j], ph + j);
     }
-    if (active) store_partial<D, 1>(p, u, wg, st, col, grp, row0);
+    if constexpr (H == 2) merge_halves<D, TW>(st, n, half, tile, active, lane, (f32x4*)&ring_v[0][0], other_m, other_l);
+    if (half == 0 && active) store_partial<D, 1>(p, u, wg, st, col, grp, row0);
   }
 }
 
@@ -1800,12 +1818,20 @@ static int check_attention_args(const bass_attn_desc* d, const LaunchShape& ls, 
 // 1 - 16 sequences of 20 - 4000 tokens: 0 - 12 %; 32 heads, 32 rows, 8 sequences of 1200 / 4000 tokens: 42.5 -> 42.4 /
 // 136 -> 110 us, 16 of 1200: 81 -> 78; 20 rows, 16 sequences of 100 / 4000: 25.0 -> 25.9 / 182.9 -> 183.7.  At head size 64
 // two blocks per phase are 0 - 17 % quicker.
+// INT8, at most two tiles: two wavefronts per tile, so that none of the four only copies, and at head size 64, where a block
+// is 4 KB and the barriers count, two blocks each per phase where there are many units (from about 256 on: 512 units
+// of 4000 tokens, 32 rows: 84 -> 76 us; 64 units of 20 - 400 tokens 4 - 8 % longer).  32 heads, 32 rows, 16 sequences of 100 /
+// 1200 / 4000 tokens, one wavefront per tile and now: head size 128 26.7 / 55.8 / 137 -> 27.1 / 49.6 / 110 us, head size 64
+// 18.6 / 41.6 / 96.8 -> 18.6 / 34.9 / 76.5.
 template <bool kFused>
 static void launch_tiles(const bass_attn_desc* d, dim3 grid, hipStream_t s, const AttnParams& p) {
   const bool big = d->D == 128, two = p.rows_max <= 32;
   if (d->dtype == BASS_DTYPE_INT8KV) {
-    if (big) hipLaunchKernelGGL((verify_attn_tiles_i8<128, kFused>), grid, dim3(256), 0, s, p);
-    else hipLaunchKernelGGL((verify_attn_tiles_i8<64, kFused>), grid, dim3(256), 0, s, p);
+    if (big && two) hipLaunchKernelGGL((verify_attn_tiles_i8<128, kFused, 2, 2, 1>), grid, dim3(256), 0, s, p);
+    else if (big) hipLaunchKernelGGL((verify_attn_tiles_i8<128, kFused, 4, 1, 1>), grid, dim3(256), 0, s, p);
+    else if (two && p.B * p.Hkv >= 256) hipLaunchKernelGGL((verify_attn_tiles_i8<64, kFused, 2, 2, 2>), grid, dim3(256), 0, s, p);
+    else if (two) hipLaunchKernelGGL((verify_attn_tiles_i8<64, kFused, 2, 2, 1>), grid, dim3(256), 0, s, p);
+    else hipLaunchKernelGGL((verify_attn_tiles_i8<64, kFused, 4, 1, 1>), grid, dim3(256), 0, s, p);
   } else if (!two) {
     if (big) hipLaunchKernelGGL((verify_attn_tiles_bf16<128, kFused, 4, 2>), grid, dim3(512), 0, s, p);
     else hipLaunchKernelGGL((verify_attn_tiles_bf16<64, kFused, 4, 2>), grid, dim3(512), 0, s, p);
