@@ -101,21 +101,23 @@ struct BlockJob {
 
 // kGrouped: all kv heads of a block of tokens go to the same XCD, one after the other: a token's rows of all heads lie
 // side by side in the row tensors, and so do its scales there (4 bytes per head), which then leave that XCD's
-// L2 as whole cache lines.  The sequences' first blocks come first, then their second ones, so that a call that uses a few of
-// its row slots loads every XCD alike (dealt sequence by sequence, 1 of 200 slots, 32 sequences, 32 heads of 128, INT8
-// append: all work on one XCD, 25.1 us).  Otherwise in the order of the caches: appends to bf16 caches, which read and write
-// whole cache lines anyway, are 3 - 10 % quicker so, 32 sequences of up to 2048 tokens, 8 heads of 128: 100 -> 97 us.
+// L2 as whole cache lines.  A sequence has an odd number of places in that order, so that every XCD is loaded alike both by a
+// call that uses a few row slots of every sequence and by one with sequences of different lengths.  (1 of 200 slots, 32
+// sequences, 32 heads of 128, INT8 append: 28.6 us with 8 places, of which one XCD held all the first ones.  8 prompts of 512 -
+// 2048 tokens by first, second ... blocks of all sequences: a sequence to an XCD, 252 instead of 205 us for 4 layers.)
+// Otherwise in the order of the caches: appends to bf16 caches, which read and write whole cache lines anyway, are 3 - 10 %
+// quicker so, 32 sequences of up to 2048 tokens, 8 heads of 128: 100 -> 97 us.
 // False (for the whole workgroup): nothing to do.
 template <bool kGrouped>
 __device__ inline bool block_job(const KvParams& p, int blocks_per_seq, BlockJob& o) {
   int j;
   if (kGrouped) {
     const int xcd = (int)(blockIdx.x % kXcds), local = (int)(blockIdx.x / kXcds);
-    const int group = local / p.Hkv * kXcds + xcd;  // over [blocks_per_seq][B]
-    j = group / p.B;
-    if (j >= blocks_per_seq) return false;
+    const int group = local / p.Hkv * kXcds + xcd, places = blocks_per_seq | 1;  // over [B][places]
+    o.b = group / places;
+    j = group - o.b * places;
+    if (o.b >= p.B || j >= blocks_per_seq) return false;
     o.kvh = local % p.Hkv;
-    o.b = group - j * p.B;
   } else {
     const int unit = (int)(blockIdx.x / blocks_per_seq);  // over [B][Hkv]; the grid may be rounded up
     j = (int)(blockIdx.x % blocks_per_seq);
@@ -482,7 +484,7 @@ static int launch_rows(const bass_attn_desc* d, void* Kc, void* Vc, void* Kr, vo
   // workgroups: 4 - 5 us, up to 20 % shorter with few rows in many slots, 0 - 5 % longer with all slots used; of 192 - 256 and
   // more: blocks 16 % and more shorter with all slots used.
   const int64_t per_seq = (d->kmax + kBlockTokens - 1) / kBlockTokens + 1;  // blocks the rows of a sequence can touch
-  const int64_t wgs = ((int64_t)d->B * per_seq + kXcds - 1) / kXcds * kXcds * d->Hkv;
+  const int64_t wgs = ((int64_t)d->B * (per_seq | 1) + kXcds - 1) / kXcds * kXcds * d->Hkv;
   const bool int8 = d->dtype == BASS_DTYPE_INT8KV;
   const bool few_rows = int8 && !kGather && items <= 192 * 256;
   if (d->dtype != BASS_DTYPE_FP32 && d->kmax >= kBlockTokens && !few_rows && wgs <= 0x7fffffff) {
