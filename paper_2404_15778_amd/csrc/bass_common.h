@@ -151,7 +151,7 @@ struct LaunchShape {
   bool tiles;       // more than one 16-row query tile per kv head: the workgroup-level kernels
   bool fused_append;  // the step's rows are appended inside the attention launch, and its plan says so
   bool tiles_append;  // longer drafts, workgroup-level kernels: they patch a block at a time and stage nothing, so
-                      // planned launches append there too; the plan is the one of a launch that does not append
+                      // planned launches may append there too; the plan is the one of a launch that does not append
   int rows_max, nwaves, nshares, used_shares, target, pad, pad_before, min_entries, per_unit, fused_reduce;
 };
 
@@ -175,7 +175,12 @@ inline LaunchShape launch_shape(const bass_attn_desc* d, bool append) {
   const bool int8 = d->dtype == BASS_DTYPE_INT8KV;
   s.tiles = s.mfma && s.rows_max > 16;
   s.fused_append = append && (d->dtype == BASS_DTYPE_FP32 || (int64_t)d->kmax * d->D <= kMaxStagedElems);
-  s.tiles_append = append && s.tiles && !s.fused_append;
+  // A patch costs a workgroup about 3 us, one after the other for each of its units; an append by itself goes by cache blocks
+  // from kBlockTokens slots on, which takes a 32-slot call 5 - 10 us.  Inside the launch / before it, us, head size 128, 32 and 64
+  // rows, 32 heads: 8 sequences (256 units) of 500 tokens, bf16 28.3 / 29.1 and 34.7 / 34.7, INT8 33.3 / 33.0 and 39.8 / 38.2; 32
+  // sequences 92.9 / 84.5 and 121.3 / 106.7, 66.1 / 62.8 and 99.1 / 88.2; 20 rows, which an append takes one by one, 8 and 32
+  // sequences: bf16 25.9 / 32.9 and 85.6 / 93.3.
+  s.tiles_append = append && s.tiles && !s.fused_append && (d->kmax < kBlockTokens || d->B * d->Hkv <= kTileShares);
   // (a launch wider than the shares it aims at, with all shares equally long -- plan_split -- was measured
   // 1 - 2 % slower than the even division on the benchmark shapes: more wavefronts, more partials to merge)
   const int aim = attention_waves(setting, s.mfma && s.rows_max > 16, int8);

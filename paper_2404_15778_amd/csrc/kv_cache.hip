@@ -24,6 +24,8 @@ struct KvParams {
   int32_t* status;
   float* Ks;  // INT8 gather only: scales out [B,kmax,Hkv]
   float* Vs;
+  const int32_t* signature;  // appends for a planned launch: nothing is written unless this word of its plan is `expected`
+  int32_t expected;
 };
 
 // One thread per (sequence b, row slot i, kv head, 16-byte chunk of the row): everything a thread
@@ -154,11 +156,12 @@ __device__ inline bool takes_part(const BlockJob& o, int w) {
 // Token slot j (0 .. 7) of a V chunk of lane group grp
 __device__ inline int v_token(int grp, int j) { return j < 4 ? 4 * grp + j : 16 + 4 * grp + (j - 4); }
 
-template <int D>
+template <int D, bool kPlanned>
 __global__ __launch_bounds__(256) void kv_blocks_bf16_append(KvParams p, int blocks_per_seq) {
   __shared__ __align__(16) uint16_t vt[kBlockTokens][D + 8];
   const int tid = threadIdx.x;
   BlockJob o;
+  if (kPlanned && *p.signature != p.expected) return;
   if (!block_job<false>(p, blocks_per_seq, o)) return;
   const size_t base = (((size_t)o.b * p.Hkv + o.kvh) * p.nblk + o.blk) * ((size_t)kBlockTokens * D);
   uint16_t* kc = (uint16_t*)p.Kc + base;
@@ -246,12 +249,13 @@ __global__ __launch_bounds__(256) void kv_blocks_bf16_gather(KvParams p, int blo
 // same row).  The codes are laid down row by row in LDS (rows 16 bytes longer than in memory: chunks of
 // different tokens start at different banks); the block's chunks are put together from there -- K: 16 codes of
 // one row, V: one byte of 16 rows each -- and stored in consecutive order.
-template <int D>
+template <int D, bool kPlanned>
 __global__ __launch_bounds__(256) void kv_blocks_i8_append(KvParams p, int blocks_per_seq) {
   __shared__ __align__(16) uint8_t kt[kBlockTokens][D + 16], vt[kBlockTokens][D + 16];
   __shared__ float kscale[kBlockTokens], vscale[kBlockTokens];
   const int tid = threadIdx.x;
   BlockJob o;
+  if (kPlanned && *p.signature != p.expected) return;
   if (!block_job<true>(p, blocks_per_seq, o)) return;
   constexpr int CPR = D / 8, kTurns = kBlockTokens * CPR / 256;  // chunks of 8 elements per row; per thread and tensor
   uint4 k[kTurns], v[kTurns];
@@ -364,10 +368,12 @@ static void launch_blocks(bool gather, bool int8, dim3 grid, hipStream_t s, cons
   const dim3 block(256);
   if (int8) {
     if (gather) hipLaunchKernelGGL(kv_blocks_i8_gather<D>, grid, block, 0, s, p, blocks_per_seq);
-    else hipLaunchKernelGGL(kv_blocks_i8_append<D>, grid, block, 0, s, p, blocks_per_seq);
+    else if (p.signature) hipLaunchKernelGGL((kv_blocks_i8_append<D, true>), grid, block, 0, s, p, blocks_per_seq);
+    else hipLaunchKernelGGL((kv_blocks_i8_append<D, false>), grid, block, 0, s, p, blocks_per_seq);
   } else {
     if (gather) hipLaunchKernelGGL(kv_blocks_bf16_gather<D>, grid, block, 0, s, p, blocks_per_seq);
-    else hipLaunchKernelGGL(kv_blocks_bf16_append<D>, grid, block, 0, s, p, blocks_per_seq);
+    else if (p.signature) hipLaunchKernelGGL((kv_blocks_bf16_append<D, true>), grid, block, 0, s, p, blocks_per_seq);
+    else hipLaunchKernelGGL((kv_blocks_bf16_append<D, false>), grid, block, 0, s, p, blocks_per_seq);
   }
 }
 
@@ -465,7 +471,8 @@ __global__ __launch_bounds__(256) void kv_rows_i8_gather(KvParams p) {
 
 template <bool kGather>
 static int launch_rows(const bass_attn_desc* d, void* Kc, void* Vc, void* Kr, void* Vr, const int32_t* off,
-                       const int32_t* cnt, int32_t* status, void* stream, float* Ks = nullptr, float* Vs = nullptr) {
+                       const int32_t* cnt, int32_t* status, void* stream, float* Ks = nullptr, float* Vs = nullptr,
+                       const int32_t* signature = nullptr, int32_t expected = 0) {
   int rc = check_desc(d);
   if (rc != BASS_OK) return rc;
   if (!Kc || !Vc || !Kr || !Vr || !off || !cnt) return BASS_ERR_INVALID_ARG;
@@ -475,7 +482,7 @@ static int launch_rows(const bass_attn_desc* d, void* Kc, void* Vc, void* Kr, vo
   const int chunk = d->dtype == BASS_DTYPE_FP32 ? 4 : 8;
   const int64_t items = (int64_t)d->B * d->kmax * d->Hkv * (d->D / chunk);
   if ((items + 255) / 256 > 0x7fffffff) return BASS_ERR_UNSUPPORTED;
-  KvParams p{d->B, d->kmax, d->Hkv, d->D, d->Lcap, num_blocks(d->Lcap), Kc, Vc, Kr, Vr, off, cnt, status, Ks, Vs};
+  KvParams p{d->B, d->kmax, d->Hkv, d->D, d->Lcap, num_blocks(d->Lcap), Kc, Vc, Kr, Vr, off, cnt, status, Ks, Vs, signature, expected};
   dim3 grid((unsigned)((items + 255) / 256));
   hipStream_t s = (hipStream_t)stream;
   // From one block of row slots on, by blocks; fewer (a step's drafts) by single rows, whose launch is one short
@@ -486,10 +493,12 @@ static int launch_rows(const bass_attn_desc* d, void* Kc, void* Vc, void* Kr, vo
   const int64_t per_seq = (d->kmax + kBlockTokens - 1) / kBlockTokens + 1;  // blocks the rows of a sequence can touch
   const int64_t wgs = ((int64_t)d->B * (per_seq | 1) + kXcds - 1) / kXcds * kXcds * d->Hkv;
   const bool int8 = d->dtype == BASS_DTYPE_INT8KV;
-  const bool few_rows = int8 && !kGather && items <= 192 * 256;
+  const bool few_rows = int8 && !kGather && !signature && items <= 192 * 256;
   if (d->dtype != BASS_DTYPE_FP32 && d->kmax >= kBlockTokens && !few_rows && wgs <= 0x7fffffff) {
     if (d->D == 128) launch_blocks<128>(kGather, int8, dim3((unsigned)wgs), s, p, (int)per_seq);
     else launch_blocks<64>(kGather, int8, dim3((unsigned)wgs), s, p, (int)per_seq);
+  } else if (signature) {
+    return BASS_ERR_UNSUPPORTED;  // not reached: appends for a planned launch bring at least a block of row slots
   } else if (int8) {
     if (kGather) hipLaunchKernelGGL(kv_rows_i8_gather, grid, dim3(256), 0, s, p);
     else hipLaunchKernelGGL(kv_rows_i8_append, grid, dim3(256), 0, s, p);
@@ -498,6 +507,12 @@ static int launch_rows(const bass_attn_desc* d, void* Kc, void* Vc, void* Kr, vo
   } else
     hipLaunchKernelGGL(kv_rows_fp32<kGather>, grid, dim3(256), 0, s, p);
   return launch_status();
+}
+
+int append_planned(const bass_attn_desc* d, void* Kcache, void* Vcache, const void* K_new, const void* V_new, const int32_t* L,
+                   const int32_t* nq, const int32_t* signature, int32_t expected, int32_t* dev_status, void* stream) {
+  return launch_rows<false>(d, Kcache, Vcache, (void*)K_new, (void*)V_new, L, nq, dev_status, stream, nullptr, nullptr,
+                            signature, expected);
 }
 
 }  // namespace bass

@@ -1786,6 +1786,9 @@ static Workspace workspace_layout(const bass_attn_desc* d, int shares) {
 PlanShape plan_shape(const bass_attn_desc* d, const LaunchShape& ls, int span);
 int launch_plan(const bass_attn_desc* d, const LaunchShape& ls, int span, const int32_t* ctx_len, const int32_t* draft_len,
                 void* plan, int32_t* dev_status, void* stream, int32_t* clear_counters);
+// bass_kv_append for a planned launch; writes nothing if the word at `signature` is not `expected`  (kv_cache.hip)
+int append_planned(const bass_attn_desc* d, void* Kcache, void* Vcache, const void* K_new, const void* V_new, const int32_t* L,
+                   const int32_t* nq, const int32_t* signature, int32_t expected, int32_t* dev_status, void* stream);
 
 }  // namespace bass
 
@@ -1998,13 +2001,12 @@ extern "C" int bass_verify_attention_planned(const bass_attn_desc* d, const void
   if (rc != BASS_OK) return rc;
   const bass::Workspace wl = bass::workspace_layout(d, bass::kMaxWaves);
   if (workspace_bytes < wl.bytes) return BASS_ERR_WORKSPACE_TOO_SMALL;
-  if (K_new && !ls.fused_append && !ls.tiles_append) {
-    // more new rows than a wavefront stages in LDS: append with a launch of its own, at the (clamped)
-    // lengths the plan holds
+  if (K_new && !ls.fused_append && !ls.tiles_append) {  // a launch of its own, at the (clamped) lengths the plan holds
     const bass::PlanLayout pl = bass::plan_layout(d->B, d->Hkv, ls.nshares);
-    const int32_t* L = (const int32_t*)((const char*)plan + pl.seq_L);
-    const int32_t* nq = (const int32_t*)((const char*)plan + pl.seq_nq);
-    rc = bass_kv_append(d, Kcache, Vcache, K_new, V_new, L, nq, dev_status, stream);
+    const char* at = (const char*)plan;
+    rc = bass::append_planned(d, Kcache, Vcache, K_new, V_new, (const int32_t*)(at + pl.seq_L), (const int32_t*)(at + pl.seq_nq),
+                              &((const bass::ShareRecord*)(at + pl.records))->signature,
+                              bass::plan_signature(bass::plan_shape(d, ls, 0), 0), dev_status, stream);
     if (rc != BASS_OK) return rc;
     return bass::launch_attention(d, ls, Q, nullptr, nullptr, Kcache, Vcache, plan, O, lse, wl, workspace, dev_status,
                                   stream);

@@ -48,7 +48,8 @@ def test_planned_append_of_long_drafts(dtype, D, kmax, Hq, Hkv):
 # tokens in either or both blocks of a phase and in later phases, and units that begin and end inside a stretch.
 @pytest.mark.parametrize("dtype", ["bf16", "int8kv"])
 @pytest.mark.parametrize("ctx", [[900, 333, 640, 64, 5], [31, 400, 1000, 959, 0]])
-@pytest.mark.parametrize("D,kmax,Hq,Hkv", [(128, 20, 2, 2), (128, 32, 1, 1), (128, 64, 2, 2), (128, 24, 4, 2), (64, 32, 2, 2), (64, 60, 2, 2)])
+@pytest.mark.parametrize("D,kmax,Hq,Hkv", [(128, 20, 2, 2), (128, 32, 1, 1), (128, 64, 2, 2), (128, 24, 4, 2), (64, 32, 2, 2), (64, 60, 2, 2),
+                                           (64, 9, 208, 104), (128, 32, 60, 60)])  # the last two: more than 256 units
 def test_stretches_of_several_blocks(dtype, ctx, D, kmax, Hq, Hkv):
     import numpy as np
     import torch
@@ -100,3 +101,29 @@ def test_stretches_of_several_blocks(dtype, ctx, D, kmax, Hq, Hkv):
     assert all(torch.equal(a, b) for a, b in zip(tokens(caches), tokens(by_append)))
     # probabilities are rounded to bf16: 2^-9 of each, times values of up to 5; the rows' sums stay in 32 bits
     assert np.abs(O.cpu().numpy() - want).max() <= 2e-2 and np.abs(lse.cpu().numpy() - want_lse).max() <= 1e-3
+
+
+@pytest.mark.parametrize("dtype", ["bf16", "int8kv"])
+def test_refused_launch_of_many_long_drafts_appends_nothing(dtype):
+    """More than 256 units of 32 row slots and more: the rows are appended by a launch of their own."""
+    import torch
+    import paper_2404_15778_amd as bass
+    dev, B, kmax, H, D, Lcap = "cuda:0", 17, 32, 16, 128, 96
+    d = bass.make_desc(B, kmax, H, H, D, Lcap, dtype, 1.0 / math.sqrt(D))
+    gen = torch.Generator(device=dev)
+    gen.manual_seed(1)
+    Q, K, V = [torch.randn((B, kmax, H, D), generator=gen, device=dev).to(torch.bfloat16) for _ in range(3)]
+    lens = [torch.full((B,), x, dtype=torch.int32, device=dev) for x in (40, 32)]
+    caches = [torch.full((bass.bass_kv_cache_bytes(d),), 3, dtype=torch.uint8, device=dev) for _ in range(2)]
+    O, status = torch.full((B, kmax, H, D), 7.0, device=dev), torch.zeros(1, dtype=torch.int32, device=dev)
+    plan, ws = bass.alloc_plan(d, dev), bass.alloc_workspace(d, dev)
+    bass.bass_attention_plan(d.replace(Lcap=Lcap + 32), *lens, bass.PLAN_APPEND, 0, plan, status)  # another shape
+    bass.bass_verify_attention_planned(d, Q, K, V, *caches, plan, O, None, ws, status)
+    assert status.item() == bass.STATUS_PLAN_MISMATCH
+    assert (O == 7.0).all() and all((c == 3).all() for c in caches)
+    status.zero_()
+    bass.bass_attention_plan(d, *lens, bass.PLAN_APPEND, 0, plan, status)
+    want = [c.clone() for c in caches]
+    bass.bass_kv_append(d, *want, K, V, *lens)
+    bass.bass_verify_attention_planned(d, Q, K, V, *caches, plan, O, None, ws, status)
+    assert status.item() == 0 and all(torch.equal(a, b) for a, b in zip(caches, want)) and not (O == 7.0).any()
