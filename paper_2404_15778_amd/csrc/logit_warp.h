@@ -255,7 +255,9 @@ __device__ __forceinline__ void warp_row(const float* z, float* out, int V, floa
       }
       int at = 0;
       if (lane == 63 && incl > 0) at = atomicAdd(&sh_listed, incl);
-      at = __builtin_amdgcn_readlane(at, 63) + incl - cnt;
+      at = __builtin_amdgcn_readlane(at, 63);
+      if (at > kListMax) collect = false;  // wave-uniform: more than fit already, the rest of the row is read for its maximum only
+      at += incl - cnt;
 #pragma unroll
       for (int k = 0; k < kStreamUnroll<W>; ++k)
 #pragma unroll
@@ -268,9 +270,8 @@ __device__ __forceinline__ void warp_row(const float* z, float* out, int V, floa
             ++at;
           }
     }
-    listed = collect;
     __syncthreads();  // redf is written again, the list is complete
-    listed = listed && sh_listed <= kListMax;
+    listed = collect && sh_listed <= kListMax;
   } else {
     for_each_group(z, [&](int, const Group<W>& gr, int) {
 #pragma unroll
