@@ -134,11 +134,16 @@ constexpr int kPlainBefore = 0;   // kernel; measured: +0.5 % with the fused app
 // with 5.  Measured with at least 1 / 4 / 5 / 6 / 9 / 12 blocks per share: 675 / 517 / 463 / 491 / 514 / 551 us for
 // the step of 32 such layers.  Units with fewer shares keep them, and more of them over INT8 caches, where
 // a block costs its wavefront about 1 us (4 sequences of 217 tokens, 32 heads, 6 shares per unit: 534 us; of 4 blocks at
-// least, 576).
+// least, 576).  Head size 64, blocks of half the size, gains as much: 1 sequence, 32 heads, 330 / 1000 / 2000 tokens, over all shares
+// and over fewer: bf16 10.8 / 17.9 / 17.8 -> 9.4 / 10.2 / 13.5 us, INT8 11.9 / 19.0 / 21.2 -> 10.6 / 13.0 / 15.5; only units of 3 - 4
+// blocks, 60 - 100 tokens, are no quicker (0 - 4 % longer).
 constexpr int kMinEntries = 5;
 constexpr int kPerUnit = 5, kPerUnitInt8 = 8;
-// Workgroups of the workgroup-level kernels.  bf16: one per compute unit (512: more partials, no faster).  INT8: two,
-// because a step's conversions and softmax leave issue slots to fill: 16 sequences of 1024 - 4096 tokens, 64/8 heads, 64
+// Workgroups of the workgroup-level kernels.  bf16: one per compute unit.  With 512 (two blocks per phase), 256 -> 512: 64/8 heads
+// of 128, 24 rows, 8 sequences of 400 tokens 13.0 -> 17.3 us; 32 heads of 128, 32 rows, 8 / 16 of 1200 42.5 -> 52.7 / 80.8 -> 75.4;
+// 16 layers of 16 of 1024 - 4096, 64/8 heads, 48 rows 759 -> 845; 32 heads of 64, 32 rows, 1 of 400 / 16 of 1200 11.4 -> 13.3 /
+// 50 -> 41: better for long lists of small blocks only, and the lists' lengths are not known when the launch is sized.
+// INT8: two, because a step's conversions and softmax leave issue slots to fill: 16 sequences of 1024 - 4096 tokens, 64/8 heads, 64
 // rows, 128 / 256 / 384 / 512 / 640 / 1024 workgroups: 1467 / 869 / 788 / 756 / 889 / 903 us for 16 layers; 32 heads and
 // 32 rows: 1665 / 972 / 835 / 745 / 919 / 949.
 constexpr int kTileShares = 256, kTileSharesInt8 = 512;
@@ -152,16 +157,14 @@ struct LaunchShape {
   bool fused_append;  // the step's rows are appended inside the attention launch, and its plan says so
   bool tiles_append;  // longer drafts, workgroup-level kernels: they patch a block at a time and stage nothing, so
                       // planned launches may append there too; the plan is the one of a launch that does not append
-  int rows_max, nwaves, nshares, used_shares, target, pad, pad_before, min_entries, per_unit, fused_reduce;
+  int rows_max, nwaves, nshares, used_shares, target, pad, pad_before, min_entries, per_unit;
 };
 
-// many_rows: more than one 16-row query tile per kv head (grouped-query attention), the workgroup-level kernels:
-// the count sizes the plan (INT8) and grades an explicit setting; how many workgroups there are by default stands
-// at kTileShares.  One query tile: 768 for INT8 caches
-// too -- as 256 workgroups of three they measured level with 1024 on the long-context shape and 2 - 3 %
-// shorter on the benchmark shape (a fourth wavefront on a compute unit costs the others issue slots).
-inline int attention_waves(int setting, bool many_rows, bool int8) {
-  int w = setting > 0 ? setting : (many_rows ? (int8 ? 1024 : 896) : kDefaultWaves);
+// One query tile per kv head: 768 wavefronts, over INT8 caches too -- as 256 workgroups of three they measured level with 1024 on
+// the long-context shape and 2 - 3 % shorter on the benchmark shape (a fourth wavefront on a compute unit costs the others
+// issue slots).  An explicit setting is clamped and rounded here.
+inline int attention_waves(int setting) {
+  int w = setting > 0 ? setting : kDefaultWaves;
   if (w < 64) w = 64;
   if (w > kMaxWaves) w = kMaxWaves;
   return w - w % kWavesPerWorkgroup;
@@ -183,21 +186,17 @@ inline LaunchShape launch_shape(const bass_attn_desc* d, bool append) {
   s.tiles_append = append && s.tiles && !s.fused_append && (d->kmax < kBlockTokens || d->B * d->Hkv <= kTileShares);
   // (a launch wider than the shares it aims at, with all shares equally long -- plan_split -- was measured
   // 1 - 2 % slower than the even division on the benchmark shapes: more wavefronts, more partials to merge)
-  const int aim = attention_waves(setting, s.mfma && s.rows_max > 16, int8);
-  s.nwaves = aim;
-  // the workgroup-level kernel takes one stretch per workgroup (default 256, measured best: fewer
-  // partials to merge; a wavefront setting W gives W / 2)
-  const int stretches = setting > 0 ? (s.nwaves / 2 > 16 ? s.nwaves / 2 : 16) : (int8 ? kTileSharesInt8 : kTileShares);
-  s.nshares = s.tiles && !int8 ? stretches : s.nwaves;  // INT8: plans keep room for a share per wavefront
-  s.used_shares = s.tiles ? imin(stretches, s.nshares) : s.nshares;
-  s.target = !s.tiles ? aim : s.nshares;
+  s.nwaves = attention_waves(setting);
+  // the workgroup-level kernels take one stretch per workgroup: half as many as an explicit setting has wavefronts
+  const int stretches = setting > 0 ? s.nwaves / 2 : (int8 ? kTileSharesInt8 : kTileShares);
+  s.used_shares = s.tiles ? stretches : s.nwaves;
+  s.nshares = s.tiles && int8 ? 2 * stretches : s.used_shares;  // INT8: plans keep room for twice the stretches
+  s.target = s.nshares;
   s.pad = s.fused_append ? kAppendPad : kPlainPad;
   s.min_entries = setting > 0 || s.tiles || !s.mfma ? 0 : kMinEntries;
   s.per_unit = int8 ? kPerUnitInt8 : kPerUnit;
   s.pad_before = 0;
   if (s.mfma && s.rows_max <= 16) s.pad_before = s.fused_append ? kAppendBefore : kPlainBefore;
-  // one query tile per kv head: the last-arriving wavefront reduces; more: a second, chip-wide launch
-  s.fused_reduce = (d->dtype == BASS_DTYPE_FP32 || s.rows_max <= 16) ? 1 : 0;
   return s;
 }
 

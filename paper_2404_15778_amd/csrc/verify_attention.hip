@@ -53,7 +53,6 @@ struct AttnParams {
   unsigned g_magic;  // ceil(2^20 / g) if g <= 64 and rows_max <= 2048 (then r / g == (r * g_magic) >> 20 for every row r), else 0
   int wpw;  // wavefronts per workgroup of the attention launch (nwaves is a multiple)
   int nshares;  // stretches the block list is cut into: one per wavefront, or one per workgroup (tile kernel)
-  int fused_reduce;  // 1: the last-arriving wavefront merges a unit's partials; 0: a second launch does
   float scale_log2;  // scale * log2(e): scores are kept in the log2 domain
   const void* Q;
   const void* Kc;
@@ -690,30 +689,30 @@ __device__ inline void patch_block_i8(KvRegsI8<D>& q, int tok0, const NewRows nr
 
 constexpr float kMaxSlack = 8.f;  // see block_step
 
-template <int D, int NT>
+template <int D>
 struct RowState {
-  f32x4 acc[NT][D / 16];
-  float m[NT];  // running max (log2 units), identical in the 4 lanes that share a query row
-  float l[NT];  // this lane's share of the running sum
+  f32x4 acc[D / 16];
+  float m;  // running max (log2 units), identical in the 4 lanes that share a query row
+  float l;  // this lane's share of the running sum
 };
 
 // One 32-token block against all query tiles.  kMasked: the block reaches beyond ctx_len, so
 // causal limits and the valid-token bound apply (wave-uniform choice).
 // INT8 caches: what the block step needs besides the widened V fragments -- the block's K codes, the
 // quantized queries and all the scales.
-template <int D, int NT>
+template <int D>
 struct I8Operands {
   const u32x4* k;                 // KvRegsI8::k of the block
-  const u32x4 (*q)[D / 64];       // query codes, B operand of the INT8 matrix instruction
-  const float* q_scale_log2;      // per tile: this lane's query-row scale * softmax scale * log2(e)
+  const u32x4* q;                 // query codes, B operand of the INT8 matrix instruction
+  float q_scale_log2;             // this lane's query-row scale * softmax scale * log2(e)
   const TokenScales* sc;
 };
 
-template <int D, int NT, bool kMasked, bool kI8 = false>
-__device__ inline void block_step(KvRegs<D>& r, const bf16x8 (&qf)[NT][D / 32], RowState<D, NT>& st, int tok0,
-                                  int n_valid, const int (&lim)[NT], float scale_log2, int lane,
+template <int D, bool kMasked, bool kI8 = false>
+__device__ inline void block_step(KvRegs<D>& r, const bf16x8* qf, RowState<D>& st, int tok0,
+                                  int n_valid, int lim, float scale_log2, int lane,
                                   bool fused = false, const NewRows& nr = NewRows{}, uint4* kdst = nullptr,
-                                  uint4* vdst = nullptr, const I8Operands<D, NT>* i8 = nullptr, bool fine = false) {
+                                  uint4* vdst = nullptr, const I8Operands<D>* i8 = nullptr, bool fine = false) {
   constexpr int KS = D / 32, MT = D / 16;
   const int grp = lane >> 4;
   // INT8 caches: a score is the integer product (q codes . k codes) * q-scale * k-scale, a value is
@@ -780,103 +779,100 @@ __device__ inline void block_step(KvRegs<D>& r, const bf16x8 (&qf)[NT][D / 32], 
       for (int mt = 0; mt < MT; ++mt) *(u32x4*)(vdst + mt * 64) = __builtin_bit_cast(u32x4, r.v[mt]);
     }
   }
+  float s[8];
+  if constexpr (kI8) {
+    i32x4 a0 = {0, 0, 0, 0}, a1 = {0, 0, 0, 0};
 #pragma unroll
-  for (int nt = 0; nt < NT; ++nt) {
-    float s[8];
-    if constexpr (kI8) {
-      i32x4 a0 = {0, 0, 0, 0}, a1 = {0, 0, 0, 0};
-#pragma unroll
-      for (int ks = 0; ks < D / 64; ++ks) {
-        a0 = __builtin_amdgcn_mfma_i32_16x16x64_i8(__builtin_bit_cast(i32x4, i8->k[ks]), __builtin_bit_cast(i32x4, i8->q[nt][ks]), a0, 0, 0, 0);
-        a1 = __builtin_amdgcn_mfma_i32_16x16x64_i8(__builtin_bit_cast(i32x4, i8->k[D / 64 + ks]), __builtin_bit_cast(i32x4, i8->q[nt][ks]), a1, 0, 0, 0);
-      }
-      const float qs = i8->q_scale_log2[nt];
-#pragma unroll
-      for (int j = 0; j < 4; ++j) {
-        s[j] = (float)a0[j] * (i8->sc->k[j] * qs);
-        s[4 + j] = (float)a1[j] * (i8->sc->k[4 + j] * qs);
-      }
-    } else {
-      f32x4 s0 = {0.f, 0.f, 0.f, 0.f}, s1 = {0.f, 0.f, 0.f, 0.f};
-#pragma unroll
-      for (int t = 0; t < KS; ++t) {
-        s0 = __builtin_amdgcn_mfma_f32_16x16x32_bf16(__builtin_bit_cast(bf16x8, r.k[t]), qf[nt][t], s0, 0, 0, 0);
-        s1 = __builtin_amdgcn_mfma_f32_16x16x32_bf16(__builtin_bit_cast(bf16x8, r.k[KS + t]), qf[nt][t], s1, 0, 0, 0);
-      }
-#pragma unroll
-      for (int j = 0; j < 4; ++j) {
-        s[j] = s0[j] * scale_log2;
-        s[4 + j] = s1[j] * scale_log2;
-      }
+    for (int ks = 0; ks < D / 64; ++ks) {
+      a0 = __builtin_amdgcn_mfma_i32_16x16x64_i8(__builtin_bit_cast(i32x4, i8->k[ks]), __builtin_bit_cast(i32x4, i8->q[ks]), a0, 0, 0, 0);
+      a1 = __builtin_amdgcn_mfma_i32_16x16x64_i8(__builtin_bit_cast(i32x4, i8->k[D / 64 + ks]), __builtin_bit_cast(i32x4, i8->q[ks]), a1, 0, 0, 0);
     }
-    if (kMasked) {
+    const float qs = i8->q_scale_log2;
 #pragma unroll
-      for (int j = 0; j < 4; ++j) {
-        if (tok0 + 4 * grp + j > lim[nt]) s[j] = -INFINITY;
-        if (tok0 + 16 + 4 * grp + j > lim[nt]) s[4 + j] = -INFINITY;
-      }
+    for (int j = 0; j < 4; ++j) {
+      s[j] = (float)a0[j] * (i8->sc->k[j] * qs);
+      s[4 + j] = (float)a1[j] * (i8->sc->k[4 + j] * qs);
     }
-    float mx = fmaxf(fmaxf(fmaxf(s[0], s[1]), fmaxf(s[2], s[3])), fmaxf(fmaxf(s[4], s[5]), fmaxf(s[6], s[7])));
-    mx = rows4_max(mx);
-    // The reference maximum of a row moves only when a block exceeds it by more than kMaxSlack (log2 units).
-    // The probabilities are then at most 2^kMaxSlack -- harmless in the fp32 sums and in the bf16 operand --
-    // and the rescale of the running sum and of the accumulator (a third of a block step's instructions at
-    // one wavefront per SIMD, where every instruction is paid for) runs in a unit's first block and hardly
-    // ever again.  Wave-uniform branch; a row that does not move has alpha = 1.
-    const float m_old = st.m[nt];
-    const bool grow = mx > m_old + kMaxSlack;
-    if (__any(grow)) {
-      const float m_new = grow ? mx : m_old;
-      const float m_to = (kMasked && m_new == -INFINITY) ? 0.f : m_new;  // rows without a visible token yet
-      const float alpha = __builtin_amdgcn_exp2f(m_old - m_to);
-      st.l[nt] *= alpha;
+  } else {
+    f32x4 s0 = {0.f, 0.f, 0.f, 0.f}, s1 = {0.f, 0.f, 0.f, 0.f};
 #pragma unroll
-      for (int mt = 0; mt < MT; ++mt) st.acc[nt][mt] *= alpha;
-      st.m[nt] = m_new;
+    for (int t = 0; t < KS; ++t) {
+      s0 = __builtin_amdgcn_mfma_f32_16x16x32_bf16(__builtin_bit_cast(bf16x8, r.k[t]), qf[t], s0, 0, 0, 0);
+      s1 = __builtin_amdgcn_mfma_f32_16x16x32_bf16(__builtin_bit_cast(bf16x8, r.k[KS + t]), qf[t], s1, 0, 0, 0);
     }
-    // a row that has seen no visible token yet keeps m = -inf; subtract 0 instead so that
-    // exp2(-inf - 0) = 0 and no inf - inf appears
-    const float m_use = (kMasked && st.m[nt] == -INFINITY) ? 0.f : st.m[nt];
-    float psum = 0.f;
-    bf16x8 pf;
 #pragma unroll
-    for (int j = 0; j < 8; ++j) {
-      const float pj = __builtin_amdgcn_exp2f(s[j] - m_use);
-      psum += pj;
-      s[j] = kI8 ? pj * vsl[j] : pj;
-      pf[j] = (__bf16)s[j];
+    for (int j = 0; j < 4; ++j) {
+      s[j] = s0[j] * scale_log2;
+      s[4 + j] = s1[j] * scale_log2;
     }
-    st.l[nt] += psum;
-    // Short lists over fewer shares (wave-uniform): what the rounding of the probabilities to bf16 left over is
-    // multiplied as well.  A share's first block holds its largest probability, 1, which is exact; with a fifth
-    // as many shares per unit that is lost for most of them (one sequence of 32 heads: error against 64 bits
-    // 1.3e-3 with 24 shares per unit, 1.6e-3 with 5, 2.3e-6 this way; the step of 32 layers 463 -> 489 us).
-    if (fine) {
-      bf16x8 pr;
+  }
+  if (kMasked) {
 #pragma unroll
-      for (int j = 0; j < 8; ++j) pr[j] = (__bf16)(s[j] - (float)pf[j]);
-#pragma unroll
-      for (int mt = 0; mt < MT; ++mt)
-        st.acc[nt][mt] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(__builtin_bit_cast(bf16x8, r.v[mt]), pr, st.acc[nt][mt], 0, 0, 0);
+    for (int j = 0; j < 4; ++j) {
+      if (tok0 + 4 * grp + j > lim) s[j] = -INFINITY;
+      if (tok0 + 16 + 4 * grp + j > lim) s[4 + j] = -INFINITY;
     }
+  }
+  float mx = fmaxf(fmaxf(fmaxf(s[0], s[1]), fmaxf(s[2], s[3])), fmaxf(fmaxf(s[4], s[5]), fmaxf(s[6], s[7])));
+  mx = rows4_max(mx);
+  // The reference maximum of a row moves only when a block exceeds it by more than kMaxSlack (log2 units).
+  // The probabilities are then at most 2^kMaxSlack -- harmless in the fp32 sums and in the bf16 operand --
+  // and the rescale of the running sum and of the accumulator (a third of a block step's instructions at
+  // one wavefront per SIMD, where every instruction is paid for) runs in a unit's first block and hardly
+  // ever again.  Wave-uniform branch; a row that does not move has alpha = 1.
+  const float m_old = st.m;
+  const bool grow = mx > m_old + kMaxSlack;
+  if (__any(grow)) {
+    const float m_new = grow ? mx : m_old;
+    const float m_to = (kMasked && m_new == -INFINITY) ? 0.f : m_new;  // rows without a visible token yet
+    const float alpha = __builtin_amdgcn_exp2f(m_old - m_to);
+    st.l *= alpha;
+#pragma unroll
+    for (int mt = 0; mt < MT; ++mt) st.acc[mt] *= alpha;
+    st.m = m_new;
+  }
+  // a row that has seen no visible token yet keeps m = -inf; subtract 0 instead so that
+  // exp2(-inf - 0) = 0 and no inf - inf appears
+  const float m_use = (kMasked && st.m == -INFINITY) ? 0.f : st.m;
+  float psum = 0.f;
+  bf16x8 pf;
+#pragma unroll
+  for (int j = 0; j < 8; ++j) {
+    const float pj = __builtin_amdgcn_exp2f(s[j] - m_use);
+    psum += pj;
+    s[j] = kI8 ? pj * vsl[j] : pj;
+    pf[j] = (__bf16)s[j];
+  }
+  st.l += psum;
+  // Short lists over fewer shares (wave-uniform): what the rounding of the probabilities to bf16 left over is
+  // multiplied as well.  A share's first block holds its largest probability, 1, which is exact; with a fifth
+  // as many shares per unit that is lost for most of them (one sequence of 32 heads: error against 64 bits
+  // 1.3e-3 with 24 shares per unit, 1.6e-3 with 5, 2.3e-6 this way; the step of 32 layers 463 -> 489 us).
+  if (fine) {
+    bf16x8 pr;
+#pragma unroll
+    for (int j = 0; j < 8; ++j) pr[j] = (__bf16)(s[j] - (float)pf[j]);
 #pragma unroll
     for (int mt = 0; mt < MT; ++mt)
-      st.acc[nt][mt] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(__builtin_bit_cast(bf16x8, r.v[mt]), pf, st.acc[nt][mt], 0, 0, 0);
+      st.acc[mt] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(__builtin_bit_cast(bf16x8, r.v[mt]), pr, st.acc[mt], 0, 0, 0);
   }
+#pragma unroll
+  for (int mt = 0; mt < MT; ++mt)
+    st.acc[mt] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(__builtin_bit_cast(bf16x8, r.v[mt]), pf, st.acc[mt], 0, 0, 0);
 }
 
-template <int D, int NT, bool kI8 = false>
-__device__ inline void block_dispatch(KvRegs<D>& r, const bf16x8 (&qf)[NT][D / 32], RowState<D, NT>& st, int blk,
-                                      int L, int n_valid, const int (&lim)[NT], float scale_log2, int lane,
+template <int D, bool kI8 = false>
+__device__ inline void block_dispatch(KvRegs<D>& r, const bf16x8* qf, RowState<D>& st, int blk,
+                                      int L, int n_valid, int lim, float scale_log2, int lane,
                                       bool fused, const NewRows& nr, uint4* kdst, uint4* vdst,
-                                      const I8Operands<D, NT>* i8 = nullptr, bool fine = false) {
+                                      const I8Operands<D>* i8 = nullptr, bool fine = false) {
   const int tok0 = blk * kBlockTokens;
   // plain step: every token of the block is visible to every query (tokens <= L) and, with a fused
   // append, none of them is new (tokens < L)
   if (tok0 + kBlockTokens - 1 < L + (fused ? 0 : 1))
-    block_step<D, NT, false, kI8>(r, qf, st, tok0, n_valid, lim, scale_log2, lane, false, NewRows{}, nullptr, nullptr, i8, fine);
+    block_step<D, false, kI8>(r, qf, st, tok0, n_valid, lim, scale_log2, lane, false, NewRows{}, nullptr, nullptr, i8, fine);
   else
-    block_step<D, NT, true, kI8>(r, qf, st, tok0, n_valid, lim, scale_log2, lane, fused, nr, kdst, vdst, i8, fine);
+    block_step<D, true, kI8>(r, qf, st, tok0, n_valid, lim, scale_log2, lane, fused, nr, kdst, vdst, i8, fine);
 }
 
 // fp32 path: the wavefront whose share holds the new rows copies them into the (token-major) cache
@@ -898,156 +894,138 @@ __device__ inline bool append_own_rows_fp32(const AttnParams& p, const Unit& u, 
   return true;
 }
 
-template <int D, int NT>
+template <int D>
 struct QFrag {
-  bf16x8 q[NT][D / 32];  // B operand: lane (col, grp) holds query row 16 nt + col, elements 32 t + 8 grp .. +7
-  int lim[NT];           // last token visible to that row
+  bf16x8 q[D / 32];  // B operand: lane (col, grp) holds query row col of the tile, elements 32 t + 8 grp .. +7
+  int lim;           // last token visible to that row
 };
 
-template <int D, int NT>
-__device__ inline void load_queries(const AttnParams& p, const Unit& u, bool enable, int col, int grp, QFrag<D, NT>& f,
+template <int D>
+__device__ inline void load_queries(const AttnParams& p, const Unit& u, bool enable, int col, int grp, QFrag<D>& f,
                                     int row0 = 0) {
   const int rows = u.nq * p.g;
+  const int rrow = row0 + col;  // row0: first query row of this wavefront (tile kernel)
+  const bool ok = enable && rrow < rows;
+  const int i = ok ? row_token(p, rrow) : 0, hg = ok ? rrow - i * p.g : 0;
+  f.lim = u.L + i;
+  const uint4* qrow = (const uint4*)((const uint16_t*)p.Q + (((size_t)u.b * p.kmax + i) * p.Hq + u.kvh * p.g + hg) * D);
 #pragma unroll
-  for (int nt = 0; nt < NT; ++nt) {
-    const int rrow = row0 + nt * 16 + col;  // row0: first query row of this wavefront (tile kernel)
-    const bool ok = enable && rrow < rows;
-    const int i = ok ? row_token(p, rrow) : 0, hg = ok ? rrow - i * p.g : 0;
-    f.lim[nt] = u.L + i;
-    const uint4* qrow = (const uint4*)((const uint16_t*)p.Q + (((size_t)u.b * p.kmax + i) * p.Hq + u.kvh * p.g + hg) * D);
-#pragma unroll
-    for (int t = 0; t < D / 32; ++t) {
-      uint4 qv = make_uint4(0, 0, 0, 0);
-      if (ok) qv = qrow[t * 4 + grp];
-      f.q[nt][t] = __builtin_bit_cast(bf16x8, qv);
-    }
+  for (int t = 0; t < D / 32; ++t) {
+    uint4 qv = make_uint4(0, 0, 0, 0);
+    if (ok) qv = qrow[t * 4 + grp];
+    f.q[t] = __builtin_bit_cast(bf16x8, qv);
   }
 }
 
 // INT8 caches: the queries are quantized like the cache rows (one scale per token and query head, codes
 // rint(x * 127 / amax)) so that QK^T runs on the INT8 matrix cores.  B operand of the 16x16x64
-// instruction: lane (col, grp) holds query row 16 nt + col, head elements 64 ks + 16 grp .. + 15.
-template <int D, int NT>
+// instruction: lane (col, grp) holds query row col of the tile, head elements 64 ks + 16 grp .. + 15.
+template <int D>
 struct QFragI8 {
-  u32x4 q[NT][D / 64];
-  float q_scale_log2[NT];  // row scale (amax / 127) * softmax scale * log2(e)
-  int lim[NT];
+  u32x4 q[D / 64];
+  float q_scale_log2;  // row scale (amax / 127) * softmax scale * log2(e)
+  int lim;
 };
 
-template <int D, int NT>
-__device__ inline void load_queries_i8(const AttnParams& p, const Unit& u, bool enable, int col, int grp, QFragI8<D, NT>& f,
+template <int D>
+__device__ inline void load_queries_i8(const AttnParams& p, const Unit& u, bool enable, int col, int grp, QFragI8<D>& f,
                                        int row0 = 0) {
   const int rows = u.nq * p.g;
+  const int rrow = row0 + col;
+  const bool ok = enable && rrow < rows;
+  const int i = ok ? row_token(p, rrow) : 0, hg = ok ? rrow - i * p.g : 0;
+  f.lim = u.L + i;
+  const uint4* qrow = (const uint4*)((const uint16_t*)p.Q + (((size_t)u.b * p.kmax + i) * p.Hq + u.kvh * p.g + hg) * D);
+  uint4 raw[D / 64][2];
+  float amax = 0.f;
 #pragma unroll
-  for (int nt = 0; nt < NT; ++nt) {
-    const int rrow = row0 + nt * 16 + col;
-    const bool ok = enable && rrow < rows;
-    const int i = ok ? row_token(p, rrow) : 0, hg = ok ? rrow - i * p.g : 0;
-    f.lim[nt] = u.L + i;
-    const uint4* qrow = (const uint4*)((const uint16_t*)p.Q + (((size_t)u.b * p.kmax + i) * p.Hq + u.kvh * p.g + hg) * D);
-    uint4 raw[D / 64][2];
-    float amax = 0.f;
+  for (int ks = 0; ks < D / 64; ++ks)
 #pragma unroll
-    for (int ks = 0; ks < D / 64; ++ks)
-#pragma unroll
-      for (int h = 0; h < 2; ++h) {
-        raw[ks][h] = ok ? qrow[ks * 8 + grp * 2 + h] : make_uint4(0, 0, 0, 0);
-        amax = fmaxf(amax, amax8(raw[ks][h]));
-      }
-    amax = rows4_max(amax);  // the four lanes of a row hold a quarter of it each
-    const float inv = amax > 0.f ? 127.0f / amax : 0.f;
-#pragma unroll
-    for (int ks = 0; ks < D / 64; ++ks) {
-      const uint2 lo = quantize8(raw[ks][0], inv), hi = quantize8(raw[ks][1], inv);
-      f.q[nt][ks] = u32x4{lo.x, lo.y, hi.x, hi.y};
+    for (int h = 0; h < 2; ++h) {
+      raw[ks][h] = ok ? qrow[ks * 8 + grp * 2 + h] : make_uint4(0, 0, 0, 0);
+      amax = fmaxf(amax, amax8(raw[ks][h]));
     }
-    f.q_scale_log2[nt] = amax / 127.0f * p.scale_log2;
+  amax = rows4_max(amax);  // the four lanes of a row hold a quarter of it each
+  const float inv = amax > 0.f ? 127.0f / amax : 0.f;
+#pragma unroll
+  for (int ks = 0; ks < D / 64; ++ks) {
+    const uint2 lo = quantize8(raw[ks][0], inv), hi = quantize8(raw[ks][1], inv);
+    f.q[ks] = u32x4{lo.x, lo.y, hi.x, hi.y};
   }
+  f.q_scale_log2 = amax / 127.0f * p.scale_log2;
 }
 
-template <int D, int NT>
-__device__ inline void clear_state(RowState<D, NT>& st) {
+template <int D>
+__device__ inline void clear_state(RowState<D>& st) {
+  st.m = -INFINITY;
+  st.l = 0.f;
 #pragma unroll
-  for (int nt = 0; nt < NT; ++nt) {
-    st.m[nt] = -INFINITY;
-    st.l[nt] = 0.f;
-#pragma unroll
-    for (int mt = 0; mt < D / 16; ++mt) st.acc[nt][mt] = f32x4{0.f, 0.f, 0.f, 0.f};
-  }
+  for (int mt = 0; mt < D / 16; ++mt) st.acc[mt] = f32x4{0.f, 0.f, 0.f, 0.f};
 }
 
 // Whether some accumulator of the wavefront is NaN or infinite (wave-uniform)
-template <int D, int NT>
-__device__ inline bool any_not_finite(const RowState<D, NT>& st) {
+template <int D>
+__device__ inline bool any_not_finite(const RowState<D>& st) {
   f32x4 t = {0.f, 0.f, 0.f, 0.f};  // 0 * finite is 0, 0 * anything else NaN
 #pragma unroll
-  for (int nt = 0; nt < NT; ++nt)
+  for (int mt = 0; mt < D / 16; ++mt)
 #pragma unroll
-    for (int mt = 0; mt < D / 16; ++mt)
-#pragma unroll
-      for (int e = 0; e < 4; ++e) t[e] = fmaf(st.acc[nt][mt][e], 0.f, t[e]);
+    for (int e = 0; e < 4; ++e) t[e] = fmaf(st.acc[mt][e], 0.f, t[e]);
   const float sum = (t[0] + t[1]) + (t[2] + t[3]);
   return __any(sum != sum);
 }
 
 // Partial of (wavefront w, unit u): slot ids w + unit are unique because both grow monotonically
 // along the flattened list.
-template <int D, int NT>
-__device__ inline void store_partial(const AttnParams& p, const Unit& u, int w, const RowState<D, NT>& st, int col, int grp,
+template <int D>
+__device__ inline void store_partial(const AttnParams& p, const Unit& u, int w, const RowState<D>& st, int col, int grp,
                                      int row0 = 0) {
   const int rows = u.nq * p.g;
   const size_t slot = (size_t)w + (size_t)u.b * p.Hkv + u.kvh;
   const __amdgpu_buffer_rsrc_t rs = dev_buffer(p.part_acc + slot * p.rows_max * D, (unsigned)p.rows_max * D * 4);
+  float l = st.l;
+  l = rows4_sum(l);
+  const int rrow = row0 + col;
+  if (rrow < rows) {
+    const unsigned off = (unsigned)(rrow * D + 4 * grp) * 4;
 #pragma unroll
-  for (int nt = 0; nt < NT; ++nt) {
-    float l = st.l[nt];
-    l = rows4_sum(l);
-    const int rrow = row0 + nt * 16 + col;
-    if (rrow < rows) {
-      const unsigned off = (unsigned)(rrow * D + 4 * grp) * 4;
-#pragma unroll
-      for (int mt = 0; mt < D / 16; ++mt) store_dev4(rs, off + 64 * mt, st.acc[nt][mt]);
-      if (grp == 0) store_dev(p.part_ml + (slot * p.rows_max + rrow) * 2, st.m[nt], l);
-    }
+    for (int mt = 0; mt < D / 16; ++mt) store_dev4(rs, off + 64 * mt, st.acc[mt]);
+    if (grp == 0) store_dev(p.part_ml + (slot * p.rows_max + rrow) * 2, st.m, l);
   }
 }
 
 // A unit that this wavefront streamed alone needs no exchange: its output rows are written straight from the
 // registers.  The arithmetic is that of the merge of a single partial (weight 2^0 = 1, the same reciprocal and
 // logarithm), so a unit's result does not depend on which of the two ways it took.
-template <int D, int NT>
-__device__ inline void finalize_single(const AttnParams& p, const Unit& u, const RowState<D, NT>& st, int col, int grp,
+template <int D>
+__device__ inline void finalize_single(const AttnParams& p, const Unit& u, const RowState<D>& st, int col, int grp,
                                        int row0 = 0) {
   const int rows = u.nq * p.g;
+  const float L = fmaf(rows4_sum(st.l), 1.0f, 0.f);
+  const int rrow = row0 + col;
+  if (rrow < rows) {
+    const float M = st.m;
+    const float invL = __builtin_amdgcn_rcpf(L);
+    const int i = row_token(p, rrow), hg = rrow - i * p.g;
+    const size_t orow = ((size_t)u.b * p.kmax + i) * p.Hq + u.kvh * p.g + hg;
 #pragma unroll
-  for (int nt = 0; nt < NT; ++nt) {
-    const float L = fmaf(rows4_sum(st.l[nt]), 1.0f, 0.f);
-    const int rrow = row0 + nt * 16 + col;
-    if (rrow < rows) {
-      const float M = st.m[nt];
-      const float invL = __builtin_amdgcn_rcpf(L);
-      const int i = row_token(p, rrow), hg = rrow - i * p.g;
-      const size_t orow = ((size_t)u.b * p.kmax + i) * p.Hq + u.kvh * p.g + hg;
-#pragma unroll
-      for (int mt = 0; mt < D / 16; ++mt) *(f32x4*)(p.O + orow * D + 16 * mt + 4 * grp) = st.acc[nt][mt] * invL;
-      if (p.lse && grp == 0) p.lse[orow] = (M + __builtin_amdgcn_logf(L)) * 0.6931471805599453f;
-    }
+    for (int mt = 0; mt < D / 16; ++mt) *(f32x4*)(p.O + orow * D + 16 * mt + 4 * grp) = st.acc[mt] * invL;
+    if (p.lse && grp == 0) p.lse[orow] = (M + __builtin_amdgcn_logf(L)) * 0.6931471805599453f;
   }
 }
 
 // kFew: so few units that a plan may have divided the list over fewer shares (the records say whether it did); the
 // others are spared the branch in every block step (1 % of a step of eight sequences).
-template <int D, int NT, bool kI8, bool kFew>
+template <int D, bool kI8, bool kFew>
 __global__ __launch_bounds__(256) void verify_attn_bf16(AttnParams p) {
   // uint4 per block: 32 tokens of D bf16, or of D INT8 codes followed by 32 fp32 scales
   constexpr ptrdiff_t kBlkVec = kI8 ? 2 * D + 8 : (ptrdiff_t)kBlockTokens * D * 2 / 16;
   using Regs = typename std::conditional<kI8, KvRegsI8<D>, KvRegs<D>>::type;
-  // With one query tile there are registers to spare for a second unit's state, so a wavefront
+  // There are registers to spare for a second unit's state, so a wavefront
   // whose share of blocks crosses a unit boundary keeps streaming: it parks the first unit's
   // accumulators, carries on with the second unit, and delivers both partials at the end.
   // (Storing the first partial at the boundary instead costs about 1 us per launch: the stores
   // sit in the ring's wait counts.)
-  constexpr bool kPair = (NT == 1);
   const int lane = threadIdx.x & 63;
   // few shares: consecutive ones go to consecutive workgroups, so that a list shorter than the launch still uses every
   // compute unit; otherwise a unit's shares stay together (32 sequences of 128 - 8192 tokens: 0.5 % shorter)
@@ -1085,29 +1063,29 @@ __global__ __launch_bounds__(256) void verify_attn_bf16(AttnParams p) {
     if (si >= nseg) break;  // an idle wavefront, or no plan for this launch
     const Unit uA = unit_of(sa);
     const int nA = sa.n;  // our real blocks of unit A: firstA .. firstA + nA - 1
-    const bool hasB = kPair && si + 1 < nseg;
+    const bool hasB = si + 1 < nseg;
     // the segments after these (shares that touch more units than the record holds) are requested now and
     // looked at when this pair is done; without any, the request re-reads the record (loads stay outside
     // branches: the wait counts of the K/V ring must stay exact)
     const int si_next = si + (hasB ? 2 : 1);
     const SegmentInFlight nextA = request_segment(si_next < nseg ? later_segment_address(p, rec, overflow, si_next) : &rec->seg[0]);
     const SegmentInFlight nextB =
-        request_segment(kPair && si_next + 1 < nseg ? later_segment_address(p, rec, overflow, si_next + 1) : &rec->seg[1]);
+        request_segment(si_next + 1 < nseg ? later_segment_address(p, rec, overflow, si_next + 1) : &rec->seg[1]);
     const Unit uB = hasB ? unit_of(sb) : uA;
     const int firstB = hasB ? sb.first : 0, nB = hasB ? sb.n : 0;
     const bool lastA = (sa.flags & kSegLast) != 0, lastB = hasB && (sb.flags & kSegLast) != 0;  // we hold the unit's last block
     const int n = nA + nB;
 
-    typename std::conditional<kI8, QFragI8<D, NT>, QFrag<D, NT>>::type qc, qB;
+    typename std::conditional<kI8, QFragI8<D>, QFrag<D>>::type qc, qB;
     if constexpr (kI8) {
-      load_queries_i8<D, NT>(p, uA, true, col, grp, qc);
-      if constexpr (kPair) load_queries_i8<D, NT>(p, uB, hasB, col, grp, qB);
+      load_queries_i8<D>(p, uA, true, col, grp, qc);
+      load_queries_i8<D>(p, uB, hasB, col, grp, qB);
     } else {
-      load_queries<D, NT>(p, uA, true, col, grp, qc);
-      if constexpr (kPair) load_queries<D, NT>(p, uB, hasB, col, grp, qB);
+      load_queries<D>(p, uA, true, col, grp, qc);
+      load_queries<D>(p, uB, hasB, col, grp, qB);
     }
-    RowState<D, NT> st, parked;
-    clear_state<D, NT>(st);
+    RowState<D> st, parked;
+    clear_state<D>(st);
     CombineJob ja = job_of(sa), jb = ja;  // who else contributes to our units
     if (hasB) jb = job_of(sb);
     int cur_L = uA.L, cur_valid = uA.L + uA.nq, cur_blk = firstA;  // block index = cur_blk + s
@@ -1170,16 +1148,14 @@ __global__ __launch_bounds__(256) void verify_attn_bf16(AttnParams p) {
       }
     };
     auto step = [&](Regs& r, int s, bool fine) {
-      if constexpr (kPair) {
-        if (s == nA) {  // first block of unit B: park A's state (register moves only)
-          parked = st;
-          clear_state<D, NT>(st);
-          qc = qB;
-          cur_L = uB.L;
-          cur_valid = uB.L + uB.nq;
-          cur_blk = firstB - nA;
-          cur_new = newB;
-        }
+      if (s == nA) {  // first block of unit B: park A's state (register moves only)
+        parked = st;
+        clear_state<D>(st);
+        qc = qB;
+        cur_L = uB.L;
+        cur_valid = uB.L + uB.nq;
+        cur_blk = firstB - nA;
+        cur_new = newB;
       }
       const ptrdiff_t own = (s < nA ? vecA : vecB) + (ptrdiff_t)s * kBlkVec + lane;  // this lane's chunks of block s
       uint4* kdst = (uint4*)const_cast<void*>(p.Kc) + own;
@@ -1193,12 +1169,11 @@ __global__ __launch_bounds__(256) void verify_attn_bf16(AttnParams p) {
         KvRegs<D> t;
         TokenScales sc;
         dequant_block<D>(r, t, sc);
-        const I8Operands<D, NT> i8{r.k, qc.q, qc.q_scale_log2, &sc};
-        const bf16x8 no_q[NT][D / 32] = {};
-        block_dispatch<D, NT, true>(t, no_q, st, cur_blk + s, cur_L, cur_valid, qc.lim, p.scale_log2, lane, false,
+        const I8Operands<D> i8{r.k, qc.q, qc.q_scale_log2, &sc};
+        block_dispatch<D, true>(t, nullptr, st, cur_blk + s, cur_L, cur_valid, qc.lim, p.scale_log2, lane, false,
                                     cur_new, nullptr, nullptr, &i8, fine);  // the codes are patched already: no fused work inside
       } else {
-        block_dispatch<D, NT>(r, qc.q, st, cur_blk + s, cur_L, cur_valid, qc.lim, p.scale_log2, lane, fused, cur_new, kdst, vdst, nullptr, fine);
+        block_dispatch<D>(r, qc.q, st, cur_blk + s, cur_L, cur_valid, qc.lim, p.scale_log2, lane, fused, cur_new, kdst, vdst, nullptr, fine);
       }
     };
     // Unused query rows of a unit are cleared by the wavefront that holds the unit's last block (it is handed
@@ -1234,18 +1209,17 @@ __global__ __launch_bounds__(256) void verify_attn_bf16(AttnParams p) {
     }
     // A unit that lies wholly inside this share (common with many short sequences) is finished from the
     // registers; the others leave a partial, and the wavefront that delivers a unit's last partial merges.
-    // (With a merge launch of its own -- more than one query tile -- every unit leaves a partial.)
-    const bool soloA = p.fused_reduce && ja.w_lo == ja.w_hi;
-    const bool soloB = p.fused_reduce && hasB && jb.w_lo == jb.w_hi;
+    const bool soloA = ja.w_lo == ja.w_hi;
+    const bool soloB = hasB && jb.w_lo == jb.w_hi;
     auto deliver = [&]() {
       if (hasB) {
-        if (soloA) finalize_single<D, NT>(p, uA, parked, col, grp);
-        else store_partial<D, NT>(p, uA, w, parked, col, grp);
-        if (soloB) finalize_single<D, NT>(p, uB, st, col, grp);
-        else store_partial<D, NT>(p, uB, w, st, col, grp);
+        if (soloA) finalize_single<D>(p, uA, parked, col, grp);
+        else store_partial<D>(p, uA, w, parked, col, grp);
+        if (soloB) finalize_single<D>(p, uB, st, col, grp);
+        else store_partial<D>(p, uB, w, st, col, grp);
       } else {
-        if (soloA) finalize_single<D, NT>(p, uA, st, col, grp);
-        else store_partial<D, NT>(p, uA, w, st, col, grp);
+        if (soloA) finalize_single<D>(p, uA, st, col, grp);
+        else store_partial<D>(p, uA, w, st, col, grp);
       }
     };
     deliver();
@@ -1255,9 +1229,9 @@ __global__ __launch_bounds__(256) void verify_attn_bf16(AttnParams p) {
     // at head size 128, 0.1 - 0.3 us of launches of 5 - 10 us at 64.  An INT8 row with an infinite element has no finite
     // scale: NaN either way.)
     if constexpr (kFew && !kI8) {
-      if (__builtin_expect(fine && (any_not_finite<D, NT>(st) || (hasB && any_not_finite<D, NT>(parked))), 0)) {
-        load_queries<D, NT>(p, uA, true, col, grp, qc);
-        clear_state<D, NT>(st);
+      if (__builtin_expect(fine && (any_not_finite<D>(st) || (hasB && any_not_finite<D>(parked))), 0)) {
+        load_queries<D>(p, uA, true, col, grp, qc);
+        clear_state<D>(st);
         cur_L = uA.L;
         cur_valid = uA.L + uA.nq;
         cur_blk = firstA;
@@ -1271,7 +1245,7 @@ __global__ __launch_bounds__(256) void verify_attn_bf16(AttnParams p) {
       }
     }
     const bool exchA = !soloA, exchB = hasB && !soloB;
-    if (p.fused_reduce && (exchA || exchB)) {
+    if (exchA || exchB) {
       partial_stores_done();
       bool mergeA = false, mergeB = false, unused;
       if (exchA) arrive(p, lane, ja, mergeA, exchB, jb, mergeB);
@@ -1309,25 +1283,25 @@ __global__ __launch_bounds__(256) void verify_attn_bf16(AttnParams p) {
 // Two wavefronts per tile: the state of the odd blocks joins that of the even ones (one that saw no visible token has
 // m = -inf and no weight).  All wavefronts call; a stretch of one block has nothing to join.  acc: LDS for TW tiles' accumulators.
 template <int D, int TW>
-__device__ inline void merge_halves(RowState<D, 1>& st, int n, int half, int tile, bool active, int lane, f32x4* acc,
+__device__ inline void merge_halves(RowState<D>& st, int n, int half, int tile, bool active, int lane, f32x4* acc,
                                     float (&other_m)[TW][64], float (&other_l)[TW][64]) {
   if (n <= 1) return;  // workgroup-uniform
   __syncthreads();     // the last steps have left the ring
   f32x4* other_acc = acc + tile * (D / 16) * 64 + lane;
   if (half == 1 && active) {
 #pragma unroll
-    for (int mt = 0; mt < D / 16; ++mt) other_acc[mt * 64] = st.acc[0][mt];
-    other_m[tile][lane] = st.m[0];
-    other_l[tile][lane] = st.l[0];
+    for (int mt = 0; mt < D / 16; ++mt) other_acc[mt * 64] = st.acc[mt];
+    other_m[tile][lane] = st.m;
+    other_l[tile][lane] = st.l;
   }
   __syncthreads();
   if (half == 0 && active) {
-    const float m1 = other_m[tile][lane], M = fmaxf(st.m[0], m1), Mf = M == -INFINITY ? 0.f : M;
-    const float w0 = __builtin_amdgcn_exp2f(st.m[0] - Mf), w1 = __builtin_amdgcn_exp2f(m1 - Mf);
-    st.m[0] = M;
-    st.l[0] = st.l[0] * w0 + other_l[tile][lane] * w1;
+    const float m1 = other_m[tile][lane], M = fmaxf(st.m, m1), Mf = M == -INFINITY ? 0.f : M;
+    const float w0 = __builtin_amdgcn_exp2f(st.m - Mf), w1 = __builtin_amdgcn_exp2f(m1 - Mf);
+    st.m = M;
+    st.l = st.l * w0 + other_l[tile][lane] * w1;
 #pragma unroll
-    for (int mt = 0; mt < D / 16; ++mt) st.acc[0][mt] = st.acc[0][mt] * w0 + other_acc[mt * 64] * w1;
+    for (int mt = 0; mt < D / 16; ++mt) st.acc[mt] = st.acc[mt] * w0 + other_acc[mt * 64] * w1;
   }
 }
 
@@ -1366,10 +1340,10 @@ __global__ __launch_bounds__(64 * TW * H, 2) void verify_attn_tiles_bf16(AttnPar
     const Unit u = unit_of(seg);
     const int n = seg.n;  // real blocks seg.first .. seg.first + n - 1 of the unit
     const bool active = uniform(row0 < u.nq * p.g);  // this wavefront owns a query tile of the unit
-    QFrag<D, 1> q;
-    load_queries<D, 1>(p, u, active, col, grp, q, row0);
-    RowState<D, 1> st;
-    clear_state<D, 1>(st);
+    QFrag<D> q;
+    load_queries<D>(p, u, active, col, grp, q, row0);
+    RowState<D> st;
+    clear_state<D>(st);
     const int blk0 = seg.first;
     const ptrdiff_t vec0 = (((ptrdiff_t)u.b * p.Hkv + u.kvh) * p.nblk_cap + blk0) * kBlkVec;
 
@@ -1436,7 +1410,7 @@ __global__ __launch_bounds__(64 * TW * H, 2) void verify_attn_tiles_bf16(AttnPar
         for (int i = 0; i < 2 * (D / 32); ++i) r.k[i] = lk[i * 64];
 #pragma unroll
         for (int i = 0; i < D / 16; ++i) r.v[i] = lv[i * 64];
-        block_dispatch<D, 1>(r, q.q, st, blk0 + H * ph + half, u.L, u.L + u.nq, q.lim, p.scale_log2, lane, false, NewRows{}, nullptr, nullptr);
+        block_dispatch<D>(r, q.q, st, blk0 + H * ph + half, u.L, u.L + u.nq, q.lim, p.scale_log2, lane, false, NewRows{}, nullptr, nullptr);
       }
     };
     __syncthreads();  // the previous unit's merge has left the ring
@@ -1448,7 +1422,7 @@ __global__ __launch_bounds__(64 * TW * H, 2) void verify_attn_tiles_bf16(AttnPar
       for (int j = 0; j < kTileAhead; ++j) phase(g[j], ph + j);
     }
     if constexpr (H == 2) merge_halves<D, TW>(st, n, half, tile, active, lane, (f32x4*)&ring_k[0][0], other_m, other_l);
-    if (half == 0 && active) store_partial<D, 1>(p, u, wg, st, col, grp, row0);
+    if (half == 0 && active) store_partial<D>(p, u, wg, st, col, grp, row0);
   }
 }
 
@@ -1500,10 +1474,10 @@ __global__ __launch_bounds__(256, 2) void verify_attn_tiles_i8(AttnParams p) {
     const Unit u = unit_of(seg);
     const int n = seg.n;
     const bool active = row0 < u.nq * p.g;  // this wavefront owns a query tile of the unit
-    QFragI8<D, 1> q;
-    load_queries_i8<D, 1>(p, u, active, col, grp, q, row0);
-    RowState<D, 1> st;
-    clear_state<D, 1>(st);
+    QFragI8<D> q;
+    load_queries_i8<D>(p, u, active, col, grp, q, row0);
+    RowState<D> st;
+    clear_state<D>(st);
     const int blk0 = seg.first;
     const ptrdiff_t vec0 = (((ptrdiff_t)u.b * p.Hkv + u.kvh) * p.nblk_cap + blk0) * kBlkVec;
 
@@ -1604,9 +1578,8 @@ __global__ __launch_bounds__(256, 2) void verify_attn_tiles_i8(AttnParams p) {
             sc.v[4 * h + j] = vs[j];
           }
         }
-        const I8Operands<D, 1> i8{k, q.q, q.q_scale_log2, &sc};
-        const bf16x8 no_q[1][D / 32] = {};
-        block_dispatch<D, 1, true>(r, no_q, st, blk0 + P * ph + bl, u.L, u.L + u.nq, q.lim, p.scale_log2, lane, false, NewRows{}, nullptr,
+        const I8Operands<D> i8{k, q.q, q.q_scale_log2, &sc};
+        block_dispatch<D, true>(r, nullptr, st, blk0 + P * ph + bl, u.L, u.L + u.nq, q.lim, p.scale_log2, lane, false, NewRows{}, nullptr,
                                    nullptr, &i8);
       }
     };
@@ -1619,7 +1592,7 @@ __global__ __launch_bounds__(256, 2) void verify_attn_tiles_i8(AttnParams p) {
       for (int j = 0; j < kAhead; ++j) phase(g[j], ph + j);
     }
     if constexpr (H == 2) merge_halves<D, TW>(st, n, half, tile, active, lane, (f32x4*)&ring_v[0][0], other_m, other_l);
-    if (half == 0 && active) store_partial<D, 1>(p, u, wg, st, col, grp, row0);
+    if (half == 0 && active) store_partial<D>(p, u, wg, st, col, grp, row0);
   }
 }
 
@@ -1794,7 +1767,7 @@ int append_planned(const bass_attn_desc* d, void* Kcache, void* Vcache, const vo
 
 extern "C" int bass_set_attention_waves(int waves) {
   bass::g_attention_waves.store(waves > 0 ? waves : 0, std::memory_order_relaxed);
-  return bass::attention_waves(bass::attention_waves_setting(), false, false);
+  return bass::attention_waves(bass::attention_waves_setting());
 }
 
 extern "C" size_t bass_verify_attention_workspace_bytes(const bass_attn_desc* d) {
@@ -1857,7 +1830,6 @@ static int launch_attention(const bass_attn_desc* d, const LaunchShape& ls, cons
   p.g_magic = (g <= 64 && rows_max <= 2048) ? ((1u << 20) + (unsigned)g - 1u) / (unsigned)g : 0u;  // exact there: checked exhaustively
   p.nwaves = ls.nwaves;
   p.nshares = ls.nshares;
-  p.fused_reduce = ls.fused_reduce;
   p.scale_log2 = d->scale * 1.4426950408889634f;
   p.Q = Q; p.Kc = Kcache; p.Vc = Vcache; p.Knew = K_new; p.Vnew = V_new;
   const PlanLayout pl = plan_layout(d->B, d->Hkv, ls.nshares);
@@ -1891,8 +1863,8 @@ static int launch_attention(const bass_attn_desc* d, const LaunchShape& ls, cons
     const bool few = may_be_few(plan_shape(d, ls, 0));
 #define BASS_LAUNCH(DD, I8)                                                                          \
   do {                                                                                               \
-    if (few) hipLaunchKernelGGL((verify_attn_bf16<DD, 1, I8, true>), grid, block, lds, s, p);        \
-    else hipLaunchKernelGGL((verify_attn_bf16<DD, 1, I8, false>), grid, block, lds, s, p);           \
+    if (few) hipLaunchKernelGGL((verify_attn_bf16<DD, I8, true>), grid, block, lds, s, p);        \
+    else hipLaunchKernelGGL((verify_attn_bf16<DD, I8, false>), grid, block, lds, s, p);           \
   } while (0)
     if (d->dtype == BASS_DTYPE_INT8KV) {
       if (d->D == 128) BASS_LAUNCH(128, true); else BASS_LAUNCH(64, true);
@@ -1902,7 +1874,7 @@ static int launch_attention(const bass_attn_desc* d, const LaunchShape& ls, cons
 #undef BASS_LAUNCH
   }
   if (launch_status() != BASS_OK) return BASS_ERR_HIP;
-  if (!p.fused_reduce) {
+  if (ls.tiles) {  // the merge is a launch of its own
     const long items = (long)d->B * d->Hkv * ((rows_max + 3) / 4);
     const dim3 rgrid((unsigned)((items + 3) / 4));
     if (d->D == 128) hipLaunchKernelGGL((reduce_partials<2, 128>), rgrid, dim3(256), 0, s, p);
