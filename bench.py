@@ -480,9 +480,9 @@ def main():
         "logits_to_acceptance_us": None if fused_us is None else {
             "bass_warp_probs x 2 + bass_spec_accept": round(two_us, 2), "bass_warp_accept": round(fused_us, 2)},
         "roofline": {
-            "kernel": ("verify_attn_bf16<128,1,int8> (quantizing append + streaming + split-context reduction, one launch)"
+            "kernel": ("verify_attn_bf16<128,int8> (quantizing append + streaming + split-context reduction, one launch)"
                        if args.kv_int8 else
-                       "verify_attn_bf16<128,1> (append + streaming + split-context reduction, one launch)"),
+                       "verify_attn_bf16<128> (append + streaming + split-context reduction, one launch)"),
             "bound": "hbm",
             "achieved": round(kv_bytes / (attn_us * 1e-6) / 1e9, 1),
             "peak": HBM_PEAK_GBPS,

@@ -17,7 +17,11 @@
  *     OR a BASS_STATUS_* bit into `*dev_status` (int32 on the device, optional, may be
  *     NULL; the caller zeroes it).
  *   - One GPU; calls on the same stream are ordered; calls on different streams must not
- *     share a workspace.
+ *     share a workspace.  Calls that write different tokens of one cache may overlap, with one
+ *     exception: an attention call for at most 16 query rows per kv head that appends the step's
+ *     rows itself writes V in groups of eight tokens, so nothing else may write to the 32-token
+ *     blocks of its new rows meanwhile.  bass_kv_append, and calls for more query rows, write
+ *     nothing but their own rows.
  */
 #ifndef BASS_H
 #define BASS_H
@@ -179,7 +183,8 @@ int bass_verify_attention_split(const bass_attn_desc* desc, const void* Q, const
  * sequences whose lengths had to be clamped are appended at the clamped positions.  Arguments as
  * in those calls.  bf16 and INT8 caches with kmax * D <= 2048 and fp32 caches append inside the
  * attention launch (INT8: the rows are quantized on the way, with the quantizer of bass_kv_append);
- * longer drafts run the append as a launch of its own inside this call.
+ * longer drafts run the append as a launch of its own inside this call (bass_verify_attention_planned appends
+ * them inside the attention launch too where that is quicker).
  */
 int bass_append_verify_attention(const bass_attn_desc* desc, const void* Q, const void* K_new,
                                  const void* V_new, void* Kcache, void* Vcache,
@@ -319,11 +324,16 @@ int32_t bass_next_draft_len(bass_draft_len_state* state, const int32_t* n_accept
 
 /*
  * Tuning knob (host state, process wide): number of wavefronts the attention kernels spread the
- * flattened (sequence, kv-head, context-block) work over.  Values are clamped to [64, 8192]; 0 restores
- * the defaults, which depend on the call: 768 with up to 16 query rows per kv head; with more, 1024 for
- * INT8 caches and 256 workgroups of four wavefronts for bf16 caches (a setting W gives W / 2 workgroups
- * there).  Returns the value in effect for the first of these cases.  (A launch of 768 wavefronts runs as 256 workgroups of three, one per compute
- * unit; every other count as workgroups of four.)
+ * flattened (sequence, kv-head, context-block) work over.  Values are clamped to [64, 8192] and rounded down to a
+ * multiple of 4; 0 restores the defaults:
+ *   up to 16 query rows per kv head, and fp32 caches: 768 wavefronts, as 256 workgroups of three, one per compute
+ *     unit (every other count: workgroups of four);
+ *   more, bf16 caches: 256 workgroups, of four wavefronts with up to 32 rows and of eight with more;
+ *   more, INT8 caches: 512 workgroups of four wavefronts.
+ * A setting W gives W wavefronts in the first case and W / 2 workgroups in the others.  Any setting but 0, also 768, divides
+ * every list of blocks over all shares; by default short lists over bf16 and INT8 caches go to fewer (up to 16 query rows per
+ * kv head), where what the rounding of the probabilities to bf16 left over is multiplied as well: a setting so changes the
+ * rounding, within the same tolerance, besides the time.  Returns the value in effect for the first case.
  */
 int bass_set_attention_waves(int waves);
 

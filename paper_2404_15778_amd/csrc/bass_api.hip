@@ -1,7 +1,7 @@
 // Version and status strings of libbass, and the host-side draft-length heuristic.
 #include "bass_common.h"
 
-extern "C" int bass_version(void) { return 213; /* 0.2.13: workgroup-level kernel for INT8 caches; caches appended and gathered by blocks; short lists over fewer shares */ }
+extern "C" int bass_version(void) { return 214; /* 0.2.14: plan signatures over the whole division; appends write nothing but their rows; two query tiles as measured over the range */ }
 
 extern "C" const char* bass_status_string(int code) {
   switch (code) {

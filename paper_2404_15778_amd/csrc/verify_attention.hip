@@ -848,6 +848,8 @@ __device__ inline void block_step(KvRegs<D>& r, const bf16x8* qf, RowState<D>& s
   // multiplied as well.  A share's first block holds its largest probability, 1, which is exact; with a fifth
   // as many shares per unit that is lost for most of them (one sequence of 32 heads: error against 64 bits
   // 1.3e-3 with 24 shares per unit, 1.6e-3 with 5, 2.3e-6 this way; the step of 32 layers 463 -> 489 us).
+  // Over INT8 caches no probability is exact, because the V scale is multiplied in before the rounding, and fewer
+  // shares lose nothing; the remainders take away the 1.7e-3 that the rounding costs there all the same.
   if (fine) {
     bf16x8 pr;
 #pragma unroll
@@ -1950,7 +1952,8 @@ extern "C" int bass_append_verify_attention(const bass_attn_desc* d, const void*
                                             size_t workspace_bytes, int32_t* dev_status, void* stream) {
   if (!K_new || !V_new) return BASS_ERR_INVALID_ARG;
   if (d && d->dtype != BASS_DTYPE_FP32 && (int64_t)d->kmax * d->D > bass::kMaxStagedElems) {
-    // more new rows than a wavefront stages in LDS: append with a launch of its own
+    // more new rows than a wavefront stages in LDS: append with a launch of its own (the workgroup-level kernels could
+    // take them, as planned launches do; this way is what those are tested against)
     const int rc = bass_kv_append(d, Kcache, Vcache, K_new, V_new, ctx_len, draft_len, dev_status, stream);
     if (rc != BASS_OK) return rc;
     return bass::plan_and_launch(d, Q, nullptr, nullptr, Kcache, Vcache, ctx_len, draft_len, O, lse, workspace,

@@ -3,7 +3,8 @@
     python -m paper_2404_15778_amd.kernel_times attention --cfg 2 [--dtype bf16|int8kv] [--waves 0,1024]
                                                            [--slabs 16] [--fused] [--planned] [--reps 3]
     python -m paper_2404_15778_amd.kernel_times logits [--reps 5] [--temperature T --top-p P]
-    python -m paper_2404_15778_amd.kernel_times summarize <kernel_trace.csv>
+    python -m paper_2404_15778_amd.kernel_times case NAME [--passes 6]
+    python -m paper_2404_15778_amd.kernel_times summarize <kernel_trace.csv> [--after-marker]
 
 `attention` fills --slabs cache slabs of one attention configuration (workloads.config2/3/4, seed 0) with
 bass_kv_append, so that consecutive calls cannot be served by the last-level cache, and calls
@@ -20,6 +21,9 @@ and 8 x 5 draft-model rows of 50 000 logits) at three settings: the paper's temp
 flat rows (1.0 / 0.9) and the plain softmax (1.0 / 1.0) -- or at the one setting given; then, at the first
 setting, bass_spec_accept on the rows made and bass_warp_accept on the logits (drafts: the draft model's
 most likely tokens).
+
+`case` prepares a listed case of perf/cases.py (seed 1), launches one small bass_bench_stream_read as a marker and runs the
+case --passes times; `summarize --after-marker` leaves out everything up to that marker.
 
 Needs the GPU and the built library (except `summarize`).
 """
@@ -136,8 +140,30 @@ def logits(args):
     print(f"bass_warp_accept at T={T} top_p={top_p}: accepted {n_acc.tolist()}, same as the two calls", flush=True)
 
 
+def case(args):
+    import importlib.util
+
+    import torch
+
+    import paper_2404_15778_amd as bass
+
+    root = os.path.dirname(os.path.dirname(os.path.abspath(__file__)))
+    spec = importlib.util.spec_from_file_location("cases", os.path.join(root, "perf", "cases.py"))
+    cases = importlib.util.module_from_spec(spec)
+    spec.loader.exec_module(cases)
+    state = cases.prepare(next(c for c in cases.listed() if c["name"] == args.name), 1)
+    kv = torch.zeros(1 << 16, dtype=torch.uint8, device="cuda:0")
+    bass.bass_bench_stream_read(kv, kv, kv.numel(), 4)
+    for _ in range(args.passes):
+        cases.run(state)
+    torch.cuda.synchronize()
+    print(f"{args.name}: {args.passes} passes", flush=True)
+
+
 def summarize(args):
-    rows = list(csv.DictReader(open(args.trace)))
+    rows = sorted(csv.DictReader(open(args.trace)), key=lambda r: int(r["Start_Timestamp"]))
+    if getattr(args, "after_marker", False):
+        rows = rows[1 + max(i for i, r in enumerate(rows) if "stream_read" in r["Kernel_Name"]):]
     agg = collections.defaultdict(list)
     for r in rows:
         name = r["Kernel_Name"]
@@ -169,8 +195,13 @@ def main():
     g.add_argument("--temperature", type=float, default=None)
     g.add_argument("--top-p", type=float, default=0.95)
     g.set_defaults(run=logits)
+    c = sub.add_parser("case")
+    c.add_argument("name")
+    c.add_argument("--passes", type=int, default=6)
+    c.set_defaults(run=case)
     s = sub.add_parser("summarize")
     s.add_argument("trace")
+    s.add_argument("--after-marker", action="store_true")
     s.set_defaults(run=summarize)
     args = ap.parse_args()
     if args.what != "summarize":
