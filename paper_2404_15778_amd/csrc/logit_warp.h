@@ -32,7 +32,7 @@
 // later passes run on the list: the row is read once, and written once, as zeros and a few values.  Whether a row
 // is peaked enough is seen from its first batch of groups; other rows write e_i into the output row and re-read it
 // from L2 or beyond (512 KB per row, 32 rows per 4 MB of L2).  480 rows of 131072 tokens at T = 0.2 (two calls and the
-// acceptance): 264 -> 167 us, of which 537 MB at memory rate are about 100 us.
+// acceptance): 265 -> 170 us, of which 537 MB at memory rate are about 100 us.
 #pragma once
 #include "bass_common.h"
 
