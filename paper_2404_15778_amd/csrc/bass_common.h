@@ -139,14 +139,25 @@ constexpr int kPlainBefore = 0;   // kernel; measured: +0.5 % with the fused app
 // blocks, 60 - 100 tokens, are no quicker (0 - 4 % longer).
 constexpr int kMinEntries = 5;
 constexpr int kPerUnit = 5, kPerUnitInt8 = 8;
-// Workgroups of the workgroup-level kernels.  bf16: one per compute unit.  With 512 (two blocks per phase), 256 -> 512: 64/8 heads
-// of 128, 24 rows, 8 sequences of 400 tokens 13.0 -> 17.3 us; 32 heads of 128, 32 rows, 8 / 16 of 1200 42.5 -> 52.7 / 80.8 -> 75.4;
-// 16 layers of 16 of 1024 - 4096, 64/8 heads, 48 rows 759 -> 845; 32 heads of 64, 32 rows, 1 of 400 / 16 of 1200 11.4 -> 13.3 /
-// 50 -> 41: better for long lists of small blocks only, and the lists' lengths are not known when the launch is sized.
-// INT8: two, because a step's conversions and softmax leave issue slots to fill: 16 sequences of 1024 - 4096 tokens, 64/8 heads, 64
-// rows, 128 / 256 / 384 / 512 / 640 / 1024 workgroups: 1467 / 869 / 788 / 756 / 889 / 903 us for 16 layers; 32 heads and
-// 32 rows: 1665 / 972 / 835 / 745 / 919 / 949.
-constexpr int kTileShares = 256, kTileSharesInt8 = 512;
+// More than 16 query rows per kv head: the workgroup-level kernels.  verify_attn_wide (a wavefront has all rows of its own blocks)
+// takes whatever has at most 32 rows, and more rows in caches of more than kShortCache blocks per sequence; below, the kernels that
+// share a block's rows between wavefronts are quicker, whose way from the first block to the last store is shorter.  48 and 64 rows,
+// 8 kv heads of 128, 1 / 4 / 8 / 32 sequences, sharing rows -> wide: bf16, at most 150 tokens 9.5 / 10.4 / 13.4 / 20.2 -> 12.0 / 12.4 / 15.0 /
+// 23.6 us, 400 tokens 9.5 / 15.3 / 15.2 / 23.1 -> 12.2 / 16.3 / 16.6 / 25.6, 700 tokens 12.3 / 15.0 / 18.9 / 30.2 -> 13.4 / 16.4 / 17.8 / 30.9,
+// 1200 tokens 18.8 / 19.5 / 21.8 / 42.0 -> 16.4 / 18.9 / 21.6 / 40.5; INT8, 400 tokens 11.4 / 17.7 / 19.1 / 25.2 -> 13.9 / 17.1 / 17.2 / 27.2, 700
+// tokens 13.2 / 19.7 / 19.9 / 30.7 -> 14.7 / 17.6 / 18.2 / 31.2, 1200 tokens 20.4 / 21.4 / 21.7 / 39.4 -> 17.4 / 19.4 / 23.8 / 35.8.
+// (The lengths themselves are known on the device only.)
+constexpr int kShortCache = 24;
+// verify_attn_wide: one workgroup per compute unit.  The end of a unit inside a stretch -- four states merged, the next unit's first
+// blocks waited for -- costs its workgroup about as much as 7 blocks: 16 layers of 16 sequences of 1024 - 4096 tokens, 64/8 heads, with 3 / 5 /
+// 7 virtual blocks per unit 769 / 758 / 758 us, 8 sequences, 32 heads, 32 rows 765 / 751 / 745.  Short lists go to fewer workgroups so that
+// every wavefront has a block: 1 sequence of 1000 tokens, 64 rows, 8 kv heads, with at least 1 / 4 / 8 / 12 entries per share 26.5 / 17.8 / 18.0 /
+// 20.8 us; from 8 on a wavefront's state spans several blocks, fewer probabilities are exactly 1 and precision is lost.
+constexpr int kTileShares = 256;
+constexpr int kWidePad = 7, kWideEntries = 4;
+// The kernels that share rows.  bf16: one workgroup per compute unit; INT8: two, because a step's conversions and softmax leave issue slots
+// to fill.  INT8 plans have room for twice the stretches.
+constexpr int kRowShares = 256, kRowSharesInt8 = 512;
 constexpr int kMaxStagedElems = 2048;  // kmax * D up to which the one-tile kernels stage the step's rows in LDS
 
 int attention_waves_setting();  // bass_set_attention_waves (0 = defaults); verify_attention.hip
@@ -154,6 +165,7 @@ int attention_waves_setting();  // bass_set_attention_waves (0 = defaults); veri
 struct LaunchShape {
   bool mfma;        // bf16 or INT8 caches: the matrix-core kernels
   bool tiles;       // more than one 16-row query tile per kv head: the workgroup-level kernels
+  bool wide;        // ... verify_attn_wide
   bool fused_append;  // the step's rows are appended inside the attention launch, and its plan says so
   bool tiles_append;  // longer drafts, workgroup-level kernels: they patch a block at a time and stage nothing, so
                       // planned launches may append there too; the plan is the one of a launch that does not append
@@ -187,14 +199,15 @@ inline LaunchShape launch_shape(const bass_attn_desc* d, bool append) {
   // (a launch wider than the shares it aims at, with all shares equally long -- plan_split -- was measured
   // 1 - 2 % slower than the even division on the benchmark shapes: more wavefronts, more partials to merge)
   s.nwaves = attention_waves(setting);
+  s.wide = s.tiles && (s.rows_max <= 32 || num_blocks(d->Lcap) > kShortCache);
   // the workgroup-level kernels take one stretch per workgroup: half as many as an explicit setting has wavefronts
-  const int stretches = setting > 0 ? s.nwaves / 2 : (int8 ? kTileSharesInt8 : kTileShares);
-  s.used_shares = s.tiles ? stretches : s.nwaves;
-  s.nshares = s.tiles && int8 ? 2 * stretches : s.used_shares;  // INT8: plans keep room for twice the stretches
+  const int stretches = setting > 0 ? s.nwaves / 2 : (int8 ? kRowSharesInt8 : kRowShares);
+  s.used_shares = !s.tiles ? s.nwaves : s.wide && setting <= 0 ? kTileShares : stretches;
+  s.nshares = !s.tiles ? s.nwaves : int8 ? 2 * stretches : stretches;
   s.target = s.nshares;
-  s.pad = s.fused_append ? kAppendPad : kPlainPad;
-  s.min_entries = setting > 0 || s.tiles || !s.mfma ? 0 : kMinEntries;
-  s.per_unit = int8 ? kPerUnitInt8 : kPerUnit;
+  s.pad = s.wide ? kWidePad : s.fused_append ? kAppendPad : kPlainPad;
+  s.min_entries = setting > 0 || !s.mfma || s.tiles != s.wide ? 0 : s.wide ? kWideEntries : kMinEntries;
+  s.per_unit = s.wide ? 1 : int8 ? kPerUnitInt8 : kPerUnit;
   s.pad_before = 0;
   if (s.mfma && s.rows_max <= 16) s.pad_before = s.fused_append ? kAppendBefore : kPlainBefore;
   return s;

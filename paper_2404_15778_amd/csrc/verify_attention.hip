@@ -19,9 +19,9 @@
 // sum per query row) and, for every unit it touches, writes one partial (max, sum,
 // unnormalised output).  The wavefront that delivers the LAST partial of a unit (found with
 // one atomic counter per unit) merges the unit's partials -- the split-context reduction --
-// and writes O and the log-sum-exp, so the whole call is a single launch.  (With more than one
-// 16-row query tile per kv head -- grouped-query attention -- the merge is a second, chip-wide
-// launch: reduce_partials.)
+// and writes O and the log-sum-exp, so the whole call is a single launch.  (More than 16 query
+// rows per kv head -- grouped-query attention, long drafts -- have kernels of their own, and with
+// more than 32 the merge is a second, chip-wide launch: reduce_wide.)
 //
 // Matrix-core mapping (v_mfma_f32_16x16x32_bf16, wave64).  Tokens sit on the M side:
 //   S^T[16 tokens x 16 query rows] = K[16 x D] * Q^T[D x 16]          (D/32 MFMAs per tile)
@@ -1267,21 +1267,695 @@ __global__ __launch_bounds__(256) void verify_attn_bf16(AttnParams p) {
 }
 
 // ---------------------------------------------------------------------------------------
-// Workgroup-level kernel for kv heads with more than 16 query rows (grouped-query attention, long drafts), bf16.
-// The accumulators of two to four 16-row tiles in ONE wavefront leave registers for a single block in
-// flight, and re-reading blocks by several wavefronts crosses the fabric twice.  Here a workgroup of
-// TW H wavefronts takes a stretch of the block list together: every K/V block is fetched from memory
-// once (each wavefront a part of it), put into a ring in LDS, and read from there by the wavefronts that own
-// a query tile (rows 16 t .. 16 t + 15), each running the one-tile block step.  A step is a serial chain (scores,
-// maximum, exponentials, products) of about a microsecond that one wavefront per SIMD cannot hide, so with H = 2 the
-// ring holds two blocks per phase and each tile has two wavefronts, one for the even and one for the odd
-// blocks, whose states are merged through LDS at the end of the unit.  One barrier per phase: a slot is rewritten
-// only after the barrier that follows the last step that read it.  Every barrier sits in workgroup-uniform
-// control flow (the stretch, the units and the block counts depend on the workgroup index and the lengths only).
-// TW: tiles a workgroup has room for (launch_tiles says which form serves which call).  H = 2, 16 layers of 16 sequences of
-// 1024 - 4096 tokens, 64/8 heads of 128, 48 rows per kv head: 817 -> 759 us (attention, merge); three and four phases
-// ahead spill: 775 and 803.
+// Workgroup-level kernel for kv heads with more than 16 query rows (grouped-query attention, long drafts): NT tiles of 32 rows,
+// bf16 and INT8 caches.  A workgroup of four wavefronts takes a stretch of the block list together and its wavefronts take the
+// blocks in turn, each with the state of ALL query rows: a block is fetched once, straight into the operand registers of the one
+// wavefront that needs it, nothing passes through LDS and nobody waits for anybody until the unit ends.  There the four
+// states are merged through LDS (each wavefront collects a quarter of the accumulators) and one partial is stored.  What this is
+// built around: a step of 32 x 32 tiles (v_mfma_f32_32x32x16_bf16) has half the matrix and cross-lane instructions per row
+// of one of 16 x 16, and with two tiles two independent chains, so that one wavefront per SIMD keeps up with its share of the
+// memory.  Attention with its merge per layer, against 16-row tiles of one wavefront each that read the blocks from a ring in LDS behind a
+// barrier per phase: 16 sequences of 1024 - 4096 tokens, 64/8 heads of 128, bf16 with 48 rows (181 MB) 42.7 -> 41.7 us, INT8 with 64 rows
+// (94 MB) 46.3 -> 36.0; 8 sequences of 512 - 2048, 32 heads, 32 rows, bf16 (182 MB) 51.8 -> 44.0, INT8 40.1 -> 33.3.  What is left over the
+// memory's time is the way in (3 us to the first block), the merges and stretches that end 22 - 33 us after the start.
+//
+// Matrix-core mapping (32 x 32, c = lane % 32, h = lane / 32):
+//   S^T[32 tokens x 32 rows] = K Q^T: row c of operand A is token wide_token(c) of the block (bits 3 and 4 of c exchanged), step ks
+//     takes head elements 8 (2 ks + h) .. + 7 (INT8: 16 (2 ks + h) .. + 15); a lane then holds, for query row c, the tokens
+//     16 ((i >> 2) & 1) + 8 (i >> 3) + 4 h + (i & 3), i = 0 .. 15,
+//   which is, eight by eight, the token order of the cache's V chunks, so that the probabilities are operand B of
+//   O^T[32 head elements x 32 rows] += V^T P^T as they are.
 // ---------------------------------------------------------------------------------------
+typedef __attribute__((ext_vector_type(16))) float f32x16;
+typedef __attribute__((ext_vector_type(16))) int i32x16;
+
+constexpr int kWideWaves = 4;
+constexpr int kAuxNonTemporal = 2;  // nt
+
+__device__ inline int wide_token(int c) { return (c & 7) | ((c & 8) << 1) | ((c & 16) >> 1); }
+__device__ inline int score_token(int i, int h) { return 16 * ((i >> 2) & 1) + 8 * (i >> 3) + 4 * h + (i & 3); }
+// First of the four consecutive head elements that registers 4 q .. 4 q + 3 of accumulator a hold
+template <bool kI8>
+__device__ inline int wide_elem(int a, int q, int h) {
+  return kI8 ? 64 * (a >> 1) + 32 * (q >> 1) + 16 * (a & 1) + 8 * (q & 1) + 4 * h : 32 * a + 8 * q + 4 * h;
+}
+
+// Place of a quad of head elements in a partial.  Slots lie 32 KB apart at 64 rows of 128: without the rotation all workgroups would
+// write to the same few memory channels at a time.
+template <int D>
+__device__ inline int wide_quad(int quad, int slot) { return (quad + slot) & (D / 4 - 1); }
+
+__device__ inline float rows2_max(float v) {  // over lanes l and l + 32, which share a query row
+  const u32x2 a = __builtin_amdgcn_permlane32_swap(__float_as_uint(v), __float_as_uint(v), false, false);
+  return fmaxf(__uint_as_float(a[0]), __uint_as_float(a[1]));
+}
+__device__ inline float rows2_sum(float v) {
+  const u32x2 a = __builtin_amdgcn_permlane32_swap(__float_as_uint(v), __float_as_uint(v), false, false);
+  return __uint_as_float(a[0]) + __uint_as_float(a[1]);
+}
+
+// A block on its way to its wavefront: one 16-byte chunk of each k-step's operand, and (INT8) one scale: lane l < 32 the K scale
+// of token l, lane l >= 32 the V scale of token l - 32.
+template <int D, bool kI8>
+struct WideBlock {
+  static constexpr int kChunks = D / (kI8 ? 32 : 16);
+  u32x4 k[kChunks], v[kChunks];
+  float scale;
+};
+
+template <int D, bool kI8>
+struct WideGeometry {
+  static constexpr int kBlkVec = kI8 ? 2 * D + 8 : 4 * D;  // uint4 per block and tensor
+  static constexpr int kTileVec = D * (kI8 ? 1 : 2);       // ... of one 16-token half of K
+};
+
+// Chunk offsets (uint4) inside a block.  K: step ks of lane (c, h).  V: bf16 chunk x = 2 a + s is d-tile a, tokens of k-step s;
+// INT8 chunk x = 2 pair + s holds d-tiles 2 pair and 2 pair + 1.
+__device__ inline int wide_k_lane(int c, int h, int tile_vec) {
+  const int t = wide_token(c);
+  return (t >> 4) * tile_vec + h * 16 + (t & 15);
+}
+__device__ inline int wide_v_lane(int c, int h) { return (c >> 4) * 64 + h * 16 + (c & 15); }
+__device__ constexpr int wide_k_step(int ks) { return (ks >> 1) * 64 + (ks & 1) * 32; }
+__device__ constexpr int wide_v_step(int x) { return (x >> 1) * 128 + (x & 1) * 32; }
+
+template <int D, bool kI8, int NT>
+struct WideQueries {
+  u32x4 q[NT][D / (kI8 ? 32 : 16)];  // operand B: query row 32 nt + c, the k-steps' head elements
+  float row_scale[NT];               // INT8: row scale * |softmax scale| * log2(e)
+  int lim[NT];                       // last token visible to the row
+};
+
+// The queries go through LDS, because an operand's rows lie far apart: fetched by the wavefronts themselves, each would touch 32
+// cache lines with every load.  The workgroup fetches them row by row (8 elements per lane: kLoads per thread), INT8 caches quantize them
+// there like cache rows (a row's D / 8 lanes agree on its largest magnitude), and every wavefront reads its operands from LDS.
+template <int D, bool kI8, int NT>
+struct WideQueryRows {
+  static constexpr int kRowBytes = D * (kI8 ? 1 : 2) + 16;  // 16 bytes apart in the banks
+  static constexpr int kLoads = 32 * NT * (D / 8) / (64 * kWideWaves);
+  __align__(16) unsigned char q[32 * NT * kRowBytes];
+  float row_scale[kI8 ? 32 * NT : 1];
+};
+
+// A negative softmax scale is moved into the queries (exact) and so is a zero, so that the factor that is left is positive: the
+// largest product is the largest score, and masked ones stay -inf.
+template <int D, bool kI8, int NT>
+__device__ inline void commit_wide_queries(const AttnParams& p, const Unit& u, int tid, const u32x4 (&raw)[WideQueryRows<D, kI8, NT>::kLoads],
+                                           WideQueryRows<D, kI8, NT>& lds) {
+  const uint32_t flip = p.scale_log2 < 0.f ? 0x80008000u : 0u;
+#pragma unroll
+  for (int x = 0; x < WideQueryRows<D, kI8, NT>::kLoads; ++x) {
+    const int at = x * 64 * kWideWaves + tid, row = at / (D / 8), ck = at % (D / 8);
+    const u32x4 v = (raw[x] ^ flip) & (row < u.nq * p.g && p.scale_log2 != 0.f ? 0xFFFFFFFFu : 0u);
+    if constexpr (kI8) {
+      const uint4 w = __builtin_bit_cast(uint4, v);
+      float amax = amax8(w);
+#pragma unroll
+      for (int o = D / 16; o >= 1; o >>= 1) amax = fmaxf(amax, __shfl_xor(amax, o));
+      const float scale = amax / 127.0f * fabsf(p.scale_log2);
+      const float inv = amax > 0.f && scale != 0.f ? 127.0f / amax : 0.f;
+      *(uint2*)&lds.q[row * lds.kRowBytes + 8 * ck] = quantize8(w, inv);
+      if (ck == 0) lds.row_scale[row] = scale != 0.f ? scale : 1.f;
+    } else {
+      *(u32x4*)&lds.q[row * lds.kRowBytes + 16 * ck] = v;
+    }
+  }
+}
+
+template <int D, bool kI8, int NT>
+__device__ inline void read_wide_queries(const AttnParams& p, const Unit& u, int c, int h, const WideQueryRows<D, kI8, NT>& lds,
+                                         WideQueries<D, kI8, NT>& q) {
+#pragma unroll
+  for (int nt = 0; nt < NT; ++nt) {
+    const int row = 32 * nt + c;
+    q.lim[nt] = u.L + (row < u.nq * p.g ? row_token(p, row) : 0);
+#pragma unroll
+    for (int ks = 0; ks < D / (kI8 ? 32 : 16); ++ks) q.q[nt][ks] = *(const u32x4*)&lds.q[row * lds.kRowBytes + 16 * (2 * ks + h)];
+    if constexpr (kI8) q.row_scale[nt] = lds.row_scale[row];
+  }
+}
+
+template <int D, int NT>
+struct WideState {
+  f32x16 acc[NT][D / 32];
+  float m[NT], l[NT];  // running maximum (log2 units; the same in both lanes of a row), this lane's share of the sum
+};
+
+// The step's own rows of a unit in LDS ([row][D] bf16, or codes and one scale per row), as in the one-tile kernel.
+template <int D, bool kI8, int NT>
+struct WideNewRows {
+  static constexpr int kRows = 32 * NT, kElem = kI8 ? 1 : 2;
+  __align__(16) unsigned char k[kRows * D * kElem], v[kRows * D * kElem];
+  float k_scale[kI8 ? kRows : 1], v_scale[kI8 ? kRows : 1];
+};
+
+// New tokens into a fetched block's registers.
+template <int D, bool kI8, int NT>
+__device__ inline void patch_wide(WideBlock<D, kI8>& r, int tok0, int L, int nq, int lane, const WideNewRows<D, kI8, NT>& nr) {
+  constexpr int n = WideBlock<D, kI8>::kChunks;
+  const int c = lane & 31, h = lane >> 5;
+  const int ik = tok0 + wide_token(c) - L;
+  if (ik >= 0 && ik < nq) {
+#pragma unroll
+    for (int ks = 0; ks < n; ++ks) r.k[ks] = *(const u32x4*)&nr.k[(size_t)ik * D * nr.kElem + 16 * (2 * ks + h)];
+  }
+  if constexpr (kI8) {
+    const int is = tok0 + c - L;
+    if (is >= 0 && is < nq) r.scale = h ? nr.v_scale[is] : nr.k_scale[is];
+  }
+#pragma unroll
+  for (int s = 0; s < 2; ++s)
+#pragma unroll
+    for (int j = 0; j < 8; ++j) {
+      const int i = tok0 + score_token(8 * s + j, h) - L;
+      if (i >= 0 && i < nq) {
+#pragma unroll
+        for (int a = 0; a < D / 32; ++a) {
+          if constexpr (kI8) {
+            const uint32_t code = nr.v[i * D + 64 * (a >> 1) + 32 * (c >> 4) + 16 * (a & 1) + (c & 15)];
+            const int word = 2 * (a & 1) + (j >> 2), sh = 8 * (j & 3);
+            u32x4& ch = r.v[2 * (a >> 1) + s];
+            ch[word] = (ch[word] & ~(0xFFu << sh)) | (code << sh);
+          } else {
+            const uint32_t val = *(const uint16_t*)&nr.v[2 * (i * D + 32 * a + c)];
+            u32x4& ch = r.v[2 * a + s];
+            ch[j >> 1] = (j & 1) ? (ch[j >> 1] & 0x0000FFFFu) | (val << 16) : (ch[j >> 1] & 0xFFFF0000u) | val;
+          }
+        }
+      }
+    }
+}
+
+// Scores of a block (INT8: integer products times the tokens' K scales; the rows' scales follow in wide_softmax).
+template <int D, bool kI8, int NT>
+__device__ inline void wide_scores(const WideBlock<D, kI8>& r, const WideQueries<D, kI8, NT>& q, int h, const float* scales,
+                                   float (&s)[NT][16]) {
+  constexpr int n = WideBlock<D, kI8>::kChunks;
+#pragma unroll
+  for (int nt = 0; nt < NT; ++nt) {
+    if constexpr (kI8) {
+      i32x16 z = {0};
+#pragma unroll
+      for (int ks = 0; ks < n; ++ks)
+        z = __builtin_amdgcn_mfma_i32_32x32x32_i8(__builtin_bit_cast(i32x4, r.k[ks]), __builtin_bit_cast(i32x4, q.q[nt][ks]), z, 0, 0, 0);
+#pragma unroll
+      for (int x = 0; x < 4; ++x) {
+        const f32x4 ks = *(const f32x4*)&scales[score_token(4 * x, h)];
+#pragma unroll
+        for (int e = 0; e < 4; ++e) s[nt][4 * x + e] = (float)z[4 * x + e] * ks[e];
+      }
+    } else {
+      f32x16 z = {0.f};
+#pragma unroll
+      for (int ks = 0; ks < n; ++ks)
+        z = __builtin_amdgcn_mfma_f32_32x32x16_bf16(__builtin_bit_cast(bf16x8, r.k[ks]), __builtin_bit_cast(bf16x8, q.q[nt][ks]), z, 0, 0, 0);
+#pragma unroll
+      for (int i = 0; i < 16; ++i) s[nt][i] = z[i];
+    }
+  }
+}
+
+// A block that reaches beyond ctx_len: causal limits; and stale cache rows may hold anything, NaN included: they are zero in V
+// (bf16), so that 0 * garbage cannot reach the accumulator.  In place and apart from the step itself: two instances of the step,
+// with and without masks, would make the compiler merge their register tuples and spill hundreds of them.
+template <int D, bool kI8, int NT>
+__device__ inline void mask_wide(float (&s)[NT][16], WideBlock<D, kI8>& r, const WideQueries<D, kI8, NT>& q, int tok0, int n_valid, int h) {
+#pragma unroll
+  for (int nt = 0; nt < NT; ++nt)
+#pragma unroll
+    for (int i = 0; i < 16; ++i)
+      if (tok0 + score_token(i, h) > q.lim[nt]) s[nt][i] = -INFINITY;
+  if constexpr (!kI8) {
+#pragma unroll
+    for (int x = 0; x < 2; ++x)
+#pragma unroll
+      for (int wd = 0; wd < 4; ++wd) {
+        const int t_lo = tok0 + score_token(8 * x + 2 * wd, h);
+        const uint32_t keep = (t_lo < n_valid ? 0x0000FFFFu : 0u) | (t_lo + 1 < n_valid ? 0xFFFF0000u : 0u);
+#pragma unroll
+        for (int a = 0; a < D / 32; ++a) r.v[2 * a + x][wd] &= keep;
+      }
+  }
+}
+
+// Online softmax of a block: scores -> probabilities as operand B of the V product (INT8: times the tokens' V scales), running
+// maximum and sum.
+template <int D, bool kI8, int NT>
+__device__ inline void wide_softmax(const float (&s)[NT][16], const WideQueries<D, kI8, NT>& q, WideState<D, NT>& st, float abs_scale_log2,
+                                    int h, const float* scales, bf16x8 (&pf)[NT][2]) {
+#pragma unroll
+  for (int nt = 0; nt < NT; ++nt) {
+    const float scale = kI8 ? q.row_scale[nt] : abs_scale_log2;  // > 0
+    float mx = s[nt][0];
+#pragma unroll
+    for (int i = 1; i < 16; ++i) mx = fmaxf(mx, s[nt][i]);
+    mx = rows2_max(mx) * scale;
+    // the lazily moving reference maximum of block_step
+    const float m_old = st.m[nt];
+    const bool grow = mx > m_old + kMaxSlack;
+    if (__any(grow)) {
+      const float m_new = grow ? mx : m_old;
+      const float alpha = __builtin_amdgcn_exp2f(m_old - (m_new == -INFINITY ? 0.f : m_new));
+      st.l[nt] *= alpha;
+#pragma unroll
+      for (int a = 0; a < D / 32; ++a) st.acc[nt][a] *= alpha;
+      st.m[nt] = m_new;
+    }
+    const float m_use = st.m[nt] == -INFINITY ? 0.f : st.m[nt];  // rows without a visible token yet
+    float psum = 0.f;
+#pragma unroll
+    for (int x = 0; x < 4; ++x) {
+      f32x4 vs = {1.f, 1.f, 1.f, 1.f};
+      if constexpr (kI8) vs = *(const f32x4*)&scales[32 + score_token(4 * x, h)];
+#pragma unroll
+      for (int e = 0; e < 4; ++e) {
+        const int i = 4 * x + e;
+        const float pj = __builtin_amdgcn_exp2f(fmaf(s[nt][i], scale, -m_use));
+        psum += pj;
+        pf[nt][i >> 3][i & 7] = (__bf16)(kI8 ? pj * vs[e] : pj);
+      }
+    }
+    st.l[nt] += psum;
+  }
+}
+
+template <int D, bool kI8, int NT>
+__device__ inline void wide_values(const WideBlock<D, kI8>& r, const bf16x8 (&pf)[NT][2], WideState<D, NT>& st) {
+#pragma unroll
+  for (int x = 0; x < WideBlock<D, kI8>::kChunks; ++x) {
+    constexpr int kFrags = kI8 ? 2 : 1;  // d-tiles of a chunk
+#pragma unroll
+    for (int f = 0; f < kFrags; ++f) {
+      bf16x8 v;
+      if constexpr (kI8) v = __builtin_bit_cast(bf16x8, codes_to_bf16(r.v[x][2 * f], r.v[x][2 * f + 1]));
+      else v = __builtin_bit_cast(bf16x8, r.v[x]);
+#pragma unroll
+      for (int nt = 0; nt < NT; ++nt) {
+        f32x16& acc = st.acc[nt][kFrags * (x >> 1) + f];
+        acc = __builtin_amdgcn_mfma_f32_32x32x16_bf16(v, pf[nt][x & 1], acc, 0, 0, 0);
+      }
+    }
+  }
+}
+
+// Merge of a unit's partials, in their order, by the workgroup that delivered the last of them: its O and lse.  Every thread has one
+// row of a tile and D / 32 quads of head elements; up to eight partials are on their way at a time.
+struct WideJob {
+  int b, kvh, nq, w_lo, n;
+};
+
+template <int D, int NT>
+__device__ inline void merge_wide(const AttnParams& p, const WideJob& j, int wv, int lane) {
+  constexpr int kQuads = D / 32, kRoundW = 4;
+  const int c = lane & 31, h = lane >> 5, rows = j.nq * p.g;
+  const int slot0 = j.w_lo + j.b * p.Hkv + j.kvh;
+  const unsigned slot_bytes = (unsigned)p.rows_max * D * 4, ml_bytes = (unsigned)p.rows_max * 8;
+  float M[NT], L[NT];
+  f32x4 o[NT][kQuads];
+#pragma unroll
+  for (int nt = 0; nt < NT; ++nt) {
+    M[nt] = -INFINITY;
+    L[nt] = 0.f;
+#pragma unroll
+    for (int k = 0; k < kQuads; ++k) o[nt][k] = f32x4{0.f, 0.f, 0.f, 0.f};
+  }
+  for (int j0 = 0; j0 < j.n; j0 += kRoundW) {
+    const int n = min(j.n - j0, kRoundW);
+    // partials that do not exist and idle rows: beyond the buffers, answered with zeros
+    const __amdgpu_buffer_rsrc_t rs = dev_buffer(p.part_acc + (size_t)(slot0 + j0) * p.rows_max * D, (unsigned)n * slot_bytes);
+    const __amdgpu_buffer_rsrc_t rs_ml = dev_buffer(p.part_ml + (size_t)(slot0 + j0) * p.rows_max * 2, (unsigned)n * ml_bytes);
+    float2 s[NT][kRoundW];
+    f32x4 a[NT][kRoundW][kQuads];
+#pragma unroll
+    for (int x = 0; x < kRoundW; ++x)
+#pragma unroll
+      for (int nt = 0; nt < NT; ++nt) {
+        const int row = 32 * nt + c;
+        s[nt][x] = load_dev2(rs_ml, row < rows ? x * ml_bytes + 8u * row : kNoSuchOffset);
+#pragma unroll
+        for (int k = 0; k < kQuads; ++k)
+          a[nt][x][k] = load_dev4(rs, row < rows ? x * slot_bytes + 16u * (wide_quad<D>(2 * (wv + kWideWaves * k) + h, slot0 + j0 + x) * p.rows_max + row)
+                                                 : kNoSuchOffset);
+      }
+#pragma unroll
+    for (int nt = 0; nt < NT; ++nt) {
+      // a valid row has a visible token (token 0) in the first partial, so M is finite from there on
+      const float M_old = M[nt];
+#pragma unroll
+      for (int x = 0; x < kRoundW; ++x)
+        if (x < n) M[nt] = fmaxf(M[nt], s[nt][x].x);
+      const float Mf = M[nt] == -INFINITY ? 0.f : M[nt], alpha = __builtin_amdgcn_exp2f(M_old - Mf);
+      L[nt] *= alpha;
+#pragma unroll
+      for (int k = 0; k < kQuads; ++k) o[nt][k] *= alpha;
+#pragma unroll
+      for (int x = 0; x < kRoundW; ++x)
+        if (x < n) {
+          const float wgt = __builtin_amdgcn_exp2f(s[nt][x].x - Mf);
+          L[nt] = fmaf(s[nt][x].y, wgt, L[nt]);
+#pragma unroll
+          for (int k = 0; k < kQuads; ++k) o[nt][k] += a[nt][x][k] * wgt;
+        }
+    }
+  }
+#pragma unroll
+  for (int nt = 0; nt < NT; ++nt) {
+    const int row = 32 * nt + c;
+    if (row < rows) {
+      const int i = row_token(p, row), hg = row - i * p.g;
+      const size_t orow = ((size_t)j.b * p.kmax + i) * p.Hq + j.kvh * p.g + hg;
+      const float inv = __builtin_amdgcn_rcpf(L[nt]);
+#pragma unroll
+      for (int k = 0; k < kQuads; ++k) *(f32x4*)(p.O + orow * D + 4 * (2 * (wv + kWideWaves * k) + h)) = o[nt][k] * inv;
+      if (p.lse && wv == 0 && h == 0) p.lse[orow] = (M[nt] + __builtin_amdgcn_logf(L[nt])) * 0.6931471805599453f;
+    }
+  }
+}
+
+template <int D, bool kI8, int NT>
+__global__ __launch_bounds__(64 * kWideWaves, 1) void verify_attn_wide(AttnParams p) {
+  constexpr int W = kWideWaves, DT = D / 32, G = NT * DT;  // G accumulators of 16 registers; wavefront g % W collects number g
+  constexpr bool kMerge = NT == 1;  // units that several workgroups share are merged here, not by reduce_wide
+  constexpr int kBlkVec = WideGeometry<D, kI8>::kBlkVec;
+  constexpr int R = 2;  // blocks a wavefront has in its registers or on the way there (three: 1 - 2 us longer)
+  using Block = WideBlock<D, kI8>;
+  __shared__ f32x4 exchange[G][W - 1][4][64];
+  __shared__ float wave_m[W][NT][32], wave_l[W][NT][32];
+  __shared__ float scales[W][kI8 ? 64 : 1];
+  __shared__ int arrived_last[2];
+  __shared__ WideQueryRows<D, kI8, NT> q_lds;
+  __shared__ WideNewRows<D, kI8, NT> rows_lds;
+  const int tid = threadIdx.x, lane = tid & 63, wv = uniform(tid >> 6);
+  const int c = lane & 31, h = lane >> 5;
+  const int wg = blockIdx.x;  // the stretch of this workgroup
+  const bool fused = p.Knew != nullptr;
+
+  const ShareRecord* rec = p.records + wg;
+  Segment seg = load_segment(&rec->seg[0]);
+  const int nseg = uniform(rec->nseg), overflow = uniform(rec->overflow), rec_flags = uniform(rec->flags);
+  if (!record_matches(p, rec)) {
+    report_mismatch(p, wg == 0 && tid == 0);
+    return;
+  }
+  if (kMerge && (rec_flags & kRecAnyInactive)) zero_unused_rows<D, true>(p, wg * W + wv, gridDim.x * W, lane);
+  if (nseg == 0) return;
+
+  const uint4* kc = (const uint4*)p.Kc;
+  const uint4* vc = (const uint4*)p.Vc;
+  const float abs_scale = p.scale_log2 == 0.f ? 1.f : fabsf(p.scale_log2);
+  const int k_lane = wide_k_lane(c, h, WideGeometry<D, kI8>::kTileVec), v_lane = wide_v_lane(c, h);
+  // The wavefronts take the stretch's blocks in turn: this one's t-th block of the segment at hand is block turn + W t.  All fetches
+  // are unconditional (exact wait counts); one past the end goes through a buffer descriptor of size zero and touches nothing.
+  int turn = wv;
+  auto block_buffer = [&](const uint4* cache, const Segment& g, int t) {
+    const int x = turn + W * t;
+    const uint4* at = cache + (((ptrdiff_t)g.b * p.Hkv + g.kvh) * p.nblk_cap + g.first + x) * kBlkVec;
+    return dev_buffer((const float*)at, x < g.n ? 16u * kBlkVec : 0u);
+  };
+  auto fetch_k = [&](Block& r, const Segment& g, int t) {
+    const __amdgpu_buffer_rsrc_t at = block_buffer(kc, g, t);
+#pragma unroll
+    for (int x = 0; x < Block::kChunks; ++x) r.k[x] = __builtin_amdgcn_raw_buffer_load_b128(at, 16 * k_lane, 16 * wide_k_step(x), kAuxNonTemporal);
+    if constexpr (kI8) {
+      const int x = turn + W * t;
+      const ptrdiff_t off = (((ptrdiff_t)g.b * p.Hkv + g.kvh) * p.nblk_cap + g.first + (x < g.n ? x : 0)) * kBlkVec;
+      r.scale = ((const float*)((h ? vc : kc) + off + 2 * D))[c];
+    }
+  };
+  auto fetch_v = [&](Block& r, const Segment& g, int t) {
+    const __amdgpu_buffer_rsrc_t at = block_buffer(vc, g, t);
+#pragma unroll
+    for (int x = 0; x < Block::kChunks; ++x) r.v[x] = __builtin_amdgcn_raw_buffer_load_b128(at, 16 * v_lane, 16 * wide_v_step(x), kAuxNonTemporal);
+  };
+
+  // Fused append: the new rows whose blocks are ours go into LDS and into the cache (nothing but the new rows is written: other
+  // appends may write other tokens of the same blocks), 8 elements of a row per lane.  The first pass is requested ahead of the
+  // first blocks; all conditions are workgroup-uniform.
+  auto first_new_row = [&](const Segment& g) { return max(0, g.first * kBlockTokens - g.L); };
+  auto new_rows_of = [&](const Segment& g) { return min(g.nq, (g.first + g.n) * kBlockTokens - g.L) - first_new_row(g); };
+  u32x4 new_k = {0u, 0u, 0u, 0u}, new_v = new_k;
+  auto request_rows = [&](const Segment& g, int c0) {
+    const int x = min(c0 + tid, new_rows_of(g) * (D / 8) - 1);  // whole rows, also past the end
+    const int i = first_new_row(g) + x / (D / 8);
+    const size_t src = (((size_t)g.b * p.kmax + i) * p.Hkv + g.kvh) * D + 8 * (tid % (D / 8));
+    new_k = *(const u32x4*)((const uint16_t*)p.Knew + src);
+    new_v = *(const u32x4*)((const uint16_t*)p.Vnew + src);
+  };
+  auto commit_rows = [&](const Segment& g, int c0) {
+    WideNewRows<D, kI8, NT>& nr = rows_lds;
+    const int n_ck = new_rows_of(g) * (D / 8), x = min(c0 + tid, n_ck - 1);
+    const int ck = tid % (D / 8), i = first_new_row(g) + x / (D / 8);
+    const int blk = (g.L + i) / kBlockTokens, tw = (g.L + i) % kBlockTokens;
+    const uint4 kv = __builtin_bit_cast(uint4, new_k), vv = __builtin_bit_cast(uint4, new_v);
+    const size_t at = (((size_t)g.b * p.Hkv + g.kvh) * p.nblk_cap + blk) * (size_t)kBlkVec * 16;
+    uint8_t* kblk = (uint8_t*)const_cast<void*>(p.Kc) + at;
+    uint8_t* vblk = (uint8_t*)const_cast<void*>(p.Vc) + at;
+    if constexpr (kI8) {  // quantized as the append kernel does: a row's D / 8 lanes agree on its largest magnitude
+      float ka = amax8(kv), va = amax8(vv);
+#pragma unroll
+      for (int o = D / 16; o >= 1; o >>= 1) {
+        ka = fmaxf(ka, __shfl_xor(ka, o));
+        va = fmaxf(va, __shfl_xor(va, o));
+      }
+      const float kinv = ka > 0.f ? 127.0f / ka : 0.f;
+      const float vinv = va > 0.f ? 127.0f / va : 0.f;
+      if (c0 + tid < n_ck) {
+        const uint2 kq = quantize8(kv, kinv), vq = quantize8(vv, vinv);
+        *(uint2*)&nr.k[i * D + 8 * ck] = kq;
+        *(uint2*)&nr.v[i * D + 8 * ck] = vq;
+        *(uint2*)(kblk + i8_k_offset(D, tw, 8 * ck)) = kq;
+#pragma unroll
+        for (int e = 0; e < 8; ++e) vblk[i8_v_offset(D, tw, 8 * ck + e)] = (uint8_t)((e < 4 ? vq.x : vq.y) >> (8 * (e & 3)));
+        if (ck == 0) {
+          const float ks = ka / 127.0f, vs = va / 127.0f;
+          nr.k_scale[i] = ks;
+          nr.v_scale[i] = vs;
+          ((float*)(kblk + kBlockTokens * D))[tw] = ks;
+          ((float*)(vblk + kBlockTokens * D))[tw] = vs;
+        }
+      }
+    } else if (c0 + tid < n_ck) {
+      *(uint4*)&nr.k[2 * (i * D + 8 * ck)] = kv;
+      *(uint4*)&nr.v[2 * (i * D + 8 * ck)] = vv;
+      *(uint4*)(kblk + 2 * k_elem_offset(D, tw, 8 * ck)) = kv;
+      const uint32_t vw[4] = {vv.x, vv.y, vv.z, vv.w};
+#pragma unroll
+      for (int e = 0; e < 8; ++e) ((uint16_t*)vblk)[v_elem_offset(D, tw, 8 * ck + e)] = (uint16_t)(vw[e >> 1] >> (16 * (e & 1)));
+    }
+  };
+
+  Block ring[R];
+  u32x4 raw_q[WideQueryRows<D, kI8, NT>::kLoads];
+  auto request_queries = [&](const Segment& g) {  // rows that do not exist read row 0
+    const int rows = g.nq * p.g;
+#pragma unroll
+    for (int x = 0; x < WideQueryRows<D, kI8, NT>::kLoads; ++x) {
+      const int at = x * 64 * W + tid, row = at / (D / 8) < rows ? at / (D / 8) : 0, ck = at % (D / 8);
+      const int i = row_token(p, row), hg = row - i * p.g;
+      raw_q[x] = ((const u32x4*)((const uint16_t*)p.Q + (((size_t)g.b * p.kmax + i) * p.Hq + g.kvh * p.g + hg) * D))[ck];
+    }
+  };
+  auto begin = [&](const Segment& g) {
+    fetch_k(ring[0], g, 0);
+    request_queries(g);
+    if (fused && new_rows_of(g) > 0) request_rows(g, 0);
+    fetch_v(ring[0], g, 0);
+#pragma unroll
+    for (int x = 1; x < R; ++x) {
+      fetch_k(ring[x], g, x);
+      fetch_v(ring[x], g, x);
+    }
+  };
+  WideJob job_a{}, job_b{};  // units that others contribute to
+  int shared = 0;
+  begin(seg);
+  for (int si = 0;; ++si) {
+    const Unit u = unit_of(seg);
+    const int rows = u.nq * p.g, tiles = (rows + 31) / 32;
+    const int first_mine = turn, n_mine = (seg.n - turn + W - 1) / W;  // 0 for n <= turn
+    commit_wide_queries<D, kI8, NT>(p, u, tid, raw_q, q_lds);
+    if (fused && new_rows_of(seg) > 0) {
+      commit_rows(seg, 0);
+      for (int c0 = 64 * W; c0 < new_rows_of(seg) * (D / 8); c0 += 64 * W) {
+        request_rows(seg, c0);
+        commit_rows(seg, c0);
+      }
+    }
+    __syncthreads();
+    WideQueries<D, kI8, NT> q;
+    read_wide_queries<D, kI8, NT>(p, u, c, h, q_lds, q);
+    WideState<D, NT> st;
+#pragma unroll
+    for (int nt = 0; nt < NT; ++nt) {
+      st.m[nt] = -INFINITY;
+      st.l[nt] = 0.f;
+#pragma unroll
+      for (int a = 0; a < DT; ++a)
+#pragma unroll
+        for (int i = 0; i < 16; ++i) st.acc[nt][a][i] = 0.f;
+    }
+    auto step = [&](Block& r, int t) {
+      const int tok0 = (seg.first + first_mine + W * t) * kBlockTokens;
+      // every token of the block is visible to every query and, with a fused append, none of them is new
+      const bool plain = tok0 + kBlockTokens - 1 < u.L + (fused ? 0 : 1);
+      if (fused && !plain) patch_wide<D, kI8, NT>(r, tok0, u.L, u.nq, lane, rows_lds);
+      float* sc = scales[wv];
+      if constexpr (kI8) {
+        sc[lane] = (h && tok0 + c >= u.L + u.nq) ? 0.f : r.scale;  // stale tokens may carry any V scale
+        __builtin_amdgcn_wave_barrier();  // a wavefront's LDS accesses stay in order
+      }
+      float s[NT][16];
+      wide_scores<D, kI8, NT>(r, q, h, sc, s);
+      fetch_k(r, seg, t + R);
+      if (!plain) mask_wide<D, kI8, NT>(s, r, q, tok0, u.L + u.nq, h);
+      bf16x8 pf[NT][2];
+      wide_softmax<D, kI8, NT>(s, q, st, abs_scale, h, sc, pf);
+      if constexpr (kI8) __builtin_amdgcn_wave_barrier();
+      wide_values<D, kI8, NT>(r, pf, st);
+      fetch_v(r, seg, t + R);
+    };
+    for (int t = 0; t < n_mine; t += R) {
+#pragma unroll
+      for (int x = 0; x < R; ++x) {
+        if (x > 0 && t + x >= n_mine) break;
+        step(ring[x], t + x);
+      }
+    }
+
+    // the next segment's queries and first blocks travel while this one's states are merged
+    const bool more = si + 1 < nseg;
+    const Segment done = seg;
+    if (more) {
+      turn = (first_mine - seg.n) & (W - 1);
+      seg = later_segment(p, rec, overflow, si + 1);
+      begin(seg);
+    }
+
+    // merge of the four wavefronts' states: M = max m_w, weights 2^(m_w - M) (a wavefront that saw no visible token has m = -inf
+    // and weight 0)
+#pragma unroll
+    for (int nt = 0; nt < NT; ++nt) {
+      const float l = rows2_sum(st.l[nt]);
+      if (h == 0) {
+        wave_m[wv][nt][c] = st.m[nt];
+        wave_l[wv][nt][c] = l;
+      }
+    }
+    __syncthreads();
+    float M[NT], sum[NT], mine[NT];
+#pragma unroll
+    for (int nt = 0; nt < NT; ++nt) {
+      M[nt] = -INFINITY;
+      sum[nt] = 0.f;
+#pragma unroll
+      for (int w = 0; w < W; ++w) M[nt] = fmaxf(M[nt], wave_m[w][nt][c]);
+      const float Mf = M[nt] == -INFINITY ? 0.f : M[nt];
+#pragma unroll
+      for (int w = 0; w < W; ++w) sum[nt] += wave_l[w][nt][c] * __builtin_amdgcn_exp2f(wave_m[w][nt][c] - Mf);
+      mine[nt] = __builtin_amdgcn_exp2f(st.m[nt] - Mf);
+    }
+#pragma unroll
+    for (int g = 0; g < G; ++g) {
+      const int nt = g / DT, a = g % DT, owner = g % W;
+      if (nt > 0 && nt >= tiles) break;
+      st.acc[nt][a] *= mine[nt];
+      if (wv != owner) {
+#pragma unroll
+        for (int x = 0; x < 4; ++x)
+          exchange[g][wv < owner ? wv : wv - 1][x][lane] = f32x4{st.acc[nt][a][4 * x], st.acc[nt][a][4 * x + 1], st.acc[nt][a][4 * x + 2], st.acc[nt][a][4 * x + 3]};
+      }
+    }
+    __syncthreads();
+    const bool solo = kMerge && seg_w_lo(done) == seg_w_hi(done);
+    const size_t slot = (size_t)wg + (size_t)done.b * p.Hkv + done.kvh;
+    const __amdgpu_buffer_rsrc_t rs = dev_buffer(p.part_acc + slot * p.rows_max * D, (unsigned)p.rows_max * D * 4);
+#pragma unroll
+    for (int g = 0; g < G; ++g) {
+      const int nt = g / DT, a = g % DT;
+      if (wv != g % W) continue;
+      if (nt > 0 && nt >= tiles) break;
+      const int rrow = 32 * nt + c, i = row_token(p, rrow), hg = rrow - i * p.g;
+      const size_t orow = ((size_t)done.b * p.kmax + i) * p.Hq + done.kvh * p.g + hg;
+      const float inv = __builtin_amdgcn_rcpf(sum[nt]);
+      f32x4 v[4];
+#pragma unroll
+      for (int x = 0; x < 4; ++x) {
+        v[x] = f32x4{st.acc[nt][a][4 * x], st.acc[nt][a][4 * x + 1], st.acc[nt][a][4 * x + 2], st.acc[nt][a][4 * x + 3]};
+#pragma unroll
+        for (int w = 0; w < W; ++w)
+          if (w != g % W) v[x] += exchange[g][w < g % W ? w : w - 1][x][lane];
+      }
+      if (rrow < rows) {
+        if (solo) {
+#pragma unroll
+          for (int x = 0; x < 4; ++x) *(f32x4*)(p.O + orow * D + wide_elem<kI8>(a, x, h)) = v[x] * inv;
+        } else {
+#pragma unroll
+          for (int x = 0; x < 4; ++x) store_dev4(rs, (unsigned)(wide_quad<D>(wide_elem<kI8>(a, x, h) / 4, (int)slot) * p.rows_max + rrow) * 16, v[x]);
+        }
+      }
+      if (a == 0 && h == 0 && rrow < rows) {
+        if (!solo) store_dev(p.part_ml + (slot * p.rows_max + rrow) * 2, M[nt], sum[nt]);
+        else if (p.lse) p.lse[orow] = (M[nt] + __builtin_amdgcn_logf(sum[nt])) * 0.6931471805599453f;
+      }
+    }
+    if (kMerge && (done.flags & kSegLast)) {  // query slots beyond draft_len are zero in O and lse
+      for (int x = tid; x < (p.rows_max - rows) * (D / 4); x += 64 * W) {
+        const int row = rows + x / (D / 4), i = row_token(p, row), hg = row - i * p.g;
+        const size_t orow = ((size_t)done.b * p.kmax + i) * p.Hq + done.kvh * p.g + hg;
+        *(f32x4*)(p.O + orow * D + 4 * (x % (D / 4))) = f32x4{0.f, 0.f, 0.f, 0.f};
+        if (p.lse && x % (D / 4) == 0) p.lse[orow] = 0.f;
+      }
+    }
+    if (kMerge && !solo) {  // a stretch's first and last unit at most
+      const WideJob job{done.b, done.kvh, done.nq, seg_w_lo(done), seg_w_hi(done) - seg_w_lo(done) + 1};
+      if (shared == 0) job_a = job;
+      job_b = job;
+      ++shared;
+    }
+    if (!more) break;
+  }
+
+  // Delivery: this workgroup's partials have reached the device-coherent level once every wavefront's stores are acknowledged; only
+  // then is its arrival counted, and who counts last merges (the ordering of the one-tile kernel's partials).
+  if (!kMerge || shared == 0) return;
+  partial_stores_done();
+  __syncthreads();
+  if (tid < shared) {
+    int32_t* counter = p.counters + (tid == 0 ? job_a.b * p.Hkv + job_a.kvh : job_b.b * p.Hkv + job_b.kvh);
+    const bool last = __hip_atomic_fetch_add(counter, 1, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT) == (tid == 0 ? job_a.n : job_b.n) - 1;
+    if (last) __hip_atomic_store(counter, 0, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);  // clean for the next call
+    arrived_last[tid] = last;
+  }
+  __syncthreads();
+  if (uniform(arrived_last[0])) merge_wide<D, NT>(p, job_a, wv, lane);
+  if (shared > 1 && uniform(arrived_last[1])) merge_wide<D, NT>(p, job_b, wv, lane);
+}
+
+// ---------------------------------------------------------------------------------------
+// Short caches (launch_shape), more than 32 query rows: a workgroup with a wavefront (bf16: two) per 16-row tile.  With few blocks per
+// unit what counts is the time of one block and of the way out: four wavefronts share a block's rows here, and no states of several
+// tiles have to be merged at the end.
+// bf16: every K/V block is fetched from memory once (each wavefront a part of it), put into a ring in LDS, two blocks per phase, and
+// read from there by the wavefronts that own a query tile (rows 16 t .. 16 t + 15), one for the even and one for the odd blocks,
+// whose states are merged through LDS at the end of the unit.  One barrier per phase: a slot is rewritten only after the barrier that
+// follows the last step that read it.  Every barrier sits in workgroup-uniform control flow (the stretch, the units and the block
+// counts depend on the workgroup index and the lengths only).
+// ---------------------------------------------------------------------------------------
+// Partial of a 16-row tile in the layout of reduce_wide.
+template <int D>
+__device__ inline void store_partial_quads(const AttnParams& p, const Unit& u, int w, const RowState<D>& st, int col, int grp, int row0) {
+  const int rrow = row0 + col;
+  const size_t slot = (size_t)w + (size_t)u.b * p.Hkv + u.kvh;
+  const __amdgpu_buffer_rsrc_t rs = dev_buffer(p.part_acc + slot * p.rows_max * D, (unsigned)p.rows_max * D * 4);
+  const float l = rows4_sum(st.l);
+  if (rrow < u.nq * p.g) {
+#pragma unroll
+    for (int mt = 0; mt < D / 16; ++mt) store_dev4(rs, (unsigned)(wide_quad<D>(4 * mt + grp, (int)slot) * p.rows_max + rrow) * 16, st.acc[mt]);
+    if (grp == 0) store_dev(p.part_ml + (slot * p.rows_max + rrow) * 2, st.m, l);
+  }
+}
+
 // Two wavefronts per tile: the state of the odd blocks joins that of the even ones (one that saw no visible token has
 // m = -inf and no weight).  All wavefronts call; a stretch of one block has nothing to join.  acc: LDS for TW tiles' accumulators.
 template <int D, int TW>
@@ -1307,16 +1981,16 @@ __device__ inline void merge_halves(RowState<D>& st, int n, int half, int tile, 
   }
 }
 
-template <int D, bool kFused, int TW, int H>
-__global__ __launch_bounds__(64 * TW * H, 2) void verify_attn_tiles_bf16(AttnParams p) {
-  constexpr int kThreads = 64 * TW * H;
-  constexpr int kTileAhead = H == 2 ? 2 : 3;          // phases a workgroup has in flight from memory
+template <int D, bool kFused>
+__global__ __launch_bounds__(512, 2) void verify_attn_tiles_bf16(AttnParams p) {
+  constexpr int TW = 4, H = 2, kThreads = 64 * TW * H;
+  constexpr int kTileAhead = 2;                       // phases a workgroup has in flight from memory
   constexpr int kBlkVec = kBlockTokens * D * 2 / 16;  // uint4 per block and tensor
   constexpr int kPhase = H * kBlkVec;                  // ... and per phase (a unit's blocks lie one after the other)
   constexpr int kLoads = kPhase / kThreads;            // 16-byte loads per lane, phase and tensor
   __shared__ uint4 ring_k[2][kPhase];
   __shared__ uint4 ring_v[2][kPhase];
-  __shared__ float other_m[H == 2 ? TW : 1][64], other_l[H == 2 ? TW : 1][64];  // states of the odd blocks' wavefronts (accumulators: in ring_k)
+  __shared__ float other_m[TW][64], other_l[TW][64];  // states of the odd blocks' wavefronts (accumulators: in ring_k)
   const int tid = threadIdx.x, lane = tid & 63, wv = tid >> 6;
   const int tile = wv % TW, half = wv / TW;
   const int col = lane & 15, grp = lane >> 4;
@@ -1353,7 +2027,7 @@ __global__ __launch_bounds__(64 * TW * H, 2) void verify_attn_tiles_bf16(AttnPar
     auto fetch = [&](Stage& g, int ph) {
 #pragma unroll
       for (int i = 0; i < kLoads; ++i) {
-        const int c = i * kThreads + tid, h = H == 1 ? 0 : i * kThreads / kBlkVec + (tid >= kBlkVec ? 1 : 0);
+        const int c = i * kThreads + tid, h = i * kThreads / kBlkVec + (tid >= kBlkVec ? 1 : 0);
         const ptrdiff_t off = vec0 + (H * ph + h < n ? (ptrdiff_t)ph * kPhase + c : (ptrdiff_t)(c - h * kBlkVec));
         g.k[i] = __builtin_bit_cast(uint4, __builtin_nontemporal_load((const u32x4*)(kc + off)));
         g.v[i] = __builtin_bit_cast(uint4, __builtin_nontemporal_load((const u32x4*)(vc + off)));
@@ -1423,39 +2097,27 @@ __global__ __launch_bounds__(64 * TW * H, 2) void verify_attn_tiles_bf16(AttnPar
 #pragma unroll
       for (int j = 0; j < kTileAhead; ++j) phase(g[j], ph + j);
     }
-    if constexpr (H == 2) merge_halves<D, TW>(st, n, half, tile, active, lane, (f32x4*)&ring_k[0][0], other_m, other_l);
-    if (half == 0 && active) store_partial<D>(p, u, wg, st, col, grp, row0);
+    merge_halves<D, TW>(st, n, half, tile, active, lane, (f32x4*)&ring_k[0][0], other_m, other_l);
+    if (half == 0 && active) store_partial_quads<D>(p, u, wg, st, col, grp, row0);
   }
 }
 
-// ---------------------------------------------------------------------------------------
-// The same for INT8 caches.  A block's codes and scales are fetched once by the workgroup; the wavefront that fetched a
-// V chunk widens it to bf16 on its way into LDS, so that every code is widened once per block instead of once per
-// query tile, and no wavefront holds more than one tile.  (Up to four tiles in one wavefront spilled registers and left
-// one wavefront per SIMD: what bounds these shapes is instruction issue, not memory.  Attention of 16 sequences of 1024 -
-// 4096 tokens, 64/8 heads of 128, 64 rows per kv head, with its merge: 72 -> 48 us per layer, 94 MB.)
-// Four wavefronts: H = 1, TW = 4, one block per phase; with at most two tiles H = 2, TW = 2, two wavefronts per tile, as above,
-// which take S blocks each per phase.
-// ---------------------------------------------------------------------------------------
-template <int D, bool kFused, int TW, int H, int S>
+// The same for INT8 caches, one block per phase: the wavefront that fetched a V chunk widens it to bf16 on its way into LDS, so that
+// every code is widened once per block.
+template <int D, bool kFused>
 __global__ __launch_bounds__(256, 2) void verify_attn_tiles_i8(AttnParams p) {
-  static_assert(TW * H == 4, "four wavefronts");
-  constexpr int P = H * S;                    // blocks per phase
-  constexpr int kAhead = P <= 2 ? 4 / P : 2;  // phases a workgroup has in flight from memory
+  constexpr int kAhead = 4;                   // blocks a workgroup has in flight from memory
   constexpr int kCodeVec = 2 * D;             // uint4 of codes per block and tensor
   constexpr int kBlkVec = kCodeVec + 8;       // ... and its 32 scales
   constexpr int kChunks = D / 32;             // 64-lane chunks of codes per tensor
   constexpr int kMoves = 2 * kChunks / 4;     // chunks a wavefront moves per block: numbers wv, wv + 4, ... of K's, then V's
-  constexpr int kLoads = P * kMoves;          // ... and per phase
-  __shared__ uint4 ring_k[2][P * kCodeVec];      // codes
-  __shared__ uint4 ring_v[2][P * 2 * kCodeVec];  // the codes as bf16, fragments as in a bf16 cache
-  __shared__ __align__(16) float ring_s[2][P * 2 * kBlockTokens];  // K scales, V scales of each block
-  __shared__ float other_m[H == 2 ? TW : 1][64], other_l[H == 2 ? TW : 1][64];  // as in the bf16 kernel (accumulators: in ring_v)
+    __shared__ uint4 ring_k[2][kCodeVec];      // codes
+  __shared__ uint4 ring_v[2][2 * kCodeVec];  // the codes as bf16, fragments as in a bf16 cache
+  __shared__ __align__(16) float ring_s[2][2 * kBlockTokens];  // K scales, V scales of each block
   const int lane = threadIdx.x & 63, wv = uniform(threadIdx.x >> 6);
   const int col = lane & 15, grp = lane >> 4;
   const int wg = blockIdx.x;
-  const int tile = wv % TW, half = wv / TW;
-  const int row0 = 16 * tile;
+  const int row0 = 16 * wv;  // the query tile of this wavefront
 
   const ShareRecord* rec = p.records + wg;
   const int nseg = uniform(rec->nseg), overflow = uniform(rec->overflow);
@@ -1467,7 +2129,7 @@ __global__ __launch_bounds__(256, 2) void verify_attn_tiles_i8(AttnParams p) {
   const uint4* kc = (const uint4*)p.Kc;
   const uint4* vc = (const uint4*)p.Vc;
   struct Stage {
-    u32x4 c[kLoads];
+    u32x4 c[kMoves];
     float scale;
   };
 
@@ -1487,40 +2149,40 @@ __global__ __launch_bounds__(256, 2) void verify_attn_tiles_i8(AttnParams p) {
     auto block_at = [&](int s) { return vec0 + (s < n ? (ptrdiff_t)s * kBlkVec : 0); };
     auto fetch = [&](Stage& g, int ph) {
 #pragma unroll
-      for (int i = 0; i < kLoads; ++i) {
-        const ptrdiff_t off = block_at(P * ph + i / kMoves);
-        const int c = wv + 4 * (i % kMoves);
+      for (int i = 0; i < kMoves; ++i) {
+        const ptrdiff_t off = block_at(ph);
+        const int c = wv + 4 * i;
         const uint4* src = (c < kChunks ? kc + off + c * 64 : vc + off + (c - kChunks) * 64) + lane;
         g.c[i] = __builtin_nontemporal_load((const u32x4*)src);
       }
-      const ptrdiff_t at = block_at(P * ph + wv % P);
+      const ptrdiff_t at = block_at(ph);
       g.scale = ((const float*)((lane < kBlockTokens ? kc : vc) + at + kCodeVec))[lane % kBlockTokens];
     };
     auto phase = [&](Stage& g, int ph) {
       const int slot = ph & 1;
 #pragma unroll
-      for (int i = 0; i < kLoads; ++i) {
-        const int h = i / kMoves, c = wv + 4 * (i % kMoves);
+      for (int i = 0; i < kMoves; ++i) {
+        const int c = wv + 4 * i;
         if (c < kChunks) {
-          ring_k[slot][h * kCodeVec + c * 64 + lane] = __builtin_bit_cast(uint4, g.c[i]);
+          ring_k[slot][c * 64 + lane] = __builtin_bit_cast(uint4, g.c[i]);
         } else {
           const int m = c - kChunks;
-          ring_v[slot][h * 2 * kCodeVec + (2 * m) * 64 + lane] = codes_to_bf16(g.c[i][0], g.c[i][1]);
-          ring_v[slot][h * 2 * kCodeVec + (2 * m + 1) * 64 + lane] = codes_to_bf16(g.c[i][2], g.c[i][3]);
+          ring_v[slot][(2 * m) * 64 + lane] = codes_to_bf16(g.c[i][0], g.c[i][1]);
+          ring_v[slot][(2 * m + 1) * 64 + lane] = codes_to_bf16(g.c[i][2], g.c[i][3]);
         }
       }
-      if (wv < P) ring_s[slot][wv * 64 + lane] = g.scale;
+      if (wv == 0) ring_s[slot][lane] = g.scale;
       fetch(g, ph + kAhead);
       // Fused append: as in the bf16 kernel; the rows are quantized as the append kernel does (a row's D / 8 lanes agree
       // on its largest magnitude), codes and scales go into LDS and into the cache.
-      const int tok0 = (blk0 + P * ph) * kBlockTokens, tok1 = (blk0 + min(P * ph + P, n)) * kBlockTokens;
+      const int tok0 = (blk0 + ph) * kBlockTokens, tok1 = (blk0 + min(ph + 1, n)) * kBlockTokens;
       if (kFused && u.nq > 0 && tok0 < min(u.L + u.nq, tok1) && tok1 > u.L) {
         __syncthreads();  // the blocks are complete in LDS
         const int i_lo = max(0, tok0 - u.L), n_ck = (min(u.nq, tok1 - u.L) - i_lo) * (D / 8);
-        for (int c0 = 0; c0 < n_ck; c0 += 256) {  // the new rows of these blocks, 8 elements per lane
+        for (int c0 = 0; c0 < n_ck; c0 += 256) {  // the new rows of this block, 8 elements per lane
           const int c = min(c0 + (int)threadIdx.x, n_ck - 1);  // whole rows: a row's lanes stay together past the end too
           const int ck = threadIdx.x % (D / 8), i = i_lo + c / (D / 8);
-          const int t = u.L + i - tok0, h = t / kBlockTokens, tw = t % kBlockTokens;  // its token slot in the phase's blocks
+          const int tw = u.L + i - tok0;  // its token slot in the block
           const size_t src = (((size_t)u.b * p.kmax + i) * p.Hkv + u.kvh) * D + 8 * ck;
           const uint4 kv = *(const uint4*)((const uint16_t*)p.Knew + src);
           const uint4 vv = *(const uint4*)((const uint16_t*)p.Vnew + src);
@@ -1534,22 +2196,22 @@ __global__ __launch_bounds__(256, 2) void verify_attn_tiles_i8(AttnParams p) {
           const float vinv = va > 0.f ? 127.0f / va : 0.f;
           if (c0 + (int)threadIdx.x < n_ck) {
             const uint2 kq = quantize8(kv, kinv), vq = quantize8(vv, vinv);
-            uint8_t* kblk = (uint8_t*)((uint4*)const_cast<void*>(p.Kc) + vec0 + (ptrdiff_t)(P * ph + h) * kBlkVec);
-            uint8_t* vblk = (uint8_t*)((uint4*)const_cast<void*>(p.Vc) + vec0 + (ptrdiff_t)(P * ph + h) * kBlkVec);
+            uint8_t* kblk = (uint8_t*)((uint4*)const_cast<void*>(p.Kc) + vec0 + (ptrdiff_t)ph * kBlkVec);
+            uint8_t* vblk = (uint8_t*)((uint4*)const_cast<void*>(p.Vc) + vec0 + (ptrdiff_t)ph * kBlkVec);
             const size_t ko = i8_k_offset(D, tw, 8 * ck);
-            *(uint2*)((uint8_t*)&ring_k[slot][h * kCodeVec] + ko) = kq;
+            *(uint2*)((uint8_t*)&ring_k[slot][0] + ko) = kq;
             *(uint2*)(kblk + ko) = kq;
             const uint4 vb = codes_to_bf16(vq.x, vq.y);
             const uint32_t vw[4] = {vb.x, vb.y, vb.z, vb.w};
 #pragma unroll
             for (int e = 0; e < 8; ++e) {
-              ((uint16_t*)&ring_v[slot][h * 2 * kCodeVec])[v_elem_offset(D, tw, 8 * ck + e)] = (uint16_t)(vw[e >> 1] >> (16 * (e & 1)));
+              ((uint16_t*)&ring_v[slot][0])[v_elem_offset(D, tw, 8 * ck + e)] = (uint16_t)(vw[e >> 1] >> (16 * (e & 1)));
               vblk[i8_v_offset(D, tw, 8 * ck + e)] = (uint8_t)((e < 4 ? vq.x : vq.y) >> (8 * (e & 3)));
             }
             if (ck == 0) {
               const float ks = ka / 127.0f, vs = va / 127.0f;
-              ring_s[slot][h * 64 + tw] = ks;
-              ring_s[slot][h * 64 + kBlockTokens + tw] = vs;
+              ring_s[slot][tw] = ks;
+              ring_s[slot][kBlockTokens + tw] = vs;
               ((float*)(kblk + kBlockTokens * D))[tw] = ks;
               ((float*)(vblk + kBlockTokens * D))[tw] = vs;
             }
@@ -1559,21 +2221,18 @@ __global__ __launch_bounds__(256, 2) void verify_attn_tiles_i8(AttnParams p) {
       } else {
         __syncthreads();
       }
-#pragma unroll
-      for (int j0 = 0; j0 < S; ++j0) {
-        const int bl = half + H * j0;
-        if (!active || P * ph + bl >= n) break;
+      if (active && ph < n) {
         KvRegs<D> r;
         u32x4 k[kChunks];
         TokenScales sc;
 #pragma unroll
-        for (int i = 0; i < kChunks; ++i) k[i] = __builtin_bit_cast(u32x4, ring_k[slot][bl * kCodeVec + i * 64 + lane]);
+        for (int i = 0; i < kChunks; ++i) k[i] = __builtin_bit_cast(u32x4, ring_k[slot][i * 64 + lane]);
 #pragma unroll
-        for (int i = 0; i < D / 16; ++i) r.v[i] = ring_v[slot][bl * 2 * kCodeVec + i * 64 + lane];
+        for (int i = 0; i < D / 16; ++i) r.v[i] = ring_v[slot][i * 64 + lane];
 #pragma unroll
         for (int h = 0; h < 2; ++h) {
-          const f32x4 ks = *(const f32x4*)&ring_s[slot][bl * 64 + 16 * h + 4 * grp];
-          const f32x4 vs = *(const f32x4*)&ring_s[slot][bl * 64 + kBlockTokens + 16 * h + 4 * grp];
+          const f32x4 ks = *(const f32x4*)&ring_s[slot][16 * h + 4 * grp];
+          const f32x4 vs = *(const f32x4*)&ring_s[slot][kBlockTokens + 16 * h + 4 * grp];
 #pragma unroll
           for (int j = 0; j < 4; ++j) {
             sc.k[4 * h + j] = ks[j];
@@ -1581,46 +2240,103 @@ __global__ __launch_bounds__(256, 2) void verify_attn_tiles_i8(AttnParams p) {
           }
         }
         const I8Operands<D> i8{k, q.q, q.q_scale_log2, &sc};
-        block_dispatch<D, true>(r, nullptr, st, blk0 + P * ph + bl, u.L, u.L + u.nq, q.lim, p.scale_log2, lane, false, NewRows{}, nullptr,
+        block_dispatch<D, true>(r, nullptr, st, blk0 + ph, u.L, u.L + u.nq, q.lim, p.scale_log2, lane, false, NewRows{}, nullptr,
                                    nullptr, &i8);
       }
     };
-    __syncthreads();  // the previous unit's last step (merge) has left the ring
+    __syncthreads();  // the previous unit's last step has left the ring
     Stage g[kAhead];
 #pragma unroll
     for (int j = 0; j < kAhead; ++j) fetch(g[j], j);
-    for (int ph = 0; P * ph < n; ph += kAhead) {  // workgroup-uniform trip count
+    for (int ph = 0; ph < n; ph += kAhead) {  // workgroup-uniform trip count
 #pragma unroll
       for (int j = 0; j < kAhead; ++j) phase(g[j], ph + j);
     }
-    if constexpr (H == 2) merge_halves<D, TW>(st, n, half, tile, active, lane, (f32x4*)&ring_v[0][0], other_m, other_l);
-    if (half == 0 && active) store_partial<D>(p, u, wg, st, col, grp, row0);
+    if (active) store_partial_quads<D>(p, u, wg, st, col, grp, row0);
   }
 }
 
 // ---------------------------------------------------------------------------------------
-// Split-context reduction as a launch of its own, used when a kv head has many query rows
-// (grouped-query attention): a unit's partials are then tens of KiB per contributor, too much
-// for the one wavefront that happens to arrive last, so the rows are spread over the whole chip:
-// one wavefront per (unit, sweep of 4 rows).
+// Split-context reduction as a launch of its own, used with more than 32 query rows: a unit's partials are then tens of KiB per
+// contributor, too much for the one workgroup that happens to arrive last, so they are spread over the whole chip.  A partial's
+// accumulators lie as [head element / 4, rotated][row][4].  A wavefront takes 16 rows: of four quads (kParts = 1), or of one, lanes l, l + 16,
+// l + 32 and l + 48 every fourth of its partials, so that up to sixteen are on their way at a time.  The latter with few units, which
+// have many partials and leave the chip empty otherwise: attention and reduction, 48 rows of 128, 16 / 64 / 128 / 256 units, kParts = 1 -> 4: 27.4
+// -> 23.2, 21.4 -> 21.2, 41.5 -> 43.3, 40.3 -> 45.7 us.
 // ---------------------------------------------------------------------------------------
-template <int KC, int DC>
-__global__ __launch_bounds__(256) void reduce_partials(AttnParams p) {
+constexpr int kReduceSplitUnits = 64;
+
+template <int D, int kParts>
+__global__ __launch_bounds__(256) void reduce_wide(AttnParams p) {
+  constexpr int kQuads = 4 / kParts, kSub = D / 4 / kQuads;  // quads of a wavefront, wavefronts per 16 rows
   const int lane = threadIdx.x & 63;
-  const int sweeps = (p.rows_max + 3) / 4;
+  const int tiles = (p.rows_max + 15) / 16;
   const long item = (long)blockIdx.x * 4 + (threadIdx.x >> 6);
-  if (item >= (long)p.B * p.Hkv * sweeps) return;
-  const int sweep = (int)(item % sweeps);
-  const int unit = (int)(item / sweeps);
-  const int b = unit / p.Hkv, kvh = unit % p.Hkv;
+  const int per_unit = tiles * kSub;
+  if (item >= (long)p.B * p.Hkv * per_unit) return;
+  const int unit = (int)(item / per_unit), sub = (int)(item - (long)unit * per_unit);
+  const int b = unit / p.Hkv, kvh = unit - b * p.Hkv;
+  const int rows = uniform(p.seq_nq[b]) * p.g, owners = uniform(p.unit_owners[unit]);  // requested together with the record
+  __builtin_amdgcn_sched_barrier(0);
   if (!record_matches(p, p.records)) return;  // reported by the attention launch
-  const int nq = uniform(p.seq_nq[b]);
-  // query slots beyond draft_len (all of them for an inactive sequence) are zero in O and lse
-  if (4 * sweep + 4 > nq * p.g) zero_rows<DC>(p, b, kvh, max(nq * p.g, 4 * sweep), lane, 4 * sweep + 4);
-  if (nq == 0 || 4 * sweep >= nq * p.g) return;
-  const int owners = uniform(p.unit_owners[unit]);
-  CombineJob job{Unit{b, kvh, uniform(p.seq_L[b]), nq}, owners & 0xFFFF, (owners >> 16) & 0xFFFF};
-  combine_sweep<KC, DC, 16, false>(p, job, 4 * sweep, lane);
+  const int row0 = 16 * (sub / kSub), row = row0 + lane % 16;
+  const int quad = kQuads * (sub % kSub) + (kParts == 1 ? lane / 16 : 0), part = kParts == 1 ? 0 : lane / 16;
+  const int i = row_token(p, row), hg = row - i * p.g;
+  const size_t orow = ((size_t)b * p.kmax + i) * p.Hq + kvh * p.g + hg;
+  const bool writes = part == 0 && row < p.rows_max;
+  f32x4 o = {0.f, 0.f, 0.f, 0.f};
+  float lse = 0.f;
+  if (row0 < rows) {  // wave-uniform; rows beyond draft_len (all of an inactive sequence) are zero in O and lse
+    const int w_lo = owners & 0xFFFF, n = ((owners >> 16) & 0xFFFF) - w_lo + 1;
+    const size_t slot0 = (size_t)w_lo + unit, stride = (size_t)p.rows_max * D;
+    const int at = min(row, p.rows_max - 1);
+    const float* acc = p.part_acc + slot0 * stride + 4 * at;
+    const float2* ml = (const float2*)p.part_ml + slot0 * p.rows_max + at;
+    float M = -INFINITY, L = 0.f;
+    for (int j0 = 0; j0 < n; j0 += 4 * kParts) {  // partials that do not exist repeat the last one, with no weight
+      float2 s[4];
+      f32x4 a[4];
+#pragma unroll
+      for (int j = 0; j < 4; ++j) {
+        if (j0 + kParts * j >= n) break;  // wave-uniform
+        const int x = min(j0 + kParts * j + part, n - 1);
+        s[j] = ml[(size_t)x * p.rows_max];
+        a[j] = *(const f32x4*)(acc + x * stride + 4 * wide_quad<D>(quad, (int)slot0 + x) * p.rows_max);
+      }
+      const float M_old = M;
+#pragma unroll
+      for (int j = 0; j < 4; ++j)
+        if (j0 + kParts * j < n) M = fmaxf(M, j0 + kParts * j + part < n ? s[j].x : -INFINITY);
+      const float Mf = M == -INFINITY ? 0.f : M, alpha = __builtin_amdgcn_exp2f(M_old - Mf);
+      L *= alpha;
+      o *= alpha;
+#pragma unroll
+      for (int j = 0; j < 4; ++j)
+        if (j0 + kParts * j < n) {
+          const float wgt = j0 + kParts * j + part < n ? __builtin_amdgcn_exp2f(s[j].x - Mf) : 0.f;
+          L = fmaf(s[j].y, wgt, L);
+          if (wgt != 0.f) o += a[j] * wgt;
+        }
+    }
+    // a valid row has a visible token (token 0) in the unit's first partial
+    float top = M;
+    if constexpr (kParts > 1) {
+      top = rows4_max(M);
+      const float wgt = __builtin_amdgcn_exp2f(M - (top == -INFINITY ? 0.f : top));
+      L = rows4_sum(L * wgt);
+#pragma unroll
+      for (int e = 0; e < 4; ++e) o[e] = rows4_sum(wgt != 0.f ? o[e] * wgt : 0.f);
+    }
+    o *= __builtin_amdgcn_rcpf(L);
+    lse = (top + __builtin_amdgcn_logf(L)) * 0.6931471805599453f;
+  }
+  if (!writes) return;
+  if (row >= rows) {
+    o = f32x4{0.f, 0.f, 0.f, 0.f};
+    lse = 0.f;
+  }
+  *(f32x4*)(p.O + orow * D + 4 * quad) = o;
+  if (p.lse && quad == 0) p.lse[orow] = lse;
 }
 
 // ---------------------------------------------------------------------------------------
@@ -1791,31 +2507,26 @@ static int check_attention_args(const bass_attn_desc* d, const LaunchShape& ls, 
   return BASS_OK;
 }
 
-// The workgroup-level kernels.  bf16: two wavefronts per query tile and two blocks per phase, but for at most two tiles of head
-// size 128: there one block per phase with two of four wavefronts only copying is as quick or quicker.  64/8 heads, 24 rows,
-// 1 - 16 sequences of 20 - 4000 tokens: 0 - 12 %; 32 heads, 32 rows, 8 sequences of 1200 / 4000 tokens: 42.5 -> 42.4 /
-// 136 -> 110 us, 16 of 1200: 81 -> 78; 20 rows, 16 sequences of 100 / 4000: 25.0 -> 25.9 / 182.9 -> 183.7.  At head size 64
-// two blocks per phase are 0 - 17 % quicker.
-// INT8, at most two tiles: two wavefronts per tile, so that none of the four only copies, and at head size 64, where a block
-// is 4 KB and the barriers count, two blocks each per phase where there are many units (from about 256 on: 512 units
-// of 4000 tokens, 32 rows: 84 -> 76 us; 64 units of 20 - 400 tokens 4 - 8 % longer).  32 heads, 32 rows, 16 sequences of 100 /
-// 1200 / 4000 tokens, one wavefront per tile and now: head size 128 26.7 / 55.8 / 137 -> 27.1 / 49.6 / 110 us, head size 64
-// 18.6 / 41.6 / 96.8 -> 18.6 / 34.9 / 76.5.
+// The workgroup-level kernels.
+template <int D, bool kI8>
+static void launch_wide(dim3 grid, hipStream_t s, const AttnParams& p) {
+  const dim3 block(64 * kWideWaves);
+  if (p.rows_max <= 32) {
+    hipLaunchKernelGGL((verify_attn_wide<D, kI8, 1>), grid, block, 0, s, p);
+  } else {
+    hipLaunchKernelGGL((verify_attn_wide<D, kI8, 2>), grid, block, 0, s, p);
+  }
+}
+
 template <bool kFused>
 static void launch_tiles(const bass_attn_desc* d, dim3 grid, hipStream_t s, const AttnParams& p) {
-  const bool big = d->D == 128, two = p.rows_max <= 32;
+  const bool big = d->D == 128;
   if (d->dtype == BASS_DTYPE_INT8KV) {
-    if (big && two) hipLaunchKernelGGL((verify_attn_tiles_i8<128, kFused, 2, 2, 1>), grid, dim3(256), 0, s, p);
-    else if (big) hipLaunchKernelGGL((verify_attn_tiles_i8<128, kFused, 4, 1, 1>), grid, dim3(256), 0, s, p);
-    else if (two && p.B * p.Hkv >= 256) hipLaunchKernelGGL((verify_attn_tiles_i8<64, kFused, 2, 2, 2>), grid, dim3(256), 0, s, p);
-    else if (two) hipLaunchKernelGGL((verify_attn_tiles_i8<64, kFused, 2, 2, 1>), grid, dim3(256), 0, s, p);
-    else hipLaunchKernelGGL((verify_attn_tiles_i8<64, kFused, 4, 1, 1>), grid, dim3(256), 0, s, p);
-  } else if (!two) {
-    if (big) hipLaunchKernelGGL((verify_attn_tiles_bf16<128, kFused, 4, 2>), grid, dim3(512), 0, s, p);
-    else hipLaunchKernelGGL((verify_attn_tiles_bf16<64, kFused, 4, 2>), grid, dim3(512), 0, s, p);
+    if (big) hipLaunchKernelGGL((verify_attn_tiles_i8<128, kFused>), grid, dim3(256), 0, s, p);
+    else hipLaunchKernelGGL((verify_attn_tiles_i8<64, kFused>), grid, dim3(256), 0, s, p);
   } else {
-    if (big) hipLaunchKernelGGL((verify_attn_tiles_bf16<128, kFused, 4, 1>), grid, dim3(256), 0, s, p);
-    else hipLaunchKernelGGL((verify_attn_tiles_bf16<64, kFused, 2, 2>), grid, dim3(256), 0, s, p);
+    if (big) hipLaunchKernelGGL((verify_attn_tiles_bf16<128, kFused>), grid, dim3(512), 0, s, p);
+    else hipLaunchKernelGGL((verify_attn_tiles_bf16<64, kFused>), grid, dim3(512), 0, s, p);
   }
 }
 
@@ -1853,10 +2564,19 @@ static int launch_attention(const bass_attn_desc* d, const LaunchShape& ls, cons
   const dim3 grid(p.nwaves / p.wpw), block(64 * p.wpw);
   if (d->dtype == BASS_DTYPE_FP32) {
     hipLaunchKernelGGL(verify_attn_fp32, grid, block, 0, s, p);
-  } else if (ls.tiles) {
+  } else if (ls.tiles && !ls.wide) {
     const dim3 tgrid((unsigned)ls.used_shares);
     if (K_new) launch_tiles<true>(d, tgrid, s, p);
     else launch_tiles<false>(d, tgrid, s, p);
+  } else if (ls.tiles) {
+    const dim3 tgrid((unsigned)ls.used_shares);
+    if (d->dtype == BASS_DTYPE_INT8KV) {
+      if (d->D == 128) launch_wide<128, true>(tgrid, s, p);
+      else launch_wide<64, true>(tgrid, s, p);
+    } else {
+      if (d->D == 128) launch_wide<128, false>(tgrid, s, p);
+      else launch_wide<64, false>(tgrid, s, p);
+    }
   } else {  // one query tile
     // LDS slice per wavefront of a fused append: K and V rows of two units (bf16, or INT8 codes + scales)
     const size_t unit_lds = d->dtype == BASS_DTYPE_INT8KV ? (size_t)2 * d->kmax * d->D + 8 * d->kmax
@@ -1876,11 +2596,14 @@ static int launch_attention(const bass_attn_desc* d, const LaunchShape& ls, cons
 #undef BASS_LAUNCH
   }
   if (launch_status() != BASS_OK) return BASS_ERR_HIP;
-  if (ls.tiles) {  // the merge is a launch of its own
-    const long items = (long)d->B * d->Hkv * ((rows_max + 3) / 4);
-    const dim3 rgrid((unsigned)((items + 3) / 4));
-    if (d->D == 128) hipLaunchKernelGGL((reduce_partials<2, 128>), rgrid, dim3(256), 0, s, p);
-    else hipLaunchKernelGGL((reduce_partials<1, 64>), rgrid, dim3(256), 0, s, p);
+  if (ls.tiles && rows_max > 32) {
+    const bool split = d->B * d->Hkv <= kReduceSplitUnits;
+    const long items = (long)d->B * d->Hkv * ((rows_max + 15) / 16) * (d->D / (split ? 4 : 16));
+    const dim3 rgrid((unsigned)((items + 3) / 4)), rblock(256);
+    if (d->D == 128 && split) hipLaunchKernelGGL((reduce_wide<128, 4>), rgrid, rblock, 0, s, p);
+    else if (d->D == 128) hipLaunchKernelGGL((reduce_wide<128, 1>), rgrid, rblock, 0, s, p);
+    else if (split) hipLaunchKernelGGL((reduce_wide<64, 4>), rgrid, rblock, 0, s, p);
+    else hipLaunchKernelGGL((reduce_wide<64, 1>), rgrid, rblock, 0, s, p);
   }
   return launch_status();
 }
