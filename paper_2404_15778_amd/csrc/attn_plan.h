@@ -91,11 +91,9 @@ struct Split {
 // Even division over exactly n shares: they differ by at most one entry.
 BASS_HD inline Split make_split(int total, int n) { return Split{total / n, total % n, total}; }
 
-// A short list is divided over fewer shares of about min_entries each: every share of a unit costs a partial
-// result, its acknowledged store, and a share of the merge that waits for the last of them.  With less than
-// kManyPerUnit shares per unit the merge is short already, and only half as many shares are worth having: 8 layers of 3
-// sequences x 32 heads, 20 / 27 blocks per unit: 117 / 134 us over all shares, 122 / 138 over 380 / 520; 8 units of 325
-// blocks: 569 over all, 376 over 520.
+// A short list is divided over fewer shares of about min_entries each: every share of a unit costs a partial result, its acknowledged
+// store, and a share of the merge that waits for the last of them.  With less than kManyPerUnit shares per unit the merge is short
+// already, and only half as many shares are worth having.
 constexpr int kManyPerUnit = 10;
 BASS_HD inline int most_shares(const PlanShape& s) { return s.used > 0 ? imin(s.used, s.nshares) : s.nshares; }
 BASS_HD inline bool worth_fewer(const PlanShape& s, int few) {
@@ -148,7 +146,7 @@ struct ShareRecord {
   int32_t signature;  // plan_signature() of the plan: what a launch checks before it trusts the record
   int32_t flags;      // kRecAnyInactive, kRecFewShares (the same in every record)
 };
-constexpr int32_t kRecFewShares = 2;    // the list was divided over fewer shares than the launch has (the same in every record)
+constexpr int32_t kRecFewShares = 2;    // the list was divided over fewer shares than there are records (the same in every record)
 constexpr int32_t kRecAnyInactive = 1;  // some sequence has no query token: its output rows still have to be cleared
 
 // What a launch and its plan must agree on, folded into one word that every record carries (a launch then

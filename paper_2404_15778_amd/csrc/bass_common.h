@@ -128,17 +128,6 @@ constexpr int kAppendPad = 3;     // virtual blocks per unit when the append is 
 constexpr int kPlainPad = 2;      // ... and when it is not (the unit's last blocks are the masked, slower ones)
 constexpr int kAppendBefore = 1;  // how many of those sit in front of the unit's last real block (one-tile matrix-core
 constexpr int kPlainBefore = 0;   // kernel; measured: +0.5 % with the fused append, slightly slower without)
-// Matrix-core kernels: where a unit would get more than kPerUnit shares of fewer than kMinEntries blocks, the list is divided over
-// fewer shares.  Every share of a unit leaves a partial result that the wavefront merging the unit has to fetch: one
-// sequence and 32 heads of 128, bf16, took 19.8 us with 24 shares per unit, 15.0 us with 8 and takes 13.2 us
-// with 5.  Measured with at least 1 / 4 / 5 / 6 / 9 / 12 blocks per share: 675 / 517 / 463 / 491 / 514 / 551 us for
-// the step of 32 such layers.  Units with fewer shares keep them, and more of them over INT8 caches, where
-// a block costs its wavefront about 1 us (4 sequences of 217 tokens, 32 heads, 6 shares per unit: 534 us; of 4 blocks at
-// least, 576).  Head size 64, blocks of half the size, gains as much: 1 sequence, 32 heads, 330 / 1000 / 2000 tokens, over all shares
-// and over fewer: bf16 10.8 / 17.9 / 17.8 -> 9.4 / 10.2 / 13.5 us, INT8 11.9 / 19.0 / 21.2 -> 10.6 / 13.0 / 15.5; only units of 3 - 4
-// blocks, 60 - 100 tokens, are no quicker (0 - 4 % longer).
-constexpr int kMinEntries = 5;
-constexpr int kPerUnit = 5, kPerUnitInt8 = 8;
 // More than 16 query rows per kv head: the workgroup-level kernels.  verify_attn_wide (a wavefront has all rows of its own blocks)
 // takes whatever has at most 32 rows, and more rows in caches of more than kShortCache blocks per sequence; below, the kernels that
 // share a block's rows between wavefronts are quicker, whose way from the first block to the last store is shorter.  48 and 64 rows,
@@ -155,6 +144,16 @@ constexpr int kShortCache = 24;
 // 20.8 us; from 8 on a wavefront's state spans several blocks, fewer probabilities are exactly 1 and precision is lost.
 constexpr int kTileShares = 256;
 constexpr int kWidePad = 7, kWideEntries = 4;
+// At most 16 query rows: up to this many units (sequence, kv head) take verify_attn_wide too, with a tile of 16 rows; more of them stay with a
+// wavefront per share (verify_attn_bf16), where a unit's merge costs no workgroup barrier.  8 query rows, a wavefront per share -> a
+// workgroup, us per layer, 32 / 64 / 96 / 128 / 192 units: head size 128, 200 - 500 tokens 12.6 / 14.2 / 14.6 / 14.3 / 16.6 -> 10.4 / 11.7 / 12.9 /
+// 15.4 / 18.0, 700 - 1500 tokens 17.2 / 19.2 / 20.6 / 21.3 / 28.4 -> 13.0 / 16.6 / 18.5 / 21.8 / 28.9, 2000 - 5000 tokens 20.8 / 30.1 / 36.8 / 44.4 /
+// 65.1 -> 18.2 / 28.2 / 36.9 / 44.5 / 67.3; head size 64, 2000 - 5000 tokens 15.4 / 20.4 / 22.1 -> 14.8 / 18.7 / 22.9; INT8 alike, 30 % quicker
+// at most (8 units of 4096 tokens: 15.9 -> 12.9).  1 sequence of 2000 tokens, 32/8 heads: 21.6 -> 12.2, 32 heads of 960: 14.1 -> 11.3.
+// There all 24 bits of the probabilities are multiplied (wide_softmax): with few shares per unit few probabilities are exactly 1, and the
+// error against 64 bits would rise from 1.3e-3 to 1.6e-3.
+constexpr int kNarrowUnits = 80;
+constexpr int kNarrowPad = 7, kNarrowEntries = 5, kNarrowShares = 256;  // (8 entries: short lists a third longer)
 // The kernels that share rows.  bf16: one workgroup per compute unit; INT8: two, because a step's conversions and softmax leave issue slots
 // to fill.  INT8 plans have room for twice the stretches.
 constexpr int kRowShares = 256, kRowSharesInt8 = 512;
@@ -165,6 +164,7 @@ int attention_waves_setting();  // bass_set_attention_waves (0 = defaults); veri
 struct LaunchShape {
   bool mfma;        // bf16 or INT8 caches: the matrix-core kernels
   bool tiles;       // more than one 16-row query tile per kv head: the workgroup-level kernels
+  bool narrow;      // at most 16 query rows and few units: verify_attn_wide with one tile of 16
   bool wide;        // ... verify_attn_wide
   bool fused_append;  // the step's rows are appended inside the attention launch, and its plan says so
   bool tiles_append;  // longer drafts, workgroup-level kernels: they patch a block at a time and stage nothing, so
@@ -199,17 +199,18 @@ inline LaunchShape launch_shape(const bass_attn_desc* d, bool append) {
   // (a launch wider than the shares it aims at, with all shares equally long -- plan_split -- was measured
   // 1 - 2 % slower than the even division on the benchmark shapes: more wavefronts, more partials to merge)
   s.nwaves = attention_waves(setting);
-  s.wide = s.tiles && (s.rows_max <= 32 || num_blocks(d->Lcap) > kShortCache);
+  s.narrow = s.mfma && !s.tiles && setting <= 0 && d->B * d->Hkv <= kNarrowUnits;
+  s.wide = s.narrow || (s.tiles && (s.rows_max <= 32 || num_blocks(d->Lcap) > kShortCache));
   // the workgroup-level kernels take one stretch per workgroup: half as many as an explicit setting has wavefronts
   const int stretches = setting > 0 ? s.nwaves / 2 : (int8 ? kRowSharesInt8 : kRowShares);
-  s.used_shares = !s.tiles ? s.nwaves : s.wide && setting <= 0 ? kTileShares : stretches;
+  s.used_shares = s.narrow ? kNarrowShares : !s.tiles ? s.nwaves : s.wide && setting <= 0 ? kTileShares : stretches;
   s.nshares = !s.tiles ? s.nwaves : int8 ? 2 * stretches : stretches;
   s.target = s.nshares;
-  s.pad = s.wide ? kWidePad : s.fused_append ? kAppendPad : kPlainPad;
-  s.min_entries = setting > 0 || !s.mfma || s.tiles != s.wide ? 0 : s.wide ? kWideEntries : kMinEntries;
-  s.per_unit = s.wide ? 1 : int8 ? kPerUnitInt8 : kPerUnit;
+  s.pad = s.narrow ? kNarrowPad : s.wide ? kWidePad : s.fused_append ? kAppendPad : kPlainPad;
+  s.min_entries = setting > 0 || !s.wide ? 0 : s.narrow ? kNarrowEntries : kWideEntries;
+  s.per_unit = 1;
   s.pad_before = 0;
-  if (s.mfma && s.rows_max <= 16) s.pad_before = s.fused_append ? kAppendBefore : kPlainBefore;
+  if (s.mfma && !s.tiles && !s.wide) s.pad_before = s.fused_append ? kAppendBefore : kPlainBefore;
   return s;
 }
 

@@ -712,7 +712,7 @@ template <int D, bool kMasked, bool kI8 = false>
 __device__ inline void block_step(KvRegs<D>& r, const bf16x8* qf, RowState<D>& st, int tok0,
                                   int n_valid, int lim, float scale_log2, int lane,
                                   bool fused = false, const NewRows& nr = NewRows{}, uint4* kdst = nullptr,
-                                  uint4* vdst = nullptr, const I8Operands<D>* i8 = nullptr, bool fine = false) {
+                                  uint4* vdst = nullptr, const I8Operands<D>* i8 = nullptr) {
   constexpr int KS = D / 32, MT = D / 16;
   const int grp = lane >> 4;
   // INT8 caches: a score is the integer product (q codes . k codes) * q-scale * k-scale, a value is
@@ -840,24 +840,9 @@ __device__ inline void block_step(KvRegs<D>& r, const bf16x8* qf, RowState<D>& s
   for (int j = 0; j < 8; ++j) {
     const float pj = __builtin_amdgcn_exp2f(s[j] - m_use);
     psum += pj;
-    s[j] = kI8 ? pj * vsl[j] : pj;
-    pf[j] = (__bf16)s[j];
+    pf[j] = (__bf16)(kI8 ? pj * vsl[j] : pj);
   }
   st.l += psum;
-  // Short lists over fewer shares (wave-uniform): what the rounding of the probabilities to bf16 left over is
-  // multiplied as well.  A share's first block holds its largest probability, 1, which is exact; with a fifth
-  // as many shares per unit that is lost for most of them (one sequence of 32 heads: error against 64 bits
-  // 1.3e-3 with 24 shares per unit, 1.6e-3 with 5, 2.3e-6 this way; the step of 32 layers 463 -> 489 us).
-  // Over INT8 caches no probability is exact, because the V scale is multiplied in before the rounding, and fewer
-  // shares lose nothing; the remainders take away the 1.7e-3 that the rounding costs there all the same.
-  if (fine) {
-    bf16x8 pr;
-#pragma unroll
-    for (int j = 0; j < 8; ++j) pr[j] = (__bf16)(s[j] - (float)pf[j]);
-#pragma unroll
-    for (int mt = 0; mt < MT; ++mt)
-      st.acc[mt] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(__builtin_bit_cast(bf16x8, r.v[mt]), pr, st.acc[mt], 0, 0, 0);
-  }
 #pragma unroll
   for (int mt = 0; mt < MT; ++mt)
     st.acc[mt] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(__builtin_bit_cast(bf16x8, r.v[mt]), pf, st.acc[mt], 0, 0, 0);
@@ -867,14 +852,14 @@ template <int D, bool kI8 = false>
 __device__ inline void block_dispatch(KvRegs<D>& r, const bf16x8* qf, RowState<D>& st, int blk,
                                       int L, int n_valid, int lim, float scale_log2, int lane,
                                       bool fused, const NewRows& nr, uint4* kdst, uint4* vdst,
-                                      const I8Operands<D>* i8 = nullptr, bool fine = false) {
+                                      const I8Operands<D>* i8 = nullptr) {
   const int tok0 = blk * kBlockTokens;
   // plain step: every token of the block is visible to every query (tokens <= L) and, with a fused
   // append, none of them is new (tokens < L)
   if (tok0 + kBlockTokens - 1 < L + (fused ? 0 : 1))
-    block_step<D, false, kI8>(r, qf, st, tok0, n_valid, lim, scale_log2, lane, false, NewRows{}, nullptr, nullptr, i8, fine);
+    block_step<D, false, kI8>(r, qf, st, tok0, n_valid, lim, scale_log2, lane, false, NewRows{}, nullptr, nullptr, i8);
   else
-    block_step<D, true, kI8>(r, qf, st, tok0, n_valid, lim, scale_log2, lane, fused, nr, kdst, vdst, i8, fine);
+    block_step<D, true, kI8>(r, qf, st, tok0, n_valid, lim, scale_log2, lane, fused, nr, kdst, vdst, i8);
 }
 
 // fp32 path: the wavefront whose share holds the new rows copies them into the (token-major) cache
@@ -965,18 +950,6 @@ __device__ inline void clear_state(RowState<D>& st) {
   for (int mt = 0; mt < D / 16; ++mt) st.acc[mt] = f32x4{0.f, 0.f, 0.f, 0.f};
 }
 
-// Whether some accumulator of the wavefront is NaN or infinite (wave-uniform)
-template <int D>
-__device__ inline bool any_not_finite(const RowState<D>& st) {
-  f32x4 t = {0.f, 0.f, 0.f, 0.f};  // 0 * finite is 0, 0 * anything else NaN
-#pragma unroll
-  for (int mt = 0; mt < D / 16; ++mt)
-#pragma unroll
-    for (int e = 0; e < 4; ++e) t[e] = fmaf(st.acc[mt][e], 0.f, t[e]);
-  const float sum = (t[0] + t[1]) + (t[2] + t[3]);
-  return __any(sum != sum);
-}
-
 // Partial of (wavefront w, unit u): slot ids w + unit are unique because both grow monotonically
 // along the flattened list.
 template <int D>
@@ -1016,9 +989,7 @@ __device__ inline void finalize_single(const AttnParams& p, const Unit& u, const
   }
 }
 
-// kFew: so few units that a plan may have divided the list over fewer shares (the records say whether it did); the
-// others are spared the branch in every block step (1 % of a step of eight sequences).
-template <int D, bool kI8, bool kFew>
+template <int D, bool kI8>
 __global__ __launch_bounds__(256) void verify_attn_bf16(AttnParams p) {
   // uint4 per block: 32 tokens of D bf16, or of D INT8 codes followed by 32 fp32 scales
   constexpr ptrdiff_t kBlkVec = kI8 ? 2 * D + 8 : (ptrdiff_t)kBlockTokens * D * 2 / 16;
@@ -1029,9 +1000,7 @@ __global__ __launch_bounds__(256) void verify_attn_bf16(AttnParams p) {
   // (Storing the first partial at the boundary instead costs about 1 us per launch: the stores
   // sit in the ring's wait counts.)
   const int lane = threadIdx.x & 63;
-  // few shares: consecutive ones go to consecutive workgroups, so that a list shorter than the launch still uses every
-  // compute unit; otherwise a unit's shares stay together (32 sequences of 128 - 8192 tokens: 0.5 % shorter)
-  const int w = uniform(kFew ? (threadIdx.x >> 6) * gridDim.x + blockIdx.x : blockIdx.x * p.wpw + (threadIdx.x >> 6));
+  const int w = uniform(blockIdx.x * p.wpw + (threadIdx.x >> 6));
   const int col = lane & 15, grp = lane >> 4;
 
   // This wavefront's share: the first two segments come with the record, in one round trip; the plan's
@@ -1042,7 +1011,6 @@ __global__ __launch_bounds__(256) void verify_attn_bf16(AttnParams p) {
   Segment sb = load_segment(&rec->seg[1]);
   int nseg_plan = uniform(rec->nseg), overflow = uniform(rec->overflow);
   const int rec_flags = uniform(rec->flags);
-  const bool fine = kFew && (rec_flags & kRecFewShares) != 0;
   __builtin_amdgcn_sched_barrier(0);  // the loads above are issued here, whatever is scheduled below
   bool ok;
   int nseg;
@@ -1149,7 +1117,7 @@ __global__ __launch_bounds__(256) void verify_attn_bf16(AttnParams p) {
         load_block<D>(r, kc + off, vc + off);
       }
     };
-    auto step = [&](Regs& r, int s, bool fine) {
+    auto step = [&](Regs& r, int s) {
       if (s == nA) {  // first block of unit B: park A's state (register moves only)
         parked = st;
         clear_state<D>(st);
@@ -1173,9 +1141,9 @@ __global__ __launch_bounds__(256) void verify_attn_bf16(AttnParams p) {
         dequant_block<D>(r, t, sc);
         const I8Operands<D> i8{r.k, qc.q, qc.q_scale_log2, &sc};
         block_dispatch<D, true>(t, nullptr, st, cur_blk + s, cur_L, cur_valid, qc.lim, p.scale_log2, lane, false,
-                                    cur_new, nullptr, nullptr, &i8, fine);  // the codes are patched already: no fused work inside
+                                    cur_new, nullptr, nullptr, &i8);  // the codes are patched already: no fused work inside
       } else {
-        block_dispatch<D>(r, qc.q, st, cur_blk + s, cur_L, cur_valid, qc.lim, p.scale_log2, lane, fused, cur_new, kdst, vdst, nullptr, fine);
+        block_dispatch<D>(r, qc.q, st, cur_blk + s, cur_L, cur_valid, qc.lim, p.scale_log2, lane, fused, cur_new, kdst, vdst);
       }
     };
     // Unused query rows of a unit are cleared by the wavefront that holds the unit's last block (it is handed
@@ -1203,48 +1171,24 @@ __global__ __launch_bounds__(256) void verify_attn_bf16(AttnParams p) {
     next_arrived();
     for (int s = 0; s < n; s += 3) {
       fetch(r2, s + 2);
-      step(r0, s, fine);
+      step(r0, s);
       fetch(r0, s + 3);
-      if (s + 1 < n) step(r1, s + 1, fine);
+      if (s + 1 < n) step(r1, s + 1);
       fetch(r1, s + 4);
-      if (s + 2 < n) step(r2, s + 2, fine);
+      if (s + 2 < n) step(r2, s + 2);
     }
     // A unit that lies wholly inside this share (common with many short sequences) is finished from the
     // registers; the others leave a partial, and the wavefront that delivers a unit's last partial merges.
     const bool soloA = ja.w_lo == ja.w_hi;
     const bool soloB = hasB && jb.w_lo == jb.w_hi;
-    auto deliver = [&]() {
-      if (hasB) {
-        if (soloA) finalize_single<D>(p, uA, parked, col, grp);
-        else store_partial<D>(p, uA, w, parked, col, grp);
-        if (soloB) finalize_single<D>(p, uB, st, col, grp);
-        else store_partial<D>(p, uB, w, st, col, grp);
-      } else {
-        if (soloA) finalize_single<D>(p, uA, st, col, grp);
-        else store_partial<D>(p, uA, w, st, col, grp);
-      }
-    };
-    deliver();
-    // An infinite element of V decides its outputs, but times the remainder of a probability, which may be zero or negative,
-    // it is NaN.  Units in which that may have happened are streamed once more without the remainder products, and what
-    // was stored is stored again; what is not finite then is so by the inputs.  (Looked at under the way of the stores: level
-    // at head size 128, 0.1 - 0.3 us of launches of 5 - 10 us at 64.  An INT8 row with an infinite element has no finite
-    // scale: NaN either way.)
-    if constexpr (kFew && !kI8) {
-      if (__builtin_expect(fine && (any_not_finite<D>(st) || (hasB && any_not_finite<D>(parked))), 0)) {
-        load_queries<D>(p, uA, true, col, grp, qc);
-        clear_state<D>(st);
-        cur_L = uA.L;
-        cur_valid = uA.L + uA.nq;
-        cur_blk = firstA;
-        cur_new = newA;
-#pragma unroll 1
-        for (int s = 0; s < n; ++s) {
-          fetch(r0, s);
-          step(r0, s, false);
-        }
-        deliver();
-      }
+    if (hasB) {
+      if (soloA) finalize_single<D>(p, uA, parked, col, grp);
+      else store_partial<D>(p, uA, w, parked, col, grp);
+      if (soloB) finalize_single<D>(p, uB, st, col, grp);
+      else store_partial<D>(p, uB, w, st, col, grp);
+    } else {
+      if (soloA) finalize_single<D>(p, uA, st, col, grp);
+      else store_partial<D>(p, uA, w, st, col, grp);
     }
     const bool exchA = !soloA, exchB = hasB && !soloB;
     if (exchA || exchB) {
@@ -1292,30 +1236,66 @@ typedef __attribute__((ext_vector_type(16))) int i32x16;
 constexpr int kWideWaves = 4;
 constexpr int kAuxNonTemporal = 2;  // nt
 
-__device__ inline int wide_token(int c) { return (c & 7) | ((c & 8) << 1) | ((c & 16) >> 1); }
-__device__ inline int score_token(int i, int h) { return 16 * ((i >> 2) & 1) + 8 * (i >> 3) + 4 * h + (i & 3); }
-// First of the four consecutive head elements that registers 4 q .. 4 q + 3 of accumulator a hold
-template <bool kI8>
-__device__ inline int wide_elem(int a, int q, int h) {
-  return kI8 ? 64 * (a >> 1) + 32 * (q >> 1) + 16 * (a & 1) + 8 * (q & 1) + 4 * h : 32 * a + 8 * q + 4 * h;
-}
+// NT tiles of 32 query rows, or (NT = 0) one of 16.  A lane belongs to row lane % kRows of a tile; h = lane / kRows.
+template <int D, bool kI8, int NT>
+struct Wide {
+  static constexpr bool kSmall = NT == 0;
+  static constexpr int kTiles = kSmall ? 1 : NT, kRows = kSmall ? 16 : 32, kLanes = 64 / kRows;  // lanes of a row
+  static constexpr int kAllRows = kRows * kTiles;
+  static constexpr int kBlkVec = kI8 ? 2 * D + 8 : 4 * D;   // uint4 per block and tensor
+  static constexpr int kChunks = D / (kI8 ? 32 : 16);       // 16-byte chunks per lane, block and tensor
+  static constexpr int kQuerySteps = D / (kLanes * (kI8 ? 16 : 8));  // operands of a score tile's queries
+  static constexpr int kScores = kSmall ? 8 : 16;           // scores of a lane per block and tile
+  static constexpr int kProbs = kScores / 8;                // operands of the V product
+  static constexpr int kAcc = D / kRows;                    // accumulators per tile ...
+  static constexpr int kQuads = kSmall ? 1 : 4;             // ... of this many quads of head elements each
+  typedef typename std::conditional<kSmall, f32x4, f32x16>::type Acc;
+
+  // Token of the block that a lane's score i belongs to; eight by eight these are the tokens of the cache's V chunks.
+  __device__ static int token(int i, int h) {
+    return kSmall ? 16 * (i >> 2) + 4 * h + (i & 3) : 16 * ((i >> 2) & 1) + 8 * (i >> 3) + 4 * h + (i & 3);
+  }
+  // Chunk x of K: this lane's token and which 16 bytes of its row.  (32 rows: bits 3 and 4 of the row exchanged.)
+  __device__ static int k_token(int x, int c) {
+    return kSmall ? 16 * (x / (kChunks / 2)) + c : (c & 7) | ((c & 8) << 1) | ((c & 16) >> 1);
+  }
+  __device__ static int k_part(int x, int h) { return kSmall ? 4 * (x % (kChunks / 2)) + h : 2 * x + h; }
+  // First head element of a lane's fragment f of V chunk x (INT8 chunks hold two fragments)
+  __device__ static int v_elem(int x, int f, int c) {
+    return kSmall ? (kI8 ? 32 * x + 16 * f + c : 16 * x + c) : kI8 ? 64 * (x >> 1) + 32 * (c >> 4) + 16 * f + (c & 15) : 32 * (x >> 1) + c;
+  }
+  // First of the four head elements of quad q of accumulator a
+  __device__ static int elem(int a, int q, int h) {
+    return kSmall ? 16 * a + 4 * h : kI8 ? 64 * (a >> 1) + 32 * (q >> 1) + 16 * (a & 1) + 8 * (q & 1) + 4 * h : 32 * a + 8 * q + 4 * h;
+  }
+  // Where a lane's chunks lie in a block (uint4): a lane offset and a step per chunk.
+  __device__ static int k_lane(int lane) {
+    const int c = lane & 31, t = k_token(0, c);
+    return kSmall ? lane : (t >> 4) * (32 * kChunks) + (lane >> 5) * 16 + (t & 15);
+  }
+  __device__ static int v_lane(int lane) { return kSmall ? lane : ((lane >> 4) & 1) * 64 + (lane >> 5) * 16 + (lane & 15); }
+  __device__ static constexpr int k_step(int x) { return kSmall ? 64 * x : (x >> 1) * 64 + (x & 1) * 32; }
+  __device__ static constexpr int v_step(int x) { return kSmall ? 64 * x : (x >> 1) * 128 + (x & 1) * 32; }
+
+  __device__ static float row_max(float v) {  // over the lanes of a row
+    if constexpr (kSmall) return rows4_max(v);
+    const u32x2 a = __builtin_amdgcn_permlane32_swap(__float_as_uint(v), __float_as_uint(v), false, false);
+    return fmaxf(__uint_as_float(a[0]), __uint_as_float(a[1]));
+  }
+  __device__ static float row_sum(float v) {
+    if constexpr (kSmall) return rows4_sum(v);
+    const u32x2 a = __builtin_amdgcn_permlane32_swap(__float_as_uint(v), __float_as_uint(v), false, false);
+    return __uint_as_float(a[0]) + __uint_as_float(a[1]);
+  }
+};
 
 // Place of a quad of head elements in a partial.  Slots lie 32 KB apart at 64 rows of 128: without the rotation all workgroups would
 // write to the same few memory channels at a time.
 template <int D>
 __device__ inline int wide_quad(int quad, int slot) { return (quad + slot) & (D / 4 - 1); }
 
-__device__ inline float rows2_max(float v) {  // over lanes l and l + 32, which share a query row
-  const u32x2 a = __builtin_amdgcn_permlane32_swap(__float_as_uint(v), __float_as_uint(v), false, false);
-  return fmaxf(__uint_as_float(a[0]), __uint_as_float(a[1]));
-}
-__device__ inline float rows2_sum(float v) {
-  const u32x2 a = __builtin_amdgcn_permlane32_swap(__float_as_uint(v), __float_as_uint(v), false, false);
-  return __uint_as_float(a[0]) + __uint_as_float(a[1]);
-}
-
-// A block on its way to its wavefront: one 16-byte chunk of each k-step's operand, and (INT8) one scale: lane l < 32 the K scale
-// of token l, lane l >= 32 the V scale of token l - 32.
+// A block on its way to its wavefront, and (INT8) one scale: lane l < 32 the K scale of token l, lane l >= 32 the V scale of
+// token l - 32.
 template <int D, bool kI8>
 struct WideBlock {
   static constexpr int kChunks = D / (kI8 ? 32 : 16);
@@ -1323,27 +1303,12 @@ struct WideBlock {
   float scale;
 };
 
-template <int D, bool kI8>
-struct WideGeometry {
-  static constexpr int kBlkVec = kI8 ? 2 * D + 8 : 4 * D;  // uint4 per block and tensor
-  static constexpr int kTileVec = D * (kI8 ? 1 : 2);       // ... of one 16-token half of K
-};
-
-// Chunk offsets (uint4) inside a block.  K: step ks of lane (c, h).  V: bf16 chunk x = 2 a + s is d-tile a, tokens of k-step s;
-// INT8 chunk x = 2 pair + s holds d-tiles 2 pair and 2 pair + 1.
-__device__ inline int wide_k_lane(int c, int h, int tile_vec) {
-  const int t = wide_token(c);
-  return (t >> 4) * tile_vec + h * 16 + (t & 15);
-}
-__device__ inline int wide_v_lane(int c, int h) { return (c >> 4) * 64 + h * 16 + (c & 15); }
-__device__ constexpr int wide_k_step(int ks) { return (ks >> 1) * 64 + (ks & 1) * 32; }
-__device__ constexpr int wide_v_step(int x) { return (x >> 1) * 128 + (x & 1) * 32; }
-
 template <int D, bool kI8, int NT>
 struct WideQueries {
-  u32x4 q[NT][D / (kI8 ? 32 : 16)];  // operand B: query row 32 nt + c, the k-steps' head elements
-  float row_scale[NT];               // INT8: row scale * |softmax scale| * log2(e)
-  int lim[NT];                       // last token visible to the row
+  using G = Wide<D, kI8, NT>;
+  u32x4 q[G::kTiles][G::kQuerySteps];  // operand B of the score tiles
+  float row_scale[G::kTiles];          // INT8: row scale * |softmax scale| * log2(e)
+  int lim[G::kTiles];                  // last token visible to the row
 };
 
 // The queries go through LDS, because an operand's rows lie far apart: fetched by the wavefronts themselves, each would touch 32
@@ -1351,10 +1316,11 @@ struct WideQueries {
 // there like cache rows (a row's D / 8 lanes agree on its largest magnitude), and every wavefront reads its operands from LDS.
 template <int D, bool kI8, int NT>
 struct WideQueryRows {
+  static constexpr int kRows = Wide<D, kI8, NT>::kAllRows;
   static constexpr int kRowBytes = D * (kI8 ? 1 : 2) + 16;  // 16 bytes apart in the banks
-  static constexpr int kLoads = 32 * NT * (D / 8) / (64 * kWideWaves);
-  __align__(16) unsigned char q[32 * NT * kRowBytes];
-  float row_scale[kI8 ? 32 * NT : 1];
+  static constexpr int kPieces = kRows * (D / 8), kLoads = (kPieces + 64 * kWideWaves - 1) / (64 * kWideWaves);
+  __align__(16) unsigned char q[kRows * kRowBytes];
+  float row_scale[kI8 ? kRows : 1];
 };
 
 // A negative softmax scale is moved into the queries (exact) and so is a zero, so that the factor that is left is positive: the
@@ -1364,7 +1330,7 @@ __device__ inline void commit_wide_queries(const AttnParams& p, const Unit& u, i
                                            WideQueryRows<D, kI8, NT>& lds) {
   const uint32_t flip = p.scale_log2 < 0.f ? 0x80008000u : 0u;
 #pragma unroll
-  for (int x = 0; x < WideQueryRows<D, kI8, NT>::kLoads; ++x) {
+  for (int x = 0; x < lds.kLoads; ++x) {
     const int at = x * 64 * kWideWaves + tid, row = at / (D / 8), ck = at % (D / 8);
     const u32x4 v = (raw[x] ^ flip) & (row < u.nq * p.g && p.scale_log2 != 0.f ? 0xFFFFFFFFu : 0u);
     if constexpr (kI8) {
@@ -1374,9 +1340,11 @@ __device__ inline void commit_wide_queries(const AttnParams& p, const Unit& u, i
       for (int o = D / 16; o >= 1; o >>= 1) amax = fmaxf(amax, __shfl_xor(amax, o));
       const float scale = amax / 127.0f * fabsf(p.scale_log2);
       const float inv = amax > 0.f && scale != 0.f ? 127.0f / amax : 0.f;
-      *(uint2*)&lds.q[row * lds.kRowBytes + 8 * ck] = quantize8(w, inv);
-      if (ck == 0) lds.row_scale[row] = scale != 0.f ? scale : 1.f;
-    } else {
+      if (row < lds.kRows) {
+        *(uint2*)&lds.q[row * lds.kRowBytes + 8 * ck] = quantize8(w, inv);
+        if (ck == 0) lds.row_scale[row] = scale != 0.f ? scale : 1.f;
+      }
+    } else if (row < lds.kRows) {
       *(u32x4*)&lds.q[row * lds.kRowBytes + 16 * ck] = v;
     }
   }
@@ -1385,26 +1353,28 @@ __device__ inline void commit_wide_queries(const AttnParams& p, const Unit& u, i
 template <int D, bool kI8, int NT>
 __device__ inline void read_wide_queries(const AttnParams& p, const Unit& u, int c, int h, const WideQueryRows<D, kI8, NT>& lds,
                                          WideQueries<D, kI8, NT>& q) {
+  using G = Wide<D, kI8, NT>;
 #pragma unroll
-  for (int nt = 0; nt < NT; ++nt) {
-    const int row = 32 * nt + c;
+  for (int nt = 0; nt < G::kTiles; ++nt) {
+    const int row = G::kRows * nt + c;
     q.lim[nt] = u.L + (row < u.nq * p.g ? row_token(p, row) : 0);
 #pragma unroll
-    for (int ks = 0; ks < D / (kI8 ? 32 : 16); ++ks) q.q[nt][ks] = *(const u32x4*)&lds.q[row * lds.kRowBytes + 16 * (2 * ks + h)];
+    for (int x = 0; x < G::kQuerySteps; ++x) q.q[nt][x] = *(const u32x4*)&lds.q[row * lds.kRowBytes + 16 * (G::kLanes * x + h)];
     if constexpr (kI8) q.row_scale[nt] = lds.row_scale[row];
   }
 }
 
-template <int D, int NT>
+template <int D, bool kI8, int NT>
 struct WideState {
-  f32x16 acc[NT][D / 32];
-  float m[NT], l[NT];  // running maximum (log2 units; the same in both lanes of a row), this lane's share of the sum
+  using G = Wide<D, kI8, NT>;
+  typename G::Acc acc[G::kTiles][G::kAcc];
+  float m[G::kTiles], l[G::kTiles];  // running maximum (log2 units; the same in all lanes of a row), this lane's share of the sum
 };
 
 // The step's own rows of a unit in LDS ([row][D] bf16, or codes and one scale per row), as in the one-tile kernel.
 template <int D, bool kI8, int NT>
 struct WideNewRows {
-  static constexpr int kRows = 32 * NT, kElem = kI8 ? 1 : 2;
+  static constexpr int kRows = Wide<D, kI8, NT>::kAllRows, kElem = kI8 ? 1 : 2;
   __align__(16) unsigned char k[kRows * D * kElem], v[kRows * D * kElem];
   float k_scale[kI8 ? kRows : 1], v_scale[kI8 ? kRows : 1];
 };
@@ -1412,34 +1382,35 @@ struct WideNewRows {
 // New tokens into a fetched block's registers.
 template <int D, bool kI8, int NT>
 __device__ inline void patch_wide(WideBlock<D, kI8>& r, int tok0, int L, int nq, int lane, const WideNewRows<D, kI8, NT>& nr) {
-  constexpr int n = WideBlock<D, kI8>::kChunks;
-  const int c = lane & 31, h = lane >> 5;
-  const int ik = tok0 + wide_token(c) - L;
-  if (ik >= 0 && ik < nq) {
+  using G = Wide<D, kI8, NT>;
+  const int c = lane % G::kRows, h = lane / G::kRows;
 #pragma unroll
-    for (int ks = 0; ks < n; ++ks) r.k[ks] = *(const u32x4*)&nr.k[(size_t)ik * D * nr.kElem + 16 * (2 * ks + h)];
+  for (int x = 0; x < G::kChunks; ++x) {
+    const int i = tok0 + G::k_token(x, c) - L;
+    if (i >= 0 && i < nq) r.k[x] = *(const u32x4*)&nr.k[(size_t)i * D * nr.kElem + 16 * G::k_part(x, h)];
   }
   if constexpr (kI8) {
-    const int is = tok0 + c - L;
-    if (is >= 0 && is < nq) r.scale = h ? nr.v_scale[is] : nr.k_scale[is];
+    const int i = tok0 + lane % 32 - L;
+    if (i >= 0 && i < nq) r.scale = lane < 32 ? nr.k_scale[i] : nr.v_scale[i];
   }
 #pragma unroll
-  for (int s = 0; s < 2; ++s)
+  for (int s = 0; s < G::kProbs; ++s)
 #pragma unroll
     for (int j = 0; j < 8; ++j) {
-      const int i = tok0 + score_token(8 * s + j, h) - L;
+      const int i = tok0 + G::token(8 * s + j, h) - L;
       if (i >= 0 && i < nq) {
 #pragma unroll
-        for (int a = 0; a < D / 32; ++a) {
+        for (int x = s; x < G::kChunks; x += G::kProbs) {  // the chunks of these tokens
           if constexpr (kI8) {
-            const uint32_t code = nr.v[i * D + 64 * (a >> 1) + 32 * (c >> 4) + 16 * (a & 1) + (c & 15)];
-            const int word = 2 * (a & 1) + (j >> 2), sh = 8 * (j & 3);
-            u32x4& ch = r.v[2 * (a >> 1) + s];
-            ch[word] = (ch[word] & ~(0xFFu << sh)) | (code << sh);
+#pragma unroll
+            for (int f = 0; f < 2; ++f) {
+              const uint32_t code = nr.v[i * D + G::v_elem(x, f, c)];
+              const int word = 2 * f + (j >> 2), sh = 8 * (j & 3);
+              r.v[x][word] = (r.v[x][word] & ~(0xFFu << sh)) | (code << sh);
+            }
           } else {
-            const uint32_t val = *(const uint16_t*)&nr.v[2 * (i * D + 32 * a + c)];
-            u32x4& ch = r.v[2 * a + s];
-            ch[j >> 1] = (j & 1) ? (ch[j >> 1] & 0x0000FFFFu) | (val << 16) : (ch[j >> 1] & 0xFFFF0000u) | val;
+            const uint32_t val = *(const uint16_t*)&nr.v[2 * (i * D + G::v_elem(x, 0, c))];
+            r.v[x][j >> 1] = (j & 1) ? (r.v[x][j >> 1] & 0x0000FFFFu) | (val << 16) : (r.v[x][j >> 1] & 0xFFFF0000u) | val;
           }
         }
       }
@@ -1449,28 +1420,52 @@ __device__ inline void patch_wide(WideBlock<D, kI8>& r, int tok0, int L, int nq,
 // Scores of a block (INT8: integer products times the tokens' K scales; the rows' scales follow in wide_softmax).
 template <int D, bool kI8, int NT>
 __device__ inline void wide_scores(const WideBlock<D, kI8>& r, const WideQueries<D, kI8, NT>& q, int h, const float* scales,
-                                   float (&s)[NT][16]) {
-  constexpr int n = WideBlock<D, kI8>::kChunks;
+                                   float (&s)[Wide<D, kI8, NT>::kTiles][Wide<D, kI8, NT>::kScores]) {
+  using G = Wide<D, kI8, NT>;
+  constexpr int n = G::kQuerySteps;
 #pragma unroll
-  for (int nt = 0; nt < NT; ++nt) {
-    if constexpr (kI8) {
+  for (int nt = 0; nt < G::kTiles; ++nt) {
+    if constexpr (G::kSmall) {
+#pragma unroll
+      for (int t = 0; t < 2; ++t) {
+        if constexpr (kI8) {
+          i32x4 z = {0, 0, 0, 0};
+#pragma unroll
+          for (int x = 0; x < n; ++x)
+            z = __builtin_amdgcn_mfma_i32_16x16x64_i8(__builtin_bit_cast(i32x4, r.k[t * n + x]), __builtin_bit_cast(i32x4, q.q[nt][x]), z, 0, 0, 0);
+#pragma unroll
+          for (int i = 0; i < 4; ++i) s[nt][4 * t + i] = (float)z[i];
+        } else {
+          f32x4 z = {0.f, 0.f, 0.f, 0.f};
+#pragma unroll
+          for (int x = 0; x < n; ++x)
+            z = __builtin_amdgcn_mfma_f32_16x16x32_bf16(__builtin_bit_cast(bf16x8, r.k[t * n + x]), __builtin_bit_cast(bf16x8, q.q[nt][x]), z, 0, 0, 0);
+#pragma unroll
+          for (int i = 0; i < 4; ++i) s[nt][4 * t + i] = z[i];
+        }
+      }
+    } else if constexpr (kI8) {
       i32x16 z = {0};
 #pragma unroll
-      for (int ks = 0; ks < n; ++ks)
-        z = __builtin_amdgcn_mfma_i32_32x32x32_i8(__builtin_bit_cast(i32x4, r.k[ks]), __builtin_bit_cast(i32x4, q.q[nt][ks]), z, 0, 0, 0);
+      for (int x = 0; x < n; ++x)
+        z = __builtin_amdgcn_mfma_i32_32x32x32_i8(__builtin_bit_cast(i32x4, r.k[x]), __builtin_bit_cast(i32x4, q.q[nt][x]), z, 0, 0, 0);
 #pragma unroll
-      for (int x = 0; x < 4; ++x) {
-        const f32x4 ks = *(const f32x4*)&scales[score_token(4 * x, h)];
-#pragma unroll
-        for (int e = 0; e < 4; ++e) s[nt][4 * x + e] = (float)z[4 * x + e] * ks[e];
-      }
+      for (int i = 0; i < 16; ++i) s[nt][i] = (float)z[i];
     } else {
       f32x16 z = {0.f};
 #pragma unroll
-      for (int ks = 0; ks < n; ++ks)
-        z = __builtin_amdgcn_mfma_f32_32x32x16_bf16(__builtin_bit_cast(bf16x8, r.k[ks]), __builtin_bit_cast(bf16x8, q.q[nt][ks]), z, 0, 0, 0);
+      for (int x = 0; x < n; ++x)
+        z = __builtin_amdgcn_mfma_f32_32x32x16_bf16(__builtin_bit_cast(bf16x8, r.k[x]), __builtin_bit_cast(bf16x8, q.q[nt][x]), z, 0, 0, 0);
 #pragma unroll
       for (int i = 0; i < 16; ++i) s[nt][i] = z[i];
+    }
+    if constexpr (kI8) {
+#pragma unroll
+      for (int y = 0; y < G::kScores / 4; ++y) {
+        const f32x4 ks = *(const f32x4*)&scales[G::token(4 * y, h)];
+#pragma unroll
+        for (int e = 0; e < 4; ++e) s[nt][4 * y + e] *= ks[e];
+      }
     }
   }
 }
@@ -1479,38 +1474,47 @@ __device__ inline void wide_scores(const WideBlock<D, kI8>& r, const WideQueries
 // (bf16), so that 0 * garbage cannot reach the accumulator.  In place and apart from the step itself: two instances of the step,
 // with and without masks, would make the compiler merge their register tuples and spill hundreds of them.
 template <int D, bool kI8, int NT>
-__device__ inline void mask_wide(float (&s)[NT][16], WideBlock<D, kI8>& r, const WideQueries<D, kI8, NT>& q, int tok0, int n_valid, int h) {
+__device__ inline void mask_wide(WideBlock<D, kI8>& r, float (&s)[Wide<D, kI8, NT>::kTiles][Wide<D, kI8, NT>::kScores],
+                                 const WideQueries<D, kI8, NT>& q, int tok0, int n_valid, int h) {
+  using G = Wide<D, kI8, NT>;
 #pragma unroll
-  for (int nt = 0; nt < NT; ++nt)
+  for (int nt = 0; nt < G::kTiles; ++nt)
 #pragma unroll
-    for (int i = 0; i < 16; ++i)
-      if (tok0 + score_token(i, h) > q.lim[nt]) s[nt][i] = -INFINITY;
+    for (int i = 0; i < G::kScores; ++i)
+      if (tok0 + G::token(i, h) > q.lim[nt]) s[nt][i] = -INFINITY;
   if constexpr (!kI8) {
 #pragma unroll
-    for (int x = 0; x < 2; ++x)
+    for (int y = 0; y < G::kProbs; ++y)
 #pragma unroll
       for (int wd = 0; wd < 4; ++wd) {
-        const int t_lo = tok0 + score_token(8 * x + 2 * wd, h);
+        const int t_lo = tok0 + G::token(8 * y + 2 * wd, h);
         const uint32_t keep = (t_lo < n_valid ? 0x0000FFFFu : 0u) | (t_lo + 1 < n_valid ? 0xFFFF0000u : 0u);
 #pragma unroll
-        for (int a = 0; a < D / 32; ++a) r.v[2 * a + x][wd] &= keep;
+        for (int x = y; x < G::kChunks; x += G::kProbs) r.v[x][wd] &= keep;
       }
   }
 }
 
 // Online softmax of a block: scores -> probabilities as operand B of the V product (INT8: times the tokens' V scales), running
-// maximum and sum.
-template <int D, bool kI8, int NT>
-__device__ inline void wide_softmax(const float (&s)[NT][16], const WideQueries<D, kI8, NT>& q, WideState<D, NT>& st, float abs_scale_log2,
-                                    int h, const float* scales, bf16x8 (&pf)[NT][2]) {
+// maximum and sum.  kFine: shapes whose lists may be divided over fewer shares, where the rounding of the probabilities to bf16 would
+// cost precision (kNarrowUnits): their 24 bits are cut into three operands of 8 and all multiplied.  No part is negative, and none is
+// zero where the probability is not, so that an infinite element of V stays infinite in every product.  (Two parts leave 2^-17: 3.6e-6
+// instead of 2.3e-6 with a rounded first part, whose remainder may be negative.)
+template <int D, bool kI8, int NT, bool kFine>
+__device__ inline void wide_softmax(const float (&s)[Wide<D, kI8, NT>::kTiles][Wide<D, kI8, NT>::kScores], const WideQueries<D, kI8, NT>& q,
+                                    WideState<D, kI8, NT>& st, float abs_scale_log2, int h, const float* scales,
+                                    bf16x8 (&pf)[Wide<D, kI8, NT>::kTiles][Wide<D, kI8, NT>::kProbs],
+                                    bf16x8 (&pr)[2][Wide<D, kI8, NT>::kTiles][Wide<D, kI8, NT>::kProbs]) {
+  using G = Wide<D, kI8, NT>;
+  auto cut = [](float z) { return __uint_as_float(__float_as_uint(z) & 0xFFFF0000u); };
 #pragma unroll
-  for (int nt = 0; nt < NT; ++nt) {
+  for (int nt = 0; nt < G::kTiles; ++nt) {
     const float scale = kI8 ? q.row_scale[nt] : abs_scale_log2;  // > 0
     float mx = s[nt][0];
 #pragma unroll
-    for (int i = 1; i < 16; ++i) mx = fmaxf(mx, s[nt][i]);
-    mx = rows2_max(mx) * scale;
-    // the lazily moving reference maximum of block_step
+    for (int i = 1; i < G::kScores; ++i) mx = fmaxf(mx, s[nt][i]);
+    mx = G::row_max(mx) * scale;
+    // The reference maximum of a row moves only when a block exceeds it by more than kMaxSlack (log2 units).
     const float m_old = st.m[nt];
     const bool grow = mx > m_old + kMaxSlack;
     if (__any(grow)) {
@@ -1518,87 +1522,109 @@ __device__ inline void wide_softmax(const float (&s)[NT][16], const WideQueries<
       const float alpha = __builtin_amdgcn_exp2f(m_old - (m_new == -INFINITY ? 0.f : m_new));
       st.l[nt] *= alpha;
 #pragma unroll
-      for (int a = 0; a < D / 32; ++a) st.acc[nt][a] *= alpha;
+      for (int a = 0; a < G::kAcc; ++a) st.acc[nt][a] *= alpha;
       st.m[nt] = m_new;
     }
     const float m_use = st.m[nt] == -INFINITY ? 0.f : st.m[nt];  // rows without a visible token yet
     float psum = 0.f;
 #pragma unroll
-    for (int x = 0; x < 4; ++x) {
+    for (int y = 0; y < G::kScores / 4; ++y) {
       f32x4 vs = {1.f, 1.f, 1.f, 1.f};
-      if constexpr (kI8) vs = *(const f32x4*)&scales[32 + score_token(4 * x, h)];
+      if constexpr (kI8) vs = *(const f32x4*)&scales[32 + G::token(4 * y, h)];
 #pragma unroll
       for (int e = 0; e < 4; ++e) {
-        const int i = 4 * x + e;
+        const int i = 4 * y + e;
         const float pj = __builtin_amdgcn_exp2f(fmaf(s[nt][i], scale, -m_use));
         psum += pj;
-        pf[nt][i >> 3][i & 7] = (__bf16)(kI8 ? pj * vs[e] : pj);
+        const float z = kI8 ? pj * vs[e] : pj;
+        if constexpr (kFine) {
+          const float a = cut(z), b = cut(z - a);
+          pf[nt][i >> 3][i & 7] = (__bf16)a;
+          pr[0][nt][i >> 3][i & 7] = (__bf16)fmaxf(b, z * 0x1p-36f);
+          pr[1][nt][i >> 3][i & 7] = (__bf16)fmaxf(z - a - b, z * 0x1p-36f);
+        } else {
+          pf[nt][i >> 3][i & 7] = (__bf16)z;
+        }
       }
     }
     st.l[nt] += psum;
   }
 }
 
-template <int D, bool kI8, int NT>
-__device__ inline void wide_values(const WideBlock<D, kI8>& r, const bf16x8 (&pf)[NT][2], WideState<D, NT>& st) {
+template <int D, bool kI8, int NT, bool kFine>
+__device__ inline void wide_values(const WideBlock<D, kI8>& r, const bf16x8 (&pf)[Wide<D, kI8, NT>::kTiles][Wide<D, kI8, NT>::kProbs],
+                                   const bf16x8 (&pr)[2][Wide<D, kI8, NT>::kTiles][Wide<D, kI8, NT>::kProbs], WideState<D, kI8, NT>& st) {
+  using G = Wide<D, kI8, NT>;
+  constexpr int kFrags = kI8 ? 2 : 1;  // V fragments of a chunk
 #pragma unroll
-  for (int x = 0; x < WideBlock<D, kI8>::kChunks; ++x) {
-    constexpr int kFrags = kI8 ? 2 : 1;  // d-tiles of a chunk
+  for (int x = 0; x < G::kChunks; ++x)
 #pragma unroll
     for (int f = 0; f < kFrags; ++f) {
       bf16x8 v;
       if constexpr (kI8) v = __builtin_bit_cast(bf16x8, codes_to_bf16(r.v[x][2 * f], r.v[x][2 * f + 1]));
       else v = __builtin_bit_cast(bf16x8, r.v[x]);
 #pragma unroll
-      for (int nt = 0; nt < NT; ++nt) {
-        f32x16& acc = st.acc[nt][kFrags * (x >> 1) + f];
-        acc = __builtin_amdgcn_mfma_f32_32x32x16_bf16(v, pf[nt][x & 1], acc, 0, 0, 0);
+      for (int nt = 0; nt < G::kTiles; ++nt) {
+        typename G::Acc& acc = st.acc[nt][kFrags * (x / G::kProbs) + f];
+        if constexpr (G::kSmall) {
+          if constexpr (kFine) {
+            acc = __builtin_amdgcn_mfma_f32_16x16x32_bf16(v, pr[1][nt][0], acc, 0, 0, 0);
+            acc = __builtin_amdgcn_mfma_f32_16x16x32_bf16(v, pr[0][nt][0], acc, 0, 0, 0);
+          }
+          acc = __builtin_amdgcn_mfma_f32_16x16x32_bf16(v, pf[nt][0], acc, 0, 0, 0);
+        } else {
+          if constexpr (kFine) {
+            acc = __builtin_amdgcn_mfma_f32_32x32x16_bf16(v, pr[1][nt][x & 1], acc, 0, 0, 0);
+            acc = __builtin_amdgcn_mfma_f32_32x32x16_bf16(v, pr[0][nt][x & 1], acc, 0, 0, 0);
+          }
+          acc = __builtin_amdgcn_mfma_f32_32x32x16_bf16(v, pf[nt][x & 1], acc, 0, 0, 0);
+        }
       }
     }
-  }
 }
 
 // Merge of a unit's partials, in their order, by the workgroup that delivered the last of them: its O and lse.  Every thread has one
-// row of a tile and D / 32 quads of head elements; up to eight partials are on their way at a time.
+// row of a tile and some quads of head elements; up to four partials (16 rows: eight) are on their way at a time.
 struct WideJob {
   int b, kvh, nq, w_lo, n;
 };
 
-template <int D, int NT>
+template <int D, bool kI8, int NT>
 __device__ inline void merge_wide(const AttnParams& p, const WideJob& j, int wv, int lane) {
-  constexpr int kQuads = D / 32, kRoundW = 4;
-  const int c = lane & 31, h = lane >> 5, rows = j.nq * p.g;
+  using G = Wide<D, kI8, NT>;
+  constexpr int kTiles = G::kTiles, kQuads = D / 4 / (kWideWaves * G::kLanes), kRoundW = G::kSmall ? 8 : 4;
+  const int c = lane % G::kRows, h = lane / G::kRows, rows = j.nq * p.g;
   const int slot0 = j.w_lo + j.b * p.Hkv + j.kvh;
   const unsigned slot_bytes = (unsigned)p.rows_max * D * 4, ml_bytes = (unsigned)p.rows_max * 8;
-  float M[NT], L[NT];
-  f32x4 o[NT][kQuads];
+  float M[kTiles], L[kTiles];
+  f32x4 o[kTiles][kQuads];
 #pragma unroll
-  for (int nt = 0; nt < NT; ++nt) {
+  for (int nt = 0; nt < kTiles; ++nt) {
     M[nt] = -INFINITY;
     L[nt] = 0.f;
 #pragma unroll
     for (int k = 0; k < kQuads; ++k) o[nt][k] = f32x4{0.f, 0.f, 0.f, 0.f};
   }
+  auto quad_of = [&](int k) { return G::kLanes * (wv + kWideWaves * k) + h; };
   for (int j0 = 0; j0 < j.n; j0 += kRoundW) {
     const int n = min(j.n - j0, kRoundW);
     // partials that do not exist and idle rows: beyond the buffers, answered with zeros
     const __amdgpu_buffer_rsrc_t rs = dev_buffer(p.part_acc + (size_t)(slot0 + j0) * p.rows_max * D, (unsigned)n * slot_bytes);
     const __amdgpu_buffer_rsrc_t rs_ml = dev_buffer(p.part_ml + (size_t)(slot0 + j0) * p.rows_max * 2, (unsigned)n * ml_bytes);
-    float2 s[NT][kRoundW];
-    f32x4 a[NT][kRoundW][kQuads];
+    float2 s[kTiles][kRoundW];
+    f32x4 a[kTiles][kRoundW][kQuads];
 #pragma unroll
     for (int x = 0; x < kRoundW; ++x)
 #pragma unroll
-      for (int nt = 0; nt < NT; ++nt) {
-        const int row = 32 * nt + c;
+      for (int nt = 0; nt < kTiles; ++nt) {
+        const int row = G::kRows * nt + c;
         s[nt][x] = load_dev2(rs_ml, row < rows ? x * ml_bytes + 8u * row : kNoSuchOffset);
 #pragma unroll
         for (int k = 0; k < kQuads; ++k)
-          a[nt][x][k] = load_dev4(rs, row < rows ? x * slot_bytes + 16u * (wide_quad<D>(2 * (wv + kWideWaves * k) + h, slot0 + j0 + x) * p.rows_max + row)
-                                                 : kNoSuchOffset);
+          a[nt][x][k] = load_dev4(rs, row < rows ? x * slot_bytes + 16u * (wide_quad<D>(quad_of(k), slot0 + j0 + x) * p.rows_max + row) : kNoSuchOffset);
       }
 #pragma unroll
-    for (int nt = 0; nt < NT; ++nt) {
+    for (int nt = 0; nt < kTiles; ++nt) {
       // a valid row has a visible token (token 0) in the first partial, so M is finite from there on
       const float M_old = M[nt];
 #pragma unroll
@@ -1619,34 +1645,36 @@ __device__ inline void merge_wide(const AttnParams& p, const WideJob& j, int wv,
     }
   }
 #pragma unroll
-  for (int nt = 0; nt < NT; ++nt) {
-    const int row = 32 * nt + c;
+  for (int nt = 0; nt < kTiles; ++nt) {
+    const int row = G::kRows * nt + c;
     if (row < rows) {
       const int i = row_token(p, row), hg = row - i * p.g;
       const size_t orow = ((size_t)j.b * p.kmax + i) * p.Hq + j.kvh * p.g + hg;
       const float inv = __builtin_amdgcn_rcpf(L[nt]);
 #pragma unroll
-      for (int k = 0; k < kQuads; ++k) *(f32x4*)(p.O + orow * D + 4 * (2 * (wv + kWideWaves * k) + h)) = o[nt][k] * inv;
+      for (int k = 0; k < kQuads; ++k) *(f32x4*)(p.O + orow * D + 4 * quad_of(k)) = o[nt][k] * inv;
       if (p.lse && wv == 0 && h == 0) p.lse[orow] = (M[nt] + __builtin_amdgcn_logf(L[nt])) * 0.6931471805599453f;
     }
   }
 }
 
-template <int D, bool kI8, int NT>
+template <int D, bool kI8, int NT, bool kFine>
 __global__ __launch_bounds__(64 * kWideWaves, 1) void verify_attn_wide(AttnParams p) {
-  constexpr int W = kWideWaves, DT = D / 32, G = NT * DT;  // G accumulators of 16 registers; wavefront g % W collects number g
-  constexpr bool kMerge = NT == 1;  // units that several workgroups share are merged here, not by reduce_wide
-  constexpr int kBlkVec = WideGeometry<D, kI8>::kBlkVec;
-  constexpr int R = 2;  // blocks a wavefront has in its registers or on the way there (three: 1 - 2 us longer)
+  using G = Wide<D, kI8, NT>;
+  constexpr int W = kWideWaves, kTiles = G::kTiles, kRows = G::kRows, kQuads = G::kQuads;
+  constexpr int kAccs = kTiles * G::kAcc;  // accumulators; wavefront x % W collects number x
+  constexpr bool kMerge = NT <= 1;  // units that several workgroups share are merged here, not by reduce_wide
+  constexpr int kBlkVec = G::kBlkVec;
+    constexpr int R = 2;  // blocks a wavefront has in its registers or on the way there (three: 1 - 2 us longer)
   using Block = WideBlock<D, kI8>;
-  __shared__ f32x4 exchange[G][W - 1][4][64];
-  __shared__ float wave_m[W][NT][32], wave_l[W][NT][32];
+  __shared__ f32x4 exchange[kAccs][W - 1][kQuads][64];
+  __shared__ float wave_m[W][kTiles][kRows], wave_l[W][kTiles][kRows];
   __shared__ float scales[W][kI8 ? 64 : 1];
   __shared__ int arrived_last[2];
   __shared__ WideQueryRows<D, kI8, NT> q_lds;
   __shared__ WideNewRows<D, kI8, NT> rows_lds;
   const int tid = threadIdx.x, lane = tid & 63, wv = uniform(tid >> 6);
-  const int c = lane & 31, h = lane >> 5;
+  const int c = lane % kRows, h = lane / kRows;
   const int wg = blockIdx.x;  // the stretch of this workgroup
   const bool fused = p.Knew != nullptr;
 
@@ -1663,7 +1691,7 @@ __global__ __launch_bounds__(64 * kWideWaves, 1) void verify_attn_wide(AttnParam
   const uint4* kc = (const uint4*)p.Kc;
   const uint4* vc = (const uint4*)p.Vc;
   const float abs_scale = p.scale_log2 == 0.f ? 1.f : fabsf(p.scale_log2);
-  const int k_lane = wide_k_lane(c, h, WideGeometry<D, kI8>::kTileVec), v_lane = wide_v_lane(c, h);
+  const int k_lane = 16 * G::k_lane(lane), v_lane = 16 * G::v_lane(lane);
   // The wavefronts take the stretch's blocks in turn: this one's t-th block of the segment at hand is block turn + W t.  All fetches
   // are unconditional (exact wait counts); one past the end goes through a buffer descriptor of size zero and touches nothing.
   int turn = wv;
@@ -1675,17 +1703,17 @@ __global__ __launch_bounds__(64 * kWideWaves, 1) void verify_attn_wide(AttnParam
   auto fetch_k = [&](Block& r, const Segment& g, int t) {
     const __amdgpu_buffer_rsrc_t at = block_buffer(kc, g, t);
 #pragma unroll
-    for (int x = 0; x < Block::kChunks; ++x) r.k[x] = __builtin_amdgcn_raw_buffer_load_b128(at, 16 * k_lane, 16 * wide_k_step(x), kAuxNonTemporal);
+    for (int x = 0; x < Block::kChunks; ++x) r.k[x] = __builtin_amdgcn_raw_buffer_load_b128(at, k_lane, 16 * G::k_step(x), kAuxNonTemporal);
     if constexpr (kI8) {
       const int x = turn + W * t;
       const ptrdiff_t off = (((ptrdiff_t)g.b * p.Hkv + g.kvh) * p.nblk_cap + g.first + (x < g.n ? x : 0)) * kBlkVec;
-      r.scale = ((const float*)((h ? vc : kc) + off + 2 * D))[c];
+      r.scale = ((const float*)((lane < 32 ? kc : vc) + off + 2 * D))[lane % 32];
     }
   };
   auto fetch_v = [&](Block& r, const Segment& g, int t) {
     const __amdgpu_buffer_rsrc_t at = block_buffer(vc, g, t);
 #pragma unroll
-    for (int x = 0; x < Block::kChunks; ++x) r.v[x] = __builtin_amdgcn_raw_buffer_load_b128(at, 16 * v_lane, 16 * wide_v_step(x), kAuxNonTemporal);
+    for (int x = 0; x < Block::kChunks; ++x) r.v[x] = __builtin_amdgcn_raw_buffer_load_b128(at, v_lane, 16 * G::v_step(x), kAuxNonTemporal);
   };
 
   // Fused append: the new rows whose blocks are ours go into LDS and into the cache (nothing but the new rows is written: other
@@ -1771,7 +1799,7 @@ __global__ __launch_bounds__(64 * kWideWaves, 1) void verify_attn_wide(AttnParam
   begin(seg);
   for (int si = 0;; ++si) {
     const Unit u = unit_of(seg);
-    const int rows = u.nq * p.g, tiles = (rows + 31) / 32;
+    const int rows = u.nq * p.g, tiles = (rows + kRows - 1) / kRows;
     const int first_mine = turn, n_mine = (seg.n - turn + W - 1) / W;  // 0 for n <= turn
     commit_wide_queries<D, kI8, NT>(p, u, tid, raw_q, q_lds);
     if (fused && new_rows_of(seg) > 0) {
@@ -1784,15 +1812,15 @@ __global__ __launch_bounds__(64 * kWideWaves, 1) void verify_attn_wide(AttnParam
     __syncthreads();
     WideQueries<D, kI8, NT> q;
     read_wide_queries<D, kI8, NT>(p, u, c, h, q_lds, q);
-    WideState<D, NT> st;
+    WideState<D, kI8, NT> st;
 #pragma unroll
-    for (int nt = 0; nt < NT; ++nt) {
+    for (int nt = 0; nt < kTiles; ++nt) {
       st.m[nt] = -INFINITY;
       st.l[nt] = 0.f;
 #pragma unroll
-      for (int a = 0; a < DT; ++a)
+      for (int a = 0; a < G::kAcc; ++a)
 #pragma unroll
-        for (int i = 0; i < 16; ++i) st.acc[nt][a][i] = 0.f;
+        for (int i = 0; i < 4 * kQuads; ++i) st.acc[nt][a][i] = 0.f;
     }
     auto step = [&](Block& r, int t) {
       const int tok0 = (seg.first + first_mine + W * t) * kBlockTokens;
@@ -1801,17 +1829,17 @@ __global__ __launch_bounds__(64 * kWideWaves, 1) void verify_attn_wide(AttnParam
       if (fused && !plain) patch_wide<D, kI8, NT>(r, tok0, u.L, u.nq, lane, rows_lds);
       float* sc = scales[wv];
       if constexpr (kI8) {
-        sc[lane] = (h && tok0 + c >= u.L + u.nq) ? 0.f : r.scale;  // stale tokens may carry any V scale
+        sc[lane] = (lane >= 32 && tok0 + lane - 32 >= u.L + u.nq) ? 0.f : r.scale;  // stale tokens may carry any V scale
         __builtin_amdgcn_wave_barrier();  // a wavefront's LDS accesses stay in order
       }
-      float s[NT][16];
+      float s[kTiles][G::kScores];
       wide_scores<D, kI8, NT>(r, q, h, sc, s);
       fetch_k(r, seg, t + R);
-      if (!plain) mask_wide<D, kI8, NT>(s, r, q, tok0, u.L + u.nq, h);
-      bf16x8 pf[NT][2];
-      wide_softmax<D, kI8, NT>(s, q, st, abs_scale, h, sc, pf);
+      if (!plain) mask_wide<D, kI8, NT>(r, s, q, tok0, u.L + u.nq, h);
+      bf16x8 pf[kTiles][G::kProbs], pr[2][kTiles][G::kProbs];
+      wide_softmax<D, kI8, NT, kFine>(s, q, st, abs_scale, h, sc, pf, pr);
       if constexpr (kI8) __builtin_amdgcn_wave_barrier();
-      wide_values<D, kI8, NT>(r, pf, st);
+      wide_values<D, kI8, NT, kFine>(r, pf, pr, st);
       fetch_v(r, seg, t + R);
     };
     for (int t = 0; t < n_mine; t += R) {
@@ -1834,17 +1862,17 @@ __global__ __launch_bounds__(64 * kWideWaves, 1) void verify_attn_wide(AttnParam
     // merge of the four wavefronts' states: M = max m_w, weights 2^(m_w - M) (a wavefront that saw no visible token has m = -inf
     // and weight 0)
 #pragma unroll
-    for (int nt = 0; nt < NT; ++nt) {
-      const float l = rows2_sum(st.l[nt]);
+    for (int nt = 0; nt < kTiles; ++nt) {
+      const float l = G::row_sum(st.l[nt]);
       if (h == 0) {
         wave_m[wv][nt][c] = st.m[nt];
         wave_l[wv][nt][c] = l;
       }
     }
     __syncthreads();
-    float M[NT], sum[NT], mine[NT];
+    float M[kTiles], sum[kTiles], mine[kTiles];
 #pragma unroll
-    for (int nt = 0; nt < NT; ++nt) {
+    for (int nt = 0; nt < kTiles; ++nt) {
       M[nt] = -INFINITY;
       sum[nt] = 0.f;
 #pragma unroll
@@ -1854,15 +1882,18 @@ __global__ __launch_bounds__(64 * kWideWaves, 1) void verify_attn_wide(AttnParam
       for (int w = 0; w < W; ++w) sum[nt] += wave_l[w][nt][c] * __builtin_amdgcn_exp2f(wave_m[w][nt][c] - Mf);
       mine[nt] = __builtin_amdgcn_exp2f(st.m[nt] - Mf);
     }
+    auto quad = [&](int x, int y) {
+      const typename G::Acc& t = st.acc[x / G::kAcc][x % G::kAcc];
+      return f32x4{t[4 * y], t[4 * y + 1], t[4 * y + 2], t[4 * y + 3]};
+    };
 #pragma unroll
-    for (int g = 0; g < G; ++g) {
-      const int nt = g / DT, a = g % DT, owner = g % W;
+    for (int x = 0; x < kAccs; ++x) {
+      const int nt = x / G::kAcc, owner = x % W;
       if (nt > 0 && nt >= tiles) break;
-      st.acc[nt][a] *= mine[nt];
+      st.acc[nt][x % G::kAcc] *= mine[nt];
       if (wv != owner) {
 #pragma unroll
-        for (int x = 0; x < 4; ++x)
-          exchange[g][wv < owner ? wv : wv - 1][x][lane] = f32x4{st.acc[nt][a][4 * x], st.acc[nt][a][4 * x + 1], st.acc[nt][a][4 * x + 2], st.acc[nt][a][4 * x + 3]};
+        for (int y = 0; y < kQuads; ++y) exchange[x][wv < owner ? wv : wv - 1][y][lane] = quad(x, y);
       }
     }
     __syncthreads();
@@ -1870,33 +1901,32 @@ __global__ __launch_bounds__(64 * kWideWaves, 1) void verify_attn_wide(AttnParam
     const size_t slot = (size_t)wg + (size_t)done.b * p.Hkv + done.kvh;
     const __amdgpu_buffer_rsrc_t rs = dev_buffer(p.part_acc + slot * p.rows_max * D, (unsigned)p.rows_max * D * 4);
 #pragma unroll
-    for (int g = 0; g < G; ++g) {
-      const int nt = g / DT, a = g % DT;
-      if (wv != g % W) continue;
+    for (int x = 0; x < kAccs; ++x) {
+      const int nt = x / G::kAcc, a = x % G::kAcc;
+      if (wv != x % W) continue;
       if (nt > 0 && nt >= tiles) break;
-      const int rrow = 32 * nt + c, i = row_token(p, rrow), hg = rrow - i * p.g;
+      const int rrow = kRows * nt + c, i = row_token(p, rrow), hg = rrow - i * p.g;
       const size_t orow = ((size_t)done.b * p.kmax + i) * p.Hq + done.kvh * p.g + hg;
-      const float inv = __builtin_amdgcn_rcpf(sum[nt]);
-      f32x4 v[4];
+      f32x4 v[kQuads];
 #pragma unroll
-      for (int x = 0; x < 4; ++x) {
-        v[x] = f32x4{st.acc[nt][a][4 * x], st.acc[nt][a][4 * x + 1], st.acc[nt][a][4 * x + 2], st.acc[nt][a][4 * x + 3]};
+      for (int y = 0; y < kQuads; ++y) {
+        v[y] = quad(x, y);
 #pragma unroll
-        for (int w = 0; w < W; ++w)
-          if (w != g % W) v[x] += exchange[g][w < g % W ? w : w - 1][x][lane];
+        for (int w = 0; w < W - 1; ++w) v[y] += exchange[x][w][y][lane];
       }
       if (rrow < rows) {
         if (solo) {
+          const float inv = __builtin_amdgcn_rcpf(sum[nt]);
 #pragma unroll
-          for (int x = 0; x < 4; ++x) *(f32x4*)(p.O + orow * D + wide_elem<kI8>(a, x, h)) = v[x] * inv;
+          for (int y = 0; y < kQuads; ++y) *(f32x4*)(p.O + orow * D + G::elem(a, y, h)) = v[y] * inv;
         } else {
 #pragma unroll
-          for (int x = 0; x < 4; ++x) store_dev4(rs, (unsigned)(wide_quad<D>(wide_elem<kI8>(a, x, h) / 4, (int)slot) * p.rows_max + rrow) * 16, v[x]);
+          for (int y = 0; y < kQuads; ++y) store_dev4(rs, (unsigned)(wide_quad<D>(G::elem(a, y, h) / 4, (int)slot) * p.rows_max + rrow) * 16, v[y]);
         }
-      }
-      if (a == 0 && h == 0 && rrow < rows) {
-        if (!solo) store_dev(p.part_ml + (slot * p.rows_max + rrow) * 2, M[nt], sum[nt]);
-        else if (p.lse) p.lse[orow] = (M[nt] + __builtin_amdgcn_logf(sum[nt])) * 0.6931471805599453f;
+        if (a == 0 && h == 0) {
+          if (!solo) store_dev(p.part_ml + (slot * p.rows_max + rrow) * 2, M[nt], sum[nt]);
+          else if (p.lse) p.lse[orow] = (M[nt] + __builtin_amdgcn_logf(sum[nt])) * 0.6931471805599453f;
+        }
       }
     }
     if (kMerge && (done.flags & kSegLast)) {  // query slots beyond draft_len are zero in O and lse
@@ -1928,8 +1958,8 @@ __global__ __launch_bounds__(64 * kWideWaves, 1) void verify_attn_wide(AttnParam
     arrived_last[tid] = last;
   }
   __syncthreads();
-  if (uniform(arrived_last[0])) merge_wide<D, NT>(p, job_a, wv, lane);
-  if (shared > 1 && uniform(arrived_last[1])) merge_wide<D, NT>(p, job_b, wv, lane);
+  if (uniform(arrived_last[0])) merge_wide<D, kI8, NT>(p, job_a, wv, lane);
+  if (shared > 1 && uniform(arrived_last[1])) merge_wide<D, kI8, NT>(p, job_b, wv, lane);
 }
 
 // ---------------------------------------------------------------------------------------
@@ -2509,13 +2539,12 @@ static int check_attention_args(const bass_attn_desc* d, const LaunchShape& ls, 
 
 // The workgroup-level kernels.
 template <int D, bool kI8>
-static void launch_wide(dim3 grid, hipStream_t s, const AttnParams& p) {
+static void launch_wide(bool few, dim3 grid, hipStream_t s, const AttnParams& p) {
   const dim3 block(64 * kWideWaves);
-  if (p.rows_max <= 32) {
-    hipLaunchKernelGGL((verify_attn_wide<D, kI8, 1>), grid, block, 0, s, p);
-  } else {
-    hipLaunchKernelGGL((verify_attn_wide<D, kI8, 2>), grid, block, 0, s, p);
-  }
+  if (p.rows_max > 32) hipLaunchKernelGGL((verify_attn_wide<D, kI8, 2, false>), grid, block, 0, s, p);
+  else if (p.rows_max > 16) hipLaunchKernelGGL((verify_attn_wide<D, kI8, 1, false>), grid, block, 0, s, p);
+  else if (few) hipLaunchKernelGGL((verify_attn_wide<D, kI8, 0, true>), grid, block, 0, s, p);
+  else hipLaunchKernelGGL((verify_attn_wide<D, kI8, 0, false>), grid, block, 0, s, p);
 }
 
 template <bool kFused>
@@ -2564,36 +2593,32 @@ static int launch_attention(const bass_attn_desc* d, const LaunchShape& ls, cons
   const dim3 grid(p.nwaves / p.wpw), block(64 * p.wpw);
   if (d->dtype == BASS_DTYPE_FP32) {
     hipLaunchKernelGGL(verify_attn_fp32, grid, block, 0, s, p);
-  } else if (ls.tiles && !ls.wide) {
+  } else if (ls.wide) {
+    const dim3 wgrid((unsigned)ls.used_shares);
+    const bool few = may_be_few(plan_shape(d, ls, 0));
+    if (d->dtype == BASS_DTYPE_INT8KV) {
+      if (d->D == 128) launch_wide<128, true>(few, wgrid, s, p);
+      else launch_wide<64, true>(few, wgrid, s, p);
+    } else {
+      if (d->D == 128) launch_wide<128, false>(few, wgrid, s, p);
+      else launch_wide<64, false>(few, wgrid, s, p);
+    }
+  } else if (ls.tiles) {
     const dim3 tgrid((unsigned)ls.used_shares);
     if (K_new) launch_tiles<true>(d, tgrid, s, p);
     else launch_tiles<false>(d, tgrid, s, p);
-  } else if (ls.tiles) {
-    const dim3 tgrid((unsigned)ls.used_shares);
-    if (d->dtype == BASS_DTYPE_INT8KV) {
-      if (d->D == 128) launch_wide<128, true>(tgrid, s, p);
-      else launch_wide<64, true>(tgrid, s, p);
-    } else {
-      if (d->D == 128) launch_wide<128, false>(tgrid, s, p);
-      else launch_wide<64, false>(tgrid, s, p);
-    }
   } else {  // one query tile
     // LDS slice per wavefront of a fused append: K and V rows of two units (bf16, or INT8 codes + scales)
     const size_t unit_lds = d->dtype == BASS_DTYPE_INT8KV ? (size_t)2 * d->kmax * d->D + 8 * d->kmax
                                                           : (size_t)2 * d->kmax * d->D * 2;
     const size_t lds = K_new ? (size_t)p.wpw * 2 * unit_lds : 0;
-    const bool few = may_be_few(plan_shape(d, ls, 0));
-#define BASS_LAUNCH(DD, I8)                                                                          \
-  do {                                                                                               \
-    if (few) hipLaunchKernelGGL((verify_attn_bf16<DD, I8, true>), grid, block, lds, s, p);        \
-    else hipLaunchKernelGGL((verify_attn_bf16<DD, I8, false>), grid, block, lds, s, p);           \
-  } while (0)
     if (d->dtype == BASS_DTYPE_INT8KV) {
-      if (d->D == 128) BASS_LAUNCH(128, true); else BASS_LAUNCH(64, true);
+      if (d->D == 128) hipLaunchKernelGGL((verify_attn_bf16<128, true>), grid, block, lds, s, p);
+      else hipLaunchKernelGGL((verify_attn_bf16<64, true>), grid, block, lds, s, p);
     } else {
-      if (d->D == 128) BASS_LAUNCH(128, false); else BASS_LAUNCH(64, false);
+      if (d->D == 128) hipLaunchKernelGGL((verify_attn_bf16<128, false>), grid, block, lds, s, p);
+      else hipLaunchKernelGGL((verify_attn_bf16<64, false>), grid, block, lds, s, p);
     }
-#undef BASS_LAUNCH
   }
   if (launch_status() != BASS_OK) return BASS_ERR_HIP;
   if (ls.tiles && rows_max > 32) {

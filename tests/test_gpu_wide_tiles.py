@@ -58,3 +58,20 @@ def test_negative_scale_is_negative_queries(dtype, D, Hq, kmax):
         out.append((O, lse))
     assert torch.equal(out[0][0], out[1][0]) and torch.equal(out[0][1], out[1][1])
     assert out[0][0].isfinite().all() and out[0][0].abs().sum() > 0
+
+
+@pytest.mark.parametrize("dtype", ["bf16", "int8kv"])
+@pytest.mark.parametrize("D,g,kmax", [(128, 1, 16), (128, 4, 3), (64, 2, 8), (64, 1, 1)])
+@pytest.mark.parametrize("Hkv", [80, 81])  # one workgroup per stretch of the list, one wavefront
+def test_units_at_the_edge_of_one_tile(dtype, D, g, kmax, Hkv):
+    from paper_2404_15778_amd import harness
+    from oracle.kv_int8 import dequantize_rows, quantize_rows
+    w = wl.make_attention("narrow", 1, g * Hkv, Hkv, D, "bf16", [333], [kmax], 7, kmax=kmax, Lcap=333 + kmax)
+    Q, K, V = w.Q, w.K, w.V
+    if dtype == "int8kv":
+        Q, K, V = (dequantize_rows(*quantize_rows(wl.bf16_bits_to_f32(x))) for x in (Q, K, V))
+        w.dtype = dtype
+    Or, lser = oracle.verify_attention(Q, K, V, w.ctx_len, w.draft_len, w.scale)
+    for fused in (False, True):
+        O, lse, status, _ = harness.run_attention_workload(w, poison=True, fused=fused)
+        assert status == 0 and np.abs(O - Or).max() <= TOL and np.abs(lse - lser).max() <= TOL
