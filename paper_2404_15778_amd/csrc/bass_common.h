@@ -190,17 +190,17 @@ inline LaunchShape launch_shape(const bass_attn_desc* d, bool append) {
   const bool int8 = d->dtype == BASS_DTYPE_INT8KV;
   s.tiles = s.mfma && s.rows_max > 16;
   s.fused_append = append && (d->dtype == BASS_DTYPE_FP32 || (int64_t)d->kmax * d->D <= kMaxStagedElems);
-  // A patch costs a workgroup about 3 us, one after the other for each of its units; an append by itself goes by cache blocks
-  // from kBlockTokens slots on, which takes a 32-slot call 5 - 10 us.  Inside the launch / before it, us, head size 128, 32 and 64
-  // rows, 32 heads: 8 sequences (256 units) of 500 tokens, bf16 28.3 / 29.1 and 34.7 / 34.7, INT8 33.3 / 33.0 and 39.8 / 38.2; 32
-  // sequences 92.9 / 84.5 and 121.3 / 106.7, 66.1 / 62.8 and 99.1 / 88.2; 20 rows, which an append takes one by one, 8 and 32
-  // sequences: bf16 25.9 / 32.9 and 85.6 / 93.3.
-  s.tiles_append = append && s.tiles && !s.fused_append && (d->kmax < kBlockTokens || d->B * d->Hkv <= kTileShares);
   // (a launch wider than the shares it aims at, with all shares equally long -- plan_split -- was measured
   // 1 - 2 % slower than the even division on the benchmark shapes: more wavefronts, more partials to merge)
   s.nwaves = attention_waves(setting);
   s.narrow = s.mfma && !s.tiles && setting <= 0 && d->B * d->Hkv <= kNarrowUnits;
   s.wide = s.narrow || (s.tiles && (s.rows_max <= 32 || num_blocks(d->Lcap) > kShortCache));
+  // Longer drafts than the wavefronts stage: a patch costs a workgroup 1 - 3 us, one after the other for each of its units; an append by
+  // itself goes by cache blocks from kBlockTokens slots on, which takes a 32-slot call 5 - 10 us.  Before the launch / inside it, us,
+  // 32 rows, 32 heads of 128, 16 sequences of 100 / 450 / 1200 tokens, 32 of 450, 12 of 2000: verify_attn_wide, bf16 30.4 / 45.9 / 79.8 / 75.1 /
+  // 90.6 -> 29.9 / 42.9 / 77.7 / 73.6 / 89.1: inside; INT8 29.8 / 37.6 / 54.9 / 57.9 / 59.0 -> 30.3 / 39.0 / 54.2 / 60.1 / 56.6: only up to 256
+  // units, as in the kernels that share rows (64 rows, 8 sequences of 500, 34.7 / 34.7, 32 sequences 121.3 / 106.7).
+  s.tiles_append = append && s.tiles && !s.fused_append && (d->kmax < kBlockTokens || d->B * d->Hkv <= kTileShares || (s.wide && !int8));
   // the workgroup-level kernels take one stretch per workgroup: half as many as an explicit setting has wavefronts
   const int stretches = setting > 0 ? s.nwaves / 2 : (int8 ? kRowSharesInt8 : kRowShares);
   s.used_shares = s.narrow ? kNarrowShares : !s.tiles ? s.nwaves : s.wide && setting <= 0 ? kTileShares : stretches;
