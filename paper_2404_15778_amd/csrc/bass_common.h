@@ -142,7 +142,10 @@ constexpr int kShortCache = 24;
 // 7 virtual blocks per unit 769 / 758 / 758 us, 8 sequences, 32 heads, 32 rows 765 / 751 / 745.  Short lists go to fewer workgroups so that
 // every wavefront has a block: 1 sequence of 1000 tokens, 64 rows, 8 kv heads, with at least 1 / 4 / 8 / 12 entries per share 26.5 / 17.8 / 18.0 /
 // 20.8 us; from 8 on a wavefront's state spans several blocks, fewer probabilities are exactly 1 and precision is lost.
-constexpr int kTileShares = 256;
+// Two where two fit (at most 32 rows of 64 elements) and the units are many: 256 units of 32 rows, 512 - 2048 tokens, INT8 23.6 -> 20.7, bf16
+// 25.7 -> 25.6; of 24 rows, 100 - 400 tokens, 15.9 -> 12.6 and 14.7 -> 13.2; 64 - 128 units 0 - 8 % longer.  Up to 1024 units: more
+// stretches need more scratch memory, which bass_verify_attention_noalloc has only so much of.  (INT8 heads of 128 held to the registers of two: short lists of 512 units 33.9 -> 29.7, but one workgroup alone 5 - 8 % longer.)
+constexpr int kTileShares = 256, kTwoUnits = 256;
 constexpr int kWidePad = 7, kWideEntries = 4;
 // At most 16 query rows: up to this many units (sequence, kv head) take verify_attn_wide too, with a tile of 16 rows; more of them stay with a
 // wavefront per share (verify_attn_bf16), where a unit's merge costs no workgroup barrier.  8 query rows, a wavefront per share -> a
@@ -203,8 +206,9 @@ inline LaunchShape launch_shape(const bass_attn_desc* d, bool append) {
   s.tiles_append = append && s.tiles && !s.fused_append && (d->kmax < kBlockTokens || d->B * d->Hkv <= kTileShares || (s.wide && !int8));
   // the workgroup-level kernels take one stretch per workgroup: half as many as an explicit setting has wavefronts
   const int stretches = setting > 0 ? s.nwaves / 2 : (int8 ? kRowSharesInt8 : kRowShares);
-  s.used_shares = s.narrow ? kNarrowShares : !s.tiles ? s.nwaves : s.wide && setting <= 0 ? kTileShares : stretches;
-  s.nshares = !s.tiles ? s.nwaves : int8 ? 2 * stretches : stretches;
+  const bool two = s.rows_max <= 32 && d->D == 64 && d->B * d->Hkv >= kTwoUnits && d->B * d->Hkv <= 4 * kTwoUnits;
+  s.used_shares = s.narrow ? kNarrowShares : !s.tiles ? s.nwaves : s.wide && setting <= 0 ? (two ? 2 * kTileShares : kTileShares) : stretches;
+  s.nshares = !s.tiles ? s.nwaves : int8 ? 2 * stretches : s.wide && two && setting <= 0 ? s.used_shares : stretches;
   s.target = s.nshares;
   s.pad = s.narrow ? kNarrowPad : s.wide ? kWidePad : s.fused_append ? kAppendPad : kPlainPad;
   s.min_entries = setting > 0 || !s.wide ? 0 : s.narrow ? kNarrowEntries : kWideEntries;
