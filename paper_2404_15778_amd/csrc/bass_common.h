@@ -144,7 +144,8 @@ constexpr int kShortCache = 24;
 // 20.8 us; from 8 on a wavefront's state spans several blocks, fewer probabilities are exactly 1 and precision is lost.
 // Two where two fit (at most 32 rows of 64 elements) and the units are many: 256 units of 32 rows, 512 - 2048 tokens, INT8 23.6 -> 20.7, bf16
 // 25.7 -> 25.6; of 24 rows, 100 - 400 tokens, 15.9 -> 12.6 and 14.7 -> 13.2; 64 - 128 units 0 - 8 % longer.  Up to 1024 units: more
-// stretches need more scratch memory, which bass_verify_attention_noalloc has only so much of.  (INT8 heads of 128 held to the registers of two: short lists of 512 units 33.9 -> 29.7, but one workgroup alone 5 - 8 % longer.)
+// stretches need more scratch memory, and bass_verify_attention_noalloc has only so much of it.  (INT8 heads of 128 held to the registers of
+// two: short lists of 512 units 33.9 -> 29.7, but one workgroup alone 5 - 8 % longer.)
 constexpr int kTileShares = 256, kTwoUnits = 256;
 constexpr int kWidePad = 7, kWideEntries = 4;
 // At most 16 query rows: up to this many units (sequence, kv head) take verify_attn_wide too, with a tile of 16 rows; more of them stay with a
