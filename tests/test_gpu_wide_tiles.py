@@ -75,3 +75,21 @@ def test_units_at_the_edge_of_one_tile(dtype, D, g, kmax, Hkv):
     for fused in (False, True):
         O, lse, status, _ = harness.run_attention_workload(w, poison=True, fused=fused)
         assert status == 0 and np.abs(O - Or).max() <= TOL and np.abs(lse - lser).max() <= TOL
+
+
+@pytest.mark.parametrize("dtype", ["bf16", "int8kv"])
+@pytest.mark.parametrize("D,g,kmax,B,Hkv", [(64, 4, 8, 3, 85), (64, 3, 8, 4, 64), (64, 2, 10, 32, 32), (64, 2, 10, 25, 41),  # 255, 256, 1024, 1025 units
+                                            (128, 6, 6, 4, 16), (128, 8, 8, 5, 13)])  # 64 and 65: a row merged in four parts or in one
+def test_units_at_the_edge_of_several_tiles(dtype, D, g, kmax, B, Hkv):
+    from paper_2404_15778_amd import harness
+    from oracle.kv_int8 import dequantize_rows, quantize_rows
+    ctx = [(333, 820, 0, 31)[b % 4] if B < 9 else (70, 33, 0, 129, 12)[b % 5] for b in range(B)]
+    w = wl.make_attention("units", B, g * Hkv, Hkv, D, "bf16", ctx, [kmax - b % 3 for b in range(B)], 11, kmax=kmax, Lcap=820 + kmax)
+    Q, K, V = w.Q, w.K, w.V
+    if dtype == "int8kv":
+        Q, K, V = (dequantize_rows(*quantize_rows(wl.bf16_bits_to_f32(x))) for x in (Q, K, V))
+        w.dtype = dtype
+    Or, lser = oracle.verify_attention(Q, K, V, w.ctx_len, w.draft_len, w.scale)
+    for fused in (False, True):
+        O, lse, status, _ = harness.run_attention_workload(w, poison=True, fused=fused)
+        assert status == 0 and np.abs(O - Or).max() <= TOL and np.abs(lse - lser).max() <= TOL
