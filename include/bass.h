@@ -327,12 +327,14 @@ int32_t bass_next_draft_len(bass_draft_len_state* state, const int32_t* n_accept
  * flattened (sequence, kv-head, context-block) work over.  Values are clamped to [64, 8192] and rounded down to a
  * multiple of 4; 0 restores the defaults:
  *   up to 16 query rows per kv head, and fp32 caches: 768 wavefronts, as 256 workgroups of three, one per compute
- *     unit (every other count: workgroups of four);
- *   more, bf16 caches: 256 workgroups, of four wavefronts with up to 32 rows and of eight with more;
- *   more, INT8 caches: 512 workgroups of four wavefronts.
- * A setting W gives W wavefronts in the first case and W / 2 workgroups in the others.  Any setting but 0, also 768, divides
- * every list of blocks over all shares; by default short lists over bf16 and INT8 caches go to fewer (up to 16 query rows per
- * kv head), where what the rounding of the probabilities to bf16 left over is multiplied as well: a setting so changes the
+ *     unit (every other count: workgroups of four); at most 80 (sequence, kv head) pairs over bf16 and INT8 caches: 256
+ *     workgroups of four wavefronts, of which short lists use fewer;
+ *   more query rows: 256 workgroups of four wavefronts (512 for 256 to 1024 pairs with heads of 64 and at most 32 rows), of
+ *     which short lists use fewer; caches of at most 24 blocks of 32 tokens with more than 32 rows: 256 workgroups of eight
+ *     wavefronts, INT8 512 of four.
+ * A setting W gives W wavefronts in the first case and W / 2 workgroups with more rows.  Any setting but 0, also 768, divides
+ * every list of blocks over all shares.  For shapes of at most 80 pairs whose lists may go to fewer
+ * workgroups, what the rounding of the probabilities to bf16 left over is multiplied as well: a setting so changes the
  * rounding, within the same tolerance, besides the time.  Returns the value in effect for the first case.
  */
 int bass_set_attention_waves(int waves);
