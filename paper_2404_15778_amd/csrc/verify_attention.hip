@@ -1482,7 +1482,7 @@ __device__ inline void mask_wide(WideBlock<D, kI8>& r, float (&s)[Wide<D, kI8, N
 // zero where the probability is not, so that an infinite element of V stays infinite in every product.  (Two parts leave 2^-17: 3.6e-6
 // instead of 2.3e-6 with a rounded first part, whose remainder may be negative.)
 template <int D, bool kI8, int NT, bool kFine>
-__device__ inline void wide_softmax(const float (&s)[Wide<D, kI8, NT>::kTiles][Wide<D, kI8, NT>::kScores], const WideQueries<D, kI8, NT>& q,
+__device__ inline void wide_softmax(const WideQueries<D, kI8, NT>& q, float (&s)[Wide<D, kI8, NT>::kTiles][Wide<D, kI8, NT>::kScores],
                                     WideState<D, kI8, NT>& st, float abs_scale_log2, int h, const float* scales,
                                     bf16x8 (&pf)[Wide<D, kI8, NT>::kTiles][Wide<D, kI8, NT>::kProbs],
                                     bf16x8 (&pr)[2][Wide<D, kI8, NT>::kTiles][Wide<D, kI8, NT>::kProbs]) {
@@ -1491,10 +1491,16 @@ __device__ inline void wide_softmax(const float (&s)[Wide<D, kI8, NT>::kTiles][W
 #pragma unroll
   for (int nt = 0; nt < G::kTiles; ++nt) {
     const float scale = kI8 ? q.row_scale[nt] : abs_scale_log2;  // > 0
+    {  // A product of its own, rounded as the maximum is: in one step with the subtraction below the largest probability is not 1 but 2
+       // to the power of what the rounding took from m, which costs precision from 2^10 on and is not finite from 2^31 on.
+#pragma clang fp contract(off)
+#pragma unroll
+      for (int i = 0; i < G::kScores; ++i) s[nt][i] *= scale;
+    }
     float mx = s[nt][0];
 #pragma unroll
     for (int i = 1; i < G::kScores; ++i) mx = fmaxf(mx, s[nt][i]);
-    mx = G::row_max(mx) * scale;
+    mx = G::row_max(mx);
     // The reference maximum of a row moves only when a block exceeds it by more than kMaxSlack (log2 units).
     const float m_old = st.m[nt];
     const bool grow = mx > m_old + kMaxSlack;
@@ -1515,7 +1521,7 @@ __device__ inline void wide_softmax(const float (&s)[Wide<D, kI8, NT>::kTiles][W
 #pragma unroll
       for (int e = 0; e < 4; ++e) {
         const int i = 4 * y + e;
-        const float pj = __builtin_amdgcn_exp2f(fmaf(s[nt][i], scale, -m_use));
+        const float pj = __builtin_amdgcn_exp2f(s[nt][i] - m_use);
         psum += pj;
         const float z = kI8 ? pj * vs[e] : pj;
         if constexpr (kFine) {
@@ -1818,7 +1824,7 @@ __global__ __launch_bounds__(64 * kWideWaves, 1) void verify_attn_wide(AttnParam
       fetch_k(r, seg, t + R);
       if (!plain) mask_wide<D, kI8, NT>(r, s, q, tok0, u.L + u.nq, h);
       bf16x8 pf[kTiles][G::kProbs], pr[2][kTiles][G::kProbs];
-      wide_softmax<D, kI8, NT, kFine>(s, q, st, abs_scale, h, sc, pf, pr);
+      wide_softmax<D, kI8, NT, kFine>(q, s, st, abs_scale, h, sc, pf, pr);
       if constexpr (kI8) __builtin_amdgcn_wave_barrier();
       wide_values<D, kI8, NT, kFine>(r, pf, pr, st);
       fetch_v(r, seg, t + R);
