@@ -1398,9 +1398,10 @@ __device__ inline void patch_wide(WideBlock<D, kI8>& r, int tok0, int L, int nq,
     }
 }
 
-// Scores of a block (INT8: integer products times the tokens' K scales; the rows' scales follow in wide_softmax).
+// Scores of a block in log2 units.  INT8: integer products times the product of the token's and the row's scale, which is in range
+// where the scales and the integers one after the other need not be.
 template <int D, bool kI8, int NT>
-__device__ inline void wide_scores(const WideBlock<D, kI8>& r, const WideQueries<D, kI8, NT>& q, int h, const float* scales,
+__device__ inline void wide_scores(const WideBlock<D, kI8>& r, const WideQueries<D, kI8, NT>& q, float abs_scale_log2, int h, const float* scales,
                                    float (&s)[Wide<D, kI8, NT>::kTiles][Wide<D, kI8, NT>::kScores]) {
   using G = Wide<D, kI8, NT>;
   constexpr int n = G::kQuerySteps;
@@ -1440,13 +1441,15 @@ __device__ inline void wide_scores(const WideBlock<D, kI8>& r, const WideQueries
 #pragma unroll
       for (int i = 0; i < 16; ++i) s[nt][i] = z[i];
     }
-    if constexpr (kI8) {
+    // A rounded product, as the maximum is: fused with the subtraction of the maximum, the largest probability would not be 1 but 2 to
+    // the power of what the rounding took from the maximum, which costs precision from 2^10 on and is not finite from 2^31 on.
 #pragma unroll
-      for (int y = 0; y < G::kScores / 4; ++y) {
-        const f32x4 ks = *(const f32x4*)&scales[G::token(4 * y, h)];
+    for (int y = 0; y < G::kScores / 4; ++y) {
+#pragma clang fp contract(off)
+      f32x4 scale = {abs_scale_log2, abs_scale_log2, abs_scale_log2, abs_scale_log2};
+      if constexpr (kI8) scale = *(const f32x4*)&scales[G::token(4 * y, h)] * q.row_scale[nt];
 #pragma unroll
-        for (int e = 0; e < 4; ++e) s[nt][4 * y + e] *= ks[e];
-      }
+      for (int e = 0; e < 4; ++e) s[nt][4 * y + e] *= scale[e];
     }
   }
 }
@@ -1482,21 +1485,13 @@ __device__ inline void mask_wide(WideBlock<D, kI8>& r, float (&s)[Wide<D, kI8, N
 // zero where the probability is not, so that an infinite element of V stays infinite in every product.  (Two parts leave 2^-17: 3.6e-6
 // instead of 2.3e-6 with a rounded first part, whose remainder may be negative.)
 template <int D, bool kI8, int NT, bool kFine>
-__device__ inline void wide_softmax(const WideQueries<D, kI8, NT>& q, float (&s)[Wide<D, kI8, NT>::kTiles][Wide<D, kI8, NT>::kScores],
-                                    WideState<D, kI8, NT>& st, float abs_scale_log2, int h, const float* scales,
+__device__ inline void wide_softmax(const float (&s)[Wide<D, kI8, NT>::kTiles][Wide<D, kI8, NT>::kScores], WideState<D, kI8, NT>& st, int h, const float* scales,
                                     bf16x8 (&pf)[Wide<D, kI8, NT>::kTiles][Wide<D, kI8, NT>::kProbs],
                                     bf16x8 (&pr)[2][Wide<D, kI8, NT>::kTiles][Wide<D, kI8, NT>::kProbs]) {
   using G = Wide<D, kI8, NT>;
   auto cut = [](float z) { return __uint_as_float(__float_as_uint(z) & 0xFFFF0000u); };
 #pragma unroll
   for (int nt = 0; nt < G::kTiles; ++nt) {
-    const float scale = kI8 ? q.row_scale[nt] : abs_scale_log2;  // > 0
-    {  // A product of its own, rounded as the maximum is: in one step with the subtraction below the largest probability is not 1 but 2
-       // to the power of what the rounding took from m, which costs precision from 2^10 on and is not finite from 2^31 on.
-#pragma clang fp contract(off)
-#pragma unroll
-      for (int i = 0; i < G::kScores; ++i) s[nt][i] *= scale;
-    }
     float mx = s[nt][0];
 #pragma unroll
     for (int i = 1; i < G::kScores; ++i) mx = fmaxf(mx, s[nt][i]);
@@ -1820,11 +1815,11 @@ __global__ __launch_bounds__(64 * kWideWaves, 1) void verify_attn_wide(AttnParam
         __builtin_amdgcn_wave_barrier();  // a wavefront's LDS accesses stay in order
       }
       float s[kTiles][G::kScores];
-      wide_scores<D, kI8, NT>(r, q, h, sc, s);
+      wide_scores<D, kI8, NT>(r, q, abs_scale, h, sc, s);
       fetch_k(r, seg, t + R);
       if (!plain) mask_wide<D, kI8, NT>(r, s, q, tok0, u.L + u.nq, h);
       bf16x8 pf[kTiles][G::kProbs], pr[2][kTiles][G::kProbs];
-      wide_softmax<D, kI8, NT, kFine>(q, s, st, abs_scale, h, sc, pf, pr);
+      wide_softmax<D, kI8, NT, kFine>(s, st, h, sc, pf, pr);
       if constexpr (kI8) __builtin_amdgcn_wave_barrier();
       wide_values<D, kI8, NT, kFine>(r, pf, pr, st);
       fetch_v(r, seg, t + R);

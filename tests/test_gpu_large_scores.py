@@ -1,4 +1,5 @@
-"""Scores far beyond what a softmax resolves, of finite rows: all of a query's weight is on its largest score, which has the probability 1."""
+"""Rows of extreme but finite size.  Scores far beyond what a softmax resolves: all of a query's weight is on its largest score, which has
+the probability 1.  Keys and queries whose sizes cancel: ordinary scores, whatever the order in which their scales are multiplied."""
 import math
 
 import numpy as np
@@ -43,3 +44,23 @@ def test_one_token_takes_all(dtype, Hq, Hkv, D, kmax, size):
                     err = np.abs(O[b, i, h] - want[b, i, h]).max()
                     assert err <= (2.0 ** -8 if dtype == "int8kv" else 1e-6) * np.abs(want[b, i, h]).max(), (b, i, h)
     assert np.isfinite(O).all()
+
+
+@pytest.mark.parametrize("dtype", ["bf16", "int8kv"])
+@pytest.mark.parametrize("Hq,Hkv,D,kmax", [(4, 2, 64, 4), (4, 4, 128, 16), (8, 2, 128, 6), (4, 1, 64, 8), (8, 1, 128, 8), (8, 1, 64, 5),
+                                           (100, 100, 64, 2)])
+@pytest.mark.parametrize("power", [120, 110, -110])
+def test_keys_and_queries_of_opposite_size(dtype, Hq, Hkv, D, kmax, power):
+    from paper_2404_15778_amd import harness
+    from oracle.kv_int8 import dequantize_rows, quantize_rows
+    w = wl.make_attention("opposite", 2, Hq, Hkv, D, "bf16", [900, 40], [kmax, kmax], 4, kmax=kmax, Lcap=960)
+    w.K = wl.to_bf16_bits(np.ldexp(wl.bf16_bits_to_f32(w.K), power))
+    w.Q = wl.to_bf16_bits(np.ldexp(wl.bf16_bits_to_f32(w.Q), -power))
+    Q, K, V = (wl.bf16_bits_to_f32(x) for x in (w.Q, w.K, w.V))
+    if dtype == "int8kv":
+        Q, K, V = (dequantize_rows(*quantize_rows(x)) for x in (Q, K, V))
+        w.dtype = dtype
+    want, want_lse = oracle.verify_attention(Q, K, V, w.ctx_len, w.draft_len, w.scale)
+    O, lse, status, _ = harness.run_attention_workload(w, fused=True)
+    # probabilities are rounded to bf16 (2^-9) for outputs of magnitude up to about 4; lse stays in 32 bits
+    assert status == 0 and np.abs(O - want).max() <= 2e-2 and np.abs(lse - want_lse).max() <= 1e-4
