@@ -1482,8 +1482,10 @@ __device__ inline void mask_wide(WideBlock<D, kI8>& r, float (&s)[Wide<D, kI8, N
 // Online softmax of a block: scores -> probabilities as operand B of the V product (INT8: times the tokens' V scales), running
 // maximum and sum.  kFine: shapes whose lists may be divided over fewer shares, where the rounding of the probabilities to bf16 would
 // cost precision (kNarrowUnits): their 24 bits are cut into three operands of 8 and all multiplied.  No part is negative, and none is
-// zero where the probability is not, so that an infinite element of V stays infinite in every product.  (Two parts leave 2^-17: 3.6e-6
-// instead of 2.3e-6 with a rounded first part, whose remainder may be negative.)
+// zero where the probability is not, so that an infinite element of V stays infinite in every product: the second and third are at
+// least 2^-133, the smallest bf16, which the matrix instruction takes as it is (a probability is 0 or at least 2^-126; together they are
+// off by at most 2^-132, 2^-22 of a probability of 2^-110).  (Two parts leave 2^-17: 3.6e-6 instead of 2.3e-6 with a rounded first part,
+// whose remainder may be negative.)
 template <int D, bool kI8, int NT, bool kFine>
 __device__ inline void wide_softmax(const float (&s)[Wide<D, kI8, NT>::kTiles][Wide<D, kI8, NT>::kScores], WideState<D, kI8, NT>& st, int h, const float* scales,
                                     bf16x8 (&pf)[Wide<D, kI8, NT>::kTiles][Wide<D, kI8, NT>::kProbs],
@@ -1520,10 +1522,10 @@ __device__ inline void wide_softmax(const float (&s)[Wide<D, kI8, NT>::kTiles][W
         psum += pj;
         const float z = kI8 ? pj * vs[e] : pj;
         if constexpr (kFine) {
-          const float a = cut(z), b = cut(z - a);
+          const float a = cut(z), b = cut(z - a), least = fminf(z, 0x1p-133f);
           pf[nt][i >> 3][i & 7] = (__bf16)a;
-          pr[0][nt][i >> 3][i & 7] = (__bf16)fmaxf(b, z * 0x1p-36f);
-          pr[1][nt][i >> 3][i & 7] = (__bf16)fmaxf(z - a - b, z * 0x1p-36f);
+          pr[0][nt][i >> 3][i & 7] = (__bf16)fmaxf(b, least);
+          pr[1][nt][i >> 3][i & 7] = (__bf16)fmaxf(z - a - b, least);
         } else {
           pf[nt][i >> 3][i & 7] = (__bf16)z;
         }

@@ -1,5 +1,5 @@
 """An infinite element of V makes its outputs infinite wherever its probability is positive, and leaves the others alone:
-also where short block lists are divided over fewer shares and remainders of the probabilities are multiplied."""
+also where the probabilities of few units are multiplied in three parts of 8 bits, none of which may become zero."""
 import numpy as np
 import pytest
 
@@ -31,3 +31,25 @@ def test_infinite_values_of_the_context(B, Hq, Hkv, D, ctx, nq, fused):
         assert (O[rows] == (np.inf if bits == INF else -np.inf)).all(), (tok, head, d)
         O[rows] = want[rows] = 0.0
     assert np.isfinite(O).all() and np.abs(O - want).max() <= 2e-2
+
+
+# One unit of 9 tokens, the first of which has the score 0, the last `below` less, the others 200 less (in powers of two)
+@pytest.mark.parametrize("dtype,least", [("bf16", 126), ("fp32", 148)])  # exponent of the smallest probability that is not taken as 0
+@pytest.mark.parametrize("Hq,D,nq", [(1, 64, 3), (4, 128, 4), (4, 128, 6), (2, 64, 16), (8, 128, 8), (5, 64, 8)])  # 3, 16, 24, 32, 64 and 40 rows
+@pytest.mark.parametrize("below", [20, 90, 97, 98, 110, 126, 140])
+def test_infinite_values_of_small_probability(Hq, D, nq, dtype, least, below):
+    from paper_2404_15778_amd import harness as hip
+    w = wl.make_attention("tiny", 1, Hq, 1, D, dtype, np.array([8], np.int32), np.array([nq], np.int32), seed=1,
+                          Lcap=64 if Hq * nq == 40 else 800)
+    w.scale = float(np.log(2.0))
+    Q, K, V = np.zeros(w.Q.shape, np.float32), np.zeros(w.K.shape, np.float32), np.ones(w.V.shape, np.float32)
+    Q[..., 0], K[:, 1:, :, 0], K[:, 7, :, 0] = 1.0, -200.0, -float(below)
+    V[:, 7, :, 3], V[:, 7, :, 5] = np.inf, -np.inf
+    to = wl.to_bf16_bits if dtype == "bf16" else np.float32
+    w.Q, w.K, w.V = to(Q), to(K), to(V)
+    O, lse, status, _ = hip.run_attention_workload(w, fused=True)
+    assert status == 0 and np.isfinite(lse).all()
+    if below <= least:
+        assert (O[..., 3] == np.inf).all() and (O[..., 5] == -np.inf).all()
+    O[..., 3] = O[..., 5] = 1.0
+    assert np.abs(O - 1.0).max() <= 1e-6
