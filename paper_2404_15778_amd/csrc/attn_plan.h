@@ -54,6 +54,8 @@ struct PlanShape {
   int32_t min_entries = 0;  // shares are not made shorter than this many entries (0: no bound) ...
   int32_t per_unit = 0;     // ... but this many per unit there may always be
   int32_t used = 0;         // the list is divided over at most this many of the shares (0: all of them)
+  int32_t longer_from = 0;  // units of so many entries on average: twice min_entries (0: never)
+  int32_t whole = 0;        // real blocks of a stretch where every unit gets stretches of its own (0: it does not); see settle_whole
 };
 
 // Real blocks of a sequence (per kv head) after clamping; 0 for an inactive sequence.
@@ -101,11 +103,26 @@ BASS_HD inline bool worth_fewer(const PlanShape& s, int few) {
   return s.min_entries > 0 && few < most && (s.B * s.Hkv <= most / kManyPerUnit || few <= most / 2);
 }
 BASS_HD inline int shares_wanted(const PlanShape& s, int total) {
-  const int few = s.min_entries > 0 ? imax(1, imax(total / s.min_entries, s.per_unit * s.B * s.Hkv)) : 0;
+  const int entries = s.longer_from > 0 && total >= s.longer_from * s.B * s.Hkv ? 2 * s.min_entries : s.min_entries;
+  const int few = entries > 0 ? imax(1, imax(total / entries, s.per_unit * s.B * s.Hkv)) : 0;
   return worth_fewer(s, few) ? few : most_shares(s);
 }
 // Whether lists of any length may be divided so: those of the fewest shares
 BASS_HD inline bool may_be_few(const PlanShape& s) { return worth_fewer(s, imax(1, s.per_unit * s.B * s.Hkv)); }
+
+// Where the units are short, virtual entries cut them apart for nothing: a unit of 3 real blocks and 7 virtual ones, divided by 4 entries,
+// is two or three partial results and their merge instead of none.  So if stretches of at most `whole` real blocks, each of one unit, are no
+// more than the shares of the even division, every unit gets its own: its length in the list is rounded up to a multiple of
+// `whole` in place of the pad, and a share is `whole` entries.  A launch asks for this by its shape; the lengths decide whether it is
+// done so, with stretches of twice the length, or not at all.
+BASS_HD inline int stretches_of(int whole, int nblk) { return (nblk + whole - 1) / whole; }
+// The shape that the lengths lead to; entries: of all units with their pads, once / twice: their stretches of `whole` and 2 `whole` blocks.
+BASS_HD inline PlanShape settle_whole(PlanShape s, int entries, int64_t once, int64_t twice) {
+  if (s.whole <= 0) return s;
+  const int64_t shares = shares_wanted(s, entries);
+  s.whole = entries <= 0 ? 0 : once <= shares ? s.whole : twice <= shares ? 2 * s.whole : 0;
+  return s;
+}
 
 // The division a plan uses.  A launch lasts as long as its longest share, and with an even division over
 // `target` shares most of them are one entry longer than total / target.  If the launch has room for more
@@ -113,6 +130,7 @@ BASS_HD inline bool may_be_few(const PlanShape& s) { return worth_fewer(s, imax(
 // are correspondingly more of them (at most nshares: the share length grows until they fit); the last one
 // takes what is left, the launch's remaining wavefronts stay idle.
 BASS_HD inline Split plan_split(const PlanShape& s, int total) {
+  if (s.whole > 0) return Split{s.whole, 0, total};
   if (s.target >= s.nshares || total <= 0) return make_split(total, shares_wanted(s, total));
   int per = imax(1, total / s.target);
   while ((total + per - 1) / per > s.nshares) ++per;
@@ -123,6 +141,11 @@ BASS_HD inline Split plan_split(const PlanShape& s, int total) {
 // no share can lie between two real blocks of a unit without holding one (every share between a unit's
 // first and last contributor then contributes).
 BASS_HD inline int pad_before_in_effect(const PlanShape& s, const Split& sp) { return sp.per > s.pad ? s.pad_before : 0; }
+
+// Entries of a unit in the flattened list
+BASS_HD inline int unit_entries(const PlanShape& s, int nblk) {
+  return s.whole > 0 ? stretches_of(s.whole, nblk) * s.whole : padded_blocks(s.pad, nblk);
+}
 
 // One stretch of one unit inside one share: real blocks first .. first + n - 1 of (sequence b, kv head kvh).
 struct Segment {
@@ -154,9 +177,9 @@ constexpr int32_t kRecAnyInactive = 1;  // some sequence has no query token: its
 // lengths and the span, and `used`, which sizes the grid of the workgroup-level kernels.  Never 0: cleared memory
 // does not match.
 BASS_HD inline int32_t plan_signature(const PlanShape& s, int flags) {
-  const int32_t v[12] = {s.B, s.kmax, s.Hkv, s.Lcap, s.nshares, s.target, s.pad, s.pad_before, s.min_entries, s.per_unit, s.used, flags};
+  const int32_t v[14] = {s.B, s.kmax, s.Hkv, s.Lcap, s.nshares, s.target, s.pad, s.pad_before, s.min_entries, s.per_unit, s.used, s.whole, s.longer_from, flags};
   uint32_t h = 2166136261u;
-  for (int i = 0; i < 12; ++i) h = (h ^ (uint32_t)v[i]) * 16777619u;
+  for (int i = 0; i < 14; ++i) h = (h ^ (uint32_t)v[i]) * 16777619u;
   return (int32_t)(h | 1u);
 }
 
@@ -168,7 +191,7 @@ struct PlanHeader {
   int32_t B, kmax, Hkv, Lcap;
   int32_t nshares, pad, pad_before, span;
   int32_t flags;
-  int32_t total;         // entries of the flattened list (all kv heads)
+  int32_t total;         // real blocks and `pad` virtual ones of every unit (all kv heads)
   int32_t any_inactive;  // some sequence has no query token (its output rows still have to be cleared)
   int32_t any_clamped;   // some length was out of range
   int32_t reserved[3];
@@ -229,7 +252,7 @@ BASS_HD inline int plan_share(const PlanShape& s, const int32_t* seq_L, const in
     const int pre = inc[b] - npad;
     const int kvh = (x - pre * s.Hkv) / npad;
     const int begin = pre * s.Hkv + kvh * npad;
-    const int nblk = npad - s.pad;
+    const int nblk = s.whole > 0 ? seq_blocks(s, seq_L[b], seq_nq[b]) : npad - s.pad;
     const int span = imin(x_end, begin + npad) - x;  // our stretch of the unit, virtual blocks included
     const int first = real_below(x - begin, nblk, pb);
     const int n = real_below(x - begin + span, nblk, pb) - first;

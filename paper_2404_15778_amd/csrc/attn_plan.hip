@@ -11,7 +11,8 @@
 
 namespace bass {
 
-// Planning kernel.  Phase 1: clamp the lengths, count blocks, inclusive prefix over the sequences.  Phase 2: one
+// Planning kernel.  Phase 0, where it is asked for: whether every unit gets stretches of its own.  Phase 1: clamp the lengths,
+// count blocks, inclusive prefix over the sequences.  Phase 2: one
 // thread per share walks its stretch of the block list and writes the record.  Phase 3: the contributors of
 // every unit, for the merge launch.  Batches of up to kPlanSeqs sequences keep phase 1's results in LDS, every
 // workgroup computes them for itself (a few hundred instructions) and the shares are spread over several
@@ -76,10 +77,12 @@ BASS_HD inline void write_record(const PlanShape& s, const int32_t* seq_L, const
   records[w].flags = (any_inactive ? kRecAnyInactive : 0) | (shares_wanted(s, total) < s.nshares ? kRecFewShares : 0);
 }
 
-BASS_HD inline int32_t owners_of_unit(const PlanShape& s, const Split& sp, int pb, const int32_t* inc, int unit) {
+BASS_HD inline int32_t owners_of_unit(const PlanShape& s, const Split& sp, int pb, const int32_t* seq_L, const int32_t* seq_nq,
+                                      const int32_t* inc, int unit) {
   const int b = unit / s.Hkv, kvh = unit - b * s.Hkv;
   const int npad = inc[b] - (b > 0 ? inc[b - 1] : 0);
-  return npad > 0 ? unit_owners(sp, (inc[b] - npad) * s.Hkv + kvh * npad, npad - s.pad, pb) : 0;
+  const int nblk = s.whole > 0 ? seq_blocks(s, seq_L[b], seq_nq[b]) : npad - s.pad;
+  return npad > 0 ? unit_owners(sp, (inc[b] - npad) * s.Hkv + kvh * npad, nblk, pb) : 0;
 }
 
 BASS_HD inline PlanHeader make_header(const PlanShape& s, int flags, int total, bool any_inactive, bool any_clamped) {
@@ -97,10 +100,14 @@ BASS_HD inline PlanHeader make_header(const PlanShape& s, int flags, int total, 
 
 // clear_counters (optional): the arrival counters of the attention launch that follows, B * Hkv words,
 // cleared here for callers whose workspace is not known to be clean.
-__global__ __launch_bounds__(kPlanThreads) void attention_plan_kernel(PlanShape s, int flags, const int32_t* ctx_len,
+// kWhole: the launch asks for stretches of whole units (PlanShape::whole).
+template <bool kWhole>
+__global__ __launch_bounds__(kPlanThreads) void attention_plan_kernel(PlanShape asked, int flags, const int32_t* ctx_len,
                                                                       const int32_t* draft_len, char* plan, int32_t* status,
                                                                       int32_t* clear_counters) {
-  __shared__ int lds[kPlanThreads / 64];
+  PlanShape s = asked;
+  if (!kWhole) s.whole = 0;
+  __shared__ int lds[kPlanThreads / 64], sums[kWhole ? 3 : 1];
   __shared__ int32_t lds_L[kPlanSeqs], lds_nq[kPlanSeqs], lds_inc[kPlanSeqs];
   const int tid = threadIdx.x;
   const int gtid = blockIdx.x * kPlanThreads + tid, gthreads = gridDim.x * kPlanThreads;
@@ -117,32 +124,63 @@ __global__ __launch_bounds__(kPlanThreads) void attention_plan_kernel(PlanShape 
   if (clear_counters)
     for (int i = gtid; i < s.B * s.Hkv; i += gthreads) clear_counters[i] = 0;
 
-  // phase 1 (every workgroup for itself; the first one also writes the plan's copy)
-  int carry = 0;
+  // the lengths of sequence b (every workgroup for itself; the first one also writes the plan's copy)
   bool bad = false, inactive = false;
+  auto read_lengths = [&](int b, int& L, int& nq) {
+    L = ctx_len[b];
+    nq = draft_len[b];
+    bad |= clamp_lengths(L, nq, s.kmax, s.Lcap);
+    inactive |= nq == 0;
+    if (first) {
+      seq_L[b] = L;
+      seq_nq[b] = nq;
+    }
+    if (in_lds) {
+      lds_L[b] = L;
+      lds_nq[b] = nq;
+    }
+  };
+
+  // phase 0: whether every unit gets stretches of its own
+  int entries = 0;
+  if constexpr (kWhole) {
+    if (tid < 3) sums[tid] = 0;
+    __syncthreads();
+    for (int b = tid; b < s.B; b += kPlanThreads) {
+      int L, nq;
+      read_lengths(b, L, nq);
+      const int nblk = seq_blocks(s, L, nq);
+      atomicAdd(&sums[0], padded_blocks(s.pad, nblk));
+      atomicAdd(&sums[1], stretches_of(s.whole, nblk));
+      atomicAdd(&sums[2], stretches_of(2 * s.whole, nblk));
+    }
+    __syncthreads();
+    int sum[3];
+    for (int i = 0; i < 3; ++i) sum[i] = __builtin_amdgcn_readfirstlane(sums[i]);
+    entries = sum[0] * s.Hkv;
+    s = settle_whole(s, entries, (int64_t)sum[1] * s.Hkv, (int64_t)sum[2] * s.Hkv);
+  }
+
+  // phase 1
+  int carry = 0;
   for (int c0 = 0; c0 < s.B; c0 += kPlanThreads) {
     const int b = c0 + tid;
-    int nb = 0, L = 0, nq = 0;
+    int nb = 0;
     if (b < s.B) {
-      L = ctx_len[b];
-      nq = draft_len[b];
-      bad |= clamp_lengths(L, nq, s.kmax, s.Lcap);
-      inactive |= nq == 0;
-      nb = padded_blocks(s.pad, seq_blocks(s, L, nq));
+      int L, nq;
+      if constexpr (kWhole) {  // what this thread wrote
+        L = in_lds ? lds_L[b] : seq_L[b];
+        nq = in_lds ? lds_nq[b] : seq_nq[b];
+      } else {
+        read_lengths(b, L, nq);
+      }
+      nb = unit_entries(s, seq_blocks(s, L, nq));
     }
     int chunk_total;
     const int incl = carry + block_incl_scan(nb, lds, tid, chunk_total);
     if (b < s.B) {
-      if (first) {
-        seq_L[b] = L;
-        seq_nq[b] = nq;
-        inc[b] = incl;
-      }
-      if (in_lds) {
-        lds_L[b] = L;
-        lds_nq[b] = nq;
-        lds_inc[b] = incl;
-      }
+      if (first) inc[b] = incl;
+      if (in_lds) lds_inc[b] = incl;
     }
     carry += chunk_total;
   }
@@ -150,7 +188,7 @@ __global__ __launch_bounds__(kPlanThreads) void attention_plan_kernel(PlanShape 
   const int any_inactive = __syncthreads_or(inactive ? 1 : 0);  // also orders the writes above before the reads below
   const int total = carry * s.Hkv;
   if (first && tid == 0) {
-    *(PlanHeader*)plan = make_header(s, flags, total, any_inactive != 0, any_bad != 0);
+    *(PlanHeader*)plan = make_header(s, flags, kWhole ? entries : total, any_inactive != 0, any_bad != 0);
     if (any_bad && status) atomicOr(status, BASS_STATUS_LEN_CLAMPED);
   }
   const int32_t* rd_L = in_lds ? lds_L : seq_L;
@@ -158,18 +196,20 @@ __global__ __launch_bounds__(kPlanThreads) void attention_plan_kernel(PlanShape 
   const int32_t* rd_inc = in_lds ? lds_inc : inc;
 
   // phase 2
-  const int32_t signature = plan_signature(s, flags);
+  const int32_t signature = plan_signature(asked, flags);
   for (int w = gtid; w < s.nshares; w += gthreads)
     write_record(s, rd_L, rd_nq, rd_inc, total, w, signature, any_inactive != 0, records, overflow);
 
   // phase 3
   const Split sp = plan_split(s, total);
   const int pb = pad_before_in_effect(s, sp);
-  for (int unit = gtid; unit < s.B * s.Hkv; unit += gthreads) owners[unit] = total > 0 ? owners_of_unit(s, sp, pb, rd_inc, unit) : 0;
+  for (int unit = gtid; unit < s.B * s.Hkv; unit += gthreads)
+    owners[unit] = total > 0 ? owners_of_unit(s, sp, pb, rd_L, rd_nq, rd_inc, unit) : 0;
 }
 
 // The same plan, byte for byte, written by the host into host memory.
-static bool plan_on_host(const PlanShape& s, int flags, const int32_t* ctx_len, const int32_t* draft_len, char* plan) {
+static bool plan_on_host(const PlanShape& asked, int flags, const int32_t* ctx_len, const int32_t* draft_len, char* plan) {
+  PlanShape s = asked;
   const PlanLayout lay = plan_layout(s.B, s.Hkv, s.nshares);
   int32_t* seq_L = (int32_t*)(plan + lay.seq_L);
   int32_t* seq_nq = (int32_t*)(plan + lay.seq_nq);
@@ -178,23 +218,32 @@ static bool plan_on_host(const PlanShape& s, int flags, const int32_t* ctx_len, 
   Segment* overflow = (Segment*)(plan + lay.overflow);
   int32_t* owners = (int32_t*)(plan + lay.unit_owners);
   bool bad = false, any_inactive = false;
-  int carry = 0;
+  int entries = 0, carry = 0;
+  int64_t once = 0, twice = 0;
   for (int b = 0; b < s.B; ++b) {
     int L = ctx_len[b], nq = draft_len[b];
     bad |= clamp_lengths(L, nq, s.kmax, s.Lcap);
     any_inactive |= nq == 0;
-    carry += padded_blocks(s.pad, seq_blocks(s, L, nq));
     seq_L[b] = L;
     seq_nq[b] = nq;
+    entries += padded_blocks(s.pad, seq_blocks(s, L, nq));
+    once += stretches_of(imax(s.whole, 1), seq_blocks(s, L, nq));
+    twice += stretches_of(imax(2 * s.whole, 1), seq_blocks(s, L, nq));
+  }
+  entries *= s.Hkv;
+  s = settle_whole(s, entries, once * s.Hkv, twice * s.Hkv);
+  for (int b = 0; b < s.B; ++b) {
+    carry += unit_entries(s, seq_blocks(s, seq_L[b], seq_nq[b]));
     inc[b] = carry;
   }
   const int total = carry * s.Hkv;
-  *(PlanHeader*)plan = make_header(s, flags, total, any_inactive, bad);
-  const int32_t signature = plan_signature(s, flags);
+  *(PlanHeader*)plan = make_header(s, flags, entries, any_inactive, bad);
+  const int32_t signature = plan_signature(asked, flags);
   for (int w = 0; w < s.nshares; ++w) write_record(s, seq_L, seq_nq, inc, total, w, signature, any_inactive, records, overflow);
   const Split sp = plan_split(s, total);
   const int pb = pad_before_in_effect(s, sp);
-  for (int unit = 0; unit < s.B * s.Hkv; ++unit) owners[unit] = total > 0 ? owners_of_unit(s, sp, pb, inc, unit) : 0;
+  for (int unit = 0; unit < s.B * s.Hkv; ++unit)
+    owners[unit] = total > 0 ? owners_of_unit(s, sp, pb, seq_L, seq_nq, inc, unit) : 0;
   return bad;
 }
 
@@ -202,7 +251,7 @@ PlanShape plan_shape(const bass_attn_desc* d, const LaunchShape& ls, int span) {
   PlanShape s;
   s.B = d->B; s.kmax = d->kmax; s.Hkv = d->Hkv; s.Lcap = d->Lcap;
   s.nshares = ls.nshares; s.target = ls.target; s.pad = ls.pad; s.pad_before = ls.pad_before; s.span = span;
-  s.min_entries = ls.min_entries; s.per_unit = ls.per_unit; s.used = ls.used_shares;
+  s.min_entries = ls.min_entries; s.per_unit = ls.per_unit; s.used = ls.used_shares; s.whole = ls.whole; s.longer_from = ls.longer_from;
   return s;
 }
 
@@ -212,8 +261,11 @@ int launch_plan(const bass_attn_desc* d, const LaunchShape& ls, int span, const 
                 void* plan, int32_t* dev_status, void* stream, int32_t* clear_counters) {
   const PlanShape s = plan_shape(d, ls, span);
   const unsigned groups = s.B <= kPlanSeqs ? (unsigned)((s.nshares + kPlanThreads - 1) / kPlanThreads) : 1u;
-  hipLaunchKernelGGL(attention_plan_kernel, dim3(groups), dim3(kPlanThreads), 0, (hipStream_t)stream, s,
-                     ls.fused_append ? kPlanAppend : 0, ctx_len, draft_len, (char*)plan, dev_status, clear_counters);
+  const dim3 grid(groups), block(kPlanThreads);
+  const int flags = ls.fused_append ? kPlanAppend : 0;
+  hipStream_t st = (hipStream_t)stream;
+  if (s.whole > 0) hipLaunchKernelGGL(attention_plan_kernel<true>, grid, block, 0, st, s, flags, ctx_len, draft_len, (char*)plan, dev_status, clear_counters);
+  else hipLaunchKernelGGL(attention_plan_kernel<false>, grid, block, 0, st, s, flags, ctx_len, draft_len, (char*)plan, dev_status, clear_counters);
   return launch_status();
 }
 

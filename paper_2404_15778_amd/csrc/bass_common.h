@@ -129,14 +129,25 @@ constexpr int kPlainPad = 2;      // ... and when it is not (the unit's last blo
 constexpr int kAppendBefore = 1;  // how many of those sit in front of the unit's last real block (one-tile matrix-core
 constexpr int kPlainBefore = 0;   // kernel; measured: +0.5 % with the fused append, slightly slower without)
 // More than 16 query rows per kv head: the workgroup-level kernels.  verify_attn_wide (a wavefront has all rows of its own blocks)
-// takes whatever has at most 32 rows, and more rows in caches of more than kShortCache blocks per sequence; below, the kernels that
-// share a block's rows between wavefronts are quicker, whose way from the first block to the last store is shorter.  48 and 64 rows,
-// 8 kv heads of 128, 1 / 4 / 8 / 32 sequences, sharing rows -> wide: bf16, at most 150 tokens 9.5 / 10.4 / 13.4 / 20.2 -> 12.0 / 12.4 / 15.0 /
-// 23.6 us, 400 tokens 9.5 / 15.3 / 15.2 / 23.1 -> 12.2 / 16.3 / 16.6 / 25.6, 700 tokens 12.3 / 15.0 / 18.9 / 30.2 -> 13.4 / 16.4 / 17.8 / 30.9,
-// 1200 tokens 18.8 / 19.5 / 21.8 / 42.0 -> 16.4 / 18.9 / 21.6 / 40.5; INT8, 400 tokens 11.4 / 17.7 / 19.1 / 25.2 -> 13.9 / 17.1 / 17.2 / 27.2, 700
-// tokens 13.2 / 19.7 / 19.9 / 30.7 -> 14.7 / 17.6 / 18.2 / 31.2, 1200 tokens 20.4 / 21.4 / 21.7 / 39.4 -> 17.4 / 19.4 / 23.8 / 35.8.
-// (The lengths themselves are known on the device only.)
+// takes whatever has at most 32 rows.  With more rows there is a choice.  The kernels that share a block's rows between wavefronts have the
+// shorter way from the first block to the last store, verify_attn_wide the shorter time per block; which counts depends on the lengths,
+// which are known on the device only.  So by what the host knows:
+// - Caches of at most kShortCache blocks per sequence share rows: 48 and 64 rows, 8 kv heads of 128, 4 / 8 / 32 sequences, sharing rows ->
+//   wide: bf16, at most 150 tokens 10.4 / 13.4 / 20.2 -> 12.4 / 15.0 / 23.6 us, 400 tokens 15.3 / 15.2 / 23.1 -> 16.3 / 16.6 / 25.6, 700 tokens
+//   15.0 / 18.9 / 30.2 -> 16.4 / 17.8 / 30.9, 1200 tokens 19.5 / 21.8 / 42.0 -> 18.9 / 21.6 / 40.5; INT8, 700 tokens 19.7 / 19.9 / 30.7 -> 17.6 / 18.2 /
+//   31.2, 1200 tokens 21.4 / 21.7 / 39.4 -> 19.4 / 23.8 / 35.8.
+// - So do few units in caches of any size, where a short list loses most: 8 units of 128, 48 rows, 60 / 150 / 400 / 1000 / 2500 / 4000 tokens,
+//   sharing rows -> wide: bf16 9.8 / 9.3 / 9.8 / 11.4 / 13.4 / 16.8 -> 12.6 / 12.7 / 12.5 / 13.3 / 14.9 / 16.6, INT8 10.9 / 10.6 / 10.7 / 12.2 / 13.8 / 17.0 ->
+//   14.1 / 14.1 / 14.0 / 14.2 / 15.3 / 16.2; 16 units bf16 10.1 / 9.6 / 11.0 / 13.1 / 19.8 / 21.0 -> 12.7 / 12.8 / 13.2 / 14.4 / 16.9 / 18.6; 32 units 10.6 / 11.0 /
+//   13.2 / 17.5 / 22.3 / 26.2 -> 13.1 / 13.8 / 14.5 / 17.1 / 21.4 / 24.9.  Heads of 64 over INT8 caches turn earlier, 16 units 9.9 / 11.1 / 10.0 / 12.6 / 16.7 /
+//   18.6 -> 11.0 / 11.1 / 11.1 / 11.4 / 13.0 / 14.2.
+//   There shares get at least kRowEntries entries, because each is a partial result to be merged, and over INT8 caches from kRowLonger
+//   entries per unit on twice as many: 8 units of 128, 48 rows, at least 0 / 2 / 4 entries, INT8 60 tokens 10.6 / 10.9 / 12.5, 1000 14.9 / 12.3 /
+//   12.1, 2500 19.6 / 16.8 / 13.9 (6 entries 16.2); bf16 9.1 / 9.8 / 10.6, 12.9 / 11.9 / 11.5, 15.2 / 15.3 / 13.6, but with 4 a wavefront has two
+//   blocks, and precision is lost as below.
 constexpr int kShortCache = 24;
+constexpr int kFewUnits = 16, kFewUnitsInt8D64 = 8;
+constexpr int kRowEntries = 2, kRowLonger = 20;
 // verify_attn_wide: one workgroup per compute unit.  The end of a unit inside a stretch -- four states merged, the next unit's first
 // blocks waited for -- costs its workgroup about as much as 7 blocks: 16 layers of 16 sequences of 1024 - 4096 tokens, 64/8 heads, with 3 / 5 /
 // 7 virtual blocks per unit 769 / 758 / 758 us, 8 sequences, 32 heads, 32 rows 765 / 751 / 745.  Short lists go to fewer workgroups so that
@@ -148,6 +159,10 @@ constexpr int kShortCache = 24;
 // two: short lists of 512 units 33.9 -> 29.7, but one workgroup alone 5 - 8 % longer.)
 constexpr int kTileShares = 256, kTwoUnits = 256;
 constexpr int kWidePad = 7, kWideEntries = 4;
+// Stretches of whole units (PlanShape::whole): a block for each of the four wavefronts, or two.  Even division -> whole stretches, head size
+// 128: 1 sequence of 960 tokens, 32 heads, 8 rows (30 blocks a unit) 11.9 -> 11.0 us; 8 kv heads, 32 rows, 1 / 16 sequences of 60 tokens
+// 9.7 / 11.4 -> 7.6 / 9.5; 48 rows, 16 sequences of 400 tokens 21.0 -> 17.9, 32 of 60 / 150 24.9 / 24.6 -> 19.7 / 20.8.
+constexpr int kWidePerStep = 4;
 // At most 16 query rows: up to this many units (sequence, kv head) take verify_attn_wide too, with a tile of 16 rows; more of them stay with a
 // wavefront per share (verify_attn_bf16), where a unit's merge costs no workgroup barrier.  8 query rows, a wavefront per share -> a
 // workgroup, us per layer, 32 / 64 / 96 / 128 / 192 units: head size 128, 200 - 500 tokens 12.6 / 14.2 / 14.6 / 14.3 / 16.6 -> 10.4 / 11.7 / 12.9 /
@@ -173,7 +188,7 @@ struct LaunchShape {
   bool fused_append;  // the step's rows are appended inside the attention launch, and its plan says so
   bool tiles_append;  // longer drafts, workgroup-level kernels: they patch a block at a time and stage nothing, so
                       // planned launches may append there too; the plan is the one of a launch that does not append
-  int rows_max, nwaves, nshares, used_shares, target, pad, pad_before, min_entries, per_unit;
+  int rows_max, nwaves, nshares, used_shares, target, pad, pad_before, min_entries, per_unit, whole, longer_from;
 };
 
 // One query tile per kv head: 768 wavefronts, over INT8 caches too -- as 256 workgroups of three they measured level with 1024 on
@@ -198,7 +213,8 @@ inline LaunchShape launch_shape(const bass_attn_desc* d, bool append) {
   // 1 - 2 % slower than the even division on the benchmark shapes: more wavefronts, more partials to merge)
   s.nwaves = attention_waves(setting);
   s.narrow = s.mfma && !s.tiles && setting <= 0 && d->B * d->Hkv <= kNarrowUnits;
-  s.wide = s.narrow || (s.tiles && (s.rows_max <= 32 || num_blocks(d->Lcap) > kShortCache));
+  const bool few_units = d->B * d->Hkv <= (int8 && d->D == 64 ? kFewUnitsInt8D64 : kFewUnits);
+  s.wide = s.narrow || (s.tiles && (s.rows_max <= 32 || (num_blocks(d->Lcap) > kShortCache && !few_units)));
   // Longer drafts than the wavefronts stage: a patch costs a workgroup 1 - 3 us, one after the other for each of its units; an append by
   // itself goes by cache blocks from kBlockTokens slots on, which takes a 32-slot call 5 - 10 us.  Before the launch / inside it, us,
   // 32 rows, 32 heads of 128, 16 sequences of 100 / 450 / 1200 tokens, 32 of 450, 12 of 2000: verify_attn_wide, bf16 30.4 / 45.9 / 79.8 / 75.1 /
@@ -212,8 +228,10 @@ inline LaunchShape launch_shape(const bass_attn_desc* d, bool append) {
   s.nshares = !s.tiles ? s.nwaves : int8 ? 2 * stretches : s.wide && two && setting <= 0 ? s.used_shares : stretches;
   s.target = s.nshares;
   s.pad = s.narrow ? kNarrowPad : s.wide ? kWidePad : s.fused_append ? kAppendPad : kPlainPad;
-  s.min_entries = setting > 0 || !s.wide ? 0 : s.narrow ? kNarrowEntries : kWideEntries;
+  s.min_entries = setting > 0 ? 0 : s.narrow ? kNarrowEntries : s.wide ? kWideEntries : s.tiles && few_units ? kRowEntries : 0;
   s.per_unit = 1;
+  s.longer_from = !s.wide && s.min_entries > 0 && int8 ? kRowLonger : 0;
+  s.whole = s.wide && s.min_entries > 0 ? kWidePerStep : 0;
   s.pad_before = 0;
   if (s.mfma && !s.tiles && !s.wide) s.pad_before = s.fused_append ? kAppendBefore : kPlainBefore;
   return s;

@@ -2032,6 +2032,9 @@ __global__ __launch_bounds__(512, 2) void verify_attn_tiles_bf16(AttnParams p) {
     const bool active = uniform(row0 < u.nq * p.g);  // this wavefront owns a query tile of the unit
     QFrag<D> q;
     load_queries<D>(p, u, active, col, grp, q, row0);
+    const uint32_t flip = p.scale_log2 < 0.f ? 0x80008000u : 0u;  // a negative scale is moved into the queries, as in verify_attn_wide
+#pragma unroll
+    for (int t = 0; t < D / 32; ++t) q.q[t] = __builtin_bit_cast(bf16x8, __builtin_bit_cast(u32x4, q.q[t]) ^ flip);
     RowState<D> st;
     clear_state<D>(st);
     const int blk0 = seg.first;
@@ -2100,7 +2103,7 @@ __global__ __launch_bounds__(512, 2) void verify_attn_tiles_bf16(AttnParams p) {
         for (int i = 0; i < 2 * (D / 32); ++i) r.k[i] = lk[i * 64];
 #pragma unroll
         for (int i = 0; i < D / 16; ++i) r.v[i] = lv[i * 64];
-        block_dispatch<D>(r, q.q, st, blk0 + H * ph + half, u.L, u.L + u.nq, q.lim, p.scale_log2, lane, false, NewRows{}, nullptr, nullptr);
+        block_dispatch<D>(r, q.q, st, blk0 + H * ph + half, u.L, u.L + u.nq, q.lim, fabsf(p.scale_log2), lane, false, NewRows{}, nullptr, nullptr);
       }
     };
     __syncthreads();  // the previous unit's merge has left the ring

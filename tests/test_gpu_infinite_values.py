@@ -33,14 +33,14 @@ def test_infinite_values_of_the_context(B, Hq, Hkv, D, ctx, nq, fused):
     assert np.isfinite(O).all() and np.abs(O - want).max() <= 2e-2
 
 
-# One unit of 9 tokens, the first of which has the score 0, the last `below` less, the others 200 less (in powers of two)
+# Units of 8 tokens and the new ones, the first of which has the score 0, the eighth `below` less, the others 200 less (in powers of two)
 @pytest.mark.parametrize("dtype,least", [("bf16", 126), ("fp32", 148)])  # exponent of the smallest probability that is not taken as 0
-@pytest.mark.parametrize("Hq,D,nq", [(1, 64, 3), (4, 128, 4), (4, 128, 6), (2, 64, 16), (8, 128, 8), (5, 64, 8)])  # 3, 16, 24, 32, 64 and 40 rows
+@pytest.mark.parametrize("Hq,Hkv,D,nq", [(1, 1, 64, 3), (4, 1, 128, 4), (4, 1, 128, 6), (2, 1, 64, 16), (8, 1, 128, 8), (5, 1, 64, 8),
+                                         (136, 17, 128, 8), (85, 17, 64, 8), (81, 81, 128, 4)])  # up to 64 rows, and each kernel
 @pytest.mark.parametrize("below", [20, 90, 97, 98, 110, 126, 140])
-def test_infinite_values_of_small_probability(Hq, D, nq, dtype, least, below):
+def test_infinite_values_of_small_probability(Hq, Hkv, D, nq, dtype, least, below):
     from paper_2404_15778_amd import harness as hip
-    w = wl.make_attention("tiny", 1, Hq, 1, D, dtype, np.array([8], np.int32), np.array([nq], np.int32), seed=1,
-                          Lcap=64 if Hq * nq == 40 else 800)
+    w = wl.make_attention("tiny", 1, Hq, Hkv, D, dtype, np.array([8], np.int32), np.array([nq], np.int32), seed=1, Lcap=800)
     w.scale = float(np.log(2.0))
     Q, K, V = np.zeros(w.Q.shape, np.float32), np.zeros(w.K.shape, np.float32), np.ones(w.V.shape, np.float32)
     Q[..., 0], K[:, 1:, :, 0], K[:, 7, :, 0] = 1.0, -200.0, -float(below)
