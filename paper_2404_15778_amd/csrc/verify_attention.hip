@@ -1653,7 +1653,8 @@ __global__ __launch_bounds__(64 * kWideWaves, 1) void verify_attn_wide(AttnParam
   using Block = WideBlock<D, kI8>;
   __shared__ f32x4 exchange[kAccs][W - 1][kQuads][64];
   __shared__ float wave_m[W][kTiles][kRows], wave_l[W][kTiles][kRows];
-  __shared__ float scales[W][kI8 ? 64 : 1];
+  __shared__ __align__(16) float scales[W][kI8 ? 64 : 1];
+  static_assert(__alignof__(scales) % 16 == 0, "read four at a time (wide_scores, wide_softmax)");
   __shared__ int arrived_last[2];
   __shared__ WideQueryRows<D, kI8, NT> q_lds;
   __shared__ WideNewRows<D, kI8, NT> rows_lds;
