@@ -167,9 +167,8 @@ struct ShareRecord {
   int32_t overflow;   // index of segment 2 in the overflow list (segments 2 .. nseg-1 are consecutive there); it is
                       // share + unit index of that segment, which keeps the runs of different shares apart
   int32_t signature;  // plan_signature() of the plan: what a launch checks before it trusts the record
-  int32_t flags;      // kRecAnyInactive, kRecFewShares (the same in every record)
+  int32_t flags;      // kRecAnyInactive (the same in every record)
 };
-constexpr int32_t kRecFewShares = 2;    // the list was divided over fewer shares than there are records (the same in every record)
 constexpr int32_t kRecAnyInactive = 1;  // some sequence has no query token: its output rows still have to be cleared
 
 // What a launch and its plan must agree on, folded into one word that every record carries (a launch then

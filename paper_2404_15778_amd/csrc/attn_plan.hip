@@ -74,7 +74,7 @@ BASS_HD inline void write_record(const PlanShape& s, const int32_t* seq_L, const
   records[w].nseg = wr.n;
   records[w].overflow = wr.base;
   records[w].signature = signature;
-  records[w].flags = (any_inactive ? kRecAnyInactive : 0) | (shares_wanted(s, total) < s.nshares ? kRecFewShares : 0);
+  records[w].flags = any_inactive ? kRecAnyInactive : 0;
 }
 
 BASS_HD inline int32_t owners_of_unit(const PlanShape& s, const Split& sp, int pb, const int32_t* seq_L, const int32_t* seq_nq,

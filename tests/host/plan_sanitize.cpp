@@ -7,6 +7,7 @@
 //   - every share between a unit's first and last contributor holds at least one real block of it,
 //   - partial slots (share + unit) never collide,
 //   - the cache layout maps are bijections onto a block.
+// Shapes whose short lists go to fewer shares (min_entries, used) and whose units may get stretches of their own (whole) are among them.
 // Prints "ok <cases>" and exits 0, or reports the first violation and exits 1.
 #include <cstdio>
 #include <cstdlib>
@@ -26,19 +27,30 @@ static int fail(const char* what, int a = 0, int b = 0, int c = 0) {
   return 1;
 }
 
-static int check_case(const PlanShape& s, const std::vector<int32_t>& ctx, const std::vector<int32_t>& dl) {
+static int check_case(PlanShape s, const std::vector<int32_t>& ctx, const std::vector<int32_t>& dl) {
   std::vector<int32_t> L(s.B), nq(s.B), inc(s.B);
-  int carry = 0;
+  int entries = 0, carry = 0;
+  int64_t once = 0, twice = 0;
   for (int b = 0; b < s.B; ++b) {
     int l = ctx[b], n = dl[b];
     clamp_lengths(l, n, s.kmax, s.Lcap);
     if (n < 0 || n > s.kmax || l < 0 || l + n > s.Lcap) return fail("clamp", b, l, n);
     L[b] = l;
     nq[b] = n;
-    carry += padded_blocks(s.pad, seq_blocks(s, l, n));
+    entries += padded_blocks(s.pad, seq_blocks(s, l, n)) * s.Hkv;
+    if (s.whole > 0) {
+      once += (int64_t)stretches_of(s.whole, seq_blocks(s, l, n)) * s.Hkv;
+      twice += (int64_t)stretches_of(2 * s.whole, seq_blocks(s, l, n)) * s.Hkv;
+    }
+  }
+  s = settle_whole(s, entries, once, twice);
+  for (int b = 0; b < s.B; ++b) {
+    carry += unit_entries(s, seq_blocks(s, L[b], nq[b]));
     inc[b] = carry;
   }
   const int total = carry * s.Hkv;
+  const int wanted = shares_wanted(s, entries);
+  if (wanted < 1 || wanted > most_shares(s)) return fail("shares wanted", wanted, most_shares(s));
   const Split sp = plan_split(s, total);
   if (sp.first(s.nshares) != total) return fail("split does not cover the list", total);
   int longest = 0, shortest = 1 << 30, nonempty = 0;
@@ -54,8 +66,10 @@ static int check_case(const PlanShape& s, const std::vector<int32_t>& ctx, const
   }
   if (total > 0) {
     if (nonempty > 1 && longest - shortest > 1) return fail("uneven shares", longest, shortest);
+    if (nonempty > most_shares(s)) return fail("more shares than there are", nonempty, most_shares(s));
     // no share is longer than an even division over the aimed-at number of shares would make it
-    if (longest > (total + s.target - 1) / s.target) return fail("a share is longer than total / target", longest, total, s.target);
+    const int aim = s.target < s.nshares ? s.target : wanted;
+    if (s.whole > 0 ? longest > s.whole || nonempty > wanted : longest > (total + aim - 1) / aim) return fail("a share is longer than total / target", longest, total, s.target);
     if (s.target < s.nshares && nonempty > 1 && total >= 2 * s.nshares && longest != shortest)
       return fail("room for more shares, but they are not equally long", longest, shortest);
   }
@@ -79,6 +93,7 @@ static int check_case(const PlanShape& s, const std::vector<int32_t>& ctx, const
       if (g.L != L[g.b] || g.nq != nq[g.b]) { err = fail("lengths", w, g.L, g.nq); return; }
       if (((g.flags & kSegLast) != 0) != (g.first + g.n == (int)cov.size())) { err = fail("last flag", w, g.first, g.n); return; }
       if (unit <= prev_unit) { err = fail("units of a share not increasing", w, unit, prev_unit); return; }
+      if (s.whole > 0 && (prev_unit >= 0 || g.n > s.whole)) { err = fail("a share of several units", w, unit, g.n); return; }
       prev_unit = unit;
       for (int j = g.first; j < g.first + g.n; ++j) cov[j]++;
       holders[unit].insert(w);
@@ -145,6 +160,14 @@ int main(int argc, char** argv) {
     s.pad = uni(0, kMaxPad);
     s.pad_before = uni(0, s.pad);
     s.span = it % 4 == 0 ? uni(0, s.Lcap + 50) : 0;
+    if (it % 3 == 2) {  // (with target = nshares, as the launches have it)
+      s.target = s.nshares;
+      s.used = uni(0, 2) ? imax(1, s.nshares / uni(1, 4)) : 0;
+      s.min_entries = uni(0, 8);
+      s.longer_from = uni(0, 1) ? uni(1, 40) : 0;
+      s.whole = s.min_entries > 0 && uni(0, 2) ? uni(1, 5) : 0;
+      if (s.whole > 0) s.pad_before = 0;
+    }
     std::vector<int32_t> ctx(s.B), dl(s.B);
     for (int b = 0; b < s.B; ++b) {
       const int mode = uni(0, 9);
@@ -153,8 +176,8 @@ int main(int argc, char** argv) {
       if (it % 11 == 0) ctx[b] = uni(0, imin(s.Lcap, 40));  // many tiny units
     }
     if (check_case(s, ctx, dl)) {
-      printf("case %d: B=%d Hkv=%d kmax=%d Lcap=%d nshares=%d target=%d pad=%d pad_before=%d span=%d\n", it, s.B, s.Hkv, s.kmax,
-             s.Lcap, s.nshares, s.target, s.pad, s.pad_before, s.span);
+      printf("case %d: B=%d Hkv=%d kmax=%d Lcap=%d nshares=%d target=%d pad=%d pad_before=%d span=%d used=%d min_entries=%d longer_from=%d whole=%d\n", it, s.B, s.Hkv, s.kmax,
+             s.Lcap, s.nshares, s.target, s.pad, s.pad_before, s.span, s.used, s.min_entries, s.longer_from, s.whole);
       return 1;
     }
     ++done;
