@@ -51,8 +51,7 @@ struct PlanShape {
   int32_t pad_before;  // how many of them sit in front of the unit's last real block
   int32_t span;        // BASS-PAD variant: every active sequence is processed over at least this many cache
                        // positions (0: over its own length); the positions beyond its length are masked
-  int32_t min_entries = 0;  // shares are not made shorter than this many entries (0: no bound) ...
-  int32_t per_unit = 0;     // ... but this many per unit there may always be
+  int32_t min_entries = 0;  // shares are not made shorter than this many entries (0: no bound), but one per unit there may always be
   int32_t used = 0;         // the list is divided over at most this many of the shares (0: all of them)
   int32_t longer_from = 0;  // units of so many entries on average: twice min_entries (0: never)
   int32_t whole = 0;        // real blocks of a stretch where every unit gets stretches of its own (0: it does not); see settle_whole
@@ -104,11 +103,9 @@ BASS_HD inline bool worth_fewer(const PlanShape& s, int few) {
 }
 BASS_HD inline int shares_wanted(const PlanShape& s, int total) {
   const int entries = s.longer_from > 0 && total >= s.longer_from * s.B * s.Hkv ? 2 * s.min_entries : s.min_entries;
-  const int few = entries > 0 ? imax(1, imax(total / entries, s.per_unit * s.B * s.Hkv)) : 0;
+  const int few = entries > 0 ? imax(1, imax(total / entries, s.B * s.Hkv)) : 0;
   return worth_fewer(s, few) ? few : most_shares(s);
 }
-// Whether lists of any length may be divided so: those of the fewest shares
-BASS_HD inline bool may_be_few(const PlanShape& s) { return worth_fewer(s, imax(1, s.per_unit * s.B * s.Hkv)); }
 
 // Where the units are short, virtual entries cut them apart for nothing: a unit of 3 real blocks and 7 virtual ones, divided by 4 entries,
 // is two or three partial results and their merge instead of none.  So if stretches of at most `whole` real blocks, each of one unit, are no
@@ -176,9 +173,9 @@ constexpr int32_t kRecAnyInactive = 1;  // some sequence has no query token: its
 // lengths and the span, and `used`, which sizes the grid of the workgroup-level kernels.  Never 0: cleared memory
 // does not match.
 BASS_HD inline int32_t plan_signature(const PlanShape& s, int flags) {
-  const int32_t v[14] = {s.B, s.kmax, s.Hkv, s.Lcap, s.nshares, s.target, s.pad, s.pad_before, s.min_entries, s.per_unit, s.used, s.whole, s.longer_from, flags};
+  const int32_t v[13] = {s.B, s.kmax, s.Hkv, s.Lcap, s.nshares, s.target, s.pad, s.pad_before, s.min_entries, s.used, s.whole, s.longer_from, flags};
   uint32_t h = 2166136261u;
-  for (int i = 0; i < 14; ++i) h = (h ^ (uint32_t)v[i]) * 16777619u;
+  for (int i = 0; i < 13; ++i) h = (h ^ (uint32_t)v[i]) * 16777619u;
   return (int32_t)(h | 1u);
 }
 

@@ -188,7 +188,7 @@ struct LaunchShape {
   bool fused_append;  // the step's rows are appended inside the attention launch, and its plan says so
   bool tiles_append;  // longer drafts, workgroup-level kernels: they patch a block at a time and stage nothing, so
                       // planned launches may append there too; the plan is the one of a launch that does not append
-  int rows_max, nwaves, nshares, used_shares, target, pad, pad_before, min_entries, per_unit, whole, longer_from;
+  int rows_max, nwaves, nshares, used_shares, target, pad, pad_before, min_entries, whole, longer_from;
 };
 
 // One query tile per kv head: 768 wavefronts, over INT8 caches too -- as 256 workgroups of three they measured level with 1024 on
@@ -229,7 +229,6 @@ inline LaunchShape launch_shape(const bass_attn_desc* d, bool append) {
   s.target = s.nshares;
   s.pad = s.narrow ? kNarrowPad : s.wide ? kWidePad : s.fused_append ? kAppendPad : kPlainPad;
   s.min_entries = setting > 0 ? 0 : s.narrow ? kNarrowEntries : s.wide ? kWideEntries : s.tiles && few_units ? kRowEntries : 0;
-  s.per_unit = 1;
   s.longer_from = !s.wide && s.min_entries > 0 && int8 ? kRowLonger : 0;
   s.whole = s.wide && s.min_entries > 0 ? kWidePerStep : 0;
   s.pad_before = 0;

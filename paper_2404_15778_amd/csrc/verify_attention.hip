@@ -52,7 +52,6 @@ struct AttnParams {
   int B, kmax, Hq, Hkv, D, Lcap, nblk_cap, g, rows_max, nwaves;
   unsigned g_magic;  // ceil(2^20 / g) if g <= 64 and rows_max <= 2048 (then r / g == (r * g_magic) >> 20 for every row r), else 0
   int wpw;  // wavefronts per workgroup of the attention launch (nwaves is a multiple)
-  int nshares;  // stretches the block list is cut into: one per wavefront, or one per workgroup (tile kernel)
   float scale_log2;  // scale * log2(e): scores are kept in the log2 domain
   const void* Q;
   const void* Kc;
@@ -61,7 +60,6 @@ struct AttnParams {
   const void* Vnew;
   // the step's plan (attn_plan.h): header, one record per share, the further segments, per-sequence
   // query counts, per-unit contributors
-  const PlanHeader* plan;
   int32_t signature;  // plan_signature() of the plan this launch expects
   const ShareRecord* records;
   const Segment* overflow;
@@ -170,15 +168,6 @@ __device__ inline f32x4 load_dev4(__amdgpu_buffer_rsrc_t rs, unsigned byte_off) 
   return __builtin_bit_cast(f32x4, __builtin_amdgcn_raw_buffer_load_b128(rs, (int)byte_off, 0, kAuxDeviceScope));
 }
 
-__device__ inline void store_dev1(float* dst, float a) {
-  __hip_atomic_store((unsigned*)dst, __float_as_uint(a), __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
-}
-
-__device__ inline float2 load_dev(const float* src) {
-  const unsigned long long v = __hip_atomic_load((const unsigned long long*)src, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
-  return make_float2(__uint_as_float((unsigned)v), __uint_as_float((unsigned)(v >> 32)));
-}
-
 // ---------------------------------------------------------------------------------------
 // Split-context reduction, done by the wavefront that completes a unit:
 //   M = max_s m_s ;  l = sum_s l_s 2^(m_s - M) ;  O = sum_s acc_s 2^(m_s - M) / l
@@ -199,18 +188,6 @@ __device__ inline void zero_rows(const AttnParams& p, int b, int kvh, int row_fr
       if (p.lse && lane % lpr == 0) p.lse[orow] = 0.f;
     }
   }
-}
-
-__device__ inline float group16_max(float v) {
-#pragma unroll
-  for (int o = 8; o >= 1; o >>= 1) v = fmaxf(v, __shfl_xor(v, o));
-  return v;
-}
-
-__device__ inline float group16_sum(float v) {
-#pragma unroll
-  for (int o = 8; o >= 1; o >>= 1) v += __shfl_xor(v, o);
-  return v;
 }
 
 // Split-context reduction of a unit, 64 / LPR query rows per sweep: LPR lanes per row, each lane owning
@@ -1480,13 +1457,13 @@ __device__ inline void mask_wide(WideBlock<D, kI8>& r, float (&s)[Wide<D, kI8, N
 }
 
 // Online softmax of a block: scores -> probabilities as operand B of the V product (INT8: times the tokens' V scales), running
-// maximum and sum.  kFine: shapes whose lists may be divided over fewer shares, where the rounding of the probabilities to bf16 would
-// cost precision (kNarrowUnits): their 24 bits are cut into three operands of 8 and all multiplied.  No part is negative, and none is
+// maximum and sum.  16 rows: with few shares per unit the rounding of the probabilities to bf16 would cost precision (kNarrowUnits); their
+// 24 bits are cut into three operands of 8 and all multiplied.  No part is negative, and none is
 // zero where the probability is not, so that an infinite element of V stays infinite in every product: the second and third are at
 // least 2^-133, the smallest bf16, which the matrix instruction takes as it is (a probability is 0 or at least 2^-126; together they are
 // off by at most 2^-132, 2^-22 of a probability of 2^-110).  (Two parts leave 2^-17: 3.6e-6 instead of 2.3e-6 with a rounded first part,
 // whose remainder may be negative.)
-template <int D, bool kI8, int NT, bool kFine>
+template <int D, bool kI8, int NT>
 __device__ inline void wide_softmax(const float (&s)[Wide<D, kI8, NT>::kTiles][Wide<D, kI8, NT>::kScores], WideState<D, kI8, NT>& st, int h, const float* scales,
                                     bf16x8 (&pf)[Wide<D, kI8, NT>::kTiles][Wide<D, kI8, NT>::kProbs],
                                     bf16x8 (&pr)[2][Wide<D, kI8, NT>::kTiles][Wide<D, kI8, NT>::kProbs]) {
@@ -1521,7 +1498,7 @@ __device__ inline void wide_softmax(const float (&s)[Wide<D, kI8, NT>::kTiles][W
         const float pj = __builtin_amdgcn_exp2f(s[nt][i] - m_use);
         psum += pj;
         const float z = kI8 ? pj * vs[e] : pj;
-        if constexpr (kFine) {
+        if constexpr (G::kSmall) {
           const float a = cut(z), b = cut(z - a), least = fminf(z, 0x1p-133f);
           pf[nt][i >> 3][i & 7] = (__bf16)a;
           pr[0][nt][i >> 3][i & 7] = (__bf16)fmaxf(b, least);
@@ -1535,7 +1512,7 @@ __device__ inline void wide_softmax(const float (&s)[Wide<D, kI8, NT>::kTiles][W
   }
 }
 
-template <int D, bool kI8, int NT, bool kFine>
+template <int D, bool kI8, int NT>
 __device__ inline void wide_values(const WideBlock<D, kI8>& r, const bf16x8 (&pf)[Wide<D, kI8, NT>::kTiles][Wide<D, kI8, NT>::kProbs],
                                    const bf16x8 (&pr)[2][Wide<D, kI8, NT>::kTiles][Wide<D, kI8, NT>::kProbs], WideState<D, kI8, NT>& st) {
   using G = Wide<D, kI8, NT>;
@@ -1551,16 +1528,10 @@ __device__ inline void wide_values(const WideBlock<D, kI8>& r, const bf16x8 (&pf
       for (int nt = 0; nt < G::kTiles; ++nt) {
         typename G::Acc& acc = st.acc[nt][kFrags * (x / G::kProbs) + f];
         if constexpr (G::kSmall) {
-          if constexpr (kFine) {
-            acc = __builtin_amdgcn_mfma_f32_16x16x32_bf16(v, pr[1][nt][0], acc, 0, 0, 0);
-            acc = __builtin_amdgcn_mfma_f32_16x16x32_bf16(v, pr[0][nt][0], acc, 0, 0, 0);
-          }
+          acc = __builtin_amdgcn_mfma_f32_16x16x32_bf16(v, pr[1][nt][0], acc, 0, 0, 0);
+          acc = __builtin_amdgcn_mfma_f32_16x16x32_bf16(v, pr[0][nt][0], acc, 0, 0, 0);
           acc = __builtin_amdgcn_mfma_f32_16x16x32_bf16(v, pf[nt][0], acc, 0, 0, 0);
         } else {
-          if constexpr (kFine) {
-            acc = __builtin_amdgcn_mfma_f32_32x32x16_bf16(v, pr[1][nt][x & 1], acc, 0, 0, 0);
-            acc = __builtin_amdgcn_mfma_f32_32x32x16_bf16(v, pr[0][nt][x & 1], acc, 0, 0, 0);
-          }
           acc = __builtin_amdgcn_mfma_f32_32x32x16_bf16(v, pf[nt][x & 1], acc, 0, 0, 0);
         }
       }
@@ -1642,7 +1613,7 @@ __device__ inline void merge_wide(const AttnParams& p, const WideJob& j, int wv,
   }
 }
 
-template <int D, bool kI8, int NT, bool kFine>
+template <int D, bool kI8, int NT>
 __global__ __launch_bounds__(64 * kWideWaves, 1) void verify_attn_wide(AttnParams p) {
   using G = Wide<D, kI8, NT>;
   constexpr int W = kWideWaves, kTiles = G::kTiles, kRows = G::kRows, kQuads = G::kQuads;
@@ -1822,9 +1793,9 @@ __global__ __launch_bounds__(64 * kWideWaves, 1) void verify_attn_wide(AttnParam
       fetch_k(r, seg, t + R);
       if (!plain) mask_wide<D, kI8, NT>(r, s, q, tok0, u.L + u.nq, h);
       bf16x8 pf[kTiles][G::kProbs], pr[2][kTiles][G::kProbs];
-      wide_softmax<D, kI8, NT, kFine>(s, st, h, sc, pf, pr);
+      wide_softmax<D, kI8, NT>(s, st, h, sc, pf, pr);
       if constexpr (kI8) __builtin_amdgcn_wave_barrier();
-      wide_values<D, kI8, NT, kFine>(r, pf, pr, st);
+      wide_values<D, kI8, NT>(r, pf, pr, st);
       fetch_v(r, seg, t + R);
     };
     for (int t = 0; t < n_mine; t += R) {
@@ -2544,12 +2515,11 @@ static int check_attention_args(const bass_attn_desc* d, const LaunchShape& ls, 
 
 // The workgroup-level kernels.
 template <int D, bool kI8>
-static void launch_wide(bool few, dim3 grid, hipStream_t s, const AttnParams& p) {
+static void launch_wide(dim3 grid, hipStream_t s, const AttnParams& p) {
   const dim3 block(64 * kWideWaves);
-  if (p.rows_max > 32) hipLaunchKernelGGL((verify_attn_wide<D, kI8, 2, false>), grid, block, 0, s, p);
-  else if (p.rows_max > 16) hipLaunchKernelGGL((verify_attn_wide<D, kI8, 1, false>), grid, block, 0, s, p);
-  else if (few) hipLaunchKernelGGL((verify_attn_wide<D, kI8, 0, true>), grid, block, 0, s, p);
-  else hipLaunchKernelGGL((verify_attn_wide<D, kI8, 0, false>), grid, block, 0, s, p);
+  if (p.rows_max > 32) hipLaunchKernelGGL((verify_attn_wide<D, kI8, 2>), grid, block, 0, s, p);
+  else if (p.rows_max > 16) hipLaunchKernelGGL((verify_attn_wide<D, kI8, 1>), grid, block, 0, s, p);
+  else hipLaunchKernelGGL((verify_attn_wide<D, kI8, 0>), grid, block, 0, s, p);
 }
 
 template <bool kFused>
@@ -2576,12 +2546,10 @@ static int launch_attention(const bass_attn_desc* d, const LaunchShape& ls, cons
   p.nblk_cap = num_blocks(d->Lcap); p.g = g; p.rows_max = rows_max;
   p.g_magic = (g <= 64 && rows_max <= 2048) ? ((1u << 20) + (unsigned)g - 1u) / (unsigned)g : 0u;  // exact there: checked exhaustively
   p.nwaves = ls.nwaves;
-  p.nshares = ls.nshares;
   p.scale_log2 = d->scale * 1.4426950408889634f;
   p.Q = Q; p.Kc = Kcache; p.Vc = Vcache; p.Knew = K_new; p.Vnew = V_new;
   const PlanLayout pl = plan_layout(d->B, d->Hkv, ls.nshares);
   const char* pb = (const char*)plan;
-  p.plan = (const PlanHeader*)pb;
   p.signature = plan_signature(plan_shape(d, ls, 0), K_new && ls.fused_append ? kPlanAppend : 0);
   p.records = (const ShareRecord*)(pb + pl.records);
   p.overflow = (const Segment*)(pb + pl.overflow);
@@ -2604,13 +2572,12 @@ static int launch_attention(const bass_attn_desc* d, const LaunchShape& ls, cons
     else hipLaunchKernelGGL((verify_attn_fp32<16, 0>), grid, block, 0, s, p);
   } else if (ls.wide) {
     const dim3 wgrid((unsigned)ls.used_shares);
-    const bool few = may_be_few(plan_shape(d, ls, 0));
     if (d->dtype == BASS_DTYPE_INT8KV) {
-      if (d->D == 128) launch_wide<128, true>(few, wgrid, s, p);
-      else launch_wide<64, true>(few, wgrid, s, p);
+      if (d->D == 128) launch_wide<128, true>(wgrid, s, p);
+      else launch_wide<64, true>(wgrid, s, p);
     } else {
-      if (d->D == 128) launch_wide<128, false>(few, wgrid, s, p);
-      else launch_wide<64, false>(few, wgrid, s, p);
+      if (d->D == 128) launch_wide<128, false>(wgrid, s, p);
+      else launch_wide<64, false>(wgrid, s, p);
     }
   } else if (ls.tiles) {
     const dim3 tgrid((unsigned)ls.used_shares);
