@@ -104,11 +104,21 @@ def test_stretches_of_several_blocks(dtype, ctx, D, kmax, Hq, Hkv):
 
 
 @pytest.mark.parametrize("dtype", ["bf16", "int8kv"])
-def test_refused_launch_of_many_long_drafts_appends_nothing(dtype):
-    """More than 256 units of 32 row slots and more: the rows are appended by a launch of their own."""
+@pytest.mark.parametrize("ctx", [[600, 333, 640, 64, 5]])
+@pytest.mark.parametrize("D,kmax,Hq,Hkv", [(128, 40, 56, 56), (64, 33, 60, 60)])
+def test_long_drafts_of_many_units_in_small_caches(dtype, ctx, D, kmax, Hq, Hkv):
+    """280 and 300 units of more than 32 rows, caches of at most 24 blocks: appended by a launch of their own over bf16 caches too."""
+    test_stretches_of_several_blocks(dtype, ctx, D, kmax, Hq, Hkv)
+
+
+@pytest.mark.parametrize("dtype", ["bf16", "int8kv"])
+@pytest.mark.parametrize("kmax", [32, 33])
+def test_refused_launch_of_many_long_drafts_appends_nothing(dtype, kmax):
+    """More than 256 units of 32 row slots and more: the rows are appended by a launch of their own, but for 32 rows over bf16 caches, which
+    the attention launch appends.  Either way a plan of another shape stops it before anything is written."""
     import torch
     import paper_2404_15778_amd as bass
-    dev, B, kmax, H, D, Lcap = "cuda:0", 17, 32, 16, 128, 96
+    dev, B, H, D, Lcap = "cuda:0", 17, 16, 128, 96
     d = bass.make_desc(B, kmax, H, H, D, Lcap, dtype, 1.0 / math.sqrt(D))
     gen = torch.Generator(device=dev)
     gen.manual_seed(1)

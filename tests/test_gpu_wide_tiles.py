@@ -9,6 +9,8 @@ import workloads as wl
 pytestmark = pytest.mark.gpu
 # probabilities and V are rounded to bf16 (2^-9 each) for outputs of magnitude up to about 4
 TOL = 2e-2
+# scores, exponentials and their sum stay in 32 bits: a few roundings of values up to about 20
+LSE_TOL = 1e-4
 
 
 @pytest.mark.parametrize("blocks", [24, 25])
@@ -23,7 +25,7 @@ def test_rows_and_cache_sizes(D, Hq, Hkv, kmax, blocks, fused):
     Or, lser = oracle.verify_attention(w.Q, w.K, w.V, w.ctx_len, w.draft_len, w.scale)
     O, lse, status, _ = harness.run_attention_workload(w, poison=True, fused=fused)
     assert status == 0 and np.isfinite(O).all()
-    assert np.abs(O - Or).max() <= TOL and np.abs(lse - lser).max() <= TOL
+    assert np.abs(O - Or).max() <= TOL and np.abs(lse - lser).max() <= LSE_TOL
 
 
 @pytest.mark.parametrize("Hq,kmax", [(4, 6), (4, 16)])  # 24 and 64 rows
@@ -74,7 +76,7 @@ def test_units_at_the_edge_of_one_tile(dtype, D, g, kmax, Hkv):
     Or, lser = oracle.verify_attention(Q, K, V, w.ctx_len, w.draft_len, w.scale)
     for fused in (False, True):
         O, lse, status, _ = harness.run_attention_workload(w, poison=True, fused=fused)
-        assert status == 0 and np.abs(O - Or).max() <= TOL and np.abs(lse - lser).max() <= TOL
+        assert status == 0 and np.abs(O - Or).max() <= TOL and np.abs(lse - lser).max() <= LSE_TOL
 
 
 @pytest.mark.parametrize("dtype", ["bf16", "int8kv"])
@@ -92,4 +94,4 @@ def test_units_at_the_edge_of_several_tiles(dtype, D, g, kmax, B, Hkv):
     Or, lser = oracle.verify_attention(Q, K, V, w.ctx_len, w.draft_len, w.scale)
     for fused in (False, True):
         O, lse, status, _ = harness.run_attention_workload(w, poison=True, fused=fused)
-        assert status == 0 and np.abs(O - Or).max() <= TOL and np.abs(lse - lser).max() <= TOL
+        assert status == 0 and np.abs(O - Or).max() <= TOL and np.abs(lse - lser).max() <= LSE_TOL
