@@ -53,7 +53,7 @@ struct PlanShape {
                        // positions (0: over its own length); the positions beyond its length are masked
   int32_t min_entries = 0;  // shares are not made shorter than this many entries (0: no bound), but one per unit there may always be
   int32_t used = 0;         // the list is divided over at most this many of the shares (0: all of them)
-  int32_t longer_from = 0;  // units of so many entries on average: twice min_entries (0: never)
+  int32_t grow = 0;         // > 0: that bound is 1 for units of fewer than so many entries on average and doubles with them, up to min_entries
   int32_t whole = 0;        // real blocks of a stretch where every unit gets stretches of its own (0: it does not); see settle_whole
 };
 
@@ -102,7 +102,9 @@ BASS_HD inline bool worth_fewer(const PlanShape& s, int few) {
   return s.min_entries > 0 && few < most && (s.B * s.Hkv <= most / kManyPerUnit || few <= most / 2);
 }
 BASS_HD inline int shares_wanted(const PlanShape& s, int total) {
-  const int entries = s.longer_from > 0 && total >= s.longer_from * s.B * s.Hkv ? 2 * s.min_entries : s.min_entries;
+  int entries = s.min_entries;
+  if (s.grow > 0)
+    for (entries = 1; 2 * entries <= s.min_entries && total / (s.B * s.Hkv) >= entries * s.grow;) entries *= 2;
   const int few = entries > 0 ? imax(1, imax(total / entries, s.B * s.Hkv)) : 0;
   return worth_fewer(s, few) ? few : most_shares(s);
 }
@@ -173,7 +175,7 @@ constexpr int32_t kRecAnyInactive = 1;  // some sequence has no query token: its
 // lengths and the span, and `used`, which sizes the grid of the workgroup-level kernels.  Never 0: cleared memory
 // does not match.
 BASS_HD inline int32_t plan_signature(const PlanShape& s, int flags) {
-  const int32_t v[13] = {s.B, s.kmax, s.Hkv, s.Lcap, s.nshares, s.target, s.pad, s.pad_before, s.min_entries, s.used, s.whole, s.longer_from, flags};
+  const int32_t v[13] = {s.B, s.kmax, s.Hkv, s.Lcap, s.nshares, s.target, s.pad, s.pad_before, s.min_entries, s.used, s.whole, s.grow, flags};
   uint32_t h = 2166136261u;
   for (int i = 0; i < 13; ++i) h = (h ^ (uint32_t)v[i]) * 16777619u;
   return (int32_t)(h | 1u);

@@ -264,7 +264,7 @@ PlanShape plan_shape(const bass_attn_desc* d, const LaunchShape& ls, int span) {
   PlanShape s;
   s.B = d->B; s.kmax = d->kmax; s.Hkv = d->Hkv; s.Lcap = d->Lcap;
   s.nshares = ls.nshares; s.target = ls.target; s.pad = ls.pad; s.pad_before = ls.pad_before; s.span = span;
-  s.min_entries = ls.min_entries; s.used = ls.used_shares; s.whole = ls.whole; s.longer_from = ls.longer_from;
+  s.min_entries = ls.min_entries; s.used = ls.used_shares; s.whole = ls.whole; s.grow = ls.grow;
   return s;
 }
 

@@ -136,18 +136,21 @@ constexpr int kPlainBefore = 0;   // kernel; measured: +0.5 % with the fused app
 //   wide: bf16, at most 150 tokens 10.4 / 13.4 / 20.2 -> 12.4 / 15.0 / 23.6 us, 400 tokens 15.3 / 15.2 / 23.1 -> 16.3 / 16.6 / 25.6, 700 tokens
 //   15.0 / 18.9 / 30.2 -> 16.4 / 17.8 / 30.9, 1200 tokens 19.5 / 21.8 / 42.0 -> 18.9 / 21.6 / 40.5; INT8, 700 tokens 19.7 / 19.9 / 30.7 -> 17.6 / 18.2 /
 //   31.2, 1200 tokens 21.4 / 21.7 / 39.4 -> 19.4 / 23.8 / 35.8.
-// - So do few units in caches of any size, where a short list loses most: 8 units of 128, 48 rows, 60 / 150 / 400 / 1000 / 2500 / 4000 tokens,
-//   sharing rows -> wide: bf16 9.8 / 9.3 / 9.8 / 11.4 / 13.4 / 16.8 -> 12.6 / 12.7 / 12.5 / 13.3 / 14.9 / 16.6, INT8 10.9 / 10.6 / 10.7 / 12.2 / 13.8 / 17.0 ->
-//   14.1 / 14.1 / 14.0 / 14.2 / 15.3 / 16.2; 16 units bf16 10.1 / 9.6 / 11.0 / 13.1 / 19.8 / 21.0 -> 12.7 / 12.8 / 13.2 / 14.4 / 16.9 / 18.6; 32 units 10.6 / 11.0 /
-//   13.2 / 17.5 / 22.3 / 26.2 -> 13.1 / 13.8 / 14.5 / 17.1 / 21.4 / 24.9.  Heads of 64 over INT8 caches turn earlier, 16 units 9.9 / 11.1 / 10.0 / 12.6 / 16.7 /
-//   18.6 -> 11.0 / 11.1 / 11.1 / 11.4 / 13.0 / 14.2.
-//   There shares get at least kRowEntries entries, because each is a partial result to be merged, and over INT8 caches from kRowLonger
-//   entries per unit on twice as many: 8 units of 128, 48 rows, at least 0 / 2 / 4 entries, INT8 60 tokens 10.6 / 10.9 / 12.5, 1000 14.9 / 12.3 /
-//   12.1, 2500 19.6 / 16.8 / 13.9 (6 entries 16.2); bf16 9.1 / 9.8 / 10.6, 12.9 / 11.9 / 11.5, 15.2 / 15.3 / 13.6, but with 4 a wavefront has two
+// - So do few units in caches of any size, where a short list loses most: units of 128, 48 rows, 60 / 150 / 400 / 1000 / 1500 / 2500 / 4000
+//   tokens, sharing rows -> wide: bf16, 8 units 9.8 / 9.3 / 9.8 / 11.9 / 13.0 / 15.3 / 16.6 -> 12.6 / 12.7 / 12.5 / 13.3 / 13.6 / 14.9 / 16.6, 16 units 10.1 / 9.6 /
+//   10.9 / 14.3 / 15.5 / 19.8 / 21.0 -> 12.7 / 12.8 / 13.2 / 14.4 / 15.3 / 16.9 / 18.6, 32 units 10.6 / 11.0 / 13.2 / 17.5 / 20.1 / 22.3 / 26.2 -> 13.1 / 13.8 / 14.5 /
+//   17.1 / 17.4 / 21.4 / 24.9, 64 units 12.8 / 13.5 / 15.3 / 22.3 / 25.0 -> 15.0 / 15.5 / 16.5 / 19.5 / 23.9; INT8, 8 units 10.9 / 10.6 / 10.7 / 12.2 / 13.8 / 13.8 /
+//   17.0 -> 14.1 / 14.1 / 14.0 / 14.2 / 14.4 / 15.3 / 16.2, 16 units 11.1 / 10.9 / 11.6 / 13.0 / 15.9 / 18.5 / 19.8 -> 14.1 / 14.3 / 14.2 / 14.8 / 15.2 / 16.8 / 17.8, 32 units
+//   11.4 / 11.5 / 14.4 / 18.4 / 19.9 / 24.1 / 26.8 -> 14.5 / 14.5 / 14.7 / 16.2 / 17.3 / 22.5 / 24.9.  Units of 64 turn at half as many: INT8, 16 units 9.9 / 11.1 / 10.0 / 12.6 /
+//   13.7 / 16.7 / 18.6 -> 11.0 / 11.1 / 11.1 / 11.4 / 12.0 / 13.0 / 14.2; bf16, 32 units 8.9 / 10.1 / 11.2 / 13.4 / 16.5 / 17.7 / 19.9 -> 10.2 / 10.4 / 10.7 / 13.2 / 13.5 / 15.8 /
+//   17.6.  So up to a quarter of the head size over bf16 caches, an eighth over INT8 ones.
+//   There shares get 2, over INT8 caches 4 entries at least where the units are long enough (kRowGrow), because each is a partial result to
+//   be merged: 8 units of 128, 48 rows, at least 1 / 2 / 4 entries, INT8 60 tokens 10.6 / 10.9 / 12.5, 700 12.5 / 11.5 / 12.8, 1000 14.9 / 12.3 / 12.1, 2500
+//   19.6 / 16.8 / 13.9 (6 entries 16.2); bf16 9.1 / 9.8 / 10.6, 11.7 / 10.7 / 11.1, 12.9 / 11.9 / 11.5, 15.2 / 15.3 / 13.6, but with 4 a wavefront has two
 //   blocks, and precision is lost as below.
 constexpr int kShortCache = 24;
-constexpr int kFewUnits = 16, kFewUnitsInt8D64 = 8;
-constexpr int kRowEntries = 2, kRowLonger = 20;
+constexpr int kFewUnitsDiv = 4, kFewUnitsDivInt8 = 8;  // ... of the head size
+constexpr int kRowEntries = 2, kRowEntriesInt8 = 4, kRowGrow = 17;
 // verify_attn_wide: one workgroup per compute unit.  The end of a unit inside a stretch -- four states merged, the next unit's first
 // blocks waited for -- costs its workgroup about as much as 7 blocks: 16 layers of 16 sequences of 1024 - 4096 tokens, 64/8 heads, with 3 / 5 /
 // 7 virtual blocks per unit 769 / 758 / 758 us, 8 sequences, 32 heads, 32 rows 765 / 751 / 745.  Short lists go to fewer workgroups so that
@@ -188,7 +191,7 @@ struct LaunchShape {
   bool fused_append;  // the step's rows are appended inside the attention launch, and its plan says so
   bool tiles_append;  // longer drafts, workgroup-level kernels: they patch a block at a time and stage nothing, so
                       // planned launches may append there too; the plan is the one of a launch that does not append
-  int rows_max, nwaves, nshares, used_shares, target, pad, pad_before, min_entries, whole, longer_from;
+  int rows_max, nwaves, nshares, used_shares, target, pad, pad_before, min_entries, whole, grow;
 };
 
 // One query tile per kv head: 768 wavefronts, over INT8 caches too -- as 256 workgroups of three they measured level with 1024 on
@@ -213,7 +216,7 @@ inline LaunchShape launch_shape(const bass_attn_desc* d, bool append) {
   // 1 - 2 % slower than the even division on the benchmark shapes: more wavefronts, more partials to merge)
   s.nwaves = attention_waves(setting);
   s.narrow = s.mfma && !s.tiles && setting <= 0 && d->B * d->Hkv <= kNarrowUnits;
-  const bool few_units = d->B * d->Hkv <= (int8 && d->D == 64 ? kFewUnitsInt8D64 : kFewUnits);
+  const bool few_units = d->B * d->Hkv <= d->D / (int8 ? kFewUnitsDivInt8 : kFewUnitsDiv);
   s.wide = s.narrow || (s.tiles && (s.rows_max <= 32 || (num_blocks(d->Lcap) > kShortCache && !few_units)));
   // Longer drafts than the wavefronts stage: a patch costs a workgroup 1 - 3 us, one after the other for each of its units; an append by
   // itself goes by cache blocks from kBlockTokens slots on, which takes a 32-slot call 5 - 10 us.  Before the launch / inside it, us,
@@ -228,8 +231,8 @@ inline LaunchShape launch_shape(const bass_attn_desc* d, bool append) {
   s.nshares = !s.tiles ? s.nwaves : int8 ? 2 * stretches : s.wide && two && setting <= 0 ? s.used_shares : stretches;
   s.target = s.nshares;
   s.pad = s.narrow ? kNarrowPad : s.wide ? kWidePad : s.fused_append ? kAppendPad : kPlainPad;
-  s.min_entries = setting > 0 ? 0 : s.narrow ? kNarrowEntries : s.wide ? kWideEntries : s.tiles && few_units ? kRowEntries : 0;
-  s.longer_from = !s.wide && s.min_entries > 0 && int8 ? kRowLonger : 0;
+  s.min_entries = setting > 0 ? 0 : s.narrow ? kNarrowEntries : s.wide ? kWideEntries : s.tiles && few_units ? (int8 ? kRowEntriesInt8 : kRowEntries) : 0;
+  s.grow = !s.wide && s.min_entries > 0 ? kRowGrow : 0;
   s.whole = s.wide && s.min_entries > 0 ? kWidePerStep : 0;
   s.pad_before = 0;
   if (s.mfma && !s.tiles && !s.wide) s.pad_before = s.fused_append ? kAppendBefore : kPlainBefore;

@@ -164,7 +164,7 @@ int main(int argc, char** argv) {
       s.target = s.nshares;
       s.used = uni(0, 2) ? imax(1, s.nshares / uni(1, 4)) : 0;
       s.min_entries = uni(0, 8);
-      s.longer_from = uni(0, 1) ? uni(1, 40) : 0;
+      s.grow = uni(0, 1) ? uni(1, 40) : 0;
       s.whole = s.min_entries > 0 && uni(0, 2) ? uni(1, 5) : 0;
       if (s.whole > 0) s.pad_before = 0;
     }
@@ -176,8 +176,8 @@ int main(int argc, char** argv) {
       if (it % 11 == 0) ctx[b] = uni(0, imin(s.Lcap, 40));  // many tiny units
     }
     if (check_case(s, ctx, dl)) {
-      printf("case %d: B=%d Hkv=%d kmax=%d Lcap=%d nshares=%d target=%d pad=%d pad_before=%d span=%d used=%d min_entries=%d longer_from=%d whole=%d\n", it, s.B, s.Hkv, s.kmax,
-             s.Lcap, s.nshares, s.target, s.pad, s.pad_before, s.span, s.used, s.min_entries, s.longer_from, s.whole);
+      printf("case %d: B=%d Hkv=%d kmax=%d Lcap=%d nshares=%d target=%d pad=%d pad_before=%d span=%d used=%d min_entries=%d grow=%d whole=%d\n", it, s.B, s.Hkv, s.kmax,
+             s.Lcap, s.nshares, s.target, s.pad, s.pad_before, s.span, s.used, s.min_entries, s.grow, s.whole);
       return 1;
     }
     ++done;

@@ -46,13 +46,14 @@ def test_fewer_shares_only_where_they_are_worth_it(B, ctx, shares):
         assert busy_shares(plan) == shares
 
 
-# More than 32 rows of few units, which share rows: at least 2 entries for a share where that leaves less than all (256, INT8 512) of them
-@pytest.mark.parametrize("dtype,ctx,shares", [("bf16", 20, 16), ("bf16", 1500, 204), ("bf16", 1900, 252), ("bf16", 2000, 256), ("bf16", 4000, 256),
-                                              ("int8kv", 400, 64), ("int8kv", 1000, 70), ("int8kv", 4000, 258)])
+# More than 32 rows of few units, which share rows: at least 1 entry for a share, 2 from units of 17 entries on, 4 from 34 over INT8 caches,
+# where that leaves less than all (256, INT8 512) of them
+@pytest.mark.parametrize("dtype,ctx,shares", [("bf16", 20, 32), ("bf16", 180, 72), ("bf16", 400, 128), ("bf16", 440, 68), ("bf16", 1500, 204), ("bf16", 1900, 252), ("bf16", 2000, 256), ("bf16", 4000, 256),
+                                              ("int8kv", 180, 72), ("int8kv", 400, 128), ("int8kv", 440, 68), ("int8kv", 930, 132), ("int8kv", 970, 68), ("int8kv", 1000, 70), ("int8kv", 4000, 258)])
 def test_shares_of_few_units_that_share_rows(dtype, ctx, shares):
     d = bass.make_desc(1, 6, 64, 8, 128, 4096, dtype, 1.0)
     plan = check_plan(d, [ctx], [6], bass.PLAN_APPEND, 0)
     entries = int(plan["hdr"][10])
-    most, least = (256, 2) if dtype == "bf16" else (512, 2 if entries < 20 * 8 else 4)
+    most, least = (256, 1 if entries < 136 else 2) if dtype == "bf16" else (512, 1 if entries < 136 else 2 if entries < 272 else 4)
     assert entries == (-(-(ctx + 6) // 32) + 3) * 8 and shares == min(most, entries // least)
     assert shares - 3 * 8 <= busy_shares(plan) <= shares

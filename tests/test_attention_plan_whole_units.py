@@ -33,8 +33,8 @@ def test_longer_lists_are_divided_evenly(Hq, Hkv, D, kmax, dtype, ctx):
     assert any(len(segments_of(plan, w)) > 1 for w in range(plan["nshares"]))
 
 
-# More than 32 rows of few units in a large cache: the kernels that share rows, whose shares have at least two entries, over INT8 caches from
-# 20 entries per unit on four (pads of 3 entries)
+# More than 32 rows of few units in a large cache: the kernels that share rows (pads of 3 entries), whose shares have at least two entries,
+# over INT8 caches four, where the units are long
 @pytest.mark.parametrize("dtype,D,ctx,shares", [("bf16", 128, 60, 24), ("bf16", 128, 1000, 140), ("int8kv", 128, 1000, 70),
                                                 ("int8kv", 64, 1000, 70), ("int8kv", 128, 500, 76)])
 def test_few_units_share_rows(dtype, D, ctx, shares):

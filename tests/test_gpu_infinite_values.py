@@ -36,7 +36,7 @@ def test_infinite_values_of_the_context(B, Hq, Hkv, D, ctx, nq, fused):
 # Units of 8 tokens and the new ones, the first of which has the score 0, the eighth `below` less, the others 200 less (in powers of two)
 @pytest.mark.parametrize("dtype,least", [("bf16", 126), ("fp32", 148)])  # exponent of the smallest probability that is not taken as 0
 @pytest.mark.parametrize("Hq,Hkv,D,nq", [(1, 1, 64, 3), (4, 1, 128, 4), (4, 1, 128, 6), (2, 1, 64, 16), (8, 1, 128, 8), (5, 1, 64, 8),
-                                         (136, 17, 128, 8), (85, 17, 64, 8), (81, 81, 128, 4)])  # up to 64 rows, and each kernel
+                                         (264, 33, 128, 8), (85, 17, 64, 8), (81, 81, 128, 4)])  # up to 64 rows, and each kernel
 @pytest.mark.parametrize("below", [20, 90, 97, 98, 110, 126, 140])
 def test_infinite_values_of_small_probability(Hq, Hkv, D, nq, dtype, least, below):
     from paper_2404_15778_amd import harness as hip

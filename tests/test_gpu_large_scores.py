@@ -13,7 +13,7 @@ pytestmark = pytest.mark.gpu
 
 @pytest.mark.parametrize("dtype", ["bf16", "int8kv"])
 @pytest.mark.parametrize("Hq,Hkv,D,kmax", [(4, 2, 64, 4), (4, 4, 128, 16), (8, 2, 128, 6), (4, 1, 64, 8), (8, 1, 128, 8), (8, 1, 64, 5),
-                                           (72, 9, 128, 8), (63, 9, 64, 5), (100, 100, 64, 2)])
+                                           (136, 17, 128, 8), (63, 9, 64, 5), (100, 100, 64, 2)])
 @pytest.mark.parametrize("size", [32.0, 2.0 ** 15, 2.0 ** 24])  # of K and Q: scores of 2^12, 2^32 and 2^50
 def test_one_token_takes_all(dtype, Hq, Hkv, D, kmax, size):
     from paper_2404_15778_amd import harness
@@ -48,7 +48,7 @@ def test_one_token_takes_all(dtype, Hq, Hkv, D, kmax, size):
 
 @pytest.mark.parametrize("dtype", ["bf16", "int8kv"])
 @pytest.mark.parametrize("Hq,Hkv,D,kmax", [(4, 2, 64, 4), (4, 4, 128, 16), (8, 2, 128, 6), (4, 1, 64, 8), (8, 1, 128, 8), (8, 1, 64, 5),
-                                           (72, 9, 128, 8), (63, 9, 64, 5), (100, 100, 64, 2)])
+                                           (136, 17, 128, 8), (63, 9, 64, 5), (100, 100, 64, 2)])
 @pytest.mark.parametrize("power", [120, 110, -110])
 def test_keys_and_queries_of_opposite_size(dtype, Hq, Hkv, D, kmax, power):
     from paper_2404_15778_amd import harness
