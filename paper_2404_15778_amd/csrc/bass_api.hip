@@ -1,7 +1,7 @@
 // Version and status strings of libbass, and the host-side draft-length heuristic.
 #include "bass_common.h"
 
-extern "C" int bass_version(void) { return 215; /* 0.2.15: workgroups whose wavefronts take whole blocks, tiles of 32 rows; few units over workgroups; fp32 matrix instructions */ }
+extern "C" int bass_version(void) { return 216; /* 0.2.16: rows of any finite size in the workgroup kernels; short units are not cut; few units share rows in caches of any size */ }
 
 extern "C" const char* bass_status_string(int code) {
   switch (code) {
