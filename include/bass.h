@@ -330,11 +330,11 @@ int32_t bass_next_draft_len(bass_draft_len_state* state, const int32_t* n_accept
  *     unit (every other count: workgroups of four); at most 80 (sequence, kv head) pairs over bf16 and INT8 caches: 256
  *     workgroups of four wavefronts, of which short lists use fewer;
  *   more query rows: 256 workgroups of four wavefronts (512 for 256 to 1024 pairs with heads of 64 and at most 32 rows), of
- *     which short lists use fewer; caches of at most 24 blocks of 32 tokens with more than 32 rows: 256 workgroups of eight
- *     wavefronts, INT8 512 of four.
+ *     which short lists use fewer; more than 32 rows in caches of at most 24 blocks of 32 tokens, or of at most D / 4 (INT8
+ *     D / 8) pairs: 256 workgroups of eight wavefronts, INT8 512 of four, of which short lists of so few pairs use fewer.
  * A setting W gives W wavefronts in the first case and W / 2 workgroups with more rows.  Any setting but 0, also 768, divides
- * every list of blocks over all shares.  For shapes of at most 80 pairs whose lists may go to fewer
- * workgroups, what the rounding of the probabilities to bf16 left over is multiplied as well: a setting so changes the
+ * every list of blocks over all shares.  By default, bf16 and INT8 caches of at most 80 pairs with at most 16 query rows per kv
+ * head multiply all 24 bits of the probabilities instead of 8: a setting so changes the
  * rounding, within the same tolerance, besides the time.  Returns the value in effect for the first case.
  */
 int bass_set_attention_waves(int waves);

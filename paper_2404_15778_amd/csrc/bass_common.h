@@ -154,8 +154,8 @@ constexpr int kRowEntries = 2, kRowEntriesInt8 = 4, kRowGrow = 17;
 // verify_attn_wide: one workgroup per compute unit.  The end of a unit inside a stretch -- four states merged, the next unit's first
 // blocks waited for -- costs its workgroup about as much as 7 blocks: 16 layers of 16 sequences of 1024 - 4096 tokens, 64/8 heads, with 3 / 5 /
 // 7 virtual blocks per unit 769 / 758 / 758 us, 8 sequences, 32 heads, 32 rows 765 / 751 / 745.  Short lists go to fewer workgroups so that
-// every wavefront has a block: 1 sequence of 1000 tokens, 64 rows, 8 kv heads, with at least 1 / 4 / 8 / 12 entries per share 26.5 / 17.8 / 18.0 /
-// 20.8 us; from 8 on a wavefront's state spans several blocks, fewer probabilities are exactly 1 and precision is lost.
+// every wavefront has a block (a target: a unit always gets a share of its own): 1 sequence of 1000 tokens, 64 rows, 8 kv heads, with at least
+// 1 / 4 / 8 / 12 entries per share 26.5 / 17.8 / 18.0 / 20.8 us (few_units takes this shape to the kernels that share rows now); from 8 on a wavefront's state spans several blocks, fewer probabilities are exactly 1 and precision is lost.
 // Two where two fit (at most 32 rows of 64 elements) and the units are many: 256 units of 32 rows, 512 - 2048 tokens, INT8 23.6 -> 20.7, bf16
 // 25.7 -> 25.6; of 24 rows, 100 - 400 tokens, 15.9 -> 12.6 and 14.7 -> 13.2; 64 - 128 units 0 - 8 % longer.  Up to 1024 units: more
 // stretches need more scratch memory, and bass_verify_attention_noalloc has only so much of it.  (INT8 heads of 128 held to the registers of
@@ -168,12 +168,16 @@ constexpr int kWidePad = 7, kWideEntries = 4;
 constexpr int kWidePerStep = 4;
 // At most 16 query rows: up to this many units (sequence, kv head) take verify_attn_wide too, with a tile of 16 rows; more of them stay with a
 // wavefront per share (verify_attn_bf16), where a unit's merge costs no workgroup barrier.  8 query rows, a wavefront per share -> a
-// workgroup, us per layer, 32 / 64 / 96 / 128 / 192 units: head size 128, 200 - 500 tokens 12.6 / 14.2 / 14.6 / 14.3 / 16.6 -> 10.4 / 11.7 / 12.9 /
-// 15.4 / 18.0, 700 - 1500 tokens 17.2 / 19.2 / 20.6 / 21.3 / 28.4 -> 13.0 / 16.6 / 18.5 / 21.8 / 28.9, 2000 - 5000 tokens 20.8 / 30.1 / 36.8 / 44.4 /
-// 65.1 -> 18.2 / 28.2 / 36.9 / 44.5 / 67.3; head size 64, 2000 - 5000 tokens 15.4 / 20.4 / 22.1 -> 14.8 / 18.7 / 22.9; INT8 alike, 30 % quicker
-// at most (8 units of 4096 tokens: 15.9 -> 12.9).  1 sequence of 2000 tokens, 32/8 heads: 21.6 -> 12.2, 32 heads of 960: 14.1 -> 11.3.
+// workgroup, us per layer, 32 / 64 / 96 / 128 / 192 units, even division over the stretches: head size 128, 200 - 500 tokens 12.6 / 14.2 / 14.6 / 14.3 /
+// 16.6 -> 10.4 / 11.7 / 12.9 / 15.4 / 18.0, 700 - 1500 tokens 17.2 / 19.2 / 20.6 / 21.3 / 28.4 -> 13.0 / 16.6 / 18.5 / 21.8 / 28.9, 2000 - 5000 tokens
+// 20.8 / 30.1 / 36.8 / 44.4 / 65.1 -> 18.2 / 28.2 / 36.9 / 44.5 / 67.3; head size 64, 2000 - 5000 tokens 15.4 / 20.4 / 22.1 -> 14.8 / 18.7 / 22.9.
+// At 96 units heads of 128 are still level or up to 12 % shorter, heads of 64 4 % longer, at 128 all are longer: one line for both.
+// With whole stretches, 32 / 64 units: head size 128, 200 - 500 tokens 13.2 / 14.4 -> 10.1 / 11.6, 600 - 1500 14.8 / 19.6 -> 11.6 / 17.9, 2000 - 5000
+// 24.9 / 34.8 -> 20.9 / 32.4, INT8 13.6 / 14.7 -> 10.1 / 10.7, 16.1 / 19.0 -> 10.8 / 16.0, 25.5 / 26.8 -> 18.5 / 23.0; head size 64 10.0 / 10.9 -> 8.2 /
+// 8.9, 11.6 / 13.8 -> 8.8 / 13.0, 17.5 / 21.2 -> 15.2 / 20.1.  1 sequence of 2000 tokens, 32/8 heads: 21.3 -> 11.0, 32 heads of 960: 14.7 -> 11.8.
 // There all 24 bits of the probabilities are multiplied (wide_softmax): with few shares per unit few probabilities are exactly 1, and the
 // error against 64 bits would rise from 1.3e-3 to 1.6e-3.
+// A share is at least 5 entries where the list is divided evenly: a target, since a unit always gets a share of its own.
 constexpr int kNarrowUnits = 80;
 constexpr int kNarrowPad = 7, kNarrowEntries = 5, kNarrowShares = 256;  // (8 entries: short lists a third longer)
 // The kernels that share rows.  bf16: one workgroup per compute unit; INT8: two, because a step's conversions and softmax leave issue slots
@@ -187,10 +191,11 @@ struct LaunchShape {
   bool mfma;        // bf16 or INT8 caches: the matrix-core kernels
   bool tiles;       // more than one 16-row query tile per kv head: the workgroup-level kernels
   bool narrow;      // at most 16 query rows and few units: verify_attn_wide with one tile of 16
-  bool wide;        // ... verify_attn_wide
+  bool wide;        // verify_attn_wide, narrow or with one or two tiles of 32
   bool fused_append;  // the step's rows are appended inside the attention launch, and its plan says so
-  bool tiles_append;  // longer drafts, workgroup-level kernels: they patch a block at a time and stage nothing, so
-                      // planned launches may append there too; the plan is the one of a launch that does not append
+  bool tiles_append;  // longer drafts, workgroup-level kernels: those that share rows patch a block at a time and stage nothing,
+                      // verify_attn_wide has LDS for all rows that it takes, so planned launches may append there too; the
+                      // plan is the one of a launch that does not append
   int rows_max, nwaves, nshares, used_shares, target, pad, pad_before, min_entries, whole, grow;
 };
 

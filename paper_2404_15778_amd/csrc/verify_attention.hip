@@ -1172,14 +1172,17 @@ __global__ __launch_bounds__(256) void verify_attn_bf16(AttnParams p) {
 // Workgroup-level kernel for kv heads with more than 16 query rows (grouped-query attention, long drafts): NT tiles of 32 rows,
 // bf16 and INT8 caches.  A workgroup of four wavefronts takes a stretch of the block list together and its wavefronts take the
 // blocks in turn, each with the state of ALL query rows: a block is fetched once, straight into the operand registers of the one
-// wavefront that needs it, nothing passes through LDS and nobody waits for anybody until the unit ends.  There the four
+// wavefront that needs it, nothing but the scales of INT8 blocks passes through LDS and nobody waits for anybody until the unit ends.  There the four
 // states are merged through LDS (each wavefront collects a quarter of the accumulators) and one partial is stored.  What this is
 // built around: a step of 32 x 32 tiles (v_mfma_f32_32x32x16_bf16) has half the matrix and cross-lane instructions per row
 // of one of 16 x 16, and with two tiles two independent chains, so that one wavefront per SIMD keeps up with its share of the
 // memory.  Attention with its merge per layer, against 16-row tiles of one wavefront each that read the blocks from a ring in LDS behind a
 // barrier per phase: 16 sequences of 1024 - 4096 tokens, 64/8 heads of 128, bf16 with 48 rows (181 MB) 42.7 -> 41.7 us, INT8 with 64 rows
-// (94 MB) 46.3 -> 36.0; 8 sequences of 512 - 2048, 32 heads, 32 rows, bf16 (182 MB) 51.8 -> 44.0, INT8 40.1 -> 33.3.  What is left over the
-// memory's time is the way in (3 us to the first block), the merges and stretches that end 22 - 33 us after the start.
+// (94 MB) 46.3 -> 36.0; 8 sequences of 512 - 2048, 32 heads, 32 rows, bf16 (182 MB) 51.8 -> 44.0, INT8 40.1 -> 33.3; rounding the scores
+// (wide_scores) has cost 0.3 / 0.4 / 0.1 us of the first three since.  What is left over the
+// memory's time is the way in (3 us to the first block), the merges and stretches that end 22 - 33 us after the start.  Counters, 48 rows:
+// bf16 executes in 33 % of its wavefronts' cycles, waits for loads and LDS in 30 %, for an instruction to issue in 38 %; INT8 57 / 33 / 10 %, bound by
+// its 615 vector instructions per block (bf16: 395).  Both tiles are computed for every unit, also where all rows are in the first.
 //
 // Matrix-core mapping (32 x 32, c = lane % 32, h = lane / 32):
 //   S^T[32 tokens x 32 rows] = K Q^T: row c of operand A is token wide_token(c) of the block (bits 3 and 4 of c exchanged), step ks
@@ -1620,7 +1623,7 @@ __global__ __launch_bounds__(64 * kWideWaves, 1) void verify_attn_wide(AttnParam
   constexpr int kAccs = kTiles * G::kAcc;  // accumulators; wavefront x % W collects number x
   constexpr bool kMerge = NT <= 1;  // units that several workgroups share are merged here, not by reduce_wide
   constexpr int kBlkVec = G::kBlkVec;
-    constexpr int R = 2;  // blocks a wavefront has in its registers or on the way there (three: 1 - 2 us longer)
+  constexpr int R = 2;  // blocks a wavefront has in its registers or on the way there (three: 1 - 2 us longer)
   using Block = WideBlock<D, kI8>;
   __shared__ f32x4 exchange[kAccs][W - 1][kQuads][64];
   __shared__ float wave_m[W][kTiles][kRows], wave_l[W][kTiles][kRows];
@@ -1919,7 +1922,7 @@ __global__ __launch_bounds__(64 * kWideWaves, 1) void verify_attn_wide(AttnParam
 }
 
 // ---------------------------------------------------------------------------------------
-// Short caches (launch_shape), more than 32 query rows: a workgroup with a wavefront (bf16: two) per 16-row tile.  With few blocks per
+// Short caches or few units (launch_shape), more than 32 query rows: a workgroup with a wavefront (bf16: two) per 16-row tile.  With few blocks per
 // unit what counts is the time of one block and of the way out: four wavefronts share a block's rows here, and no states of several
 // tiles have to be merged at the end.
 // bf16: every K/V block is fetched from memory once (each wavefront a part of it), put into a ring in LDS, two blocks per phase, and
